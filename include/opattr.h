@@ -435,7 +435,9 @@ int opattr_attribute(const opattr_kernels *k, const opattr_profiled *p, const op
    process ends, set up on the first call on that device) and runs every
    stage on `stream` alone (no side streams). Same arguments, outputs and
    diag as opattr_attribute. Returns OPATTR_ERR_SCRATCH, enqueueing nothing,
-   when opattr_workspace_bytes(k, p, r, d) exceeds the scratch, and
+   when the call's arrays do not fit the scratch (opattr_workspace_bytes may
+   exceed it a little: it has room for partial results that this call adds
+   up in place instead), and
    OPATTR_ERR_HIP when the scratch's address cannot be had. Every call on a
    device shares that device's scratch: calls that may overlap on one device
    (other streams, other host threads) race and must be ordered by the

@@ -26,7 +26,7 @@ static bool has_dedup(const opattr_kernels *k, const opattr_dims *d) {
 }
 
 Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_ranges *r,
-               const opattr_dims *d, bool second_match) {
+               const opattr_dims *d, bool second_match, PlanMode mode) {
   Plan pl{};
   pl.T = k ? k->n : 0;
   pl.P = p ? p->n : 0;
@@ -48,7 +48,8 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
   // stream-major order when the fused path would then take them (not under
   // OPATTR_VALIDATE, which checks the caller's layout as given)
   const bool remap_ok = !sm_hint && seg_ok && !(d->flags & OPATTR_VALIDATE) && !second_match &&
-                        r != nullptr && pl.G <= kFusedMaxRows && pl.R * 16 <= pl.T && pl.T > 0;
+                        r != nullptr && pl.G <= kFusedMaxRows && pl.T > 0 &&
+                        (mode != PlanMode::kPlain || pl.R * 16 <= pl.T);
   pl.seg = (sm_hint || remap_ok) && seg_ok;  // sizes; reset below for the remapped case
   pl.nt = (pl.T + OPA_TILE - 1) / OPA_TILE;
   pl.ntp = (pl.P + OPA_TILE - 1) / OPA_TILE;
@@ -89,17 +90,6 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
   pl.mbs = b.take(dd || pl.seg ? T * 4 : 0);
   pl.nbs = b.take(T * 4);  // dedup source names, or the fast path's key and in-tile rank
   pl.bcnt = b.take(pl.seg ? (size_t)pl.nt * 4 : 0);
-  // the fused attribution keeps one partial result per run of launches of
-  // one operator row; ranges at most one per 16 launches keep the runs long
-  // enough for its per-block capacity (the rest would go through atomics)
-  // (only opattr_attribute, which always has ranges, takes it: a plan
-  // without ranges must stay within the size of the plan with them)
-  pl.fused = pl.seg && r != nullptr && pl.G <= kFusedMaxRows && pl.R * 16 <= pl.T && pl.T > 0;
-  pl.acc = b.take(pl.fused ? fused_acc_bytes(pl.G) : 0);
-  pl.fbkt = b.take(pl.fused ? fused_bkt_bytes(pl.T) : 0);
-  pl.forder = b.take(pl.fused ? (size_t)fused_agg_blocks(pl.T) * 4 : 0);
-  pl.fsplit = b.take(pl.fused ? fused_split_bytes(pl.G) : 0);
-  pl.fhot = b.take(pl.fused ? fused_hot_bytes() : 0);
   const bool rs = !pl.ranges_nested;
   pl.rperm = b.take(rs ? R * 4 : 0);
   pl.rs_c = b.take(rs ? R * 8 : 0);
@@ -127,42 +117,6 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
   pl.tfirst = b.take(ntr * 4);
   pl.tlast = b.take(ntr * 4);
   pl.sflag = b.take((size_t)sflag_words(pl.NS) * 4);
-  // aggregation: items (at most one per launch), partial rows (at most
-  // kEncRowsPerWave per 64 * 8 launches), windows of 64 sorted items
-  pl.cap_items = pl.T;
-  pl.cap_rows = pl.nencb * (kEncThreads / OPA_WAVE) * kEncRowsPerWave;
-  pl.max_windows = pl.cap_items / 64 + 1;
-  pl.wi = b.take((size_t)pl.nencb * (kEncThreads / OPA_WAVE) * 4);
-  pl.wr = b.take((size_t)pl.nencb * (kEncThreads / OPA_WAVE) * 4);
-  pl.hmb = b.take((size_t)pl.nencb * kEncThreads);
-  pl.ig = b.take((size_t)pl.cap_items * 4);
-  pl.ia = b.take((size_t)pl.cap_items * 4);
-  pl.ib = b.take((size_t)pl.cap_items * 4);
-  pl.rows = b.take((size_t)pl.cap_rows * 200);
-  pl.fparts = pl.rows;  // the fused attribution's kept partials (never both in one call)
-  pl.meta = b.take(8 * 8);
-  // item sort: per-tile row histograms for few rows, else one radix sort
-  const bool few_rows = pl.G <= kFastKeys;
-  pl.ith = b.take(few_rows ? (size_t)pl.ntrt * pl.G * 4 : 0);
-  pl.itch = b.take(few_rows ? (size_t)pl.nchr * pl.G * 4 : 0);
-  const size_t ni = few_rows ? 0 : (size_t)pl.cap_items;
-  pl.isort_k0 = b.take(ni * 4);
-  pl.isort_k1 = b.take(ni * 4);
-  pl.isort_v0 = b.take(ni * 4);
-  pl.isort_v1 = b.take(ni * 4);
-  pl.isort_hist = b.take(few_rows ? 0 : radix_hist_entries((int64_t)ni) * 4);
-  pl.gcnt = b.take((size_t)pl.G * 4);
-  pl.goff = b.take(((size_t)pl.G + 1) * 4);
-  // heavy rows (over 256 windows of 64 items, so at most items / 16320 of
-  // them) as (row, first chunk) pairs, and their chunks of 256 windows: at
-  // most about items / 8000, below max_windows / 64
-  pl.heavy = b.take((size_t)pl.G * 8);
-  pl.hcap = pl.max_windows / 64 + 64;
-  pl.hch = b.take((size_t)pl.hcap * 8);
-  pl.hpart = b.take((size_t)pl.hcap * 200);
-  pl.multi = b.take((size_t)pl.G * 4);
-  pl.sit = b.take((size_t)pl.cap_items * 8);
-  pl.part = b.take((size_t)pl.max_windows * 2 * 200);
   // class discovery: per partition, and the key table
   const size_t NPc = d->n_parts, TS = (size_t)class_table_slots(d->n_parts);
   pl.c_first = b.take(NPc * 4);
@@ -193,6 +147,27 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
     pl.slot2 = b.take(P * 4);
     pl.nbs2 = b.take(T * 4);
   }
+  // The fused attribution (only opattr_attribute, which always has ranges,
+  // takes it: a plan without ranges must stay within the size of the plan
+  // with them). Ranges at most one per 16 launches of a long list keep the
+  // runs of one operator row long: reduced in place. Shorter runs and shorter
+  // lists are ordered by row inside each block.
+  const bool long_runs = pl.R * 16 <= pl.T;
+  pl.fused = pl.seg && r != nullptr && pl.G <= kFusedMaxRows && pl.T > 0 &&
+             (mode != PlanMode::kPlain || long_runs);
+  // (2M launches with 20k ranges and 200 rows take 201 us
+  // reduced in place and 203 us by row tables; 1M with 250k ranges 625 us in
+  // place, 185 us ordered by row and 161 us by row tables)
+  if (mode != PlanMode::kPlain && !(long_runs && pl.T > kFusedShort)) {
+    // launches per lane: as few as leave no CU without a block, up to the
+    // point where more blocks only write more partials
+    pl.fper = pl.T <= (1 << 18) ? 2 : pl.T <= (1 << 20) ? 4 : 8;
+    if (pl.fused && pl.G <= kTabMaxRows) {  // the whole table fits in LDS
+      pl.fper = pl.T <= (1 << 18) ? 1 : pl.T <= (1 << 19) ? 2 : 4;
+      const int64_t chunks = fused_agg_blocks(pl.T, 1024 * pl.fper);
+      pl.ftabs = (int)(chunks < kTabBlocks ? chunks : kTabBlocks);
+    }
+  }
   pl.remap = remap_ok && pl.fused;
   if (pl.remap) {
     pl.rm_hist = b.take(remap_hist_entries(pl) * 4);
@@ -207,6 +182,67 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
     pl.rm_part = b.take(k->part_id ? T * 4 : 0);
     pl.rm_match = b.take(T * 4);
     pl.rm_rid = b.take(T * 4);
+  }
+  // Last, the two aggregations' arrays in one place (never both in one call).
+  const size_t shared = b.off;
+  // aggregation: items (at most one per launch), partial rows (at most
+  // kEncRowsPerWave per 64 * 8 launches), windows of 64 sorted items
+  pl.cap_items = pl.T;
+  pl.cap_rows = pl.nencb * (kEncThreads / OPA_WAVE) * kEncRowsPerWave;
+  pl.max_windows = pl.cap_items / 64 + 1;
+  pl.wi = b.take((size_t)pl.nencb * (kEncThreads / OPA_WAVE) * 4);
+  pl.wr = b.take((size_t)pl.nencb * (kEncThreads / OPA_WAVE) * 4);
+  pl.hmb = b.take((size_t)pl.nencb * kEncThreads);
+  pl.ig = b.take((size_t)pl.cap_items * 4);
+  pl.ia = b.take((size_t)pl.cap_items * 4);
+  pl.ib = b.take((size_t)pl.cap_items * 4);
+  pl.rows = b.take((size_t)pl.cap_rows * 200);
+  pl.meta = b.take(8 * 8);
+  // item sort: per-tile row histograms for few rows, else one radix sort
+  const bool few_rows = pl.G <= kFastKeys;
+  pl.ith = b.take(few_rows ? (size_t)pl.ntrt * pl.G * 4 : 0);
+  pl.itch = b.take(few_rows ? (size_t)pl.nchr * pl.G * 4 : 0);
+  const size_t ni = few_rows ? 0 : (size_t)pl.cap_items;
+  pl.isort_k0 = b.take(ni * 4);
+  pl.isort_k1 = b.take(ni * 4);
+  pl.isort_v0 = b.take(ni * 4);
+  pl.isort_v1 = b.take(ni * 4);
+  pl.isort_hist = b.take(few_rows ? 0 : radix_hist_entries((int64_t)ni) * 4);
+  pl.gcnt = b.take((size_t)pl.G * 4);
+  pl.goff = b.take(((size_t)pl.G + 1) * 4);
+  // heavy rows (over 256 windows of 64 items, so at most items / 16320 of
+  // them) as (row, first chunk) pairs, and their chunks of 256 windows: at
+  // most about items / 8000, below max_windows / 64
+  pl.heavy = b.take((size_t)pl.G * 8);
+  pl.hcap = pl.max_windows / 64 + 64;
+  pl.hch = b.take((size_t)pl.hcap * 8);
+  pl.hpart = b.take((size_t)pl.hcap * 200);
+  pl.multi = b.take((size_t)pl.G * 4);
+  pl.sit = b.take((size_t)pl.cap_items * 8);
+  pl.part = b.take((size_t)pl.max_windows * 2 * 200);
+  const size_t general = b.off;
+  if (pl.fused) {
+    b.off = shared;
+    const int64_t nfb = fused_agg_blocks(pl.T, fused_span(pl));
+    pl.acc = b.take(fused_acc_bytes(pl.G));
+    pl.fbkt = b.take(fused_bkt_bytes(nfb));
+    pl.fbase = b.take((size_t)nfb * 4);
+    pl.forder = b.take((size_t)nfb * 4);
+    pl.fsplit = b.take(fused_split_bytes(pl.G));
+    pl.fhot = b.take(fused_hot_bytes());
+    // Partials: the run reduction keeps a fixed count per block, the
+    // row-ordered reduction at most one per change of the innermost range and
+    // one per wave (half a partial per launch at most; what finds no room
+    // goes to the row accumulators).
+    const int64_t turns = 2 * pl.R + (int64_t)pl.NS + 1, half = pl.T / 2 + 1;
+    pl.fcap = pl.fper ? (turns < half ? turns : half) + 4 * nfb : nfb * fused_block_cap();
+    if (pl.ftabs) pl.fcap = (int64_t)pl.ftabs * pl.G;
+    if (mode == PlanMode::kLean && pl.fper && !pl.ftabs) {  // no more than the other aggregation takes
+      const int64_t room = general > b.off ? (int64_t)((general - b.off) / 200) : 0;
+      pl.fcap = pl.fcap < room ? pl.fcap : room;
+    }
+    pl.fparts = b.take(fused_parts_bytes(pl.fcap));
+    if (b.off < general) b.off = general;
   }
   if (!sm_hint) pl.seg = pl.fused = false;  // the launches as given
   pl.total = b.off;
@@ -626,7 +662,8 @@ static int attribute_fused(const opattr_kernels *k, const opattr_profiled *p,
   if (ss) note(hipEventRecord(ss->join, s2));
   IomArgs a{k, p, d, policy, match, name_counts, diag, ws, &pl, true, validate};
   a.buckets = true;
-  a.fused_order = ss != nullptr;  // only where the profiled side has a stream of its own
+  // only for the run reduction, and where the profiled side has a stream of its own
+  a.fused_order = ss != nullptr && !pl.fper;
   if (ss) {
     a.pf_stream = ss->s2;
     a.pf_fork = ss->fork2;
@@ -771,7 +808,9 @@ int opattr_attribute_noalloc(const opattr_kernels *k, const opattr_profiled *p,
                              opattr_summary *sum, opattr_diag *diag, void *stream) {
   if (!attribute_args_ok(k, p, r, d, policy, agg_kind, match, range_id, table, sum, diag))
     return OPATTR_ERR_INVALID_ARG;
-  const Plan pl = make_plan(k, p, r, d);
+  Plan pl = make_plan(k, p, r, d, false, PlanMode::kLean);
+  if (pl.total > OPATTR_NOALLOC_SCRATCH_BYTES)
+    pl = make_plan(k, p, r, d, false, PlanMode::kPlain);
   if (pl.total > OPATTR_NOALLOC_SCRATCH_BYTES) return OPATTR_ERR_SCRATCH;
   void *ws = scratch_ptr();
   if (!ws) return OPATTR_ERR_HIP;

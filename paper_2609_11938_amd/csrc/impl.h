@@ -52,7 +52,10 @@ struct Plan {
   // accumulators, kept partials (aliasing the partial rows of the other
   // aggregation), their bucket entries, and the per-bucket shares
   bool fused;
-  size_t acc, fparts, fbkt, fsplit, forder, fhot;
+  int fper;      // launches per lane of the row-ordered reduction (0: the run reduction)
+  int ftabs;     // blocks of the reduction with the whole table in LDS (0: another one)
+  int64_t fcap;  // partials there is room for
+  size_t acc, fparts, fbkt, fbase, fsplit, forder, fhot;
   bool m2;  // the second set below exists
   size_t kblk2, tbnd2, tlh2, pfh2, tlch2, pfch2, tlc2, pfc2, off2, slot2, nbs2;
   // ranges
@@ -71,9 +74,14 @@ struct Plan {
   size_t misc;   // small device scalars
 };
 
+// How much the fused attribution may take: all it can use; no partials past
+// the space of the other aggregation's arrays; or only the run reduction
+// (kPlain, never larger than a plan without the row-ordered reduction).
+enum class PlanMode { kFull, kLean, kPlain };
+
 // second_match: also a second set of the segment path's matching arrays
 Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_ranges *r,
-               const opattr_dims *d, bool second_match = false);
+               const opattr_dims *d, bool second_match = false, PlanMode mode = PlanMode::kFull);
 
 // First HIP error of the calling host thread since the last reset; entry
 // points report it as OPATTR_ERR_HIP.
@@ -356,15 +364,21 @@ struct FusedIn {
 void run_fused_agg(const FusedIn &x, hipStream_t s);
 // the processing order of the run reduction's blocks (reads only seq)
 void run_fused_order(const opattr_kernels *k, void *ws, const Plan &pl, hipStream_t s);
-int64_t fused_agg_blocks(int64_t T);  // blocks of the run reduction
+int fused_span(const Plan &pl);                   // launches per block of the reduction
+int64_t fused_agg_blocks(int64_t T, int span);    // its blocks
+int64_t fused_block_cap();                        // partials a block of the run reduction keeps
 // the clear of the row accumulators and the done count, as a fill job
 void fused_acc_clear(FillJobs &j, void *ws, const Plan &pl);
 // workspace sizes of the fused aggregation
-size_t fused_parts_bytes(int64_t T);
-size_t fused_bkt_bytes(int64_t T);
+size_t fused_parts_bytes(int64_t cap);
+size_t fused_tab_bytes(uint32_t G);  // a block's whole table
+size_t fused_bkt_bytes(int64_t nb);
 size_t fused_split_bytes(uint32_t G);
 size_t fused_hot_bytes();
 size_t fused_acc_bytes(uint32_t G);
+constexpr int64_t kFusedShort = 1 << 20;   // launches up to which blocks always order by row
+constexpr uint32_t kTabMaxRows = 704;      // rows of 200 B whose table a block holds in LDS
+constexpr int kTabBlocks = 256;
 constexpr uint32_t kFusedMaxRows = 16384;  // rows the per-bucket LDS tables hold
 
 // ---- finish (api.hip) ---------------------------------------------------------

@@ -114,6 +114,43 @@ def test_fused_unattributed(with_ranges):
     parity.assert_attribute(out, want, diag)
 
 
+@pytest.mark.parametrize("T,per_range,n_ops,S", [
+    (1, 1, 1, 1), (511, 2, 16383, 1), (512, 3, 2, 2), (513, 2, 700, 3),
+    (2 ** 18 + 1, 2, 5000, 4), (2 ** 20 + 1, 3, 900, 5),  # four, eight launches a lane
+    (1023, 2, 703, 2), (1025, 2, 704, 2),                  # the largest table in LDS, one row more
+    (2 ** 18 + 1, 40, 703, 3), (2 ** 19 + 1, 2, 50, 2), (2 ** 20 + 1, 5, 300, 4),
+])
+def test_row_order_edges(T, per_range, n_ops, S):
+    """Launches ordered by operator row inside each block, or added to a
+    table in LDS: block, wave and lane edges, one launch, the widest row
+    table, the sizes at which the launches per lane change; rows inside a
+    lane, across lanes and waves."""
+    tr = cases.random_trace(6000 + T % 977, T=T, S=S, n_names=9, R=max(1, T // per_range),
+                            n_ops=n_ops, t_max=4 * T + 8, max_depth=4)
+    tr, _, _ = cases.stream_major(tr)
+    print(f"case row order T={T} R={tr['r_start'].size} G={n_ops + 1}", flush=True)
+    want = O.attribute(tr)
+    out, diag = _run(tr)
+    parity.assert_attribute(out, want, diag)
+
+
+@pytest.mark.parametrize("kinds", [False, True])
+def test_row_order_more_partials_than_room(kinds):
+    """Query points that jump back and forth change the innermost range far
+    more often than the ranges' starts and ends: the partials past the room
+    for them go to the row accumulators."""
+    rng = np.random.default_rng(5)
+    T, R = 120_000, 400
+    tr = _regular_trace(T=T, run=T // R, n_ops=900, cycle=R, seed=93)
+    tr["start_ns"] = (rng.permutation(T).astype(np.uint64) * 10).astype(np.uint64)
+    kw = dict(agg_kind=np.array([(c * 7 + 1) % 3 for c in range(20)], np.uint8)) if kinds else {}
+    tr["counters"][::971, 5] = np.nan
+    print(f"case row order overflow T={T} R={R} kinds={kinds}", flush=True)
+    want = O.attribute(tr, **kw)
+    out, diag = _run(tr, **kw)
+    parity.assert_attribute(out, want, diag)
+
+
 def test_fused_dedup_errors():
     """Duplicates whose representative is shorter or has another name at a
     position, and a partition split in two: the same dedup errors, statuses
