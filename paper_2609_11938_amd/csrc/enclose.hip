@@ -23,6 +23,7 @@
 // threads; the rows then go out with coalesced stores at the planned indices.
 #include "accum.h"
 #include "common.h"
+#include "enclose_dev.h"
 #include "impl.h"
 
 namespace opa {
@@ -59,77 +60,12 @@ struct EncParams {
   uint8_t *range_depth;
 };
 
-// first index in [lo, hi) with a[idx] > x (or hi); called by a whole wave
-__device__ inline int64_t wave_upper_bound(const uint64_t *a, int64_t lo, int64_t hi, uint64_t x) {
-  const int l = lane_id();
-  while (hi - lo > OPA_WAVE) {
-    const int64_t step = (hi - lo + OPA_WAVE - 1) / OPA_WAVE;
-    int64_t p = lo + (int64_t)(l + 1) * step - 1;
-    if (p > hi - 1) p = hi - 1;
-    const uint64_t m = __ballot(a[p] > x);
-    if (m == 0) return hi;
-    const int f = __ffsll((unsigned long long)m) - 1;
-    const int64_t nlo = f == 0 ? lo : lo + (int64_t)f * step;
-    int64_t pf = lo + (int64_t)(f + 1) * step - 1;
-    if (pf > hi - 1) pf = hi - 1;
-    lo = nlo;
-    hi = pf + 1;
-  }
-  const int64_t p = lo + l;
-  const uint64_t m = __ballot(p < hi && a[p] > x);
-  return m ? lo + __ffsll((unsigned long long)m) - 1 : hi;
-}
-
-__device__ __forceinline__ int64_t thread_upper_bound(const uint64_t *a, int64_t lo, int64_t hi,
-                                                      uint64_t x) {
-  while (lo < hi) {
-    const int64_t mid = (lo + hi) >> 1;
-    if (a[mid] <= x) lo = mid + 1;
-    else hi = mid;
-  }
-  return lo;
-}
-
-// kPer consecutive elements from p[i..), 16-byte vector loads when aligned
-template <typename T>
-__device__ __forceinline__ void load_run(const T *p, int64_t i, int nv, T (&o)[kPer]) {
-  static_assert(sizeof(T) * kPer % 16 == 0, "vector width");
-  if (nv == kPer && (reinterpret_cast<uintptr_t>(p + i) & 15) == 0) {
-    const uint4 *v = reinterpret_cast<const uint4 *>(p + i);
-#pragma unroll
-    for (int q = 0; q < (int)(sizeof(T) * kPer / 16); ++q) {
-      const uint4 t = v[q];
-      memcpy(reinterpret_cast<char *>(o) + 16 * q, &t, 16);
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < kPer; ++k) o[k] = k < nv ? p[i + k] : T(0);
-  }
-}
-
-template <typename T>
-__device__ __forceinline__ void store_run(T *p, int64_t i, int nv, const T (&o)[kPer]) {
-  if (nv == kPer && (reinterpret_cast<uintptr_t>(p + i) & 15) == 0) {
-    uint4 *v = reinterpret_cast<uint4 *>(p + i);
-#pragma unroll
-    for (int q = 0; q < (int)(sizeof(T) * kPer / 16); ++q) {
-      uint4 t;
-      memcpy(&t, reinterpret_cast<const char *>(o) + 16 * q, 16);
-      v[q] = t;
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < kPer; ++k)
-      if (k < nv) p[i + k] = o[k];
-  }
-}
-
 // The operator rows of a thread's launches from input range ids (plan from a
 // given range_id array, and the reduction). Counts malformed range ids.
 __device__ __forceinline__ uint32_t rows_from_ids(const EncParams &a, int64_t ib, int nv,
                                                   uint32_t (&g)[kPer]) {
   int32_t rin[kPer];
-  load_run(a.range_id, ib, nv, rin);
+  load_run<kPer>(a.range_id, ib, nv, rin);
   uint32_t bad = 0;
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
@@ -201,8 +137,8 @@ k_enclose(EncParams a) {
   if (MODE & 1) {
     uint16_t st[kPer];
     uint64_t q[kPer];
-    load_run(a.stream, ib, nv, st);
-    load_run(a.q, ib, nv, q);
+    load_run<kPer>(a.stream, ib, nv, st);
+    load_run<kPer>(a.q, ib, nv, q);
     const uint16_t s0 = a.stream[i0];
     // smallest and largest query point of the block's main stream
     uint64_t mn = ~0ull, mx = 0ull;
@@ -361,7 +297,7 @@ k_enclose(EncParams a) {
 
     int32_t rout[kPer];
     if (a.core_id) {
-      store_run(a.core_id, ib, nv, ridk);
+      store_run<kPer>(a.core_id, ib, nv, ridk);
     } else if (!a.cr.kind && !a.fused) {
       // Phase 3 without kinds: the innermost range is the op range; its row
       // and output id for every launch, loads in flight together
@@ -375,7 +311,7 @@ k_enclose(EncParams a) {
 #pragma unroll
         for (int k = 0; k < kPer; ++k)
           if (k < nv) a.range_any[ib + k] = rout[k];
-      store_run(a.range_id, ib, nv, rout);
+      store_run<kPer>(a.range_id, ib, nv, rout);
     } else {
       // Phase 3 with kinds or fused wanted: Alg. 2's walk outward from the
       // innermost range, once per change of (innermost range, touching)
@@ -444,8 +380,8 @@ k_enclose(EncParams a) {
       }
       // stored after the walks, so that no store sits between the loads of
       // consecutive launches
-      store_run(a.range_id, ib, nv, rout);
-      if (a.range_any) store_run(a.range_any, ib, nv, aout);
+      store_run<kPer>(a.range_id, ib, nv, rout);
+      if (a.range_any) store_run<kPer>(a.range_any, ib, nv, aout);
       if (a.fused)
 #pragma unroll
         for (int k = 0; k < kPer; ++k)
@@ -551,7 +487,7 @@ __global__ void __launch_bounds__(kEncThreads) k_emit(EncParams a) {
   // the operator rows of the thread's run and piece starts (hp holds hm),
   // all loaded before any item is stored
   int32_t rin[kPer];
-  load_run(a.range_id, ib, nv, rin);
+  load_run<kPer>(a.range_id, ib, nv, rin);
   uint32_t gk[kPer];
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
@@ -622,8 +558,8 @@ k_agg_rows(EncParams a) {
   const uint32_t hm = a.em.hmb[bid * kEncThreads + tid];
   uint32_t mt[kPer];  // profiled row indices (as stored, -1 = unmatched)
   uint32_t du[kPer];
-  load_run(reinterpret_cast<const uint32_t *>(in.match), ib, nv, mt);
-  load_run(in.dur, ib, nv, du);
+  load_run<kPer>(reinterpret_cast<const uint32_t *>(in.match), ib, nv, mt);
+  load_run<kPer>(in.dur, ib, nv, du);
   uint32_t bad = 0;
 #pragma unroll
   for (int k = 0; k < kPer; ++k)

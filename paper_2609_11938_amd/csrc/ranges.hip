@@ -8,33 +8,13 @@
 // range whose end is not before the query point.
 //
 // Parents are "nearest previous greater-or-equal" values, found without a
-// sequential stack: pointer jumping inside LDS tiles of 1024 ranges, the same
-// jumping over tile maxima, then one bounded walk for the ranges whose parent
-// lies in an earlier tile. While jumping, each range also records the largest
-// end it skipped; a skipped end beyond the range's start is a crossing.
-#include "common.h"
-#include "impl.h"
+// sequential stack: a search in a maximum tree inside LDS tiles of 1024 ranges,
+// the same over the tile maxima, then one bounded walk for the ranges whose
+// parent lies in an earlier tile. On the way each range also records the
+// largest end it skipped; a skipped end beyond the range's start is a crossing.
+#include "ranges_dev.h"
 
 namespace opa {
-
-constexpr uint64_t kEndLimit = 1ull << 63;  // valid ends stay below 2^63
-
-// validity and effective end of range x (-1 marks a bad range); parents unknown
-__device__ __forceinline__ bool rprep_one(const CoreRanges &cr, uint32_t NS, uint32_t NOPS,
-                                          int64_t *ree, int32_t *npg, int64_t x) {
-  const uint64_t s = cr.s[x], e = cr.e[x];
-  const bool ok = cr.st[x] < NS && cr.op[x] < NOPS && s <= e && e < kEndLimit &&
-                  (!cr.kind || cr.kind[x] <= OPATTR_KIND_SKIP);
-  ree[x] = ok ? (int64_t)e : -1;
-  npg[x] = -1;
-  return !ok;
-}
-
-__device__ __forceinline__ void count_bad(bool bad, opattr_diag *diag) {
-  const uint64_t m = __ballot(bad);
-  if (m && lane_id() == __ffsll((unsigned long long)m) - 1)
-    atomicAdd((unsigned long long *)&diag->bad_records, (unsigned long long)__popcll(m));
-}
 
 __global__ void k_rprep(CoreRanges cr, uint32_t NS, uint32_t NOPS, int64_t *ree, int32_t *npg,
                         opattr_diag *diag) {
@@ -102,127 +82,22 @@ void launch_stream_blocks(const uint16_t *st, int64_t n, uint32_t NS, int64_t *b
   k_blocks16<<<(waves + 3) / 4, 256, 0, s>>>(st, n, NS, blk);
 }
 
-// tbase[s] = first tile of stream s (tiles never straddle streams), by one
-// block of 1024 threads
-__device__ inline void tile_bases(const int64_t *rblk, uint32_t NS, int32_t *tbase) {
-  __shared__ uint32_t sh[16];
-  uint32_t carry = 0;
-  for (uint32_t base = 0; base < NS; base += 1024) {
-    const uint32_t s = base + threadIdx.x;
-    uint32_t c = 0;
-    if (s < NS) c = (uint32_t)((rblk[s + 1] - rblk[s] + kRangeTile - 1) / kRangeTile);
-    uint32_t tot;
-    const uint32_t pre = block_excl_scan_add<uint32_t>(c, sh, &tot);
-    if (s < NS) tbase[s] = (int32_t)(carry + pre);
-    carry += tot;
-  }
-  if (threadIdx.x == 0) tbase[NS] = (int32_t)carry;
-}
-
 __global__ void __launch_bounds__(1024) k_rtile_base(const int64_t *rblk, uint32_t NS,
                                                      int32_t *tbase) {
   tile_bases(rblk, NS, tbase);
 }
 
-constexpr uint32_t kInlineBases = 1024;  // streams whose tile bases k_rlocal finds itself
-
-__device__ __forceinline__ uint32_t stream_of_tile(const int32_t *tbase, uint32_t NS, int32_t t) {
-  uint32_t lo = 0, hi = NS;  // last s with tbase[s] <= t
-  while (lo + 1 < hi) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (tbase[mid] <= t) lo = mid;
-    else hi = mid;
-  }
-  return lo;
-}
-
-struct RangeWork {
-  CoreRanges cr;
-  uint32_t NS;
-  const int64_t *rblk;
-  int32_t *tbase;  // written by k_rtile_base, or by k_rlocal with inline_bases
-  int64_t *ree;
-  int32_t *npg;
-  int64_t *mxv;
-  int64_t *tM;
-  int32_t *tnpg, *tnpg2;
-  int64_t *tmx, *tmx2;
-  int32_t *tstr, *tlast;
-  uint8_t *sflag;
-  opattr_diag *diag;
-  int inline_bases;  // k_rlocal finds the tile bases (NS <= kInlineBases)
-};
-
-// Local parents inside one tile by pointer jumping (Jacobi rounds): cand[i]
-// starts at i-1; while the candidate's end is before ours, jump to the
-// candidate's candidate. Every skipped range ends before ours, so cand stays a
-// valid candidate and converges to the nearest one with end >= ours, or -1 when
-// none is in the tile. mx[i] accumulates the largest end skipped.
-__global__ void __launch_bounds__(kRangeTile) k_rlocal(RangeWork w) {
-  __shared__ int64_t e[kRangeTile];
-  __shared__ int64_t mx[kRangeTile];
-  __shared__ int32_t cand[kRangeTile];
-  __shared__ int64_t red[kRangeTile / OPA_WAVE];
+// Local parents inside every tile.
+__global__ void __launch_bounds__(kRlThreads) k_rlocal(RangeWork w) {
+  __shared__ int64_t tree[kTreeNodes];
   __shared__ int32_t stb[kInlineBases + 1];
-  static_assert(kRangeTile == 1024, "one thread per range of a tile, 1024 for the bases");
-  const int32_t *tb = w.tbase;
-  if (w.inline_bases) {
-    tile_bases(w.rblk, w.NS, stb);
-    __syncthreads();
-    if (blockIdx.x == 0)
-      for (uint32_t k = threadIdx.x; k <= w.NS; k += blockDim.x) w.tbase[k] = stb[k];
-    tb = stb;
-  }
-  const int32_t t = blockIdx.x, ntr = tb[w.NS];
-  if (t >= ntr) return;
-  const uint32_t s = stream_of_tile(tb, w.NS, t);
-  const int64_t x0 = w.rblk[s] + (int64_t)(t - tb[s]) * kRangeTile;
-  const int64_t x1 = min(x0 + kRangeTile, w.rblk[s + 1]);
-  const int i = threadIdx.x;
-  const bool valid = x0 + i < x1;
-  e[i] = valid ? w.ree[x0 + i] : -1;
-  mx[i] = -1;
-  cand[i] = i - 1;
-  __syncthreads();
-  for (;;) {
-    const int c = cand[i];
-    int nc = c;
-    int64_t nm = mx[i];
-    if (valid && c >= 0 && e[c] < e[i]) {
-      nc = cand[c];
-      const int64_t v = e[c] > mx[c] ? e[c] : mx[c];
-      nm = v > nm ? v : nm;
-    }
-    __syncthreads();
-    cand[i] = nc;
-    mx[i] = nm;
-    if (!__syncthreads_or(nc != c)) break;
-  }
-  if (valid) {
-    const int64_t x = x0 + i;
-    const int c = cand[i];
-    w.npg[x] = c >= 0 ? (int32_t)(x0 + c) : -2;  // -2: parent lies before the tile
-    w.mxv[x] = mx[i];
-    if (c >= 0 && e[i] >= 0 && mx[i] > (int64_t)w.cr.s[x]) w.sflag[s] = 1;
-  }
-  // tile maximum
-  int64_t v = e[i];
-  for (int o = OPA_WAVE / 2; o > 0; o >>= 1) {
-    const int64_t y = __shfl_xor(v, o, OPA_WAVE);
-    v = y > v ? y : v;
-  }
-  if (lane_id() == 0) red[wave_id()] = v;
-  __syncthreads();
-  if (i == 0) {
-    int64_t m = -1;
-    for (int k = 0; k < kRangeTile / OPA_WAVE; ++k) m = red[k] > m ? red[k] : m;
-    w.tM[t] = m;
-    w.tstr[t] = (int32_t)s;
-    w.tlast[t] = (int32_t)(x1 - 1);
-  }
+  rlocal_tile(w, (int32_t)blockIdx.x, tree, stb);
 }
 
-// The same jumping over tile maxima (one block, tiles in global memory).
+// Pointer jumping over the tile maxima (one block, tiles in
+// global memory). The candidate of a tile starts at the tile before it;
+// while the candidate's maximum is below the tile's, jump to the
+// candidate's candidate.
 __global__ void __launch_bounds__(1024) k_rtiles(RangeWork w) {
   const int32_t ntr = w.tbase[w.NS];
   int32_t *cn = w.tnpg, *nn = w.tnpg2;
@@ -283,21 +158,7 @@ __global__ void k_rresolve(RangeWork w) {
     u = w.tnpg[u];
     ++steps;
   }
-  int32_t par = -1;
-  if (u >= 0) {
-    int32_t y = w.tlast[u];
-    steps = 0;
-    while (w.ree[y] < ex && steps < (1 << 20)) {
-      const int64_t v = w.ree[y] > w.mxv[y] ? w.ree[y] : w.mxv[y];
-      acc = v > acc ? v : acc;
-      y = w.npg[y];
-      ++steps;
-      if (y < 0) break;  // defensive: cannot happen, a tile maximum stops the walk
-    }
-    par = y;
-  }
-  w.npg[x] = par;
-  if (ex >= 0 && acc > (int64_t)w.cr.s[x]) w.sflag[s] = 1;
+  rresolve_in_tile(w, x, s, ex, u, acc);
 }
 
 // depth = length of the parent chain (1 for a root, 0 for a bad range)
@@ -306,7 +167,7 @@ __global__ void k_rdepth(RangeWork w, uint8_t *range_depth) {
   range_depth_one(w.npg, w.ree, w.cr.st, w.cr.perm, w.cr.n, w.NS, x, range_depth, w.diag);
 }
 
-static RangeWork range_work(const CoreRanges &cr, const opattr_dims *d, void *ws, const Plan &pl,
+RangeWork range_work(const CoreRanges &cr, const opattr_dims *d, void *ws, const Plan &pl,
                             opattr_diag *diag) {
   RangeWork w;
   w.cr = cr;
@@ -325,6 +186,7 @@ static RangeWork range_work(const CoreRanges &cr, const opattr_dims *d, void *ws
   w.tlast = at<int32_t>(ws, pl.tlast);
   w.sflag = at<uint8_t>(ws, pl.sflag);
   w.diag = diag;
+  w.ntr_max = (int32_t)pl.ntr_max;
   w.inline_bases = d->n_streams <= kInlineBases ? 1 : 0;
   return w;
 }
@@ -625,9 +487,9 @@ void resolve_ranges(const CoreRanges &cr, const opattr_dims *d, void *ws, const 
   }
   RangeWork w = range_work(cr, d, ws, pl, diag);
   if (!w.inline_bases) k_rtile_base<<<1, 1024, 0, s>>>(w.rblk, NS, at<int32_t>(ws, pl.tbase));
-  k_rlocal<<<(unsigned)pl.ntr_max, kRangeTile, 0, s>>>(w);
-  k_rtiles<<<1, 1024, 0, s>>>(w);
+  k_rlocal<<<(unsigned)pl.ntr_max, kRlThreads, 0, s>>>(w);
   const unsigned nb = (unsigned)((pl.R + 255) / 256);
+  k_rtiles<<<1, 1024, 0, s>>>(w);
   k_rresolve<<<nb, 256, 0, s>>>(w);
   if (!defer_depth) k_rdepth<<<nb, 256, 0, s>>>(w, range_depth);
   if (cr.kind)
