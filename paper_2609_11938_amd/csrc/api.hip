@@ -158,18 +158,29 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
   // (2M launches with 20k ranges and 200 rows take 201 us
   // reduced in place and 203 us by row tables; 1M with 250k ranges 625 us in
   // place, 185 us ordered by row and 161 us by row tables)
+  // Few launches: the compact path (single stream, five launches). Its tiles'
+  // name counts are a column of at most 1024 values per name, and its ranges'
+  // tiles fit one maximum tree.
+  pl.ctshift = pl.T > (1 << 18) || pl.P > (1 << 18) ? 12 : 10;
+  pl.nct = (pl.T + (1 << pl.ctshift) - 1) >> pl.ctshift;
+  pl.ncp = (pl.P + (1 << pl.ctshift) - 1) >> pl.ctshift;
+  pl.compact = mode != PlanMode::kPlain && !second_match && p != nullptr && r != nullptr &&
+               !r->kind && pl.T > 0 && pl.T <= kCompactMax && pl.P <= kCompactMax && pl.NN >= 1 &&
+               pl.NN <= kCompactNames && (pl.nct + pl.ncp) * pl.NN <= kCompactCells &&
+               pl.NS >= 1 && pl.ntr_max <= kRangeTile && pl.G <= kFusedMaxRows;
   if (mode != PlanMode::kPlain && !(long_runs && pl.T > kFusedShort)) {
     // launches per lane: as few as leave no CU without a block, up to the
     // point where more blocks only write more partials
     pl.fper = pl.T <= (1 << 18) ? 2 : pl.T <= (1 << 20) ? 4 : 8;
-    if (pl.fused && pl.G <= kTabMaxRows) {  // the whole table fits in LDS
+    if ((pl.fused || pl.compact) && pl.G <= kTabMaxRows) {  // the whole table fits in LDS
       pl.fper = pl.T <= (1 << 18) ? 1 : pl.T <= (1 << 19) ? 2 : 4;
       const int64_t chunks = fused_agg_blocks(pl.T, 1024 * pl.fper);
       pl.ftabs = (int)(chunks < kTabBlocks ? chunks : kTabBlocks);
     }
   }
-  pl.remap = remap_ok && pl.fused;
-  if (pl.remap) {
+  pl.remap = remap_ok && pl.fused && !pl.compact;
+  const size_t permuted = b.off;
+  if (remap_ok && pl.fused) {  // the compact path has its partials there
     pl.rm_hist = b.take(remap_hist_entries(pl) * 4);
     pl.rm_perm = b.take(T * 4);
     pl.rm_inv = b.take(T * 4);
@@ -221,23 +232,31 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
   pl.sit = b.take((size_t)pl.cap_items * 8);
   pl.part = b.take((size_t)pl.max_windows * 2 * 200);
   const size_t general = b.off;
-  if (pl.fused) {
-    b.off = shared;
+  if (pl.fused || pl.compact) {
+    b.off = pl.compact ? permuted : shared;
     const int64_t nfb = fused_agg_blocks(pl.T, fused_span(pl));
     pl.acc = b.take(fused_acc_bytes(pl.G));
     pl.fbkt = b.take(fused_bkt_bytes(nfb));
     pl.fbase = b.take((size_t)nfb * 4);
     pl.forder = b.take((size_t)nfb * 4);
-    pl.fsplit = b.take(fused_split_bytes(pl.G));
+    pl.fsplit = b.take(pl.compact ? 0 : fused_split_bytes(pl.G));
     pl.fhot = b.take(fused_hot_bytes());
     // Partials: the run reduction keeps a fixed count per block, the
     // row-ordered reduction at most one per change of the innermost range and
-    // one per wave (half a partial per launch at most; what finds no room
-    // goes to the row accumulators).
+    // one per wave (half a partial per launch at most). What finds no room
+    // goes to the row accumulators by atomics, which costs little when the
+    // rows are many (96k launches over 5,014 rows in 188 blocks: 62 us for
+    // the reduction and the rows, 52 us with room), so launches in any order
+    // get what the other arrays leave.
+    if (pl.compact) {
+      pl.ctl = b.take((size_t)pl.nct * NN * 4);
+      pl.cpf = b.take((size_t)pl.ncp * NN * 4);
+      pl.csum = b.take((size_t)nfb * 4 * 8);
+    }
     const int64_t turns = 2 * pl.R + (int64_t)pl.NS + 1, half = pl.T / 2 + 1;
     pl.fcap = pl.fper ? (turns < half ? turns : half) + 4 * nfb : nfb * fused_block_cap();
     if (pl.ftabs) pl.fcap = (int64_t)pl.ftabs * pl.G;
-    if (mode == PlanMode::kLean && pl.fper && !pl.ftabs) {  // no more than the other aggregation takes
+    if ((mode == PlanMode::kLean || (pl.compact && !sm_hint)) && pl.fper && !pl.ftabs) {  // no more than the other aggregation takes
       const int64_t room = general > b.off ? (int64_t)((general - b.off) / 200) : 0;
       pl.fcap = pl.fcap < room ? pl.fcap : room;
     }
@@ -245,6 +264,7 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
     if (b.off < general) b.off = general;
   }
   if (!sm_hint) pl.seg = pl.fused = false;  // the launches as given
+
   pl.total = b.off;
   return pl;
 }
@@ -729,6 +749,12 @@ static int attribute_call(const opattr_kernels *k, const opattr_profiled *p,
                           uint8_t *range_depth, uint32_t *name_counts, opattr_op_row *table,
                           opattr_summary *sum, opattr_diag *diag, void *ws, const Plan &pl,
                           hipStream_t s, bool fork) {
+  if (pl.compact) {
+    const CompactIn x{k, p, r, d, policy, agg_kind ? agg_kind : kDefaultKind, match, range_id,
+                      range_depth, name_counts, table, sum, diag, ws, &pl};
+    run_compact(x, s);
+    return launch_status();
+  }
   if (pl.remap) return attribute_remapped(k, p, r, d, policy, agg_kind, match, range_id,
                                           range_depth, name_counts, table, sum, diag, ws, pl, s,
                                           fork);

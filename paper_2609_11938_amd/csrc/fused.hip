@@ -29,9 +29,7 @@
 // Integer fields are exact in any order; fp64 sums are added in an order
 // that depends on scheduling (well inside the 1e-9 tolerance); maxima are
 // exact.
-#include "accum.h"
-#include "common.h"
-#include "impl.h"
+#include "rowagg.h"
 
 namespace opa {
 
@@ -41,66 +39,15 @@ constexpr int kAThreads = 256;                 // threads per block
 constexpr int kASpan = kAPer * kAThreads;      // launches per block
 constexpr int kASlots = 32;                    // partial results a wave keeps
 constexpr int kABlockCap = kASlots * (kAThreads / OPA_WAVE);  // and a block
-constexpr int kFFields = 25;                   // kc, tns, mc, mns, 20 counters, NaN bits
-constexpr int kBuckets = 256;                  // buckets of operator rows
-// A block's bucket entries: the buckets, then the unattributed row (NOPS) on
-// its own: it has a partial in almost every block, which would make its
-// bucket's combine waves the last to finish by far.
-constexpr int kBktStride = kBuckets + 1;
 constexpr int kHot = 32;                       // combine waves of the unattributed row
 constexpr int kSplits = 16;                    // shares of the blocks per bucket
 constexpr int kPre = 8;                        // bucket entries a combine lane fetches at once
-constexpr int kList = 512;                     // partials a combine wave lists in LDS at once
-constexpr int kBatch = 8;                      // partial loads per lane in flight
 constexpr uint32_t kNoSrc = 0xFFFFFFFFu;
 constexpr uint32_t kHash = 256;                // LDS table of a block's rows (> 2 x kept)
 
 
 static_assert(kABlockCap <= 255, "bucket offsets fit in a byte");
 static_assert(kBuckets <= kSumBlocks, "one summary partial per bucket fits the summary workspace");
-
-// vector of kN 32-bit elements (at most 16 bytes)
-template <int kN> struct VecOf { using type = uint4; };
-template <> struct VecOf<2> { using type = uint2; };
-template <> struct VecOf<1> { using type = uint32_t; };
-
-// kN consecutive 32-bit elements from p[i..), vector loads when aligned
-template <int kN, typename T>
-__device__ __forceinline__ void load_n(const T *p, int64_t i, int nv, T (&o)[kN]) {
-  static_assert(sizeof(T) == 4 && (kN <= 2 || kN % 4 == 0), "32-bit elements, whole vectors");
-  using V = typename VecOf<kN>::type;
-  constexpr int kB = (int)sizeof(V);
-  if (nv == kN && (reinterpret_cast<uintptr_t>(p + i) & (kB - 1)) == 0) {
-    const V *v = reinterpret_cast<const V *>(p + i);
-#pragma unroll
-    for (int q = 0; q < kN * 4 / kB; ++q) {
-      const V t = v[q];
-      memcpy(reinterpret_cast<char *>(o) + kB * q, &t, kB);
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < kN; ++k) o[k] = k < nv ? p[i + k] : T(0);
-  }
-}
-
-template <int kN, typename T>
-__device__ __forceinline__ void store_n(T *p, int64_t i, int nv, const T (&o)[kN]) {
-  using V = typename VecOf<kN>::type;
-  constexpr int kB = (int)sizeof(V);
-  if (nv == kN && (reinterpret_cast<uintptr_t>(p + i) & (kB - 1)) == 0) {
-    V *v = reinterpret_cast<V *>(p + i);
-#pragma unroll
-    for (int q = 0; q < kN * 4 / kB; ++q) {
-      V t;
-      memcpy(&t, reinterpret_cast<const char *>(o) + kB * q, kB);
-      v[q] = t;
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < kN; ++k)
-      if (k < nv) p[i + k] = o[k];
-  }
-}
 
 // ---------------------------------------------------------------------------
 // matches
@@ -228,14 +175,8 @@ struct AggParams {
   const int32_t *range_id;  // innermost (or walked) range, input index, or -1
   const uint32_t *op_in;    // op id of each input range
   int64_t R_in;
-  uint32_t NOPS, rb;        // rb: operator rows per bucket
   AggIn in;
-  PartRow *acc;             // [G] row accumulators for what blocks do not keep (zeroed)
-  PartRow *parts;           // kept partials, each block's by bucket (row in pad)
-  uint32_t *bkt;            // [blocks][kBktStride] offset << 16 | count
-  uint32_t *pbase;          // [blocks] first partial of each block
-  uint32_t *pcount;         // partials kept so far (zero at launch)
-  uint32_t pcap;            // partials there is room for
+  RowOut o;
   const uint32_t *order;    // [blocks] processing order (k_f_order), or NULL
 };
 
@@ -245,30 +186,6 @@ struct Slot {
   unsigned long long f[kFFields];
   uint32_t g, live;
 };
-
-__device__ __forceinline__ void wave_sync_lds() {
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// a += partial result of some launches of row g, one lane at a time
-// (device-scope atomics; only for what a block cannot keep)
-__device__ __forceinline__ void acc_to_table(PartRow *acc, uint32_t g, const Acc &a,
-                                             uint32_t mx) {
-  PartRow *r = acc + g;
-  atomicAdd(&r->kc, a.kc);
-  atomicAdd(&r->tns, a.tns);
-  if (a.mc == 0) return;  // no counter row reached: every counter field is still zero
-  atomicAdd(&r->mc, a.mc);
-  atomicAdd(&r->mns, a.mns);
-#pragma unroll
-  for (int c = 0; c < OPATTR_NUM_COUNTERS; ++c) {
-    if ((mx >> c) & 1u) atomicMax(&r->v[c], a.v[c]);
-    else unsafeAtomicAdd(reinterpret_cast<double *>(&r->v[c]), bits2d(a.v[c]));
-  }
-  if (a.nan) atomicOr(&r->nan, a.nan);
-}
 
 // Stage the partial of every lane with want set (row g) in the wave's slots;
 // returns the lane's slot, or -1 when the slots are full (then the partial
@@ -317,10 +234,10 @@ __device__ __forceinline__ void acc_merge_slot(Acc &a, const Slot *q, uint32_t m
 }
 
 __device__ __forceinline__ uint32_t row_of(const AggParams &a, int32_t rid) {
-  uint32_t g = a.NOPS;
+  uint32_t g = a.o.NOPS;
   if (rid >= 0 && rid < a.R_in) {
     const uint32_t o = a.op_in[rid];
-    g = o < a.NOPS ? o : a.NOPS;
+    g = o < a.o.NOPS ? o : a.o.NOPS;
   }
   return g;
 }
@@ -337,12 +254,12 @@ __device__ __forceinline__ void rows_of(const AggParams &a, const int32_t (&rid)
     for (int k = 0; k < kN; ++k) o[k] = a.op_in[(rid[k] >= 0 && rid[k] < a.R_in) ? rid[k] : 0];
 #pragma unroll
     for (int k = 0; k < kN; ++k) {
-      const bool ok = rid[k] >= 0 && rid[k] < a.R_in && o[k] < a.NOPS;
-      g[k] = k < nh ? (ok ? o[k] : a.NOPS) : 0xFFFFFFFFu;
+      const bool ok = rid[k] >= 0 && rid[k] < a.R_in && o[k] < a.o.NOPS;
+      g[k] = k < nh ? (ok ? o[k] : a.o.NOPS) : 0xFFFFFFFFu;
     }
   } else {
 #pragma unroll
-    for (int k = 0; k < kN; ++k) g[k] = k < nh ? a.NOPS : 0xFFFFFFFFu;
+    for (int k = 0; k < kN; ++k) g[k] = k < nh ? a.o.NOPS : 0xFFFFFFFFu;
   }
 }
 
@@ -397,7 +314,7 @@ k_f_agg(AggParams a) {
     for (int k = 0; k < kAHalf; ++k) {
       const int kk = h * kAHalf + k;
       const bool cut = kk > 0 && k < nh && ((hm >> kk) & 1u);
-      const int idx = stage_put(cut, gcur, inc, wslot, nst, a.acc, mx);
+      const int idx = stage_put(cut, gcur, inc, wslot, nst, a.o.acc, mx);
       // the lane's first piece continues the previous lane's run
       if (cut && (hm & 1u) == 0 && (hm & ((1u << kk) - 1u)) == 0) fslot = idx;
       if (cut) {
@@ -434,7 +351,7 @@ k_f_agg(AggParams a) {
   // no run start at all
   const uint32_t nvn = __shfl_down((uint32_t)nv, 1, OPA_WAVE);
   const uint32_t hmn = __shfl_down(hm, 1, OPA_WAVE);
-  stage_put(nv > 0 && (ln == OPA_WAVE - 1 || nvn == 0 || hmn != 0), gcur, inc, wslot, nst, a.acc,
+  stage_put(nv > 0 && (ln == OPA_WAVE - 1 || nvn == 0 || hmn != 0), gcur, inc, wslot, nst, a.o.acc,
             mx);
   if (ln == 0) nslot[w] = nst;
   {
@@ -493,7 +410,7 @@ k_f_agg(AggParams a) {
   uint32_t bq = 0xFFFFFFFFu, rk = 0;
   if (own) {
     const uint32_t g = slots[tid / kASlots][tid % kASlots].g;
-    bq = g == a.NOPS ? (uint32_t)kBuckets : g / a.rb;
+    bq = g == a.o.NOPS ? (uint32_t)kBuckets : g / a.o.rb;
     rk = atomicAdd(&hist[bq], 1u);
   }
   __syncthreads();
@@ -502,10 +419,10 @@ k_f_agg(AggParams a) {
   const uint32_t off = block_excl_scan_add<uint32_t>(tid < kBuckets ? cnt : 0u, sh, &tot);
   const uint32_t hcnt = hist[kBuckets];  // the unattributed row's partial goes last
   if (tid < kBuckets)
-    a.bkt[blk * kBktStride + tid] = (off << 16) | cnt;
+    a.o.bkt[blk * kBktStride + tid] = (off << 16) | cnt;
   if (tid == 0) {
-    a.bkt[blk * kBktStride + kBuckets] = (tot << 16) | hcnt;
-    a.pbase[blk] = (uint32_t)(blk * kABlockCap);
+    a.o.bkt[blk * kBktStride + kBuckets] = (tot << 16) | hcnt;
+    a.o.pbase[blk] = (uint32_t)(blk * kABlockCap);
   }
   __syncthreads();
   if (tid < kBuckets) hist[tid] = off;
@@ -514,7 +431,7 @@ k_f_agg(AggParams a) {
   if (tid < kABlockCap) spos[tid] = bq != 0xFFFFFFFFu ? hist[bq] + rk : 0xFFFFFFFFu;
   __syncthreads();
   // coalesced copy: consecutive threads take consecutive fields
-  PartRow *dst = a.parts + blk * kABlockCap;
+  PartRow *dst = a.o.parts + blk * kABlockCap;
   for (int x = tid; x < kABlockCap * kFFields; x += kAThreads) {
     const int s = x / kFFields, f = x % kFFields;
     const uint32_t p = spos[s];
@@ -541,57 +458,14 @@ k_f_agg(AggParams a) {
 // 96k launches, 62,800 ranges, 5,014 rows take 24 us, where the items of
 // the general aggregation took eleven launches and about 90 us.
 // ---------------------------------------------------------------------------
-constexpr int kRThreads = 256;
-
-// LDS of k_r_agg: the row histogram, later the crossing rows' slots
-__host__ __device__ inline uint32_t r_hist_words(uint32_t G) { return (G + 1) / 2; }
-inline size_t r_agg_lds(uint32_t G) {
-  const size_t h = (size_t)r_hist_words(G) * 4, sl = (size_t)kRThreads * kFFields * 8;
-  return h > sl ? h : sl;
-}
-
-// one lane's partial result to parts[x] (row g)
-__device__ __forceinline__ void part_store(PartRow *parts, size_t x, uint32_t g, const Acc &a) {
-  unsigned long long *d = reinterpret_cast<unsigned long long *>(parts + x);
-  d[0] = a.kc;
-  d[1] = a.tns;
-  d[2] = a.mc;
-  d[3] = a.mns;
-#pragma unroll
-  for (int c = 0; c < OPATTR_NUM_COUNTERS; ++c) d[4 + c] = a.v[c];
-  d[24] = (unsigned long long)a.nan | ((unsigned long long)g << 32);
-}
-
-// a lane's partial result added into an LDS slot
-__device__ __forceinline__ void slot_add(unsigned long long *q, const Acc &a, uint32_t mx) {
-  atomicAdd(&q[0], a.kc);
-  atomicAdd(&q[1], a.tns);
-  if (a.mc == 0) return;  // no counter row reached
-  atomicAdd(&q[2], a.mc);
-  atomicAdd(&q[3], a.mns);
-#pragma unroll
-  for (int c = 0; c < OPATTR_NUM_COUNTERS; ++c) {
-    if ((mx >> c) & 1u) atomicMax(&q[4 + c], a.v[c]);
-    else unsafeAtomicAdd(reinterpret_cast<double *>(&q[4 + c]), bits2d(a.v[c]));
-  }
-  if (a.nan) atomicOr(reinterpret_cast<unsigned int *>(&q[24]), a.nan);
-}
-
 template <bool DEF, int kPer>  // DEF: the default aggregation kinds; kPer launches per lane
 __global__ void __launch_bounds__(kRThreads) k_r_agg(AggParams a) {
   constexpr int kN = kRThreads * kPer;
   extern __shared__ __align__(16) unsigned char ragg_raw[];
-  uint32_t *hist = reinterpret_cast<uint32_t *>(ragg_raw);  // two rows a word
-  unsigned long long *slots = reinterpret_cast<unsigned long long *>(ragg_raw);
-  __shared__ uint2 md[kN];      // match and duration, in row order
-  __shared__ uint16_t sg[kN];   // row, in row order
-  __shared__ uint16_t hx[kRThreads + 1];  // row starts before each thread's positions
-  __shared__ uint8_t hms[kRThreads];
-  __shared__ uint32_t sh[4], sbase;
-  const int tid = threadIdx.x, ln = lane_id(), w = wave_id();
-  const AggIn &in = a.in;
-  const uint32_t mx = DEF ? kDefMaxMask : in.maxmask, dw = DEF ? kDefDwMask : in.dwmask;
-  const uint32_t G = a.NOPS + 1u, words = r_hist_words(G);
+  __shared__ RowLds<kPer> lds;
+  const int tid = threadIdx.x;
+  const uint32_t words = r_hist_words(a.o.NOPS + 1u);
+  uint32_t *hist = reinterpret_cast<uint32_t *>(ragg_raw);
   const int64_t blk = order_slot(a.order, blockIdx.x, gridDim.x);
   const int64_t b0 = blk * kN;
   const int nb = (int)(a.T - b0 < kN ? a.T - b0 : kN);  // launches of the block
@@ -599,180 +473,19 @@ __global__ void __launch_bounds__(kRThreads) k_r_agg(AggParams a) {
   const int nv = (int)(a.T - ib < 0 ? 0 : (a.T - ib < kPer ? a.T - ib : kPer));
   for (uint32_t x = tid; x < words; x += kRThreads) hist[x] = 0;
   int32_t mt[kPer], rid[kPer];
-  uint32_t du[kPer], g[kPer], rk[kPer];
+  uint32_t du[kPer], g[kPer];
   uint32_t err = 0;
   match_of<kPer>(a.m, ib, nv, mt, err);
-  load_n<kPer>(in.dur, ib, nv, du);
+  load_n<kPer>(a.in.dur, ib, nv, du);
   load_n<kPer>(a.range_id, ib, nv, rid);
   rows_of<kPer>(a, rid, nv, g);
   {
     const unsigned long long e = wave_reduce_add((unsigned long long)err);
-    if (ln == 0 && e) atomicAdd((unsigned long long *)&a.m.diag->dedup_errors, e);
+    if (lane_id() == 0 && e) atomicAdd((unsigned long long *)&a.m.diag->dedup_errors, e);
   }
-  __syncthreads();
-  // rank of every launch in its row: one atomic per run of the thread
-#pragma unroll
-  for (int k = 0; k < kPer; ++k) {
-    if (k >= nv) continue;
-    if (k > 0 && g[k] == g[k - 1]) {
-      rk[k] = rk[k - 1] + 1u;
-      continue;
-    }
-    uint32_t len = 1;
-#pragma unroll
-    for (int j = 1; j < kPer; ++j)
-      if (k + j < nv && len == (uint32_t)j && g[k + j < kPer ? k + j : 0] == g[k]) ++len;
-    const int s16 = (int)(g[k] & 1u) * 16;
-    rk[k] = (atomicAdd(&hist[g[k] >> 1], len << s16) >> s16) & 0xFFFFu;
-  }
-  __syncthreads();
-  // first position of every row: each thread scans a stretch of the words
-  // (an odd count of them, so that the stretches start in different banks)
-  const uint32_t ch = ((words + kRThreads - 1) / kRThreads) | 1u;
-  const uint32_t wlo = tid * ch, whi = wlo + ch < words ? wlo + ch : words;
-  uint32_t mine = 0;
-  for (uint32_t x = wlo; x < whi; ++x) mine += (hist[x] & 0xFFFFu) + (hist[x] >> 16);
-  uint32_t run = block_excl_scan_add<uint32_t>(mine, sh, nullptr);
-  for (uint32_t x = wlo; x < whi; ++x) {
-    const uint32_t v = hist[x];
-    hist[x] = run | ((run + (v & 0xFFFFu)) << 16);
-    run += (v & 0xFFFFu) + (v >> 16);
-  }
-  __syncthreads();
-  auto row_pos = [&](uint32_t r) -> uint32_t {  // first position of row r (r <= NOPS)
-    return (hist[r >> 1] >> ((r & 1u) * 16)) & 0xFFFFu;
-  };
-#pragma unroll
-  for (int k = 0; k < kPer; ++k)
-    if (k < nv) {
-      const uint32_t p = row_pos(g[k]) + rk[k];
-      md[p] = make_uint2((uint32_t)mt[k], du[k]);
-      sg[p] = (uint16_t)g[k];
-    }
-  // positions at which this thread's bucket starts and ends (kBuckets
-  // threads), and the unattributed row's first
-  const uint32_t bl = (uint32_t)tid * a.rb, bh = bl + a.rb;
-  const uint32_t p_lo = row_pos(bl < a.NOPS ? bl : a.NOPS), p_hi = row_pos(bh < a.NOPS ? bh : a.NOPS);
-  const uint32_t p_un = row_pos(a.NOPS);
-  __syncthreads();  // the histogram's space becomes the slots
-  // row starts among the thread's positions (a wave's first position is one)
-  const int p0 = tid * kPer;
-  uint32_t hm = 0;
-#pragma unroll
-  for (int k = 0; k < kPer; ++k) {
-    const int p = p0 + k;
-    if (p < nb && ((ln == 0 && k == 0) || p == 0 || sg[p] != sg[p - 1])) hm |= 1u << k;
-  }
-  uint32_t nh;
-  const uint32_t h0 = block_excl_scan_add<uint32_t>((uint32_t)__popc(hm), sh, &nh);
-  hx[tid] = (uint16_t)h0;
-  hms[tid] = (uint8_t)hm;
-  if (tid == 0) {
-    hx[kRThreads] = (uint16_t)nh;
-    // room for the block's partials; a block that finds none left adds its
-    // results to the row accumulators
-    uint32_t base = atomicAdd(a.pcount, nh);
-    if (base > a.pcap || nh > a.pcap - base) base = 0xFFFFFFFFu;
-    sbase = base;
-  }
-  unsigned long long *wslot = slots + (size_t)w * OPA_WAVE * kFFields;
-  for (int x = ln; x < OPA_WAVE * kFFields; x += OPA_WAVE) wslot[x] = 0;
-  __syncthreads();
-  const uint32_t base = sbase;
-  const bool keep = base != 0xFFFFFFFFu;
-  auto starts_before = [&](uint32_t p) -> uint32_t {  // row starts at positions below p
-    const uint32_t t = p / kPer;
-    return t >= (uint32_t)kRThreads ? nh
-                                    : hx[t] + (uint32_t)__popc(hms[t] & ((1u << (p % kPer)) - 1u));
-  };
-  {
-    const uint32_t o = starts_before(p_lo), e = starts_before(p_hi), u = starts_before(p_un);
-    a.bkt[blk * kBktStride + tid] = keep ? (o << 16) | (e - o) : 0u;
-    if (tid == 0) {
-      a.bkt[blk * kBktStride + kBuckets] = keep ? (u << 16) | (nh - u) : 0u;
-      a.pbase[blk] = keep ? base : 0u;
-    }
-  }
-  // the lane's launches; kind of a piece: started in an earlier lane (its
-  // slot's lane is the nearest below with a row start), started here
-  const unsigned long long hl = __ballot(hm != 0);
-  const unsigned long long below = hl & lanemask_lt();
-  const int from = below ? 63 - __clzll((long long)below) : 0;
-  const int np = nb - p0 < 0 ? 0 : (nb - p0 < kPer ? nb - p0 : kPer);
-  // the next lane goes on with this lane's last row
-  const uint32_t np_n = __shfl_down((uint32_t)np, 1, OPA_WAVE), hm_n = __shfl_down(hm, 1, OPA_WAVE);
-  const bool out = ln < OPA_WAVE - 1 && np_n > 0 && (hm_n & 1u) == 0;
-  Acc acc;
-  acc_zero(acc);
-  bool here = false;  // the piece started in this lane
-  uint32_t hi = h0;   // row starts before the piece
-  uint32_t gc = 0;
-  auto flush_inside = [&]() {  // a row that ends in this lane
-    if (!here) slot_add(wslot + (size_t)from * kFFields, acc, mx);
-    else if (keep) part_store(a.parts, (size_t)base + hi, gc, acc);
-    else acc_to_table(a.acc, gc, acc, mx);
-  };
-  // a wave inside one row: reduced across the lanes
-  const bool whole = hl == 1ull && __popc(__shfl(hm, 0, OPA_WAVE)) == 1;
-#pragma unroll 1
-  for (int k = 0; k < kPer; ++k) {
-    if (k >= np) break;
-    if ((hm >> k) & 1u) {
-      if (k > 0) {
-        flush_inside();
-        acc_zero(acc);
-        if (here) ++hi;
-      }
-      here = true;
-      gc = sg[p0 + k];
-    }
-    const uint2 e = md[p0 + k];
-    acc_launch(acc, in, (int32_t)e.x, e.y, mx, dw);
-  }
-  if (whole) {
-    acc_wave_reduce(acc, mx);
-    if (ln == 0) {
-      if (keep) part_store(a.parts, (size_t)base + hi, gc, acc);
-      else acc_to_table(a.acc, gc, acc, mx);
-    }
-    return;
-  }
-  const bool mine_out = here && out;  // this lane's slot holds a row that goes on
-  if (np > 0) {
-    if (mine_out) slot_add(wslot + (size_t)ln * kFFields, acc, mx);
-    else flush_inside();
-  }
-  wave_sync_lds();
-  // the crossing rows, coalesced: consecutive lanes take consecutive fields
-  const unsigned long long live = __ballot(mine_out);
-  const int nl = __popcll(live);
-  for (int x = ln; x < nl * kFFields; x += OPA_WAVE) {
-    const int r = x / kFFields, f = x - r * kFFields;
-    unsigned long long m = live;  // the r-th live lane
-    for (int j = 0; j < r; ++j) m &= m - 1;
-    const int s = __ffsll((unsigned long long)m) - 1;
-    const int st = w * OPA_WAVE + s;  // its thread: the slot's row is the thread's last start
-    const uint32_t hs = hms[st];
-    const uint32_t sk = 31u - (uint32_t)__clz((int)hs);
-    const uint32_t row = sg[st * kPer + (int)sk];
-    const uint32_t idx = hx[st] + (uint32_t)__popc(hs) - 1u;
-    const unsigned long long v = wslot[(size_t)s * kFFields + f];
-    if (keep) {
-      unsigned long long *d = reinterpret_cast<unsigned long long *>(a.parts + (size_t)base + idx);
-      d[f] = f < 24 ? v : ((v & 0xFFFFFFFFull) | ((unsigned long long)row << 32));
-    } else {
-      unsigned long long *d = reinterpret_cast<unsigned long long *>(a.acc + row);
-      if (f < 4) {
-        atomicAdd(&d[f], v);
-      } else if (f < 24) {
-        if ((mx >> (f - 4)) & 1u) atomicMax(&d[f], v);
-        else unsafeAtomicAdd(reinterpret_cast<double *>(&d[f]), bits2d(v));
-      } else if ((uint32_t)v) {
-        atomicOr(reinterpret_cast<unsigned int *>(&d[24]), (uint32_t)v);
-      }
-    }
-  }
+  row_order_block<DEF, kPer>(a.o, a.in, blk, nb, nv, mt, du, g, ragg_raw, lds);
 }
+
 
 // ---------------------------------------------------------------------------
 // 1''. the reduction for few operator rows: a block holds the whole table in
@@ -786,9 +499,6 @@ __global__ void __launch_bounds__(kRThreads) k_r_agg(AggParams a) {
 // k_r_agg, whose 977 blocks each write nearly every row), 192 us with the
 // items of the general aggregation.
 // ---------------------------------------------------------------------------
-constexpr int kTThreads = 1024;
-constexpr int kTHot = 12;  // lanes of one row above which they are reduced first
-
 template <bool DEF, int kPer>
 __global__ void __launch_bounds__(kTThreads) k_t_agg(AggParams a, unsigned long long *tabs) {
   constexpr int kN = kTThreads * kPer;
@@ -796,8 +506,7 @@ __global__ void __launch_bounds__(kTThreads) k_t_agg(AggParams a, unsigned long 
   unsigned long long *tab = reinterpret_cast<unsigned long long *>(tagg_raw);  // [G][kFFields]
   const int tid = threadIdx.x, ln = lane_id();
   const AggIn &in = a.in;
-  const uint32_t mx = DEF ? kDefMaxMask : in.maxmask, dw = DEF ? kDefDwMask : in.dwmask;
-  const uint32_t ne = (a.NOPS + 1u) * kFFields;
+  const uint32_t ne = (a.o.NOPS + 1u) * kFFields;
   for (uint32_t x = tid; x < ne; x += kTThreads) tab[x] = 0;
   __syncthreads();
   uint32_t err = 0;
@@ -812,38 +521,7 @@ __global__ void __launch_bounds__(kTThreads) k_t_agg(AggParams a, unsigned long 
     load_n<kPer>(in.dur, ib, nv, du);
     load_n<kPer>(a.range_id, ib, nv, rid);
     rows_of<kPer>(a, rid, nv, g);
-    Acc acc;
-    acc_zero(acc);
-    uint32_t gc = g[0];
-    // launch k is always at position 0 of the arrays (see k_f_agg)
-#pragma unroll 1
-    for (int k = 0; k < kPer; ++k) {
-      if (k < nv) {
-        if (g[0] != gc) {
-          slot_add(tab + (size_t)gc * kFFields, acc, mx);
-          acc_zero(acc);
-          gc = g[0];
-        }
-        acc_launch(acc, in, mt[0], du[0], mx, dw);
-      }
-#pragma unroll
-      for (int j = 0; j + 1 < kPer; ++j) {
-        mt[j] = mt[j + 1];
-        du[j] = du[j + 1];
-        g[j] = g[j + 1];
-      }
-    }
-    const uint32_t gm = (uint32_t)__builtin_amdgcn_readlane((int)gc, 31);
-    const bool in_hot = nv > 0 && gc == gm;
-    if (__popcll(__ballot(in_hot)) >= kTHot) {
-      Acc t = acc;
-      if (!in_hot) acc_zero(t);
-      acc_wave_reduce(t, mx);
-      if (ln == 0) slot_add(tab + (size_t)gm * kFFields, t, mx);
-      if (nv > 0 && !in_hot) slot_add(tab + (size_t)gc * kFFields, acc, mx);
-    } else if (nv > 0) {
-      slot_add(tab + (size_t)gc * kFFields, acc, mx);
-    }
+    tab_add<DEF, kPer>(tab, in, nv, mt, du, g);
   }
   {
     const unsigned long long e = wave_reduce_add((unsigned long long)err);
@@ -854,67 +532,9 @@ __global__ void __launch_bounds__(kTThreads) k_t_agg(AggParams a, unsigned long 
   for (uint32_t x = tid; x < ne; x += kTThreads) dst[x] = tab[x];
 }
 
-// The blocks' tables added up, kTRows rows a block (one element per thread
-// and share of the tables), the table rows, and per block the summary sums;
-// the last block to finish writes the summary and the status.
-constexpr int kTRows = 10, kTShares = 4;
-static_assert(kTRows * kFFields * kTShares <= 1024, "one block");
-
 // ---------------------------------------------------------------------------
 // 2. per bucket: the kept partials of a share of the blocks, added in LDS
 // ---------------------------------------------------------------------------
-struct CombParams {
-  int64_t nblocks;
-  uint32_t rb, G, NOPS;
-  uint32_t mx, dw, absent;
-  const PartRow *parts;
-  const uint32_t *bkt, *pbase;
-  PartRow *split;              // [kBuckets][kSplits][rb]
-  PartRow *hot;                // [kHot] the unattributed row's shares
-  const PartRow *acc;          // [G] row accumulators (the blocks' overflow)
-  opattr_op_row *table;
-  unsigned long long *part;    // [kBuckets][4] summary sums per bucket
-  // the finalisation, by the last block of the per-row reduction to finish
-  uint32_t *done;              // blocks finished (zero at launch)
-  opattr_diag *diag;
-  const uint8_t *sflag;        // [ns] per-stream crossing flags
-  uint32_t ns;
-  opattr_summary *sum;
-};
-
-__device__ __forceinline__ unsigned long long merge_field(int f, unsigned long long x,
-                                                          unsigned long long y, uint32_t mx) {
-  if (f < 4) return x + y;
-  if (f < 24) return ((mx >> (f - 4)) & 1u) ? (x > y ? x : y) : d2bits(bits2d(x) + bits2d(y));
-  return x | y;
-}
-
-// output field o (four counts, then the counters) of a row from its 25
-// accumulated fields p
-__device__ __forceinline__ unsigned long long row_field(const unsigned long long *p, int o,
-                                                        uint32_t absent, uint32_t mx, uint32_t dw) {
-  if (o < 4) return p[o];
-  const int c = o - 4;
-  const unsigned long long qnan = 0x7FF8000000000000ull;
-  if (((absent >> c) & 1u) || p[2] == 0) return qnan;
-  if ((mx >> c) & 1u) return (((uint32_t)p[24] >> c) & 1u) ? qnan : d2bits((double)key2f((uint32_t)p[o]));
-  if ((dw >> c) & 1u) return p[3] ? d2bits(bits2d(p[o]) / (double)p[3]) : qnan;
-  return p[o];
-}
-
-// t (one field f of an LDS row) += the field's value x
-__device__ __forceinline__ void field_add(unsigned long long *t, int f, unsigned long long x,
-                                          uint32_t mx) {
-  if (f < 4) {
-    atomicAdd(t, x);
-  } else if (f < 24) {
-    if ((mx >> (f - 4)) & 1u) atomicMax(t, x);
-    else unsafeAtomicAdd(reinterpret_cast<double *>(t), bits2d(x));
-  } else if ((uint32_t)x) {
-    atomicOr(reinterpret_cast<unsigned int *>(t), (uint32_t)x);
-  }
-}
-
 // A wave takes a share of the blocks for one bucket: its lanes fetch the
 // blocks' bucket entries eight at a time, list the partial results those
 // entries point to in LDS, and then read each partial with 25 lanes (one
@@ -969,7 +589,6 @@ __global__ void __launch_bounds__(64) k_f_comb(CombParams a) {
   const int64_t b_lo = (int64_t)s * per, b_hi = b_lo + per < a.nblocks ? b_lo + per : a.nblocks;
   uint32_t *list = reinterpret_cast<uint32_t *>(tab + ne);  // [kList] partial indices
   const unsigned long long *parts64 = reinterpret_cast<const unsigned long long *>(a.parts);
-  const int half = ln >> 5, f = ln & 31;
   for (int64_t b0 = b_lo; b0 < b_hi; b0 += (int64_t)OPA_WAVE * kPre) {
     // the lane's next kPre blocks' entries for the bucket, loads in flight together
     uint32_t ev[kPre], xv[kPre], mine = 0;  // count, first partial
@@ -981,59 +600,7 @@ __global__ void __launch_bounds__(64) k_f_comb(CombParams a) {
       xv[k] = (b < b_hi ? a.pbase[b] : 0u) + (e >> 16);
       mine += ev[k];
     }
-    const uint32_t incl = wave_incl_scan_add<uint32_t>(mine);
-    const uint32_t n = __shfl(incl, OPA_WAVE - 1, OPA_WAVE);
-    if (n == 0) continue;
-    if (n <= (uint32_t)kList) {
-      // the partials listed in LDS, then read by 25 lanes each (two
-      // partials per instruction, kBatch instructions in flight) and added
-      // field by field
-      uint32_t w = incl - mine;
-#pragma unroll
-      for (int k = 0; k < kPre; ++k) {
-        for (uint32_t p = 0; p < ev[k]; ++p) list[w++] = xv[k] + p;
-      }
-      wave_sync_lds();
-      for (uint32_t i = 0; i < n; i += 2 * kBatch) {
-        unsigned long long v[kBatch];
-#pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-          const uint32_t idx = i + 2 * j + half;
-          v[j] = (idx < n && f < kFFields)
-                     ? parts64[(size_t)list[idx] * (sizeof(PartRow) / 8) + f] : 0ull;
-        }
-#pragma unroll
-        for (int j = 0; j < kBatch; ++j) {
-          const uint32_t g = (uint32_t)(__shfl(v[j], (ln & 32) + 24, OPA_WAVE) >> 32);
-          const uint32_t idx = i + 2 * j + half;
-          if (idx < n && f < kFFields) field_add(tab + (size_t)(g % rb) * kFFields + f, f, v[j], mx);
-        }
-      }
-    } else {
-      // more partials than the list holds (rare): one lane's entry at a
-      // time, its partials read two at a time by 25 lanes each
-#pragma unroll 1
-      for (int k = 0; k < kPre; ++k) {
-        uint32_t e = 0, xe = 0;
-#pragma unroll
-        for (int j = 0; j < kPre; ++j) {
-          e = k == j ? ev[j] : e;
-          xe = k == j ? xv[j] : xe;
-        }
-        for (uint64_t m = __ballot(e != 0); m; m &= m - 1) {
-          const int src = __ffsll((unsigned long long)m) - 1;
-          const uint32_t c = __shfl(e, src, OPA_WAVE);
-          const uint64_t x0 = __shfl(xe, src, OPA_WAVE);
-          for (uint32_t p = 0; p < c; p += 2) {
-            const uint32_t pp = p + half;
-            const unsigned long long v = (pp < c && f < kFFields)
-                ? parts64[(x0 + pp) * (sizeof(PartRow) / 8) + f] : 0ull;
-            const uint32_t g = (uint32_t)(__shfl(v, (ln & 32) + 24, OPA_WAVE) >> 32);
-            if (pp < c && f < kFFields) field_add(tab + (size_t)(g % rb) * kFFields + f, f, v, mx);
-          }
-        }
-      }
-    }
+    comb_add<kPre>(tab, list, parts64, ev, xv, mine, rb, mx);
     wave_sync_lds();
   }
   unsigned long long *out =
@@ -1137,78 +704,6 @@ __global__ void __launch_bounds__(256) k_f_rows(CombParams a) {
   finish_block(a.diag, a.sflag, a.ns, a.part, (int)gridDim.x, a.sum);
 }
 
-template <bool DEF>
-__global__ void __launch_bounds__(1024) k_t_rows(CombParams a, const unsigned long long *tabs,
-                                                 int ntabs) {
-  constexpr int kEl = kTRows * kFFields;
-  __shared__ unsigned long long part[kTShares][kEl];
-  __shared__ unsigned long long red[4][kTRows];
-  const uint32_t mx = DEF ? kDefMaxMask : a.mx, dw = DEF ? kDefDwMask : a.dw;
-  const int tid = threadIdx.x, sh = tid / kEl, e = tid - sh * kEl, f = e % kFFields;
-  const uint32_t g0 = blockIdx.x * kTRows, ne = a.G * kFFields;
-  const uint32_t x = g0 * kFFields + e;
-  if (sh < kTShares && x < ne) {
-    unsigned long long v = 0;
-    constexpr int kB = 16;
-    for (int t0 = sh; t0 < ntabs; t0 += kTShares * kB) {
-      unsigned long long y[kB];
-#pragma unroll
-      for (int j = 0; j < kB; ++j) {
-        const int t = t0 + j * kTShares;
-        y[j] = t < ntabs ? tabs[(size_t)t * ne + x] : 0ull;
-      }
-#pragma unroll
-      for (int j = 0; j < kB; ++j)
-        if (t0 + j * kTShares < ntabs) v = merge_field(f, v, y[j], mx);
-    }
-    part[sh][e] = v;
-  }
-  __syncthreads();
-  if (tid < kEl && x < ne) {
-    unsigned long long v = part[0][tid];
-#pragma unroll
-    for (int s = 1; s < kTShares; ++s) v = merge_field(f, v, part[s][tid], mx);
-    part[0][tid] = v;
-  }
-  __syncthreads();
-  // 24 output fields a row
-  if (tid < kTRows * 24) {
-    const int r = tid / 24, o = tid - r * 24;
-    const uint32_t g = g0 + r;
-    if (g < a.G) {
-      const unsigned long long *p = part[0] + r * kFFields;
-      unsigned long long *row = reinterpret_cast<unsigned long long *>(a.table + g);
-      row[o] = row_field(p, o, a.absent, mx, dw);
-      if (o == 0) {
-        red[0][r] = g < a.NOPS ? p[1] : 0ull;
-        red[1][r] = g < a.NOPS ? 0ull : p[1];
-        red[2][r] = p[1];
-        red[3][r] = p[3];
-      }
-    } else if (o == 0) {
-      red[0][r] = red[1][r] = red[2][r] = red[3][r] = 0;
-    }
-  }
-  __syncthreads();
-  if (tid < 4) {
-    unsigned long long v = 0;
-    for (int r = 0; r < kTRows; ++r) v += red[tid][r];
-    a.part[blockIdx.x * 4 + tid] = v;
-  }
-  __shared__ uint32_t last;
-  if (tid < OPA_WAVE) {
-    __threadfence();
-    uint32_t l = 0;
-    if (tid == 0) l = atomicAdd(a.done, 1u) == gridDim.x - 1 ? 1u : 0u;
-    l = __shfl(l, 0);
-    if (l) __threadfence();
-    if (tid == 0) last = l;
-  }
-  __syncthreads();
-  if (!last) return;
-  finish_block(a.diag, a.sflag, a.ns, a.part, (int)gridDim.x, a.sum);
-}
-
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
@@ -1268,29 +763,28 @@ void run_fused_agg(const FusedIn &x, hipStream_t s) {
   a.range_id = x.range_id;
   a.op_in = x.r->op_id;
   a.R_in = x.r->n;
-  a.NOPS = x.d->n_ops;
-  a.rb = rb;
+  a.o.NOPS = x.d->n_ops;
+  a.o.rb = rb;
   a.in = *x.in;
-  a.acc = at<PartRow>(x.ws, pl.acc);
-  a.parts = at<PartRow>(x.ws, pl.fparts);
-  a.bkt = at<uint32_t>(x.ws, pl.fbkt);
-  a.pbase = at<uint32_t>(x.ws, pl.fbase);
+  a.o.acc = at<PartRow>(x.ws, pl.acc);
+  a.o.parts = at<PartRow>(x.ws, pl.fparts);
+  a.o.bkt = at<uint32_t>(x.ws, pl.fbkt);
+  a.o.pbase = at<uint32_t>(x.ws, pl.fbase);
   uint32_t *counts = reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(x.ws) + pl.acc +
                                                   (size_t)pl.G * sizeof(PartRow));
-  a.pcount = counts + 1;
-  a.pcap = (uint32_t)pl.fcap;
+  a.o.pcount = counts + 1;
+  a.o.pcap = (uint32_t)pl.fcap;
   const bool def = a.in.maxmask == kDefMaxMask && a.in.dwmask == kDefDwMask;
   const int64_t nb = fused_agg_blocks(pl.T, fused_span(pl));
   a.order = x.ordered ? at<uint32_t>(x.ws, pl.forder) : nullptr;  // from run_fused_order
   probe_begin(OPATTR_PROBE_AGG_RUNS, s);
   if (pl.ftabs && nb > 0) {
-    unsigned long long *tabs = reinterpret_cast<unsigned long long *>(a.parts);
+    unsigned long long *tabs = reinterpret_cast<unsigned long long *>(a.o.parts);
     const size_t lt = (size_t)pl.G * kFFields * 8;
     const unsigned gt = (unsigned)pl.ftabs;
     if (pl.fper == 1) def ? k_t_agg<true, 1><<<gt, kTThreads, lt, s>>>(a, tabs) : k_t_agg<false, 1><<<gt, kTThreads, lt, s>>>(a, tabs);
     else if (pl.fper == 2) def ? k_t_agg<true, 2><<<gt, kTThreads, lt, s>>>(a, tabs) : k_t_agg<false, 2><<<gt, kTThreads, lt, s>>>(a, tabs);
-    else if (pl.fper == 4) def ? k_t_agg<true, 4><<<gt, kTThreads, lt, s>>>(a, tabs) : k_t_agg<false, 4><<<gt, kTThreads, lt, s>>>(a, tabs);
-    else def ? k_t_agg<true, 8><<<gt, kTThreads, lt, s>>>(a, tabs) : k_t_agg<false, 8><<<gt, kTThreads, lt, s>>>(a, tabs);
+    else def ? k_t_agg<true, 4><<<gt, kTThreads, lt, s>>>(a, tabs) : k_t_agg<false, 4><<<gt, kTThreads, lt, s>>>(a, tabs);
   } else if (nb > 0) {
     const size_t lr = r_agg_lds(pl.G);
     const dim3 gr((unsigned)nb), bl(kRThreads);
@@ -1310,12 +804,12 @@ void run_fused_agg(const FusedIn &x, hipStream_t s) {
   c.mx = a.in.maxmask;
   c.dw = a.in.dwmask;
   c.absent = x.absent;
-  c.parts = a.parts;
-  c.bkt = a.bkt;
-  c.pbase = a.pbase;
+  c.parts = a.o.parts;
+  c.bkt = a.o.bkt;
+  c.pbase = a.o.pbase;
   c.split = at<PartRow>(x.ws, pl.fsplit);
   c.hot = at<PartRow>(x.ws, pl.fhot);
-  c.acc = a.acc;
+  c.acc = a.o.acc;
   c.table = x.table;
   c.part = at<unsigned long long>(x.ws, pl.sumpart);
   c.done = counts;
@@ -1324,10 +818,10 @@ void run_fused_agg(const FusedIn &x, hipStream_t s) {
   c.ns = x.d->n_streams;
   c.sum = x.sum;
   if (pl.ftabs) {
-    const unsigned long long *tabs = reinterpret_cast<const unsigned long long *>(a.parts);
+    const unsigned long long *tabs = reinterpret_cast<const unsigned long long *>(a.o.parts);
     const unsigned gr = (pl.G + kTRows - 1) / kTRows;
-    if (def) k_t_rows<true><<<gr, 1024, 0, s>>>(c, tabs, pl.ftabs);
-    else k_t_rows<false><<<gr, 1024, 0, s>>>(c, tabs, pl.ftabs);
+    if (def) k_t_rows<true, true><<<gr, 1024, 0, s>>>(c, tabs, pl.ftabs);
+    else k_t_rows<false, true><<<gr, 1024, 0, s>>>(c, tabs, pl.ftabs);
     probe_end(OPATTR_PROBE_AGGREGATE, s);
     return;
   }

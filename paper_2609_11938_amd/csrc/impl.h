@@ -52,6 +52,12 @@ struct Plan {
   // accumulators, kept partials (aliasing the partial rows of the other
   // aggregation), their bucket entries, and the per-bucket shares
   bool fused;
+  // opattr_attribute of at most kCompactMax launches: five multi-job launches
+  // on the caller's stream (compact.hip), whatever the launches' order
+  bool compact;
+  int ctshift;       // log2 of its tiles' size
+  int64_t nct, ncp;  // its tiles of launches and of profiled rows
+  size_t ctl, cpf, csum;
   int fper;      // launches per lane of the row-ordered reduction (0: the run reduction)
   int ftabs;     // blocks of the reduction with the whole table in LDS (0: another one)
   int64_t fcap;  // partials there is room for
@@ -267,6 +273,10 @@ void launch_dispatch_keys(const int32_t *range_id, const int32_t *op, const opat
                           opattr_diag *diag, hipStream_t s);
 
 // ---- ranges and enclosure (ranges.hip, enclose.hip) ----------------------------
+// the ranges in nesting order (sorted when that is not promised, else checked
+// under OPATTR_VALIDATE)
+CoreRanges order_ranges(const opattr_ranges *r, void *ws, const Plan &pl, opattr_diag *diag,
+                        bool validate, hipStream_t s);
 // nesting order, validity, effective ends and stream blocks of the ranges,
 // with the range stage's clears and the caller's extra clears (extra)
 CoreRanges prepare_ranges(const opattr_ranges *r, const opattr_dims *d, void *ws, const Plan &pl,
@@ -371,6 +381,7 @@ int64_t fused_block_cap();                        // partials a block of the run
 void fused_acc_clear(FillJobs &j, void *ws, const Plan &pl);
 // workspace sizes of the fused aggregation
 size_t fused_parts_bytes(int64_t cap);
+uint32_t fused_rows_per_bucket(uint32_t G);
 size_t fused_tab_bytes(uint32_t G);  // a block's whole table
 size_t fused_bkt_bytes(int64_t nb);
 size_t fused_split_bytes(uint32_t G);
@@ -380,6 +391,29 @@ constexpr int64_t kFusedShort = 1 << 20;   // launches up to which blocks always
 constexpr uint32_t kTabMaxRows = 704;      // rows of 200 B whose table a block holds in LDS
 constexpr int kTabBlocks = 256;
 constexpr uint32_t kFusedMaxRows = 16384;  // rows the per-bucket LDS tables hold
+
+// ---- compact attribution (compact.hip) -------------------------------------------
+struct CompactIn {
+  const opattr_kernels *k;
+  const opattr_profiled *p;
+  const opattr_ranges *r;
+  const opattr_dims *d;
+  int policy;
+  const uint8_t *agg_kind;
+  int32_t *match, *range_id;
+  uint8_t *range_depth;
+  uint32_t *name_counts;
+  opattr_op_row *table;
+  opattr_summary *sum;
+  opattr_diag *diag;
+  void *ws;
+  const Plan *pl;
+};
+void run_compact(const CompactIn &x, hipStream_t s);
+constexpr int kCompactTile = 1024;           // launches (or profiled rows) per tile at least
+constexpr int64_t kCompactMax = 1 << 20;     // launches, profiled rows
+constexpr uint32_t kCompactNames = 2048;     // 16 counters of 2 B a name in LDS
+constexpr int64_t kCompactCells = 1 << 20;   // entries of the two tables of name counts per tile
 
 // ---- finish (api.hip) ---------------------------------------------------------
 // status of the diag record; with a table, also the summary over its G rows

@@ -19,8 +19,7 @@
 // Seq tiles are read through a launch-order view (sv[seq] = input index), or,
 // when the kernels are promised stream-major with dense seq, straight from one
 // storage segment per stream (no view is built).
-#include "common.h"
-#include "impl.h"
+#include "match_dev.h"
 
 namespace opa {
 
@@ -443,44 +442,18 @@ __global__ void __launch_bounds__(256) k_part_edges(TlArgs a, uint32_t *pfirst, 
   part_edges(sm.lp, base, sm.sg.edge[0], sm.sg.edge[1], pfirst, plast, pheads);
 }
 
-// The record of every partition (PartRec, see impl.h); also raises
-// PARTITION for every partition seen in more than one run.
-
+// The record of every partition
 __global__ void k_part_prep(const int32_t *__restrict__ part_rep, uint32_t NP,
                             const uint32_t *__restrict__ pfirst, const uint32_t *__restrict__ plast,
                             const uint32_t *__restrict__ pheads, PartRec *prec,
                             opattr_diag *diag) {
-  const uint32_t p = blockIdx.x * blockDim.x + threadIdx.x;
-  bool nc = false;
-  if (p < NP) {
-    nc = pheads[p] > 1;
-    if (prec) {
-      const int32_t r = part_rep[p];
-      PartRec q{0, kRecNone};
-      if (r == (int32_t)p) {
-        q.hi = kRecEligible;
-      } else if (r >= 0 && (uint32_t)r < NP) {
-        q.hi = 0;
-        const uint32_t f = pfirst[r];
-        if (pheads[p] == 1u && pheads[r] == 1u && part_rep[r] == r && f != 0xFFFFFFFFu) {
-          q.delta = (int32_t)(f - pfirst[p]);
-          const uint64_t hi = (uint64_t)pfirst[p] + (plast[r] - f + 1u);
-          q.hi = (uint32_t)(hi < 0x7FFFFFFFull ? hi : 0x7FFFFFFFull);  // seq ranks are < 2^31
-        }
-      }
-      prec[p] = q;
-    }
-  }
-  if (__ballot(nc) && lane_id() == 0) atomicOr(&diag->flags, OPATTR_F_PARTITION);
+  part_prep_one(part_rep, NP, pfirst, plast, pheads, prec, diag,
+                blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // bad class-map entries are counted once, with the other bad ids of the match
 __global__ void k_rep_check(const int32_t *__restrict__ part_rep, uint32_t NP, opattr_diag *diag) {
-  const uint32_t q = blockIdx.x * blockDim.x + threadIdx.x;
-  const bool bad = q < NP && (part_rep[q] < 0 || (uint32_t)part_rep[q] >= NP);
-  const uint64_t m = __ballot(bad);
-  if (m && lane_id() == __ffsll((unsigned long long)m) - 1)
-    atomicAdd((unsigned long long *)&diag->bad_records, (unsigned long long)__popcll(m));
+  rep_check_one(part_rep, NP, diag, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
 // The matching's first launch on the segment path, three jobs in one grid
@@ -507,11 +480,7 @@ __global__ void __launch_bounds__(256) k_seg_prologue(ProArgs a) {
       for (int64_t i = (int64_t)b * blockDim.x + threadIdx.x; i < a.fill.n[q]; i += stride)
         a.fill.p[q][i] = a.fill.v[q];
   } else if (b < a.nf + a.nr) {
-    const uint32_t q = (uint32_t)(b - a.nf) * blockDim.x + threadIdx.x;
-    const bool bad = q < a.NP && (a.part_rep[q] < 0 || (uint32_t)a.part_rep[q] >= a.NP);
-    const uint64_t m = __ballot(bad);
-    if (m && lane_id() == __ffsll((unsigned long long)m) - 1)
-      atomicAdd((unsigned long long *)&a.diag->bad_records, (unsigned long long)__popcll(m));
+    rep_check_one(a.part_rep, a.NP, a.diag, (uint32_t)(b - a.nf) * blockDim.x + threadIdx.x);
   } else {
     const uint32_t sw = (uint32_t)(b - a.nf - a.nr) * (blockDim.x / OPA_WAVE) + wave_id();
     if (sw <= a.NS) stream_block_wave(a.st, a.T, sw, a.kblk);
@@ -738,50 +707,6 @@ __global__ void __launch_bounds__(256) k_f_pass1(TlArgs a, BucketOut o) {
   __syncthreads();
   if (tid == 0 && sm.bad)
     atomicAdd((unsigned long long *)&o.diag->bad_records, (unsigned long long)sm.bad);
-}
-
-// count validation (Sec. 3.3): per name, eligible launches against rows;
-// run by one block of up to 1024 threads
-__device__ void names_check(const uint32_t *__restrict__ tlc, const uint32_t *__restrict__ pfc,
-                            uint32_t NN, uint32_t *name_counts, opattr_diag *diag, int strict) {
-  __shared__ unsigned long long red[3][16];
-  unsigned long long mism = 0, tlu = 0, pfu = 0;
-  for (uint32_t n = threadIdx.x; n < NN; n += blockDim.x) {
-    const uint32_t tl = tlc[n], pf = pfc[n];
-    if (name_counts) {
-      name_counts[2 * (size_t)n] = tl;
-      name_counts[2 * (size_t)n + 1] = pf;
-    }
-    if (tl != pf) {
-      mism++;
-      if (tl > pf) tlu += tl - pf;
-      else pfu += pf - tl;
-    }
-  }
-  mism = wave_reduce_add(mism);
-  tlu = wave_reduce_add(tlu);
-  pfu = wave_reduce_add(pfu);
-  if (lane_id() == 0) {
-    red[0][wave_id()] = mism;
-    red[1][wave_id()] = tlu;
-    red[2][wave_id()] = pfu;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    unsigned long long a = 0, b = 0, c = 0;
-    for (uint32_t i = 0; i < blockDim.x / OPA_WAVE; ++i) {
-      a += red[0][i];
-      b += red[1][i];
-      c += red[2][i];
-    }
-    if (a) {
-      atomicAdd(&diag->names_mismatched, (uint32_t)a);
-      atomicOr(&diag->flags, OPATTR_F_COUNT);
-    }
-    if (b) atomicAdd((unsigned long long *)&diag->tl_unmatched, b);
-    if (c) atomicAdd((unsigned long long *)&diag->pf_unmatched, c);
-    if (strict) diag->strict = 1u;
-  }
 }
 
 __global__ void __launch_bounds__(1024) k_names(const uint32_t *__restrict__ tlc,

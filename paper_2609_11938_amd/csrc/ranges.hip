@@ -393,8 +393,8 @@ void write_range_parents(const CoreRanges &cr, void *ws, const Plan &pl, int32_t
         cr, at<int64_t>(ws, pl.ree), at<int32_t>(ws, pl.npg), range_parent);
 }
 
-CoreRanges prepare_ranges(const opattr_ranges *r, const opattr_dims *d, void *ws, const Plan &pl,
-                          opattr_diag *diag, bool validate, hipStream_t s, const FillJobs *extra) {
+CoreRanges order_ranges(const opattr_ranges *r, void *ws, const Plan &pl, opattr_diag *diag,
+                        bool validate, hipStream_t s) {
   CoreRanges cr;
   cr.n = pl.R;
   const int64_t R = pl.R;
@@ -427,6 +427,13 @@ CoreRanges prepare_ranges(const opattr_ranges *r, const opattr_dims *d, void *ws
     cr.kind = nullptr;
     cr.perm = nullptr;
   }
+  return cr;
+}
+
+CoreRanges prepare_ranges(const opattr_ranges *r, const opattr_dims *d, void *ws, const Plan &pl,
+                          opattr_diag *diag, bool validate, hipStream_t s, const FillJobs *extra) {
+  const CoreRanges cr = order_ranges(r, ws, pl, diag, validate, s);
+  const int64_t R = pl.R;
   const uint32_t NS = d->n_streams;
   int64_t *rblk = at<int64_t>(ws, pl.rblk);
   // the clears: the caller's and the crossing flags

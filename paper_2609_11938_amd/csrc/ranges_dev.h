@@ -75,6 +75,10 @@ struct RangeWork {
 };
 
 
+// (ranges.hip)
+RangeWork range_work(const CoreRanges &cr, const opattr_dims *d, void *ws, const Plan &pl,
+                     opattr_diag *diag);
+
 // A maximum tree in LDS over kRangeTile values: leaf i at t[kRangeTile + i],
 // node n covers the leaves of 2n and 2n + 1. Finding a nearest previous
 // greater-or-equal value in it takes at most 2 log2(kRangeTile) LDS reads,

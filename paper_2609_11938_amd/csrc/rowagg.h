@@ -1,0 +1,601 @@
+// Device code of the aggregation by operator row shared by the fused path's
+// kernels and the compact path's: partial results, the reduction of a block of
+// launches ordered by row, the table in LDS, and the rows of the table.
+#pragma once
+#include "accum.h"
+#include "common.h"
+#include "impl.h"
+
+namespace opa {
+
+constexpr int kFFields = 25;                   // kc, tns, mc, mns, 20 counters, NaN bits
+constexpr int kBuckets = 256;                  // buckets of operator rows
+// A block's bucket entries: the buckets, then the unattributed row (NOPS) on
+// its own: it has a partial in almost every block, which would make its
+// bucket's combine waves the last to finish by far.
+constexpr int kBktStride = kBuckets + 1;
+constexpr int kRThreads = 256;
+
+// LDS of k_r_agg: the row histogram, later the crossing rows' slots
+__host__ __device__ inline uint32_t r_hist_words(uint32_t G) { return (G + 1) / 2; }
+inline size_t r_agg_lds(uint32_t G) {
+  const size_t h = (size_t)r_hist_words(G) * 4, sl = (size_t)kRThreads * kFFields * 8;
+  return h > sl ? h : sl;
+}
+
+
+// vector of kN 32-bit elements (at most 16 bytes)
+template <int kN> struct VecOf { using type = uint4; };
+template <> struct VecOf<2> { using type = uint2; };
+template <> struct VecOf<1> { using type = uint32_t; };
+
+// kN consecutive 32-bit elements from p[i..), vector loads when aligned
+template <int kN, typename T>
+__device__ __forceinline__ void load_n(const T *p, int64_t i, int nv, T (&o)[kN]) {
+  static_assert(sizeof(T) == 4 && (kN <= 2 || kN % 4 == 0), "32-bit elements, whole vectors");
+  using V = typename VecOf<kN>::type;
+  constexpr int kB = (int)sizeof(V);
+  if (nv == kN && (reinterpret_cast<uintptr_t>(p + i) & (kB - 1)) == 0) {
+    const V *v = reinterpret_cast<const V *>(p + i);
+#pragma unroll
+    for (int q = 0; q < kN * 4 / kB; ++q) {
+      const V t = v[q];
+      memcpy(reinterpret_cast<char *>(o) + kB * q, &t, kB);
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < kN; ++k) o[k] = k < nv ? p[i + k] : T(0);
+  }
+}
+
+template <int kN, typename T>
+__device__ __forceinline__ void store_n(T *p, int64_t i, int nv, const T (&o)[kN]) {
+  using V = typename VecOf<kN>::type;
+  constexpr int kB = (int)sizeof(V);
+  if (nv == kN && (reinterpret_cast<uintptr_t>(p + i) & (kB - 1)) == 0) {
+    V *v = reinterpret_cast<V *>(p + i);
+#pragma unroll
+    for (int q = 0; q < kN * 4 / kB; ++q) {
+      V t;
+      memcpy(&t, reinterpret_cast<const char *>(o) + kB * q, kB);
+      v[q] = t;
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < kN; ++k)
+      if (k < nv) p[i + k] = o[k];
+  }
+}
+
+__device__ __forceinline__ void wave_sync_lds() {
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// a += partial result of some launches of row g, one lane at a time
+// (device-scope atomics; only for what a block cannot keep)
+__device__ __forceinline__ void acc_to_table(PartRow *acc, uint32_t g, const Acc &a,
+                                             uint32_t mx) {
+  PartRow *r = acc + g;
+  atomicAdd(&r->kc, a.kc);
+  atomicAdd(&r->tns, a.tns);
+  if (a.mc == 0) return;  // no counter row reached: every counter field is still zero
+  atomicAdd(&r->mc, a.mc);
+  atomicAdd(&r->mns, a.mns);
+#pragma unroll
+  for (int c = 0; c < OPATTR_NUM_COUNTERS; ++c) {
+    if ((mx >> c) & 1u) atomicMax(&r->v[c], a.v[c]);
+    else unsafeAtomicAdd(reinterpret_cast<double *>(&r->v[c]), bits2d(a.v[c]));
+  }
+  if (a.nan) atomicOr(&r->nan, a.nan);
+}
+
+// one lane's partial result to parts[x] (row g)
+__device__ __forceinline__ void part_store(PartRow *parts, size_t x, uint32_t g, const Acc &a) {
+  unsigned long long *d = reinterpret_cast<unsigned long long *>(parts + x);
+  d[0] = a.kc;
+  d[1] = a.tns;
+  d[2] = a.mc;
+  d[3] = a.mns;
+#pragma unroll
+  for (int c = 0; c < OPATTR_NUM_COUNTERS; ++c) d[4 + c] = a.v[c];
+  d[24] = (unsigned long long)a.nan | ((unsigned long long)g << 32);
+}
+
+// a lane's partial result added into an LDS slot
+__device__ __forceinline__ void slot_add(unsigned long long *q, const Acc &a, uint32_t mx) {
+  atomicAdd(&q[0], a.kc);
+  atomicAdd(&q[1], a.tns);
+  if (a.mc == 0) return;  // no counter row reached
+  atomicAdd(&q[2], a.mc);
+  atomicAdd(&q[3], a.mns);
+#pragma unroll
+  for (int c = 0; c < OPATTR_NUM_COUNTERS; ++c) {
+    if ((mx >> c) & 1u) atomicMax(&q[4 + c], a.v[c]);
+    else unsafeAtomicAdd(reinterpret_cast<double *>(&q[4 + c]), bits2d(a.v[c]));
+  }
+  if (a.nan) atomicOr(reinterpret_cast<unsigned int *>(&q[24]), a.nan);
+}
+
+// What a block of the row-ordered reduction writes to.
+struct RowOut {
+  uint32_t NOPS, rb;  // rb: operator rows per bucket
+  PartRow *acc;       // [G] row accumulators for what finds no room (zeroed)
+  PartRow *parts;     // kept partials, each block's by bucket (row in pad)
+  uint32_t *bkt;      // [blocks][kBktStride] offset << 16 | count
+  uint32_t *pbase;    // [blocks] first partial of each block
+  uint32_t *pcount;   // partials kept so far (zero at launch)
+  uint32_t pcap;      // partials there is room for
+};
+template <int kPer>
+struct RowLds {
+  uint2 md[kRThreads * kPer];     // match and duration, in row order
+  uint16_t sg[kRThreads * kPer];  // row, in row order
+  uint16_t hx[kRThreads + 1];     // row starts before each thread's positions
+  uint8_t hms[kRThreads];
+  uint8_t ord[kRThreads / OPA_WAVE][OPA_WAVE];
+  uint32_t sh[4], sbase;
+};
+constexpr int kMidLanes = 6;  // lanes inside one row above which they are added up first
+
+// The reduction of one block of launches (the thread's kPer consecutive ones:
+// match mt, duration du, row g, nv of them exist; nb in the block), by a
+// whole block of kRThreads. raw: r_agg_lds bytes, its first r_hist_words
+// words zeroed.
+template <bool DEF, int kPer>
+__device__ __forceinline__ void row_order_block(const RowOut &o, const AggIn &in, int64_t blk,
+                                                int nb, int nv, const int32_t (&mt)[kPer],
+                                                const uint32_t (&du)[kPer],
+                                                const uint32_t (&g)[kPer], unsigned char *raw,
+                                                RowLds<kPer> &lds) {
+  uint32_t *hist = reinterpret_cast<uint32_t *>(raw);  // two rows a word
+  unsigned long long *slots = reinterpret_cast<unsigned long long *>(raw);
+  auto &md = lds.md;
+  auto &sg = lds.sg;
+  auto &hx = lds.hx;
+  auto &hms = lds.hms;
+  auto &sh = lds.sh;
+  auto &sbase = lds.sbase;
+  const int tid = threadIdx.x, ln = lane_id(), w = wave_id();
+  const uint32_t mx = DEF ? kDefMaxMask : in.maxmask, dw = DEF ? kDefDwMask : in.dwmask;
+  const uint32_t words = r_hist_words(o.NOPS + 1u);
+  uint32_t rk[kPer];
+  __syncthreads();
+  // rank of every launch in its row: one atomic per run of the thread
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    if (k >= nv) continue;
+    if (k > 0 && g[k] == g[k - 1]) {
+      rk[k] = rk[k - 1] + 1u;
+      continue;
+    }
+    uint32_t len = 1;
+#pragma unroll
+    for (int j = 1; j < kPer; ++j)
+      if (k + j < nv && len == (uint32_t)j && g[k + j < kPer ? k + j : 0] == g[k]) ++len;
+    const int s16 = (int)(g[k] & 1u) * 16;
+    rk[k] = (atomicAdd(&hist[g[k] >> 1], len << s16) >> s16) & 0xFFFFu;
+  }
+  __syncthreads();
+  // first position of every row: each thread scans a stretch of the words
+  // (an odd count of them, so that the stretches start in different banks)
+  const uint32_t ch = ((words + kRThreads - 1) / kRThreads) | 1u;
+  const uint32_t wlo = tid * ch, whi = wlo + ch < words ? wlo + ch : words;
+  uint32_t mine = 0;
+  for (uint32_t x = wlo; x < whi; ++x) mine += (hist[x] & 0xFFFFu) + (hist[x] >> 16);
+  uint32_t run = block_excl_scan_add<uint32_t>(mine, sh, nullptr);
+  for (uint32_t x = wlo; x < whi; ++x) {
+    const uint32_t v = hist[x];
+    hist[x] = run | ((run + (v & 0xFFFFu)) << 16);
+    run += (v & 0xFFFFu) + (v >> 16);
+  }
+  __syncthreads();
+  auto row_pos = [&](uint32_t r) -> uint32_t {  // first position of row r (r <= NOPS)
+    return (hist[r >> 1] >> ((r & 1u) * 16)) & 0xFFFFu;
+  };
+#pragma unroll
+  for (int k = 0; k < kPer; ++k)
+    if (k < nv) {
+      const uint32_t p = row_pos(g[k]) + rk[k];
+      md[p] = make_uint2((uint32_t)mt[k], du[k]);
+      sg[p] = (uint16_t)g[k];
+    }
+  // positions at which this thread's bucket starts and ends (kBuckets
+  // threads), and the unattributed row's first
+  const uint32_t bl = (uint32_t)tid * o.rb, bh = bl + o.rb;
+  const uint32_t p_lo = row_pos(bl < o.NOPS ? bl : o.NOPS), p_hi = row_pos(bh < o.NOPS ? bh : o.NOPS);
+  const uint32_t p_un = row_pos(o.NOPS);
+  __syncthreads();  // the histogram's space becomes the slots
+  // row starts among the thread's positions (a wave's first position is one)
+  const int p0 = tid * kPer;
+  uint32_t hm = 0;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    const int p = p0 + k;
+    if (p < nb && ((ln == 0 && k == 0) || p == 0 || sg[p] != sg[p - 1])) hm |= 1u << k;
+  }
+  uint32_t nh;
+  const uint32_t h0 = block_excl_scan_add<uint32_t>((uint32_t)__popc(hm), sh, &nh);
+  hx[tid] = (uint16_t)h0;
+  hms[tid] = (uint8_t)hm;
+  if (tid == 0) {
+    hx[kRThreads] = (uint16_t)nh;
+    // room for the block's partials; a block that finds none left adds its
+    // results to the row accumulators
+    uint32_t base = atomicAdd(o.pcount, nh);
+    if (base > o.pcap || nh > o.pcap - base) base = 0xFFFFFFFFu;
+    sbase = base;
+  }
+  unsigned long long *wslot = slots + (size_t)w * OPA_WAVE * kFFields;
+  for (int x = ln; x < OPA_WAVE * kFFields; x += OPA_WAVE) wslot[x] = 0;
+  __syncthreads();
+  const uint32_t base = sbase;
+  const bool keep = base != 0xFFFFFFFFu;
+  auto starts_before = [&](uint32_t p) -> uint32_t {  // row starts at positions below p
+    const uint32_t t = p / kPer;
+    return t >= (uint32_t)kRThreads ? nh
+                                    : hx[t] + (uint32_t)__popc(hms[t] & ((1u << (p % kPer)) - 1u));
+  };
+  {
+    const uint32_t first = starts_before(p_lo), e = starts_before(p_hi), u = starts_before(p_un);
+    o.bkt[blk * kBktStride + tid] = keep ? (first << 16) | (e - first) : 0u;
+    if (tid == 0) {
+      o.bkt[blk * kBktStride + kBuckets] = keep ? (u << 16) | (nh - u) : 0u;
+      o.pbase[blk] = keep ? base : 0u;
+    }
+  }
+  // the lane's launches; kind of a piece: started in an earlier lane (its
+  // slot's lane is the nearest below with a row start), started here
+  const unsigned long long hl = __ballot(hm != 0);
+  const unsigned long long below = hl & lanemask_lt();
+  const int from = below ? 63 - __clzll((long long)below) : 0;
+  const int np = nb - p0 < 0 ? 0 : (nb - p0 < kPer ? nb - p0 : kPer);
+  // the next lane goes on with this lane's last row
+  const uint32_t np_n = __shfl_down((uint32_t)np, 1, OPA_WAVE), hm_n = __shfl_down(hm, 1, OPA_WAVE);
+  const bool out = ln < OPA_WAVE - 1 && np_n > 0 && (hm_n & 1u) == 0;
+  Acc acc;
+  acc_zero(acc);
+  bool here = false;  // the piece started in this lane
+  uint32_t hi = h0;   // row starts before the piece
+  uint32_t gc = 0;
+  auto flush_inside = [&]() {  // a row that ends in this lane
+    if (!here) slot_add(wslot + (size_t)from * kFFields, acc, mx);
+    else if (keep) part_store(o.parts, (size_t)base + hi, gc, acc);
+    else acc_to_table(o.acc, gc, acc, mx);
+  };
+#pragma unroll 1
+  for (int k = 0; k < kPer; ++k) {
+    if (k >= np) break;
+    if ((hm >> k) & 1u) {
+      if (k > 0) {
+        flush_inside();
+        acc_zero(acc);
+        if (here) ++hi;
+      }
+      here = true;
+      gc = sg[p0 + k];
+    }
+    const uint2 e = md[p0 + k];
+    acc_launch(acc, in, (int32_t)e.x, e.y, mx, dw);
+  }
+  const bool mine_out = here && out;  // this lane's slot holds a row that goes on
+  // lanes inside one row: where they are many, they are added up across the
+  // lanes first (LDS atomics on one address go one after the other), and the
+  // last one adds their total to the slot of the lane the row starts in
+  const bool mid = np > 0 && hm == 0;
+  if (__popcll(__ballot(mid)) >= kMidLanes) {
+    acc_seg_scan(acc, hm != 0 ? ln : from, mx);
+    const bool last = ln == OPA_WAVE - 1 || np_n == 0 || hm_n != 0;
+    if (np > 0 && last) {
+      if (mid) slot_add(wslot + (size_t)from * kFFields, acc, mx);
+      else if (mine_out) slot_add(wslot + (size_t)ln * kFFields, acc, mx);
+      else flush_inside();
+    }
+  } else if (np > 0) {
+    if (mine_out) slot_add(wslot + (size_t)ln * kFFields, acc, mx);
+    else flush_inside();
+  }
+  const unsigned long long live = __ballot(mine_out);
+  const int nl = __popcll(live);
+  uint8_t *ord = lds.ord[w];  // the live lanes in order
+  if (mine_out) ord[__popcll(live & lanemask_lt())] = (uint8_t)ln;
+  wave_sync_lds();
+  // the crossing rows, coalesced: consecutive lanes take consecutive fields
+  for (int x = ln; x < nl * kFFields; x += OPA_WAVE) {
+    const int r = x / kFFields, f = x - r * kFFields, s = ord[r];
+    const int st = w * OPA_WAVE + s;  // its thread: the slot's row is the thread's last start
+    const uint32_t hs = hms[st];
+    const uint32_t sk = 31u - (uint32_t)__clz((int)hs);
+    const uint32_t row = sg[st * kPer + (int)sk];
+    const uint32_t idx = hx[st] + (uint32_t)__popc(hs) - 1u;
+    const unsigned long long v = wslot[(size_t)s * kFFields + f];
+    if (keep) {
+      unsigned long long *d = reinterpret_cast<unsigned long long *>(o.parts + (size_t)base + idx);
+      d[f] = f < 24 ? v : ((v & 0xFFFFFFFFull) | ((unsigned long long)row << 32));
+    } else {
+      unsigned long long *d = reinterpret_cast<unsigned long long *>(o.acc + row);
+      if (f < 4) {
+        atomicAdd(&d[f], v);
+      } else if (f < 24) {
+        if ((mx >> (f - 4)) & 1u) atomicMax(&d[f], v);
+        else unsafeAtomicAdd(reinterpret_cast<double *>(&d[f]), bits2d(v));
+      } else if ((uint32_t)v) {
+        atomicOr(reinterpret_cast<unsigned int *>(&d[24]), (uint32_t)v);
+      }
+    }
+  }
+}
+
+constexpr int kTThreads = 1024;
+constexpr int kTHot = 12;   // lanes of one row above which they are reduced first
+constexpr int kTSegs = 40;  // stretches of lanes of one row up to which they are scanned
+
+// the thread's kPer consecutive launches (nv of them exist) added to the
+// block's table in LDS
+template <bool DEF, int kPer>
+__device__ __forceinline__ void tab_add(unsigned long long *tab, const AggIn &in, int nv,
+                                        int32_t (&mt)[kPer], uint32_t (&du)[kPer],
+                                        uint32_t (&g)[kPer]) {
+  const uint32_t mx = DEF ? kDefMaxMask : in.maxmask, dw = DEF ? kDefDwMask : in.dwmask;
+  const int ln = lane_id();
+  Acc acc;
+  acc_zero(acc);
+  const uint32_t g0 = g[0];
+  uint32_t gc = g0;
+  bool changed = false;
+  // launch k is always at position 0 of the arrays (see k_f_agg)
+#pragma unroll 1
+  for (int k = 0; k < kPer; ++k) {
+    if (k < nv) {
+      if (g[0] != gc) {
+        slot_add(tab + (size_t)gc * kFFields, acc, mx);
+        acc_zero(acc);
+        gc = g[0];
+        changed = true;
+      }
+      acc_launch(acc, in, mt[0], du[0], mx, dw);
+    }
+#pragma unroll
+    for (int j = 0; j + 1 < kPer; ++j) {
+      mt[j] = mt[j + 1];
+      du[j] = du[j + 1];
+      g[j] = g[j + 1];
+    }
+  }
+  // Each lane's last piece. Neighbouring lanes of one row are added up across
+  // the lanes first (a lane belongs to the one before it when it holds only
+  // that lane's last row): with LDS atomics alone, lanes of one row go one
+  // after the other, 24 fields each. Launches in an order of their own have
+  // few neighbours; a row that many lanes hold is then reduced on its own.
+  const uint32_t gp = __shfl_up(gc, 1, OPA_WAVE);
+  const bool start = ln == 0 || changed || nv == 0 || g0 != gp;
+  const unsigned long long sm = __ballot(start);
+  const unsigned long long act = __ballot(nv > 0);
+  if (__popcll(sm & act) <= kTSegs) {
+    const unsigned long long upto = ln == OPA_WAVE - 1 ? sm : sm & ((2ull << ln) - 1);
+    acc_seg_scan(acc, 63 - __clzll((long long)upto), mx);
+    const bool last = ln == OPA_WAVE - 1 || ((sm >> (ln + 1)) & 1ull);
+    if (nv > 0 && last) slot_add(tab + (size_t)gc * kFFields, acc, mx);
+    return;
+  }
+  const uint32_t gm = (uint32_t)__builtin_amdgcn_readlane((int)gc, 31);
+  const bool in_hot = nv > 0 && gc == gm;
+  if (__popcll(__ballot(in_hot)) >= kTHot) {
+    Acc t = acc;
+    if (!in_hot) acc_zero(t);
+    acc_wave_reduce(t, mx);
+    if (ln == 0) slot_add(tab + (size_t)gm * kFFields, t, mx);
+    if (nv > 0 && !in_hot) slot_add(tab + (size_t)gc * kFFields, acc, mx);
+  } else if (nv > 0) {
+    slot_add(tab + (size_t)gc * kFFields, acc, mx);
+  }
+}
+
+__device__ __forceinline__ unsigned long long merge_field(int f, unsigned long long x,
+                                                          unsigned long long y, uint32_t mx) {
+  if (f < 4) return x + y;
+  if (f < 24) return ((mx >> (f - 4)) & 1u) ? (x > y ? x : y) : d2bits(bits2d(x) + bits2d(y));
+  return x | y;
+}
+
+// output field o (four counts, then the counters) of a row from its 25
+// accumulated fields p
+__device__ __forceinline__ unsigned long long row_field(const unsigned long long *p, int o,
+                                                        uint32_t absent, uint32_t mx, uint32_t dw) {
+  if (o < 4) return p[o];
+  const int c = o - 4;
+  const unsigned long long qnan = 0x7FF8000000000000ull;
+  if (((absent >> c) & 1u) || p[2] == 0) return qnan;
+  if ((mx >> c) & 1u) return (((uint32_t)p[24] >> c) & 1u) ? qnan : d2bits((double)key2f((uint32_t)p[o]));
+  if ((dw >> c) & 1u) return p[3] ? d2bits(bits2d(p[o]) / (double)p[3]) : qnan;
+  return p[o];
+}
+
+// t (one field f of an LDS row) += the field's value x
+__device__ __forceinline__ void field_add(unsigned long long *t, int f, unsigned long long x,
+                                          uint32_t mx) {
+  if (f < 4) {
+    atomicAdd(t, x);
+  } else if (f < 24) {
+    if ((mx >> (f - 4)) & 1u) atomicMax(t, x);
+    else unsafeAtomicAdd(reinterpret_cast<double *>(t), bits2d(x));
+  } else if ((uint32_t)x) {
+    atomicOr(reinterpret_cast<unsigned int *>(t), (uint32_t)x);
+  }
+}
+
+
+struct CombParams {
+  int64_t nblocks;
+  uint32_t rb, G, NOPS;
+  uint32_t mx, dw, absent;
+  const PartRow *parts;
+  const uint32_t *bkt, *pbase;
+  PartRow *split;              // [kBuckets][kSplits][rb]
+  PartRow *hot;                // [kHot] the unattributed row's shares
+  const PartRow *acc;          // [G] row accumulators (the blocks' overflow)
+  opattr_op_row *table;
+  unsigned long long *part;    // [kBuckets][4] summary sums per bucket
+  // the finalisation, by the last block of the per-row reduction to finish
+  uint32_t *done;              // blocks finished (zero at launch)
+  opattr_diag *diag;
+  const uint8_t *sflag;        // [ns] per-stream crossing flags
+  uint32_t ns;
+  opattr_summary *sum;
+};
+
+// The partials of a wave's bucket entries (per lane kPre entries: ev partials
+// from xv on, mine in all) added into an LDS table of rb rows, field by field:
+// the partials are listed in LDS and read with 25 lanes each (two per load
+// instruction, kBatch in flight), so that a partial costs two cache lines of
+// requests instead of 25.
+constexpr int kList = 512;                     // partials a combine wave lists in LDS at once
+constexpr int kBatch = 8;                      // partial loads per lane in flight
+template <int kPre>
+__device__ __forceinline__ void comb_add(unsigned long long *tab, uint32_t *list,
+                                         const unsigned long long *parts64,
+                                         const uint32_t (&ev)[kPre], const uint32_t (&xv)[kPre],
+                                         uint32_t mine, uint32_t rb, uint32_t mx) {
+  const int ln = lane_id(), half = ln >> 5, f = ln & 31;
+  const uint32_t incl = wave_incl_scan_add<uint32_t>(mine);
+  const uint32_t n = __shfl(incl, OPA_WAVE - 1, OPA_WAVE);
+  if (n == 0) return;
+  if (n <= (uint32_t)kList) {
+    // the partials listed in LDS, then read by 25 lanes each (two
+    // partials per instruction, kBatch instructions in flight) and added
+    // field by field
+    uint32_t w = incl - mine;
+#pragma unroll
+    for (int k = 0; k < kPre; ++k) {
+      for (uint32_t p = 0; p < ev[k]; ++p) list[w++] = xv[k] + p;
+    }
+    wave_sync_lds();
+    for (uint32_t i = 0; i < n; i += 2 * kBatch) {
+      unsigned long long v[kBatch];
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j) {
+        const uint32_t idx = i + 2 * j + half;
+        v[j] = (idx < n && f < kFFields)
+                   ? parts64[(size_t)list[idx] * (sizeof(PartRow) / 8) + f] : 0ull;
+      }
+#pragma unroll
+      for (int j = 0; j < kBatch; ++j) {
+        const uint32_t g = (uint32_t)(__shfl(v[j], (ln & 32) + 24, OPA_WAVE) >> 32);
+        const uint32_t idx = i + 2 * j + half;
+        if (idx < n && f < kFFields) field_add(tab + (size_t)(g % rb) * kFFields + f, f, v[j], mx);
+      }
+    }
+  } else {
+    // more partials than the list holds (rare): one lane's entry at a
+    // time, its partials read two at a time by 25 lanes each
+#pragma unroll 1
+    for (int k = 0; k < kPre; ++k) {
+      uint32_t e = 0, xe = 0;
+#pragma unroll
+      for (int j = 0; j < kPre; ++j) {
+        e = k == j ? ev[j] : e;
+        xe = k == j ? xv[j] : xe;
+      }
+      for (uint64_t m = __ballot(e != 0); m; m &= m - 1) {
+        const int src = __ffsll((unsigned long long)m) - 1;
+        const uint32_t c = __shfl(e, src, OPA_WAVE);
+        const uint64_t x0 = __shfl(xe, src, OPA_WAVE);
+        for (uint32_t p = 0; p < c; p += 2) {
+          const uint32_t pp = p + half;
+          const unsigned long long v = (pp < c && f < kFFields)
+              ? parts64[(x0 + pp) * (sizeof(PartRow) / 8) + f] : 0ull;
+          const uint32_t g = (uint32_t)(__shfl(v, (ln & 32) + 24, OPA_WAVE) >> 32);
+          if (pp < c && f < kFFields) field_add(tab + (size_t)(g % rb) * kFFields + f, f, v, mx);
+        }
+      }
+    }
+  }
+}
+
+// The blocks' tables added up, kTRows rows a block (one element per thread
+// and share of the tables), and the table rows. With kLast the blocks also
+// leave their summary sums and the last one to finish writes the summary and
+// the status; without, the launches' blocks left the sums (a.part) and the
+// block after the rows' does that.
+constexpr int kTRows = 4, kTShares = 10;
+static_assert(kTRows * kFFields * kTShares <= 1024, "one block");
+
+template <bool DEF, bool kLast>
+__global__ void __launch_bounds__(1024) k_t_rows(CombParams a, const unsigned long long *tabs,
+                                                 int ntabs) {
+  constexpr int kEl = kTRows * kFFields;
+  if (!kLast && blockIdx.x * kTRows >= a.G) {
+    finish_block(a.diag, a.sflag, a.ns, a.part, ntabs, a.sum);
+    return;
+  }
+  __shared__ unsigned long long part[kTShares][kEl];
+  __shared__ unsigned long long red[4][kTRows];
+  const uint32_t mx = DEF ? kDefMaxMask : a.mx, dw = DEF ? kDefDwMask : a.dw;
+  const int tid = threadIdx.x, sh = tid / kEl, e = tid - sh * kEl, f = e % kFFields;
+  const uint32_t g0 = blockIdx.x * kTRows, ne = a.G * kFFields;
+  const uint32_t x = g0 * kFFields + e;
+  if (sh < kTShares && x < ne) {
+    unsigned long long v = 0;
+    constexpr int kB = 16;
+    for (int t0 = sh; t0 < ntabs; t0 += kTShares * kB) {
+      unsigned long long y[kB];
+#pragma unroll
+      for (int j = 0; j < kB; ++j) {
+        const int t = t0 + j * kTShares;
+        y[j] = t < ntabs ? tabs[(size_t)t * ne + x] : 0ull;
+      }
+#pragma unroll
+      for (int j = 0; j < kB; ++j)
+        if (t0 + j * kTShares < ntabs) v = merge_field(f, v, y[j], mx);
+    }
+    part[sh][e] = v;
+  }
+  __syncthreads();
+  if (tid < kEl && x < ne) {
+    unsigned long long v = part[0][tid];
+#pragma unroll
+    for (int s = 1; s < kTShares; ++s) v = merge_field(f, v, part[s][tid], mx);
+    part[0][tid] = v;
+  }
+  __syncthreads();
+  // 24 output fields a row
+  if (tid < kTRows * 24) {
+    const int r = tid / 24, o = tid - r * 24;
+    const uint32_t g = g0 + r;
+    if (g < a.G) {
+      const unsigned long long *p = part[0] + r * kFFields;
+      unsigned long long *row = reinterpret_cast<unsigned long long *>(a.table + g);
+      row[o] = row_field(p, o, a.absent, mx, dw);
+      if (o == 0) {
+        red[0][r] = g < a.NOPS ? p[1] : 0ull;
+        red[1][r] = g < a.NOPS ? 0ull : p[1];
+        red[2][r] = p[1];
+        red[3][r] = p[3];
+      }
+    } else if (o == 0) {
+      red[0][r] = red[1][r] = red[2][r] = red[3][r] = 0;
+    }
+  }
+  if (!kLast) return;
+  __syncthreads();
+  if (tid < 4) {
+    unsigned long long v = 0;
+    for (int r = 0; r < kTRows; ++r) v += red[tid][r];
+    a.part[blockIdx.x * 4 + tid] = v;
+  }
+  __shared__ uint32_t last;
+  if (tid < OPA_WAVE) {
+    __threadfence();
+    uint32_t l = 0;
+    if (tid == 0) l = atomicAdd(a.done, 1u) == gridDim.x - 1 ? 1u : 0u;
+    l = __shfl(l, 0);
+    if (l) __threadfence();
+    if (tid == 0) last = l;
+  }
+  __syncthreads();
+  if (!last) return;
+  finish_block(a.diag, a.sflag, a.ns, a.part, (int)gridDim.x, a.sum);
+}
+
+}  // namespace opa

@@ -134,6 +134,32 @@ def test_row_order_edges(T, per_range, n_ops, S):
     parity.assert_attribute(out, want, diag)
 
 
+@pytest.mark.parametrize("T,S,n_names,n_ops,order", [
+    (1, 1, 1, 1, "any"), (1024, 3, 2048, 40, "any"), (1025, 3, 2048, 900, "gaps"),
+    (1023, 2, 2049, 40, "stream"),            # more names than the compact tiles count
+    (70_001, 5, 33, 703, "gaps"), (70_001, 5, 33, 704, "any"),
+    (2 ** 18 + 3, 4, 700, 60, "any"),         # four launches a thread of a tile from here on
+    (2 ** 20, 7, 300, 500, "stream"), (2 ** 20, 7, 300, 5000, "gaps"),
+    (40_000, 1000, 20, 300, "any"),           # a range tile per stream
+])
+def test_compact_edges(T, S, n_names, n_ops, order):
+    """At most a million launches in any order: tile and block edges, the
+    most names, streams and rows of each form, dense seq in any order and
+    seq with gaps, duplicate layers, drops, more rows than launches."""
+    tr = cases.random_trace(6500 + T % 991 + S, T=T, S=S, n_names=n_names, R=T // 6, n_ops=n_ops,
+                            t_max=8 * T + 8, max_depth=5, dedup=T > 100, drop=0.02,
+                            extra_pf=0.5 if T < 2000 else 0.01, seq_gaps=order == "gaps")
+    flags = {"any": opattr.SEQ_DENSE, "gaps": 0, "stream": HINTS}[order]
+    if order == "stream":
+        tr, _, _ = cases.stream_major(tr)  # and starts that do not decrease along a stream
+        tr["start_ns"] = tr["start_ns"][np.lexsort((tr["start_ns"], tr["stream_id"]))]
+    print(f"case compact T={T} S={S} names={n_names} ops={n_ops} {order}", flush=True)
+    for extra in (0, opattr.VALIDATE):
+        want = O.attribute(tr)
+        out, diag = _run(tr, flags=flags | extra)
+        parity.assert_attribute(out, want, diag)
+
+
 @pytest.mark.parametrize("kinds", [False, True])
 def test_row_order_more_partials_than_room(kinds):
     """Query points that jump back and forth change the innermost range far
