@@ -194,7 +194,7 @@ RangeWork range_work(const CoreRanges &cr, const opattr_dims *d, void *ws, const
 // ---------------------------------------------------------------------------
 // Nesting order of ranges given in any order: a merge sort of the records
 // (stream, start, end, index) by stream asc, start asc, end desc, index asc.
-// Blocks first sort tiles of kRsTile records in LDS (bitonic network), then
+// Blocks first sort tiles of kRsSort records in LDS, then
 // each pass merges pairs of sorted runs; a block takes kRsTile outputs of one
 // pair, finds where they begin in each run along the merge path (a search on
 // the diagonal, 64 probes per step across a wave), stages the two slices in
@@ -257,32 +257,85 @@ __device__ __forceinline__ void rrec_store(const RSortBuf &b, const RSortOut &f,
   }
 }
 
-__global__ void __launch_bounds__(kRsThreads) k_rsort_tile(const opattr_ranges r, int64_t R,
-                                                           RSortBuf out, RSortOut f, int last) {
-  __shared__ RsLds t;
-  const int tid = threadIdx.x;
-  const int64_t base = (int64_t)blockIdx.x * kRsTile;
-  for (int k = tid; k < kRsTile; k += kRsThreads) {
-    const int64_t i = base + k;
-    // records past R sort after every real one (streams are 16-bit)
-    t.put(k, i < R ? RRec{r.start_ns[i], r.end_ns[i], (uint32_t)i, r.stream_id[i]}
-                   : RRec{~0ull, 0ull, 0xFFFFFFFFu, 0xFFFFFFFFu});
+// Tiles of kRsSort records sorted in LDS by merging: runs double in length
+// per round; a record's place in the merged run is its place in its own run
+// plus the count of the other run's records before it (a binary search). 10
+// rounds of at most 10 LDS steps, one record per thread, against 55 rounds of
+// a bitonic network at two pairs a thread (39 us). Tiles of 4096, four records
+// a thread, took 97 us: LDS reads bound them.
+constexpr int kRsSort = 1024, kRsSortThreads = 1024, kRsSortPer = kRsSort / kRsSortThreads;
+struct RsSortLds {
+  uint64_t s[kRsSort], e[kRsSort];
+  uint32_t x[kRsSort], st[kRsSort];
+  __device__ __forceinline__ RRec get(int k) const { return RRec{s[k], e[k], x[k], st[k]}; }
+  __device__ __forceinline__ void put(int k, const RRec &r) {
+    s[k] = r.s;
+    e[k] = r.e;
+    x[k] = r.x;
+    st[k] = r.st;
   }
-  __syncthreads();
-  for (int k = 2; k <= kRsTile; k <<= 1)
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int q = tid; q < kRsTile / 2; q += kRsThreads) {
-        const int i = 2 * q - (q & (j - 1)), p = i + j;
-        const RRec a = t.get(i), b = t.get(p);
-        if (rrec_less(b, a) == ((i & k) == 0)) {
-          t.put(i, b);
-          t.put(p, a);
-        }
-      }
-      __syncthreads();
+  // whether record k precedes r; the end and the index are read only on ties
+  __device__ __forceinline__ bool less(int k, const RRec &r) const {
+    const uint32_t sk = st[k];
+    const uint64_t ss = s[k];
+    if (sk != r.st) return sk < r.st;
+    if (ss != r.s) return ss < r.s;
+    const uint64_t ee = e[k];
+    if (ee != r.e) return ee > r.e;
+    return x[k] < r.x;
+  }
+};
+
+__global__ void __launch_bounds__(kRsSortThreads) k_rsort_tile(const opattr_ranges r, int64_t R,
+                                                               RSortBuf out, RSortOut f, int last) {
+  extern __shared__ __align__(16) unsigned char rs_raw[];
+  RsSortLds &t = *reinterpret_cast<RsSortLds *>(rs_raw);
+  const int tid = threadIdx.x;
+  const int64_t base = (int64_t)blockIdx.x * kRsSort;
+  const int n = (int)(R - base < kRsSort ? R - base : kRsSort);
+  RRec v[kRsSortPer];
+  int pos[kRsSortPer];
+#pragma unroll
+  for (int u = 0; u < kRsSortPer; ++u) {
+    const int k = tid + u * kRsSortThreads;
+    pos[u] = k;
+    // records past n sort after every real one (streams are 16-bit)
+    v[u] = RRec{~0ull, 0ull, 0xFFFFFFFFu, 0xFFFFFFFFu};
+    if (k < n) v[u] = RRec{r.start_ns[base + k], r.end_ns[base + k], (uint32_t)(base + k), r.stream_id[base + k]};
+  }
+  for (int w = 1; w < n; w <<= 1) {
+#pragma unroll
+    for (int u = 0; u < kRsSortPer; ++u)
+      if (pos[u] < n) t.put(pos[u], v[u]);
+    __syncthreads();
+    int lo[kRsSortPer], hi[kRsSortPer], ob[kRsSortPer];
+#pragma unroll
+    for (int u = 0; u < kRsSortPer; ++u) {
+      const int p = pos[u], run = p & ~(w - 1), other = run ^ w;
+      ob[u] = other < n ? other : n;
+      lo[u] = ob[u];
+      hi[u] = other + w < n ? other + w : n;
+      if (p >= n || hi[u] < lo[u]) hi[u] = lo[u];
     }
-  const int n = (int)(R - base < kRsTile ? R - base : kRsTile);
-  for (int k = tid; k < n; k += kRsThreads) rrec_store(out, f, last != 0, base + k, t.get(k));
+    for (int step = w; step > 0; step >>= 1)  // enough for a run of w records
+#pragma unroll
+      for (int u = 0; u < kRsSortPer; ++u)
+        if (lo[u] < hi[u]) {
+          const int mid = (lo[u] + hi[u]) >> 1;
+          if (t.less(mid, v[u])) lo[u] = mid + 1;
+          else hi[u] = mid;
+        }
+#pragma unroll
+    for (int u = 0; u < kRsSortPer; ++u)
+      if (pos[u] < n) {
+        const int p = pos[u], run = p & ~(w - 1);
+        pos[u] = (run & ~w) + (p - run) + (lo[u] - ob[u]);
+      }
+    __syncthreads();  // every search is done before the next round's records
+  }
+#pragma unroll
+  for (int u = 0; u < kRsSortPer; ++u)
+    if (pos[u] < n) rrec_store(out, f, last != 0, base + pos[u], v[u]);
 }
 
 // Records of run A among the first d outputs of merging A = in[pa, pa + la)
@@ -363,13 +416,14 @@ __global__ void __launch_bounds__(kRsThreads) k_rsort_merge(RSortBuf in, RSortBu
 static void sort_ranges(const opattr_ranges *r, int64_t R, const RSortBuf &fin,
                         const RSortBuf &tmp, const RSortOut &f, hipStream_t s) {
   int np = 0;
-  for (int64_t w = kRsTile; w < R; w *= 2) ++np;
+  for (int64_t w = kRsSort; w < R; w *= 2) ++np;
   const unsigned nb = (unsigned)((R + kRsTile - 1) / kRsTile);
   // the passes alternate buffers; start so that the last one writes fin
   const RSortBuf *cur = (np % 2 == 0) ? &fin : &tmp;
-  k_rsort_tile<<<nb, kRsThreads, 0, s>>>(*r, R, *cur, f, np == 0 ? 1 : 0);
+  k_rsort_tile<<<(unsigned)((R + kRsSort - 1) / kRsSort), kRsSortThreads, sizeof(RsSortLds), s>>>(
+      *r, R, *cur, f, np == 0 ? 1 : 0);
   int q = 0;
-  for (int64_t w = kRsTile; w < R; w *= 2, ++q) {
+  for (int64_t w = kRsSort; w < R; w *= 2, ++q) {
     const RSortBuf *nxt = cur == &fin ? &tmp : &fin;
     k_rsort_merge<<<nb, kRsThreads, 0, s>>>(*cur, *nxt, R, w, f, q == np - 1 ? 1 : 0);
     cur = nxt;
