@@ -252,6 +252,7 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
       pl.ctl = b.take((size_t)pl.nct * NN * 4);
       pl.cpf = b.take((size_t)pl.ncp * NN * 4);
       pl.csum = b.take((size_t)nfb * 4 * 8);
+      pl.csamp = b.take((size_t)kCWindow * 8);
     }
     const int64_t turns = 2 * pl.R + (int64_t)pl.NS + 1, half = pl.T / 2 + 1;
     pl.fcap = pl.fper ? (turns < half ? turns : half) + 4 * nfb : nfb * fused_block_cap();

@@ -28,7 +28,6 @@ namespace opa {
 
 constexpr int kCThreads = kCompactTile;
 constexpr int kCWaves = kCThreads / OPA_WAVE;
-constexpr int kCWindow = 2048;  // range starts staged in LDS by a block of launches
 static_assert(kCThreads == kRlThreads, "the range tiles' threads");
 
 struct CompactArgs {
@@ -38,6 +37,9 @@ struct CompactArgs {
   const uint16_t *stream;
   const uint64_t *q;
   const int32_t *rk;  // launch-order rank of each launch; NULL: its seq
+  int via;            // step 4 takes the launches by rank, not by position
+  uint64_t *samp;     // every (1 << sshift)-th range start (via)
+  int sshift;
   uint32_t NN, NP, NS, NOPS;
   int32_t *sv;   // launch at each rank
   uint32_t *kr;  // by rank: key << 16 | in-tile rank
@@ -107,6 +109,8 @@ __global__ void __launch_bounds__(kCThreads) k_c_pro(CompactArgs a) {
     case 1: {  // validity and effective ends of the ranges
       const int64_t x = (int64_t)b * kCThreads + tid;
       count_bad(x < a.rw.cr.n && rprep_one(a.rw.cr, a.NS, a.NOPS, a.rw.ree, a.rw.npg, x), a.diag);
+      if (a.via && x < a.rw.cr.n && (x & (((int64_t)1 << a.sshift) - 1)) == 0)
+        a.samp[x >> a.sshift] = a.rw.cr.s[x];
       break;
     }
     case 2: {  // stream blocks of the ranges, one wave per stream s = 0..NS
@@ -368,20 +372,25 @@ struct CWin {
   uint32_t op[kCWindow];
 };
 
-// The thread's kPer consecutive launches from position ib on (nv of them
-// exist; the block's first is i0): their outputs, match, duration and operator
-// row.
+// The thread's kPer consecutive launches from ib on (nv of them exist; the
+// block's first is i0): their outputs, match, duration and operator row
+// (0xFFFFFFFF: no launch).
+// The launches are taken by position where they come stream-major, else by
+// launch-order rank through the view (kVia): launches near in launch order
+// share operator rows, which keeps a block's partial results few, in whatever
+// order they are given (500k shuffled launches over 1,001 rows by position:
+// 480 rows in a block of 1024).
 // Enclosure: the innermost range is the last one starting at or before the
-// query point, or its first ancestor that ends at or after it. The ranges
-// between the smallest and largest query point of the block's main stream are
-// staged in LDS, so that the search and the walk outward cost no memory round
-// trips there.
+// query point, or its first ancestor that ends at or after it. By position,
+// the ranges between the smallest and largest query point of the block's main
+// stream are staged in LDS, so that the search and the walk outward cost no
+// memory round trips there; by rank, samples of all range starts are.
 // Matching (see k_tl_look): the rank of the launch, or of the
 // representative's launch at its position, among its name's eligible launches
 // gives the profiled row. Its four levels of dependent loads are issued
 // between the enclosure's, so that they cost no time of their own: a block's
 // chain of memory round trips is what small calls wait for.
-template <int kPer, int kThreads>
+template <int kPer, int kThreads, bool kVia>
 __device__ __forceinline__ void c_launches(const CompactArgs &a, int64_t i0, int64_t ib, int nv,
                                            CWin &win, CFind &sm, int32_t (&mt)[kPer],
                                            uint32_t (&du)[kPer], uint32_t (&g)[kPer]) {
@@ -389,49 +398,73 @@ __device__ __forceinline__ void c_launches(const CompactArgs &a, int64_t i0, int
   constexpr uint32_t kNone = 0xFFFFFFFFu;
   const int tid = threadIdx.x, w = wave_id(), ln = lane_id();
   uint32_t bad = 0, err = 0;
-  // level 1: everything by position
+  // level 1: everything of the launches
   uint16_t st[kPer];
   uint64_t q[kPer];
   uint32_t sq[kPer], nm[kPer];
-  int32_t pt[kPer];
-  if constexpr (kPer == 1) {
-    st[0] = nv > 0 ? a.stream[ib] : 0;
-    q[0] = nv > 0 ? a.q[ib] : 0;
+  int32_t pt[kPer], at_[kPer];
+  bool ex[kPer];
+  if constexpr (kVia) {
+    load_n<kPer>(a.sv, ib, nv, at_);
+    if (a.rw.cr.n > 0) {
+      const int64_t ns = ((a.rw.cr.n - 1) >> a.sshift) + 1;
+      for (int64_t k = tid; k < ns; k += kThreads) win.s[k] = a.samp[k];
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      // (a false density promise can leave any entry in the view)
+      ex[k] = k < nv && at_[k] >= 0 && (int64_t)at_[k] < a.T;
+      const int64_t i = ex[k] ? at_[k] : 0;
+      st[k] = a.stream[i];
+      q[k] = a.q[i];
+      nm[k] = a.name[i];
+      du[k] = ex[k] ? a.dur[i] : 0u;
+      pt[k] = a.part ? a.part[i] : -1;
+      sq[k] = (uint32_t)(ib + k);
+    }
   } else {
-    load_run<kPer>(a.stream, ib, nv, st);
-    load_run<kPer>(a.q, ib, nv, q);
+    if constexpr (kPer == 1) {
+      st[0] = nv > 0 ? a.stream[ib] : 0;
+      q[0] = nv > 0 ? a.q[ib] : 0;
+    } else {
+      load_run<kPer>(a.stream, ib, nv, st);
+      load_run<kPer>(a.q, ib, nv, q);
+    }
+    load_n<kPer>(a.rk ? reinterpret_cast<const uint32_t *>(a.rk) : a.seq, ib, nv, sq);
+    load_n<kPer>(a.name, ib, nv, nm);
+    if (a.part) load_n<kPer>(a.part, ib, nv, pt);
+    load_n<kPer>(a.dur, ib, nv, du);
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) ex[k] = k < nv;
   }
-  load_n<kPer>(a.rk ? reinterpret_cast<const uint32_t *>(a.rk) : a.seq, ib, nv, sq);
-  load_n<kPer>(a.name, ib, nv, nm);
-  if (a.part) load_n<kPer>(a.part, ib, nv, pt);
-  load_n<kPer>(a.dur, ib, nv, du);
-  const uint16_t s0 = a.stream[i0];
+  const uint16_t s0 = kVia ? (uint16_t)0 : a.stream[i0];
   // level 2: partition records
   PartRec rc[kPer];
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
     const int32_t p = a.part ? pt[k] : -1;
-    const bool ok = k < nv && nm[k] < a.NN && (int64_t)sq[k] < a.T && p >= -1 &&
+    const bool ok = ex[k] && nm[k] < a.NN && (int64_t)sq[k] < a.T && p >= -1 &&
                     (p < 0 || (uint32_t)p < a.NP);
     rc[k] = PartRec{0, ok ? kRecEligible : kRecNone};
     if (ok && p >= 0) rc[k] = a.prec[p];
   }
-  // smallest and largest query point of the block's main stream
-  uint64_t mn = ~0ull, mx = 0ull;
+  if constexpr (!kVia) {  // smallest and largest query point of the block's main stream
+    uint64_t mn = ~0ull, mx = 0ull;
 #pragma unroll
-  for (int k = 0; k < kPer; ++k)
-    if (k < nv && st[k] == s0) {
-      mn = q[k] < mn ? q[k] : mn;
-      mx = q[k] > mx ? q[k] : mx;
+    for (int k = 0; k < kPer; ++k)
+      if (ex[k] && st[k] == s0) {
+        mn = q[k] < mn ? q[k] : mn;
+        mx = q[k] > mx ? q[k] : mx;
+      }
+    for (int o = OPA_WAVE / 2; o > 0; o >>= 1) {
+      const uint64_t y = __shfl_xor(mn, o, OPA_WAVE), z = __shfl_xor(mx, o, OPA_WAVE);
+      mn = y < mn ? y : mn;
+      mx = z > mx ? z : mx;
     }
-  for (int o = OPA_WAVE / 2; o > 0; o >>= 1) {
-    const uint64_t y = __shfl_xor(mn, o, OPA_WAVE), z = __shfl_xor(mx, o, OPA_WAVE);
-    mn = y < mn ? y : mn;
-    mx = z > mx ? z : mx;
-  }
-  if (ln == 0) {
-    sm.red[0][w] = mn;
-    sm.red[1][w] = mx;
+    if (ln == 0) {
+      sm.red[0][w] = mn;
+      sm.red[1][w] = mx;
+    }
   }
   // level 3: the rank that gives the row, and its name's place in the slots
   uint32_t kr[kPer], pre[kPer], rows[kPer], ro[kPer], dup = 0;
@@ -460,19 +493,21 @@ __device__ __forceinline__ void c_launches(const CompactArgs &a, int64_t i0, int
     }
   }
   __syncthreads();
-  if (w < 2) {  // wave 0 finds the window's start, wave 1 its end
-    uint64_t qa = ~0ull, qb = 0;
-    for (int k = 0; k < kWaves; ++k) {
-      qa = sm.red[0][k] < qa ? sm.red[0][k] : qa;
-      qb = sm.red[1][k] > qb ? sm.red[1][k] : qb;
+  if constexpr (!kVia) {
+    if (w < 2) {  // wave 0 finds the window's start, wave 1 its end
+      uint64_t qa = ~0ull, qb = 0;
+      for (int k = 0; k < kWaves; ++k) {
+        qa = sm.red[0][k] < qa ? sm.red[0][k] : qa;
+        qb = sm.red[1][k] > qb ? sm.red[1][k] : qb;
+      }
+      int64_t p = -1;
+      if (s0 < a.NS && qa <= qb) {
+        const int64_t lo = a.rblk[s0], hi = a.rblk[s0 + 1];
+        p = wave_upper_bound(a.rw.cr.s, lo, hi, w == 0 ? qa : qb) - 1;
+        if (w == 0 && p < lo) p = lo;
+      }
+      if (ln == 0) sm.win[w] = p;
     }
-    int64_t p = -1;
-    if (s0 < a.NS && qa <= qb) {
-      const int64_t lo = a.rblk[s0], hi = a.rblk[s0 + 1];
-      p = wave_upper_bound(a.rw.cr.s, lo, hi, w == 0 ? qa : qb) - 1;
-      if (w == 0 && p < lo) p = lo;
-    }
-    if (ln == 0) sm.win[w] = p;
   }
   // level 4: the row
 #pragma unroll
@@ -486,30 +521,34 @@ __device__ __forceinline__ void c_launches(const CompactArgs &a, int64_t i0, int
     const uint32_t r = pre[k] + (kr[k] & 0xFFFFu);
     if (r < rows[k]) mt[k] = a.slot[ro[k] + r];
   }
-  __syncthreads();
-  const int64_t wlo = sm.win[0];
-  int64_t wn = s0 < a.NS ? sm.win[1] - wlo + 1 : 0;
-  if (wn < 0) wn = 0;
-  const bool staged = wn <= kCWindow;
-  if (staged)
-    for (int k = tid; k < wn; k += kThreads) {
-      win.s[k] = a.rw.cr.s[wlo + k];
-      win.e[k] = a.rw.ree[wlo + k];
-      win.par[k] = a.rw.npg[wlo + k];
-      win.op[k] = a.rw.cr.op[wlo + k];
-    }
-  __syncthreads();
+  int64_t wlo = 0, wn = 0;
+  bool staged = false;
+  if constexpr (!kVia) {
+    __syncthreads();
+    wlo = sm.win[0];
+    wn = s0 < a.NS ? sm.win[1] - wlo + 1 : 0;
+    if (wn < 0) wn = 0;
+    staged = wn <= kCWindow;
+    if (staged)
+      for (int k = tid; k < wn; k += kThreads) {
+        win.s[k] = a.rw.cr.s[wlo + k];
+        win.e[k] = a.rw.ree[wlo + k];
+        win.par[k] = a.rw.npg[wlo + k];
+        win.op[k] = a.rw.cr.op[wlo + k];
+      }
+    __syncthreads();
+  }
   const int32_t w0 = (int32_t)wlo, w1 = staged ? (int32_t)wn : 0;
-  auto in_win = [&](int32_t j) { return (uint32_t)(j - w0) < (uint32_t)w1; };
+  auto in_win = [&](int32_t j) { return !kVia && (uint32_t)(j - w0) < (uint32_t)w1; };
   int32_t pk[kPer], lok[kPer];
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
     pk[k] = -1;
     lok[k] = 0;
-    if (k < nv && st[k] < a.NS && q[k] < (1ull << 63)) {
+    if (ex[k] && st[k] < a.NS && q[k] < (1ull << 63)) {
       const int64_t lo = a.rblk[st[k]], hi = a.rblk[st[k] + 1];
       lok[k] = (int32_t)lo;
-      if (staged && st[k] == s0) {
+      if (!kVia && staged && st[k] == s0) {
         int l2 = 0, h2 = (int)wn;
         while (l2 < h2) {
           const int mid = (l2 + h2) >> 1;
@@ -518,10 +557,25 @@ __device__ __forceinline__ void c_launches(const CompactArgs &a, int64_t i0, int
         }
         const int64_t p = wlo + l2 - 1;
         pk[k] = (int32_t)(wn == 0 || p < lo ? lo - 1 : p);
+      } else if constexpr (kVia) {
+        // the samples inside the stream's block first, then between two of them
+        const int sh = a.sshift;
+        const int m0 = (int)((lo + ((int64_t)1 << sh) - 1) >> sh);
+        int l2 = m0, h2 = hi > lo ? (int)((hi - 1) >> sh) + 1 : m0;
+        while (l2 < h2) {
+          const int mid = (l2 + h2) >> 1;
+          if (win.s[mid] <= q[k]) l2 = mid + 1;
+          else h2 = mid;
+        }
+        // every sample below l2 starts at or before the query point
+        int64_t x0 = l2 > m0 ? (int64_t)(l2 - 1) << sh : lo, x1 = (int64_t)l2 << sh;
+        x0 = x0 < lo ? lo : x0;
+        x1 = x1 < hi ? x1 : hi;
+        pk[k] = (int32_t)(thread_upper_bound(a.rw.cr.s, x0, x1, q[k]) - 1);
       } else {
         pk[k] = (int32_t)(thread_upper_bound(a.rw.cr.s, lo, hi, q[k]) - 1);
       }
-    } else if (k < nv && st[k] >= a.NS) {
+    } else if (ex[k] && st[k] >= a.NS) {
       bad++;
     }
   }
@@ -529,12 +583,12 @@ __device__ __forceinline__ void c_launches(const CompactArgs &a, int64_t i0, int
   int64_t ek[kPer];
 #pragma unroll
   for (int k = 0; k < kPer; ++k)
-    ek[k] = (k < nv && pk[k] >= lok[k]) ? (in_win(pk[k]) ? win.e[pk[k] - w0] : a.rw.ree[pk[k]]) : 0;
+    ek[k] = (ex[k] && pk[k] >= lok[k]) ? (in_win(pk[k]) ? win.e[pk[k] - w0] : a.rw.ree[pk[k]]) : 0;
   for (int step = 0; step < kMaxWalk; ++step) {
     bool act[kPer], any = false;
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
-      act[k] = k < nv && pk[k] >= lok[k] && ek[k] < (int64_t)q[k];
+      act[k] = ex[k] && pk[k] >= lok[k] && ek[k] < (int64_t)q[k];
       any |= act[k];
     }
     if (!any) break;
@@ -549,15 +603,24 @@ __device__ __forceinline__ void c_launches(const CompactArgs &a, int64_t i0, int
   int32_t rid[kPer];
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
-    rid[k] = (k < nv && pk[k] >= lok[k] && ek[k] >= (int64_t)q[k]) ? pk[k] : -1;
+    rid[k] = (ex[k] && pk[k] >= lok[k] && ek[k] >= (int64_t)q[k]) ? pk[k] : -1;
     g[k] = k < nv ? a.NOPS : 0xFFFFFFFFu;
     if (rid[k] >= 0) {
       g[k] = in_win(rid[k]) ? win.op[rid[k] - w0] : a.rw.cr.op[rid[k]];
       if (a.rw.cr.perm) rid[k] = a.rw.cr.perm[rid[k]];
     }
   }
-  store_n<kPer>(a.range_id, ib, nv, rid);
-  store_n<kPer>(a.match, ib, nv, mt);
+  if constexpr (kVia) {
+#pragma unroll
+    for (int k = 0; k < kPer; ++k)
+      if (ex[k]) {
+        a.range_id[at_[k]] = rid[k];
+        a.match[at_[k]] = mt[k];
+      }
+  } else {
+    store_n<kPer>(a.range_id, ib, nv, rid);
+    store_n<kPer>(a.match, ib, nv, mt);
+  }
   const unsigned long long e = wave_reduce_add((unsigned long long)err);
   const uint32_t bb = wave_reduce_add(bad);
   if (ln == 0) {
@@ -577,7 +640,7 @@ __device__ __forceinline__ void c_extra(const CompactArgs &a, int b) {
   }
 }
 
-template <bool DEF, int kPer>
+template <bool DEF, int kPer, bool kVia>
 __global__ void __launch_bounds__(kTThreads) k_c_tab(CompactArgs a) {
   extern __shared__ __align__(16) unsigned char c_raw[];
   __shared__ CFind sm;
@@ -592,7 +655,7 @@ __global__ void __launch_bounds__(kTThreads) k_c_tab(CompactArgs a) {
   const int nv = (int)(a.T - ib < 0 ? 0 : (a.T - ib < kPer ? a.T - ib : kPer));
   int32_t mt[kPer];
   uint32_t du[kPer], g[kPer];
-  c_launches<kPer, kTThreads>(a, i0, ib, nv, *reinterpret_cast<CWin *>(c_raw), sm, mt, du, g);
+  c_launches<kPer, kTThreads, kVia>(a, i0, ib, nv, *reinterpret_cast<CWin *>(c_raw), sm, mt, du, g);
   unsigned long long *tab = reinterpret_cast<unsigned long long *>(c_raw);
   const uint32_t G = a.NOPS + 1u, ne = G * kFFields;
   __syncthreads();  // the window's space becomes the table
@@ -627,7 +690,7 @@ __global__ void __launch_bounds__(kTThreads) k_c_tab(CompactArgs a) {
   }
 }
 
-template <bool DEF, int kPer>
+template <bool DEF, int kPer, bool kVia>
 __global__ void __launch_bounds__(kRThreads) k_c_row(CompactArgs a) {
   extern __shared__ __align__(16) unsigned char c_raw[];
   __shared__ CFind sm;
@@ -644,7 +707,7 @@ __global__ void __launch_bounds__(kRThreads) k_c_row(CompactArgs a) {
   const int nv = (int)(a.T - ib < 0 ? 0 : (a.T - ib < kPer ? a.T - ib : kPer));
   int32_t mt[kPer];
   uint32_t du[kPer], g[kPer];
-  c_launches<kPer, kRThreads>(a, i0, ib, nv, *reinterpret_cast<CWin *>(c_raw), sm, mt, du, g);
+  c_launches<kPer, kRThreads, kVia>(a, i0, ib, nv, *reinterpret_cast<CWin *>(c_raw), sm, mt, du, g);
   // the block's summary sums
   unsigned long long at_ = 0, un = 0, mt_ = 0;
 #pragma unroll
@@ -734,6 +797,12 @@ __global__ void __launch_bounds__(kCRowThreads) k_c_rows(CombParams a) {
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
+#define OPA_C_LAUNCH(kernel, per, threads, lds)                                       \
+  (a.via ? (def ? kernel<true, per, true><<<g, threads, lds, s>>>(a)                  \
+                : kernel<false, per, true><<<g, threads, lds, s>>>(a))                \
+         : (def ? kernel<true, per, false><<<g, threads, lds, s>>>(a)                 \
+                : kernel<false, per, false><<<g, threads, lds, s>>>(a)))
+
 static int blocks_of(int64_t n, int per) { return (int)((n + per - 1) / per); }
 
 void run_compact(const CompactIn &x, hipStream_t s) {
@@ -757,6 +826,9 @@ void run_compact(const CompactIn &x, hipStream_t s) {
   a.stream = k->stream_id;
   a.q = k->query_ns ? k->query_ns : k->start_ns;
   a.rk = pl.seq_dense ? nullptr : at<int32_t>(ws, pl.rk);
+  a.via = (d->flags & OPATTR_KERNELS_STREAM_MAJOR) ? 0 : 1;
+  a.samp = at<uint64_t>(ws, pl.csamp);
+  while (pl.R > ((int64_t)kCWindow << a.sshift)) ++a.sshift;
   a.NN = pl.NN;
   a.NP = parts ? pl.NP : 0;
   a.NS = pl.NS;
@@ -867,14 +939,14 @@ void run_compact(const CompactIn &x, hipStream_t s) {
   if (pl.ftabs) {
     const size_t lt = most(fused_tab_bytes(pl.G), sizeof(CWin));
     g = grid(pl.ftabs, nbR, 1, 0, 0, 0);
-    if (pl.fper == 1) def ? k_c_tab<true, 1><<<g, kTThreads, lt, s>>>(a) : k_c_tab<false, 1><<<g, kTThreads, lt, s>>>(a);
-    else if (pl.fper == 2) def ? k_c_tab<true, 2><<<g, kTThreads, lt, s>>>(a) : k_c_tab<false, 2><<<g, kTThreads, lt, s>>>(a);
-    else def ? k_c_tab<true, 4><<<g, kTThreads, lt, s>>>(a) : k_c_tab<false, 4><<<g, kTThreads, lt, s>>>(a);
+    if (pl.fper == 1) OPA_C_LAUNCH(k_c_tab, 1, kTThreads, lt);
+    else if (pl.fper == 2) OPA_C_LAUNCH(k_c_tab, 2, kTThreads, lt);
+    else OPA_C_LAUNCH(k_c_tab, 4, kTThreads, lt);
   } else {
     const size_t lr = most(r_agg_lds(pl.G), sizeof(CWin));
     g = grid((int)c.nblocks, blocks_of(pl.R, kRThreads), 1, 0, 0, 0);
-    if (pl.fper == 2) def ? k_c_row<true, 2><<<g, kRThreads, lr, s>>>(a) : k_c_row<false, 2><<<g, kRThreads, lr, s>>>(a);
-    else def ? k_c_row<true, 4><<<g, kRThreads, lr, s>>>(a) : k_c_row<false, 4><<<g, kRThreads, lr, s>>>(a);
+    if (pl.fper == 2) OPA_C_LAUNCH(k_c_row, 2, kRThreads, lr);
+    else OPA_C_LAUNCH(k_c_row, 4, kRThreads, lr);
   }
   probe_end(OPATTR_PROBE_MAIN_PASS, s);
   probe_begin(OPATTR_PROBE_AGGREGATE, s);

@@ -57,7 +57,7 @@ struct Plan {
   bool compact;
   int ctshift;       // log2 of its tiles' size
   int64_t nct, ncp;  // its tiles of launches and of profiled rows
-  size_t ctl, cpf, csum;
+  size_t ctl, cpf, csum, csamp;
   int fper;      // launches per lane of the row-ordered reduction (0: the run reduction)
   int ftabs;     // blocks of the reduction with the whole table in LDS (0: another one)
   int64_t fcap;  // partials there is room for
@@ -410,6 +410,7 @@ struct CompactIn {
   const Plan *pl;
 };
 void run_compact(const CompactIn &x, hipStream_t s);
+constexpr int kCWindow = 2048;  // range starts staged in LDS by a block of the compact path
 constexpr int kCompactTile = 1024;           // launches (or profiled rows) per tile at least
 constexpr int64_t kCompactMax = 1 << 20;     // launches, profiled rows
 constexpr uint32_t kCompactNames = 2048;     // 16 counters of 2 B a name in LDS
