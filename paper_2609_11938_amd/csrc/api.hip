@@ -73,8 +73,11 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
   pl.seqsort_k1 = b.take(pl.seq_dense ? 0 : T * 4);
   pl.seqsort_v0 = b.take(pl.seq_dense ? 0 : T * 4);
   pl.seqsort_v1 = b.take(pl.seq_dense ? 0 : T * 4);
-  // radix histograms of the seq sort
-  pl.rs_hist = b.take(radix_hist_entries(pl.seq_dense ? 0 : pl.T) * 4);
+  // the bucket view's counts, or the radix histograms of the seq sort (in a
+  // plan that must not grow)
+  pl.rank_view = !pl.seq_dense && mode != PlanMode::kPlain;
+  pl.rv = b.take(pl.rank_view ? rank_view_entries() * 4 : 0);
+  pl.rs_hist = b.take(radix_hist_entries(pl.seq_dense || pl.rank_view ? 0 : pl.T) * 4);
   pl.tlh = b.take((size_t)pl.nt * NN * 4);
   pl.pfh = b.take((size_t)pl.ntp * NN * 4);
   pl.tlch = b.take((size_t)pl.ncht * NN * 4);

@@ -44,6 +44,8 @@ struct Plan {
       rm_rid;
   size_t total;
   // IOM
+  bool rank_view;  // not dense: the view by buckets (rankview.hip), else by a sort
+  size_t rv;
   size_t sv, rk, seqsort_k0, seqsort_k1, seqsort_v0, seqsort_v1, rs_hist, kblk, tbnd;
   size_t tlh, pfh, tlch, pfch, tlc, pfc, off, slot;
   size_t pfirst, plast, pheads, prec, mbs, nbs;
@@ -210,6 +212,12 @@ struct IomArgs {
 void build_seq_view(const opattr_kernels *k, const opattr_dims *d, void *ws, const Plan &pl,
                     opattr_diag *diag, bool validate, hipStream_t s);
 void run_match(const IomArgs &a, hipStream_t s);
+// the view when seq is not promised dense (rankview.hip)
+constexpr int kRvWidthBits = 18;                      // values of the widest bucket
+constexpr int kRvBuckets = 1 << (32 - kRvWidthBits);  // buckets that cover any 32-bit range
+size_t rank_view_entries();
+void run_rank_view(const opattr_kernels *k, void *ws, const Plan &pl, opattr_diag *diag,
+                   hipStream_t s);
 // the launches of a remapped call in stream-major order (the launch-order
 // view must be built): the permutation and the permuted arrays into the
 // plan's rm_* regions; *out gets the arrays

@@ -88,6 +88,11 @@ void build_seq_view(const opattr_kernels *k, const opattr_dims *d, void *ws, con
     return;
   }
   probe_begin(OPATTR_PROBE_SEQ_VIEW, s);
+  if (pl.rank_view) {
+    run_rank_view(k, ws, pl, diag, s);
+    probe_end(OPATTR_PROBE_SEQ_VIEW, s);
+    return;
+  }
   uint32_t *k0 = at<uint32_t>(ws, pl.seqsort_k0), *k1 = at<uint32_t>(ws, pl.seqsort_k1);
   uint32_t *v0 = at<uint32_t>(ws, pl.seqsort_v0), *v1 = at<uint32_t>(ws, pl.seqsort_v1);
   launch_key_pairs(k->seq, k0, v0, T, s);

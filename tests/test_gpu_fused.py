@@ -160,6 +160,41 @@ def test_compact_edges(T, S, n_names, n_ops, order):
         parity.assert_attribute(out, want, diag)
 
 
+@pytest.mark.parametrize("T,kind", [
+    (1, "even"), (1023, "even"), (50_001, "even"), (2 ** 20 + 9, "even"), (8192, "dense"),
+    (70_000, "far"), (70_000, "ends"), (300_000, "captures"),
+    (70_000, "pairs"), (20_000, "same"), (1025, "same")])
+def test_launch_ranks_by_buckets(T, kind):
+    """Ranks of launches whose seq is not promised dense: the smallest and
+    largest values, one far value beside a dense run (buckets of 2^18 values,
+    most of them empty), two captures far apart, and equal values, whose
+    ranks go by input index, in small buckets and in one larger than a
+    bucket's own count of smaller launches takes."""
+    rng = np.random.default_rng(T)
+    tr = cases.random_trace(6900 + T % 977, T=T, S=3, n_names=min(T, 70), R=T // 8, n_ops=50,
+                            t_max=8 * T + 8, max_depth=5, dedup=False)
+    if kind == "even":
+        seq = np.sort(rng.choice(np.arange(0, 2 ** 32 - 1, 2 ** 32 // (2 * T)), T, replace=False))
+    elif kind == "dense":
+        seq = np.arange(T) + 77
+    elif kind == "far":
+        seq = np.append(np.arange(T - 1) + 5, 2 ** 32 - 1)
+    elif kind == "ends":
+        seq = np.append(np.arange(T // 2), 2 ** 32 - T + T // 2 + np.arange(T - T // 2))
+    elif kind == "captures":
+        seq = np.append(np.arange(T // 2), 3_000_000_000 + 7 * np.arange(T - T // 2))
+    elif kind == "pairs":
+        seq = np.arange(T) // 2 * 1000
+    else:
+        seq = np.full(T, 12345)
+    tr["seq"] = rng.permutation(seq).astype(np.uint32)
+    print(f"case launch ranks T={T} {kind}", flush=True)
+    want = O.attribute(tr)
+    out, diag = _run(tr, flags=0)
+    parity.assert_attribute(out, want, diag)
+    assert bool(diag["flags"] & opattr.F_ORDER) == (kind in ("pairs", "same"))
+
+
 @pytest.mark.parametrize("kinds", [False, True])
 def test_row_order_more_partials_than_room(kinds):
     """Query points that jump back and forth change the innermost range far
