@@ -37,25 +37,42 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
   pl.NP = d->n_parts;
   pl.seq_dense = (d->flags & OPATTR_SEQ_DENSE) != 0;
   pl.ranges_nested = (d->flags & OPATTR_RANGES_NESTED) != 0;
+  const bool sm_hint = (d->flags & OPATTR_KERNELS_STREAM_MAJOR) != 0;
+  // Few launches: the compact path (single stream, five launches). Its tiles'
+  // name counts are a column of at most 1024 values per name, and its ranges'
+  // tiles fit one maximum tree.
+  pl.ctshift = pl.T > (1 << 18) || pl.P > (1 << 18) ? 12 : 10;
+  pl.nct = (pl.T + (1 << pl.ctshift) - 1) >> pl.ctshift;
+  pl.ncp = (pl.P + (1 << pl.ctshift) - 1) >> pl.ctshift;
+  pl.ntr_max = pl.R / kRangeTile + (int64_t)pl.NS + 1;
+  pl.compact = mode != PlanMode::kPlain && !second_match && p != nullptr && r != nullptr &&
+               !r->kind && pl.T > 0 && pl.T <= kCompactMax && pl.P <= kCompactMax && pl.NN >= 1 &&
+               pl.NN <= kCompactNames && (pl.nct + pl.ncp) * pl.NN <= kCompactCells &&
+               pl.NS >= 1 && pl.ntr_max <= kRangeTile && pl.G <= kFusedMaxRows;
   // seq tiles straight from per-stream segments: needs both kernel promises,
   // a matching stage (profiled rows given) and few streams and names (under
   // OPATTR_VALIDATE both promises are checked beside it: the layout by
   // check_kernel_layout, the density by the launch-order view's scatter)
-  const bool seg_ok = pl.seq_dense && p != nullptr && pl.NS >= 1 && pl.NS <= 64 &&
-                      pl.NN <= kFastNames;
-  const bool sm_hint = (d->flags & OPATTR_KERNELS_STREAM_MAJOR) != 0;
-  // dense seq in another order: opattr_attribute permutes the launches into
-  // stream-major order when the fused path would then take them (not under
-  // OPATTR_VALIDATE, which checks the caller's layout as given)
-  const bool remap_ok = !sm_hint && seg_ok && !(d->flags & OPATTR_VALIDATE) && !second_match &&
-                        r != nullptr && pl.G <= kFusedMaxRows && pl.T > 0 &&
-                        (mode != PlanMode::kPlain || pl.R * 16 <= pl.T);
-  pl.seg = (sm_hint || remap_ok) && seg_ok;  // sizes; reset below for the remapped case
+  const bool few_ok = p != nullptr && pl.NS >= 1 && pl.NS <= 64 && pl.NN <= kFastNames;
+  // launches in another order: opattr_attribute permutes them into
+  // stream-major order, their ranks as seq, when the fused path would then
+  // take them (not under OPATTR_VALIDATE, which checks the caller's layout as
+  // given). 2M shuffled launches with gaps in seq: 674 us on the general path,
+  // 570 us so. Stream-major launches with gaps in seq stay on the general
+  // path: with their ranks as seq the fused path took 372 us for 3M, the
+  // general one 360 us (400k ranges for 2M launches: 340 us and 348 us).
+  // (ids past the last stream take a segment of their own, or, with 64
+  // streams and dense seq, none: their launches are not matched then)
+  const bool remap_ok = few_ok && (pl.seq_dense || pl.NS < 64) && !sm_hint && !second_match &&
+                        !(d->flags & OPATTR_VALIDATE) && r != nullptr && pl.G <= kFusedMaxRows &&
+                        pl.T > 0 && (pl.seq_dense || !pl.compact) &&
+                        (mode != PlanMode::kPlain || (pl.seq_dense && pl.R * 16 <= pl.T));
+  pl.seg = (sm_hint && pl.seq_dense && few_ok) || remap_ok;  // sizes; reset below
+  pl.nseg = remap_ok && pl.NS < 64 ? pl.NS + 1 : pl.NS;
   pl.nt = (pl.T + OPA_TILE - 1) / OPA_TILE;
   pl.ntp = (pl.P + OPA_TILE - 1) / OPA_TILE;
   pl.ncht = (pl.nt + kColChunk - 1) / kColChunk;
   pl.nchp = (pl.ntp + kColChunk - 1) / kColChunk;
-  pl.ntr_max = pl.R / kRangeTile + (int64_t)pl.NS + 1;
   pl.nencb = (pl.T + kEncSpan - 1) / kEncSpan;
   pl.ntrt = (pl.T + OPA_TILE - 1) / OPA_TILE;
   pl.nchr = (pl.ntrt + kColChunk - 1) / kColChunk;
@@ -66,8 +83,8 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
   // dedup (no profiled rows, so never the segment path) needs it, and the
   // size for all inputs must cover every entry point
   pl.sv = b.take(T * 4);
-  pl.kblk = b.take(pl.seg ? ((size_t)pl.NS + 2) * 8 : 0);
-  pl.tbnd = b.take(pl.seg ? ((size_t)pl.nt + 1) * pl.NS * 4 : 0);
+  pl.kblk = b.take(pl.seg ? ((size_t)pl.nseg + 2) * 8 : 0);
+  pl.tbnd = b.take(pl.seg ? ((size_t)pl.nt + 1) * pl.nseg * 4 : 0);
   pl.rk = b.take(pl.seq_dense ? 0 : T * 4);
   pl.seqsort_k0 = b.take(pl.seq_dense ? 0 : T * 4);
   pl.seqsort_k1 = b.take(pl.seq_dense ? 0 : T * 4);
@@ -161,16 +178,6 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
   // (2M launches with 20k ranges and 200 rows take 201 us
   // reduced in place and 203 us by row tables; 1M with 250k ranges 625 us in
   // place, 185 us ordered by row and 161 us by row tables)
-  // Few launches: the compact path (single stream, five launches). Its tiles'
-  // name counts are a column of at most 1024 values per name, and its ranges'
-  // tiles fit one maximum tree.
-  pl.ctshift = pl.T > (1 << 18) || pl.P > (1 << 18) ? 12 : 10;
-  pl.nct = (pl.T + (1 << pl.ctshift) - 1) >> pl.ctshift;
-  pl.ncp = (pl.P + (1 << pl.ctshift) - 1) >> pl.ctshift;
-  pl.compact = mode != PlanMode::kPlain && !second_match && p != nullptr && r != nullptr &&
-               !r->kind && pl.T > 0 && pl.T <= kCompactMax && pl.P <= kCompactMax && pl.NN >= 1 &&
-               pl.NN <= kCompactNames && (pl.nct + pl.ncp) * pl.NN <= kCompactCells &&
-               pl.NS >= 1 && pl.ntr_max <= kRangeTile && pl.G <= kFusedMaxRows;
   if (mode != PlanMode::kPlain && !(long_runs && pl.T > kFusedShort)) {
     // launches per lane: as few as leave no CU without a block, up to the
     // point where more blocks only write more partials
@@ -185,11 +192,11 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
   const size_t permuted = b.off;
   if (remap_ok && pl.fused) {  // the compact path has its partials there
     pl.rm_hist = b.take(remap_hist_entries(pl) * 4);
-    pl.rm_perm = b.take(T * 4);
-    pl.rm_inv = b.take(T * 4);
-    pl.rm_seq = b.take(T * 4);
-    pl.rm_name = b.take(T * 4);
-    pl.rm_dur = b.take(T * 4);
+    // in place of the ranks' own scratch where there is one
+    pl.rm_inv = pl.seq_dense ? b.take(T * 4) : pl.seqsort_k0;
+    pl.rm_seq = pl.seq_dense ? b.take(T * 4) : pl.seqsort_k1;
+    pl.rm_name = pl.seq_dense ? b.take(T * 4) : pl.seqsort_v0;
+    pl.rm_dur = pl.seq_dense ? b.take(T * 4) : pl.seqsort_v1;
     pl.rm_st = b.take(T * 2);
     pl.rm_start = b.take(T * 8);
     pl.rm_query = b.take(k->query_ns ? T * 8 : 0);
@@ -632,7 +639,8 @@ static int attribute_fused(const opattr_kernels *k, const opattr_profiled *p,
                            const uint8_t *agg_kind, int32_t *match, int32_t *range_id,
                            uint8_t *range_depth, uint32_t *name_counts, opattr_op_row *table,
                            opattr_summary *sum, opattr_diag *diag, void *ws, const Plan &pl,
-                           hipStream_t s, bool fork, const opattr_kernels *k_given = nullptr) {
+                           hipStream_t s, bool fork, const opattr_kernels *k_given = nullptr,
+                           const Plan *given = nullptr) {
   SideStream *ss = fork ? side_stream() : nullptr;
   const hipStream_t s2 = ss ? ss->s : s;
   if (ss) {
@@ -657,10 +665,8 @@ static int attribute_fused(const opattr_kernels *k, const opattr_profiled *p,
   if (k_given) {
     // the launches given in another order: permuted (into k's arrays) on the
     // caller's stream while the ranges are sorted; the enclosure waits
-    Plan pv = pl;
-    pv.seg = false;  // the view is built here (the segment path reads none)
-    build_seq_view(k_given, d, ws, pv, diag, false, s);
-    remap_launches(k_given, d, ws, pl, nullptr, s);
+    build_seq_view(k_given, d, ws, *given, diag, false, s);
+    remap_launches(k_given, d, ws, *given, s);
     if (ss) {
       note(hipEventRecord(ss->join3, s));
       note(hipStreamWaitEvent(s2, ss->join3, 0));
@@ -723,9 +729,10 @@ static bool attribute_args_ok(const opattr_kernels *k, const opattr_profiled *p,
          kinds_ok(agg_kind) && (k->n == 0 || (match && range_id));
 }
 
-// opattr_attribute on dense seq given in another order: the launches
-// permuted into stream-major order (through the launch-order view), the
-// fused path on them, and the per-launch outputs permuted back.
+// opattr_attribute on launches given in another order than the fused path
+// reads: permuted into stream-major order (through the launch-order view) with
+// their ranks as seq, the fused path on them, and the per-launch outputs
+// permuted back.
 static int attribute_remapped(const opattr_kernels *k, const opattr_profiled *p,
                               const opattr_ranges *r, const opattr_dims *d, int policy,
                               const uint8_t *agg_kind, int32_t *match, int32_t *range_id,
@@ -735,12 +742,12 @@ static int attribute_remapped(const opattr_kernels *k, const opattr_profiled *p,
   opattr_kernels k2;
   remap_view(k, ws, pl, &k2);
   opattr_dims d2 = *d;
-  d2.flags |= OPATTR_KERNELS_STREAM_MAJOR;
+  d2.flags |= OPATTR_KERNELS_STREAM_MAJOR | OPATTR_SEQ_DENSE;
   Plan pf = pl;
-  pf.seg = pf.fused = true;
+  pf.seg = pf.fused = pf.seq_dense = true;
   attribute_fused(&k2, p, r, &d2, policy, agg_kind, at<int32_t>(ws, pl.rm_match),
                   at<int32_t>(ws, pl.rm_rid), range_depth, name_counts, table, sum, diag, ws, pf,
-                  s, fork, k);
+                  s, fork, k, &pl);
   remap_back(ws, pl, match, range_id, s);
   return launch_status();
 }

@@ -35,12 +35,13 @@ struct Plan {
   int64_t nt, ntp, ncht, nchp, ntr_max, nencb, ntrt, nchr;
   bool seq_dense, ranges_nested;
   bool seg;  // seq tiles read from per-stream segments (kernels stream-major, seq dense)
-  // opattr_attribute on dense seq in another order: the launches permuted
-  // into stream-major order first, then the fused path (the sizes below and
+  // opattr_attribute on launches in another order: permuted into stream-major
+  // order first, their ranks as seq, then the fused path (the sizes below and
   // the segment path's are taken; seg and fused stay false for the other
   // entry points, which read the launches as given)
   bool remap;
-  size_t rm_hist, rm_perm, rm_inv, rm_seq, rm_name, rm_dur, rm_st, rm_start, rm_query, rm_part, rm_match,
+  uint32_t nseg;  // streams of the segment tiles (remap: and one of the ids past the last)
+  size_t rm_hist, rm_inv, rm_seq, rm_name, rm_dur, rm_st, rm_start, rm_query, rm_part, rm_match,
       rm_rid;
   size_t total;
   // IOM
@@ -220,9 +221,9 @@ void run_rank_view(const opattr_kernels *k, void *ws, const Plan &pl, opattr_dia
                    hipStream_t s);
 // the launches of a remapped call in stream-major order (the launch-order
 // view must be built): the permutation and the permuted arrays into the
-// plan's rm_* regions; *out gets the arrays
+// plan's rm_* regions
 void remap_launches(const opattr_kernels *k, const opattr_dims *d, void *ws, const Plan &pl,
-                    opattr_kernels *out, hipStream_t s);
+                    hipStream_t s);
 size_t remap_hist_entries(const Plan &pl);
 // the permuted launch arrays' addresses (host only)
 void remap_view(const opattr_kernels *k, void *ws, const Plan &pl, opattr_kernels *out);

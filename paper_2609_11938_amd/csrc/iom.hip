@@ -1131,115 +1131,148 @@ __global__ void __launch_bounds__(1024) k_pf_off(const uint32_t *__restrict__ pf
 
 
 // ---------------------------------------------------------------------------
-// Stream-major order for launches with dense seq given in another order
-// (opattr_attribute): a stable counting sort by stream of the launch-order
-// view, one 4096-rank tile of it per block, that also gathers the launch
-// arrays into that order. Launches with a stream id past the last stream
-// sort after all others (the fused path counts them as bad records); seq
-// ranks no launch claims (a false density promise) leave slots at the end,
-// filled with records the fused path leaves out.
+// Stream-major order for launches given in another order (opattr_attribute):
+// a stable counting sort by stream of the launch-order view, one 4096-rank
+// tile of it per block, that also gathers the launch arrays into that order;
+// a launch's seq there is its rank. Launches with a stream id past the last
+// stream sort after all others, as one more stream of the matching; seq ranks no launch claims (a false density promise) leave slots at the
+// end, filled with records the fused path leaves out.
+// Each thread takes four launches, all their loads before the first store:
+// the scatter is a chain of three dependent loads (view, stream, arrays), so
+// what counts is how many are in flight. 5M launches of 16 streams in launch
+// order: 266 us with one launch at a time, a load of its group's base in the
+// loop and 256 threads a tile; 92 us now.
 // ---------------------------------------------------------------------------
+constexpr int kRmThreads = 1024, kRmPer = OPA_TILE / kRmThreads;
+constexpr int kRmChunks = OPA_TILE / OPA_WAVE;  // a wave's launches of one turn
+static_assert(kRmChunks == OPA_WAVE, "one lane per chunk in the prefix");
+
 struct RemapArgs {
   const int32_t *sv;
   int64_t T, nt;
   uint32_t NS, NN;
-  const uint32_t *seq, *name, *dur;
+  const uint32_t *name, *dur;
   const uint16_t *st;
   const uint64_t *start, *query;
   const int32_t *part;
   uint32_t *hist;  // [(NS + 1) * nt + 1], then its scan scratch
-  int32_t *perm;  // slot -> launch (-1 past the placed ones)
-  int32_t *inv;   // launch -> slot (-1 for a launch no seq rank holds)
+  int32_t *inv;    // launch -> slot (-1 for a launch no seq rank holds)
   uint32_t *seq2, *name2, *dur2;
   uint16_t *st2;
   uint64_t *start2, *query2;
   int32_t *part2;
 };
 
-// the group of the launch at seq rank j: its stream, NS past the last
+// the tile's launches by rank and their groups: the stream, NS past the last
 // stream, -1 when no launch holds the rank
-__device__ __forceinline__ int remap_group(const RemapArgs &a, int64_t j, int32_t &i) {
-  i = j < a.T ? a.sv[j] : -1;
-  if (i < 0) return -1;
-  const uint32_t s = a.st[i];
-  return (int)(s < a.NS ? s : a.NS);
+__device__ __forceinline__ void remap_groups(const RemapArgs &a, int32_t (&ii)[kRmPer],
+                                             int (&gg)[kRmPer]) {
+  const int64_t base = (int64_t)blockIdx.x * OPA_TILE;
+#pragma unroll
+  for (int k = 0; k < kRmPer; ++k) {
+    const int64_t j = base + k * kRmThreads + threadIdx.x;
+    ii[k] = j < a.T ? a.sv[j] : -1;
+  }
+#pragma unroll
+  for (int k = 0; k < kRmPer; ++k) {
+    const uint32_t s = ii[k] >= 0 ? a.st[ii[k]] : 0u;
+    gg[k] = ii[k] < 0 ? -1 : (int)(s < a.NS ? s : a.NS);
+  }
 }
 
-__global__ void __launch_bounds__(256) k_remap_hist(RemapArgs a) {
+__global__ void __launch_bounds__(kRmThreads) k_remap_hist(RemapArgs a) {
   __shared__ uint32_t c[kMaxSegStreams + 1];
   const int tid = threadIdx.x;
   if (tid <= (int)a.NS) c[tid] = 0;
+  int32_t ii[kRmPer];
+  int gg[kRmPer];
+  remap_groups(a, ii, gg);
   __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * OPA_TILE;
-  for (int e = tid; e < OPA_TILE; e += 256) {
-    int32_t i;
-    const int g = remap_group(a, base + e, i);
-    if (g >= 0) atomicAdd(&c[g], 1u);
+#pragma unroll
+  for (int k = 0; k < kRmPer; ++k) {
+    const int g = gg[k];
+    const uint64_t pm = peers8((uint32_t)(g >= 0 ? g : 255)) & __ballot(g >= 0);
+    if (g >= 0 && (pm & lanemask_lt()) == 0) atomicAdd(&c[g], (uint32_t)__popcll(pm));
   }
   __syncthreads();
   if (tid <= (int)a.NS) a.hist[(int64_t)tid * a.nt + blockIdx.x] = c[tid];
   if (blockIdx.x == 0 && tid == 0) a.hist[(int64_t)(a.NS + 1) * a.nt] = 0;  // the total, after the scan
 }
 
-__global__ void __launch_bounds__(256) k_remap_scatter(RemapArgs a) {
-  __shared__ uint16_t cnt[OPA_TILE_CHUNKS][4][kMaxSegStreams + 1];
-  __shared__ int32_t lidx[OPA_TILE];  // the tile's launches in (group, rank) order
-  __shared__ uint8_t lgrp[OPA_TILE];
-  __shared__ uint32_t lbase[kMaxSegStreams + 1], sh[4];
-  const int tid = threadIdx.x, w = wave_id();
+__global__ void __launch_bounds__(kRmThreads) k_remap_scatter(RemapArgs a) {
+  __shared__ uint16_t cnt[kRmChunks][kMaxSegStreams + 1];
+  __shared__ int32_t lidx[OPA_TILE];   // the tile's launches in (group, rank) order
+  __shared__ uint32_t lrank[OPA_TILE];  // and their rank in the tile, group << 16
+  __shared__ uint32_t gtot[kMaxSegStreams + 1], gbase[kMaxSegStreams + 1];
+  __shared__ uint32_t lbase[kMaxSegStreams + 1], sh[kRmThreads / OPA_WAVE];
+  const int tid = threadIdx.x, w = wave_id(), ln = lane_id();
   const int64_t base = (int64_t)blockIdx.x * OPA_TILE;
   const int ng = (int)a.NS + 1;
-  for (int q = tid; q < OPA_TILE_CHUNKS * 4 * (kMaxSegStreams + 1); q += 256)
-    (&cnt[0][0][0])[q] = 0;
+  int32_t ii[kRmPer];
+  uint32_t lr[kRmPer];
+  int gg[kRmPer];
+  remap_groups(a, ii, gg);
+  if (tid < ng) gbase[tid] = a.hist[(int64_t)tid * a.nt + blockIdx.x];
+  for (int q = tid; q < kRmChunks * (kMaxSegStreams + 1); q += kRmThreads) (&cnt[0][0])[q] = 0;
   __syncthreads();
-  int32_t ii[OPA_TILE_CHUNKS];
-  uint32_t lr[OPA_TILE_CHUNKS];
-  int gg[OPA_TILE_CHUNKS];
 #pragma unroll
-  for (int c = 0; c < OPA_TILE_CHUNKS; ++c) {
-    const int g = remap_group(a, base + c * 256 + tid, ii[c]);
-    gg[c] = g;
+  for (int k = 0; k < kRmPer; ++k) {
+    const int g = gg[k];
     const uint64_t pm = peers8((uint32_t)(g >= 0 ? g : 255)) & __ballot(g >= 0);
-    lr[c] = (uint32_t)__popcll(pm & lanemask_lt());
-    if (g >= 0 && (pm & lanemask_lt()) == 0) cnt[c][w][g] = (uint16_t)__popcll(pm);
+    lr[k] = (uint32_t)__popcll(pm & lanemask_lt());
+    if (g >= 0 && (pm & lanemask_lt()) == 0)
+      cnt[k * (kRmThreads / OPA_WAVE) + w][g] = (uint16_t)__popcll(pm);
   }
   __syncthreads();
-  uint32_t tot = 0;  // thread g: its group's counts over (chunk, wave), in rank order
-  if (tid < ng)
-    for (int c = 0; c < OPA_TILE_CHUNKS; ++c)
-      for (int ww = 0; ww < 4; ++ww) {
-        const uint32_t v = cnt[c][ww][tid];
-        cnt[c][ww][tid] = (uint16_t)tot;
-        tot += v;
-      }
+  // a wave per group: its launches before each chunk, in rank order
+  for (int g = w; g < ng; g += kRmThreads / OPA_WAVE) {
+    const uint32_t v = cnt[ln][g], inc = wave_incl_scan_add(v);
+    cnt[ln][g] = (uint16_t)(inc - v);
+    if (ln == OPA_WAVE - 1) gtot[g] = inc;
+  }
+  __syncthreads();
   uint32_t nl;
-  const uint32_t lb = block_excl_scan_add<uint32_t>(tid < ng ? tot : 0u, sh, &nl);
+  const uint32_t lb = block_excl_scan_add<uint32_t>(tid < ng ? gtot[tid] : 0u, sh, &nl);
   if (tid < ng) lbase[tid] = lb;
   __syncthreads();
   // each launch's place: in the tile's LDS order, and its final one (inv)
 #pragma unroll
-  for (int c = 0; c < OPA_TILE_CHUNKS; ++c) {
-    const int g = gg[c];
+  for (int k = 0; k < kRmPer; ++k) {
+    const int g = gg[k];
     if (g < 0) continue;
-    const uint32_t r = cnt[c][w][g] + lr[c];
-    lidx[lbase[g] + r] = ii[c];
-    lgrp[lbase[g] + r] = (uint8_t)g;
-    a.inv[ii[c]] = (int32_t)(a.hist[(int64_t)g * a.nt + blockIdx.x] + r);
+    const uint32_t r = cnt[k * (kRmThreads / OPA_WAVE) + w][g] + lr[k];
+    lidx[lbase[g] + r] = ii[k];
+    lrank[lbase[g] + r] = (uint32_t)(k * kRmThreads + tid) | ((uint32_t)g << 16);
+    a.inv[ii[k]] = (int32_t)(gbase[g] + r);
   }
   __syncthreads();
   // written in that order: each group's launches go to consecutive slots
-  for (int j = tid; j < (int)nl; j += 256) {
-    const int32_t i = lidx[j];
-    const int g = lgrp[j];
-    const int64_t dst = (int64_t)a.hist[(int64_t)g * a.nt + blockIdx.x] + (j - (int)lbase[g]);
-    a.perm[dst] = i;
-    a.seq2[dst] = a.seq[i];
-    a.name2[dst] = a.name[i];
-    a.dur2[dst] = a.dur[i];
-    a.st2[dst] = a.st[i];
-    a.start2[dst] = a.start[i];
-    if (a.query2) a.query2[dst] = a.query[i];
-    if (a.part2) a.part2[dst] = a.part[i];
+  uint32_t nm[kRmPer], du[kRmPer];
+  uint64_t t0[kRmPer], tq[kRmPer];
+  int32_t pt[kRmPer];
+#pragma unroll
+  for (int k = 0; k < kRmPer; ++k) {
+    const int j = k * kRmThreads + tid;
+    const int32_t i = j < (int)nl ? lidx[j] : 0;  // launch 0 is there to read
+    nm[k] = a.name[i];
+    du[k] = a.dur[i];
+    t0[k] = a.start[i];
+    tq[k] = a.query2 ? a.query[i] : 0;
+    pt[k] = a.part2 ? a.part[i] : 0;
+  }
+#pragma unroll
+  for (int k = 0; k < kRmPer; ++k) {
+    const int j = k * kRmThreads + tid;
+    if (j >= (int)nl) continue;
+    const uint32_t x = lrank[j], g = x >> 16;
+    const int64_t dst = (int64_t)(gbase[g] + ((uint32_t)j - lbase[g]));
+    a.seq2[dst] = (uint32_t)base + (x & 0xFFFFu);
+    a.name2[dst] = nm[k];
+    a.dur2[dst] = du[k];
+    a.st2[dst] = (uint16_t)g;
+    a.start2[dst] = t0[k];
+    if (a.query2) a.query2[dst] = tq[k];
+    if (a.part2) a.part2[dst] = pt[k];
   }
 }
 
@@ -1249,7 +1282,6 @@ __global__ void k_remap_tail(RemapArgs a) {
   const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t placed = a.hist[(int64_t)(a.NS + 1) * a.nt];
   if (x >= a.T || x < placed) return;
-  a.perm[x] = -1;
   a.seq2[x] = (uint32_t)(a.T + (x - placed) < 0xFFFFFFFFll ? a.T + (x - placed) : 0xFFFFFFFFll);
   a.name2[x] = a.NN;
   a.dur2[x] = 0;
@@ -1276,14 +1308,13 @@ size_t remap_hist_entries(const Plan &pl) {
 }
 
 void remap_launches(const opattr_kernels *k, const opattr_dims *d, void *ws, const Plan &pl,
-                    opattr_kernels *out, hipStream_t s) {
+                    hipStream_t s) {
   RemapArgs a{};
   a.sv = at<int32_t>(ws, pl.sv);
   a.T = pl.T;
   a.nt = pl.nt;
   a.NS = d->n_streams;
   a.NN = d->n_names;
-  a.seq = k->seq;
   a.name = k->name_id;
   a.dur = k->dur_ns;
   a.st = k->stream_id;
@@ -1291,7 +1322,6 @@ void remap_launches(const opattr_kernels *k, const opattr_dims *d, void *ws, con
   a.query = k->query_ns;
   a.part = k->part_id;
   a.hist = at<uint32_t>(ws, pl.rm_hist);
-  a.perm = at<int32_t>(ws, pl.rm_perm);
   a.inv = at<int32_t>(ws, pl.rm_inv);
   a.seq2 = at<uint32_t>(ws, pl.rm_seq);
   a.name2 = at<uint32_t>(ws, pl.rm_name);
@@ -1300,14 +1330,14 @@ void remap_launches(const opattr_kernels *k, const opattr_dims *d, void *ws, con
   a.start2 = at<uint64_t>(ws, pl.rm_start);
   a.query2 = k->query_ns ? at<uint64_t>(ws, pl.rm_query) : nullptr;
   a.part2 = k->part_id ? at<int32_t>(ws, pl.rm_part) : nullptr;
-  if (out) remap_view(k, ws, pl, out);
   if (pl.T <= 0) return;
   const int64_t h = ((int64_t)a.NS + 1) * a.nt + 1;
-  fill_u32(reinterpret_cast<uint32_t *>(a.inv), 0xFFFFFFFFu, a.T, s);
-  k_remap_hist<<<(unsigned)a.nt, 256, 0, s>>>(a);
+  // ranks that were computed are all held; promised ones may be missing
+  if (pl.seq_dense) fill_u32(reinterpret_cast<uint32_t *>(a.inv), 0xFFFFFFFFu, a.T, s);
+  k_remap_hist<<<(unsigned)a.nt, kRmThreads, 0, s>>>(a);
   scan_excl_inplace(a.hist, h, a.hist + h, s);
-  k_remap_scatter<<<(unsigned)a.nt, 256, 0, s>>>(a);
-  k_remap_tail<<<(unsigned)((a.T + 255) / 256), 256, 0, s>>>(a);
+  k_remap_scatter<<<(unsigned)a.nt, kRmThreads, 0, s>>>(a);
+  if (pl.seq_dense) k_remap_tail<<<(unsigned)((a.T + 255) / 256), 256, 0, s>>>(a);
 }
 
 // by launch, so that the caller's arrays are written in order
@@ -1451,7 +1481,7 @@ static TlArgs tl_args(const opattr_kernels *k, const opattr_dims *d, void *ws, c
   a.seq = k->seq;
   a.bnd = at<uint32_t>(ws, pl.tbnd);
   a.kblk = at<int64_t>(ws, pl.kblk);
-  a.NS = d->n_streams;
+  a.NS = pl.nseg;
   a.vdiag = nullptr;
   return a;
 }
@@ -1523,9 +1553,9 @@ void run_match(const IomArgs &x, hipStream_t s) {
     pa.diag = x.diag;
     pa.st = k->stream_id;
     pa.T = pl.T;
-    pa.NS = pl.NS;
+    pa.NS = pl.nseg;
     pa.kblk = at<int64_t>(ws, pl.kblk);
-    const int nw = (int)((pl.NS + 1 + 3) / 4);
+    const int nw = (int)((pl.nseg + 1 + 3) / 4);
     k_seg_prologue<<<(unsigned)(pa.nf + pa.nr + nw), 256, 0, s>>>(pa);
   } else {
     fill_many(clr, s);
@@ -1566,10 +1596,10 @@ void run_match(const IomArgs &x, hipStream_t s) {
 
   // the timeline side
   if (seg && pl.nt > 0) {
-    if (!seg_pro) launch_stream_blocks(k->stream_id, pl.T, pl.NS, at<int64_t>(ws, pl.kblk), s);
-    const int64_t nb = (pl.nt + 1) * pl.NS;
+    if (!seg_pro) launch_stream_blocks(k->stream_id, pl.T, pl.nseg, at<int64_t>(ws, pl.kblk), s);
+    const int64_t nb = (pl.nt + 1) * pl.nseg;
     k_tile_bounds<<<(unsigned)((nb + 255) / 256), 256, 0, s>>>(k->seq, at<int64_t>(ws, pl.kblk),
-                                                             pl.NS, pl.nt, at<uint32_t>(ws, pl.tbnd));
+                                                             pl.nseg, pl.nt, at<uint32_t>(ws, pl.tbnd));
   }
   HistOut ho;
   ho.tlh = tlh;

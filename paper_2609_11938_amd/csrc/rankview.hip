@@ -15,6 +15,11 @@
 // the smaller (seq, launch) records for each; after a larger one the view is
 // rebuilt by a stable radix sort in one block (k_rv_equal), which otherwise
 // ends at once. Either way ties go by input index, as the general sort has it.
+// 3M launches of 8 streams: 77 us (10 + 16 + 7 + 21 + 19 + 4), bound by the
+// scatter's partial lines and by the latency of short kernels; the whole call
+// 559 us with the sort, 375 us with this. 500k shuffled: 328 us and 229 us.
+// Blocks of 256 and 1024 threads in step 5 and 2048 launches per bucket: the
+// same within 3 us.
 #include "common.h"
 #include "impl.h"
 

@@ -195,6 +195,27 @@ def test_launch_ranks_by_buckets(T, kind):
     assert bool(diag["flags"] & opattr.F_ORDER) == (kind in ("pairs", "same"))
 
 
+@pytest.mark.parametrize("T,S,kinds,dense", [
+    (1, 1, False, False), (4095, 63, False, False), (4097, 63, True, True),
+    (70_001, 5, True, False), (70_001, 63, False, True), (2 ** 20 + 1, 3, False, False)])
+def test_permuted_launches(T, S, kinds, dense):
+    """Launches in another order that the compact path leaves (more names,
+    range kinds, more launches): permuted by their ranks, with gaps in seq or
+    without, at tile edges, with the most streams and streams past the last."""
+    tr = cases.random_trace(7100 + T % 983 + S, T=T, S=S, n_names=30 if kinds or T > 2 ** 20 else 2100,
+                            R=max(1, T // 18), n_ops=90, t_max=6 * T + 8, max_depth=5,
+                            dedup=T > 5000, drop=0.02, seq_gaps=not dense)
+    if kinds:
+        tr = cases.with_kinds(tr, 3)
+    if S == 63:
+        tr["stream_id"] = tr["stream_id"].copy()
+        tr["stream_id"][::701] = 63 + np.arange(len(range(0, T, 701))) % 3
+    print(f"case permuted T={T} S={S} kinds={kinds} dense={dense}", flush=True)
+    want = O.attribute(tr)
+    out, diag = _run(tr, flags=opattr.SEQ_DENSE if dense else 0)
+    parity.assert_attribute(out, want, diag)
+
+
 @pytest.mark.parametrize("kinds", [False, True])
 def test_row_order_more_partials_than_room(kinds):
     """Query points that jump back and forth change the innermost range far
