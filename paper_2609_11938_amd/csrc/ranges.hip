@@ -195,7 +195,8 @@ RangeWork range_work(const CoreRanges &cr, const opattr_dims *d, void *ws, const
 // Nesting order of ranges given in any order: a merge sort of the records
 // (stream, start, end, index) by stream asc, start asc, end desc, index asc.
 // Blocks first sort tiles of kRsSort records in LDS, then
-// each pass merges pairs of sorted runs; a block takes kRsTile outputs of one
+// each pass merges pairs of sorted runs (of few ranges four at once,
+// k_rsort_ways); a block takes kRsTile outputs of one
 // pair, finds where they begin in each run along the merge path (a search on
 // the diagonal, 64 probes per step across a wave), stages the two slices in
 // LDS and places every record by its rank in the other slice (binary
@@ -411,21 +412,85 @@ __global__ void __launch_bounds__(kRsThreads) k_rsort_merge(RSortBuf in, RSortBu
   }
 }
 
+// Few ranges: a pass merges up to kRsWay sorted runs of w records (a power of
+// two) at once: a record's place is its place in its own run plus, for every other
+// run of the group, the count of records there that precede it. A thread
+// takes one record and does the binary searches of all runs together, so a
+// step costs one round trip to the cache whatever the number of runs;
+// neighbouring records probe neighbouring places. 60,000 ranges: three passes
+// of 12 us instead of six of the pairwise merge (eight runs at once: two of 20).
+// Many ranges are bound by the probes, which the pairwise merge makes in LDS:
+// 250,000 take 73 us so and 106 us pairwise but slow the streams beside them
+// (launch order, 5M launches: 494 us and 488 us the call), 1,000,000 take
+// 262 us and 213 us.
+constexpr int kRsWay = 4;
+constexpr int64_t kRsWayMax = 1 << 17;
+static_assert(kRsSort % kRsThreads == 0, "a block's records lie in one run");
+
+__global__ void __launch_bounds__(kRsThreads) k_rsort_ways(RSortBuf in, RSortBuf out, int64_t R,
+                                                            int64_t w, RSortOut f, int last) {
+  const int64_t b0 = (int64_t)blockIdx.x * kRsThreads, i = b0 + threadIdx.x;
+  const int64_t g0 = b0 / (w * kRsWay) * (w * kRsWay);  // the group's first record
+  const int own = (int)((b0 - g0) / w);                 // uniform over the block
+  const RRec v = rrec_load(in, i < R ? i : R - 1);
+  int64_t pos[kRsWay], n[kRsWay];
+#pragma unroll
+  for (int q = 0; q < kRsWay; ++q) {
+    const int64_t left = R - (g0 + q * w);
+    pos[q] = 0;
+    n[q] = left < 0 || q == own ? 0 : (left < w ? left : w);
+  }
+  for (int64_t step = w; step > 0; step >>= 1) {
+    uint32_t sk[kRsWay];
+    uint64_t ss[kRsWay];
+#pragma unroll
+    for (int q = 0; q < kRsWay; ++q)
+      if (pos[q] + step <= n[q]) {
+        const int64_t m = g0 + q * w + pos[q] + step - 1;
+        sk[q] = in.st[m];
+        ss[q] = in.s[m];
+      } else {
+        sk[q] = 0xFFFFFFFFu;  // follows every record
+        ss[q] = 0;
+      }
+#pragma unroll
+    for (int q = 0; q < kRsWay; ++q) {
+      bool before = sk[q] != v.st ? sk[q] < v.st : ss[q] < v.s;
+      if (sk[q] == v.st && ss[q] == v.s) {
+        const int64_t m = g0 + q * w + pos[q] + step - 1;
+        const uint64_t e = in.e[m];
+        before = e != v.e ? e > v.e : in.x[m] < v.x;
+      }
+      pos[q] += before ? step : 0;
+    }
+  }
+  int64_t o = i - own * w;  // the group's first record and the place in the own run
+#pragma unroll
+  for (int q = 0; q < kRsWay; ++q) o += pos[q];
+  if (i < R) rrec_store(out, f, last != 0, o, v);
+}
+
 // Sorts ranges into nesting order; the result lands in `fin` (with op and
 // kind in f), `tmp` is the other buffer of the passes.
 static void sort_ranges(const opattr_ranges *r, int64_t R, const RSortBuf &fin,
                         const RSortBuf &tmp, const RSortOut &f, hipStream_t s) {
+  const int way = R <= kRsWayMax ? kRsWay : 2;
   int np = 0;
-  for (int64_t w = kRsSort; w < R; w *= 2) ++np;
-  const unsigned nb = (unsigned)((R + kRsTile - 1) / kRsTile);
+  for (int64_t w = kRsSort; w < R; w *= way) ++np;
   // the passes alternate buffers; start so that the last one writes fin
   const RSortBuf *cur = (np % 2 == 0) ? &fin : &tmp;
   k_rsort_tile<<<(unsigned)((R + kRsSort - 1) / kRsSort), kRsSortThreads, sizeof(RsSortLds), s>>>(
       *r, R, *cur, f, np == 0 ? 1 : 0);
   int q = 0;
-  for (int64_t w = kRsSort; w < R; w *= 2, ++q) {
+  for (int64_t w = kRsSort; w < R; w *= way, ++q) {
     const RSortBuf *nxt = cur == &fin ? &tmp : &fin;
-    k_rsort_merge<<<nb, kRsThreads, 0, s>>>(*cur, *nxt, R, w, f, q == np - 1 ? 1 : 0);
+    const int last = q == np - 1 ? 1 : 0;
+    if (way == kRsWay)
+      k_rsort_ways<<<(unsigned)((R + kRsThreads - 1) / kRsThreads), kRsThreads, 0, s>>>(
+          *cur, *nxt, R, w, f, last);
+    else
+      k_rsort_merge<<<(unsigned)((R + kRsTile - 1) / kRsTile), kRsThreads, 0, s>>>(
+          *cur, *nxt, R, w, f, last);
     cur = nxt;
   }
 }

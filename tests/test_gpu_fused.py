@@ -195,6 +195,23 @@ def test_launch_ranks_by_buckets(T, kind):
     assert bool(diag["flags"] & opattr.F_ORDER) == (kind in ("pairs", "same"))
 
 
+@pytest.mark.parametrize("R,t_max", [(1024, 4000), (1025, 50), (4097, 9000), (5000, 3),
+                                     (2 ** 17, 300_000), (2 ** 17 + 1, 300_000)])
+def test_unordered_ranges_merge_passes(R, t_max):
+    """Ranges in any order around the tile of the sort, a group of runs and
+    the size from which runs are merged in pairs, some with many ties."""
+    rng = np.random.default_rng(R)
+    tr = cases.random_trace(7200 + R % 97, T=20_000, S=3, n_names=20, R=64, n_ops=30, t_max=t_max)
+    st = rng.integers(0, 3, R).astype(np.uint16)
+    start = rng.integers(0, t_max + 1, R).astype(np.uint64)
+    tr.update(r_stream=st, r_start=start, r_end=start + rng.integers(0, 4, R).astype(np.uint64),
+              r_op=rng.integers(0, 30, R).astype(np.uint32))
+    print(f"case merge passes R={R} t_max={t_max}", flush=True)
+    want = O.attribute(tr)
+    out, diag = _run(tr, flags=0)
+    parity.assert_attribute(out, want, diag)
+
+
 @pytest.mark.parametrize("T,S,kinds,dense", [
     (1, 1, False, False), (4095, 63, False, False), (4097, 63, True, True),
     (70_001, 5, True, False), (70_001, 63, False, True), (2 ** 20 + 1, 3, False, False)])
