@@ -388,6 +388,42 @@ def test_stage_dedup_and_aggregate_on_given_inputs():
     parity.assert_table(a.table_host(), want["table"])
 
 
+@pytest.mark.parametrize("layout", ["rows", "row_stride_24", "row_stride_21", "row_offset",
+                                    "columns", "out_offset"])
+@pytest.mark.parametrize("T", [1, 255, 257, 1031])
+def test_counters_out_layouts(T, layout):
+    """Inherited counter rows in 16-byte pieces (aligned row-major rows) and
+    one by one (odd strides, offsets, columns), with absent counters and
+    matches out of range, on either side of a block's launches."""
+    import torch
+
+    print(f"case counters_out T={T} {layout}", flush=True)
+    tr = cases.random_trace(77, T=T, P=300)
+    rng = np.random.default_rng(T)
+    tr["counters"] = rng.random((300, 20), dtype=np.float32)
+    tr["pf_name"] = np.zeros(300, np.uint32)
+    match = rng.integers(-1, 302, size=T).astype(np.int32)
+    absent = (1 << 3) | (1 << 16) | (1 << 19)
+    dt = opattr.to_device(tr, DEV)
+    cnt = dt["counters"]
+    if layout.startswith("row_stride"):
+        wide = torch.full((300, int(layout[-2:])), 7.0, device=DEV)
+        wide[:, :20] = cnt
+        dt["counters"] = wide[:, :20]
+    elif layout == "row_offset":
+        flat = torch.zeros(300 * 20 + 1, device=DEV)
+        flat[1:] = cnt.flatten()
+        dt["counters"] = flat[1:].view(300, 20)
+    elif layout == "columns":
+        dt["counters"] = cnt.t().contiguous().t()
+    out = torch.empty(T * 20 + 1, dtype=torch.float32, device=DEV)
+    out = (out[1:] if layout == "out_offset" else out[:-1]).view(T, 20)
+    opattr.opattr_dedup_broadcast(dt, torch.from_numpy(match).to(DEV), counters_out=out,
+                                  absent_mask=absent)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(parity.host(out), O.counters_out(tr, match, absent_mask=absent))
+
+
 def test_determinism_and_poisoned_outputs():
     import torch
 
