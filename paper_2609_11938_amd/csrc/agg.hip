@@ -578,9 +578,9 @@ void plan_items(const EncArgs &x, hipStream_t s) {
     bool in1 = false;
     if (cap > 0) {
       k_item_keys<<<(unsigned)((cap + 255) / 256), 256, 0, s>>>(w, k0, v0, cap);
-      const int bits = (bits_for_host(pl.G) + 7) & ~7;
-      in1 = radix_sort_pairs(k0, v0, k1, v1, cap, 0, bits,
-                             at<uint32_t>(x.ws, pl.isort_hist), s, w.meta);
+      // (the digits' totals in the heavy rows' space, over 2 * kFastKeys words, not used yet)
+      in1 = radix_sort_pairs(k0, v0, k1, v1, cap, 0, bits_for_host(pl.G),
+                             at<uint32_t>(x.ws, pl.isort_hist), s, w.meta, pl.idigit, w.heavy);
     }
     if (cap > 0)
       k_item_place<<<(unsigned)((cap + 255) / 256), 256, 0, s>>>(w, in1 ? k1 : k0, in1 ? v1 : v0,

@@ -21,17 +21,19 @@ __device__ __forceinline__ uint64_t lanemask_lt() {
   return (1ull << lane_id()) - 1ull;
 }
 
-// Lanes of the wave holding the same 8-bit digit (match-any built from one
-// ballot per bit: the published warp-multisplit peer-mask construction).
-__device__ __forceinline__ uint64_t peers8(uint32_t d) {
+// Lanes of the wave holding the same digit (match-any built from one ballot
+// per bit: the published warp-multisplit peer-mask construction).
+template <int kBits>
+__device__ __forceinline__ uint64_t peers_of(uint32_t d) {
   uint64_t m = ~0ull;
 #pragma unroll
-  for (int b = 0; b < 8; ++b) {
+  for (int b = 0; b < kBits; ++b) {
     const uint64_t v = __ballot((d >> b) & 1u);
     m &= ((d >> b) & 1u) ? v : ~v;
   }
   return m;
 }
+__device__ __forceinline__ uint64_t peers8(uint32_t d) { return peers_of<8>(d); }
 
 // Lanes whose keys agree on bits [0, nbits) (nbits uniform across the wave).
 __device__ __forceinline__ uint64_t match_any_bits(uint32_t key, int nbits) {

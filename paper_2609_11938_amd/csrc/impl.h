@@ -75,6 +75,7 @@ struct Plan {
   int64_t cap_items, cap_rows, max_windows, hcap;
   size_t wi, wr, hmb, ig, ia, ib, rows, meta, ith, itch, gcnt, goff, heavy, multi, sit, part;
   size_t hch, hpart;
+  int idigit;  // bits of the item sort's digits
   size_t isort_k0, isort_k1, isort_v0, isort_v1, isort_hist;  // item sort, many rows
   // dedup class discovery
   size_t c_first, c_last, c_runs, c_key, c_cand, c_fail, c_list, c_tkey, c_tmin;
@@ -149,13 +150,15 @@ inline int bits_for_host(uint32_t v) {
 // inclusive scan of n int64 values in place; scratch holds n / 4096 + 1 values
 void scan_incl_i64_inplace(int64_t *a, int64_t n, int64_t *scratch, hipStream_t s);
 // Stable LSD sort of (32-bit key, value) pairs by key bits [begin_bit,
-// end_bit), 8 bits a pass; true when the result is in (k1, v1). n_dev
-// (optional): the element count on the device (<= n); only that many are
-// sorted
+// end_bit), digit_bits (8 or 9) a pass; true when the result is in (k1, v1).
+// n_dev (optional): the element count on the device (<= n); only that many
+// are sorted. totals (optional): 1 << digit_bits entries; the scan of a pass
+// is then one launch instead of three
 bool radix_sort_pairs(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32_t *v1, int64_t n,
                       int begin_bit, int end_bit, uint32_t *hist, hipStream_t s,
-                      const int64_t *n_dev = nullptr);
-size_t radix_hist_entries(int64_t n);
+                      const int64_t *n_dev = nullptr, int digit_bits = 8,
+                      uint32_t *totals = nullptr);
+size_t radix_hist_entries(int64_t n, int digit_bits = 8);
 // Several 32-bit fills in one launch (up to 8 arrays).
 struct FillJobs {
   static constexpr int kMaxJobs = 8;

@@ -1,6 +1,7 @@
-// Stable LSD radix sort of (u64 key, u32 value) pairs, 8-bit digits.
+// Stable LSD radix sort of (u32 key, u32 value) pairs, digits of 8 or 9 bits.
 // Each pass: per-tile digit histograms -> one exclusive scan in digit-major
-// order -> a scatter that ranks equal digits stably inside the tile with
+// order (or each digit's column on its own, the digits' bases then taken by
+// the scatter's blocks) -> a scatter that ranks equal digits stably inside the tile with
 // wave ballots (per-digit peer masks) and per-(chunk, wave) counts in LDS.
 #include "common.h"
 #include "impl.h"
@@ -15,20 +16,49 @@ __device__ __forceinline__ int64_t sort_count(int64_t n, const int64_t *n_dev) {
   return m < n ? (m > 0 ? m : 0) : n;
 }
 
+template <int kBits>
 __global__ void __launch_bounds__(256) k_rs_hist(const uint32_t *__restrict__ keys, int64_t n_cap,
                                                  const int64_t *n_dev, int shift,
                                                  uint32_t *__restrict__ hist, int64_t ntiles) {
-  __shared__ uint32_t c[256];
-  c[threadIdx.x] = 0;
+  constexpr int kDigits = 1 << kBits;
+  __shared__ uint32_t c[kDigits];
+  for (int i = threadIdx.x; i < kDigits; i += 256) c[i] = 0;
   __syncthreads();
   const int64_t n = sort_count(n_cap, n_dev);
   const int64_t base = (int64_t)blockIdx.x * OPA_TILE;
   for (int i = threadIdx.x; i < OPA_TILE; i += 256) {
     const int64_t x = base + i;
-    if (x < n) atomicAdd(&c[(keys[x] >> shift) & 255u], 1u);
+    if (x < n) atomicAdd(&c[(keys[x] >> shift) & (kDigits - 1)], 1u);
   }
   __syncthreads();
-  hist[(int64_t)threadIdx.x * ntiles + blockIdx.x] = c[threadIdx.x];
+  for (int i = threadIdx.x; i < kDigits; i += 256) hist[(int64_t)i * ntiles + blockIdx.x] = c[i];
+}
+
+// One digit's counts over the tiles scanned in place, and its total (a block
+// per digit).
+__global__ void __launch_bounds__(256) k_rs_column(uint32_t *__restrict__ hist, int64_t ntiles,
+                                                   uint32_t *__restrict__ totals) {
+  __shared__ uint32_t sh[4];
+  uint32_t *col = hist + (int64_t)blockIdx.x * ntiles;
+  uint32_t carry = 0;
+  for (int64_t t0 = 0; t0 < ntiles; t0 += 1024) {
+    const int64_t t = t0 + (int64_t)threadIdx.x * 4;
+    uint32_t v[4], sum = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      v[k] = t + k < ntiles ? col[t + k] : 0u;
+      sum += v[k];
+    }
+    uint32_t tot;
+    uint32_t run = carry + block_excl_scan_add<uint32_t>(sum, sh, &tot);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (t + k < ntiles) col[t + k] = run;
+      run += v[k];
+    }
+    carry += tot;
+  }
+  if (threadIdx.x == 0) totals[blockIdx.x] = carry;
 }
 
 // Exclusive scan of in[0..n) into out (in place when they are the same) by
@@ -221,21 +251,29 @@ void launch_scan_excl(const uint32_t *in, uint32_t *out, int64_t n, int64_t *tot
 // then the counts scanned over chunks and waves), the pairs placed in digit
 // order in LDS, then written out in that order so that each digit's run goes
 // to consecutive addresses.
+// totals (optional): offs holds each digit's own column scan, and a digit's
+// base is the sum of the totals before it.
+template <int kBits>
 __global__ void __launch_bounds__(256) k_rs_scatter(const uint32_t *__restrict__ kin,
                                                     const uint32_t *__restrict__ vin,
                                                     uint32_t *__restrict__ kout,
                                                     uint32_t *__restrict__ vout, int64_t n_cap,
                                                     const int64_t *n_dev, int shift,
                                                     const uint32_t *__restrict__ offs,
-                                                    int64_t ntiles) {
-  __shared__ uint16_t cnt[OPA_TILE_CHUNKS][4][256];
+                                                    int64_t ntiles,
+                                                    const uint32_t *__restrict__ totals) {
+  constexpr int kDigits = 1 << kBits, kPer = kDigits / 256;  // digits; and per thread
+  __shared__ uint16_t cnt[OPA_TILE_CHUNKS][4][kDigits];
   __shared__ uint32_t lk[OPA_TILE], lv[OPA_TILE];
-  __shared__ uint32_t dbase[256], gbase[256], sh[4];
+  __shared__ uint32_t dbase[kDigits], gbase[kDigits], sh[4];
   const int tid = threadIdx.x, w = wave_id();
   const int64_t n = sort_count(n_cap, n_dev);
   const int64_t base = (int64_t)blockIdx.x * OPA_TILE;
   if (base >= n) return;  // uniform over the block
-  for (int i = tid; i < OPA_TILE_CHUNKS * 4 * 256; i += 256) (&cnt[0][0][0])[i] = 0;
+  {
+    uint32_t *c32 = reinterpret_cast<uint32_t *>(&cnt[0][0][0]);
+    for (int i = tid; i < OPA_TILE_CHUNKS * 4 * kDigits / 2; i += 256) c32[i] = 0;
+  }
   __syncthreads();
   uint32_t key[OPA_TILE_CHUNKS], val[OPA_TILE_CHUNKS], lr[OPA_TILE_CHUNKS];
 #pragma unroll
@@ -244,28 +282,46 @@ __global__ void __launch_bounds__(256) k_rs_scatter(const uint32_t *__restrict__
     const bool ok = x < n;  // pairs past n are the wave's last lanes
     key[c] = ok ? kin[x] : 0u;
     val[c] = ok ? vin[x] : 0u;
-    const uint32_t d = (key[c] >> shift) & 255u;
-    const uint64_t pm = peers8(d) & __ballot(ok);
+    const uint32_t d = (key[c] >> shift) & (kDigits - 1);
+    const uint64_t pm = peers_of<kBits>(d) & __ballot(ok);
     lr[c] = (uint32_t)__popcll(pm & lanemask_lt());
     if (ok && (pm & lanemask_lt()) == 0) cnt[c][w][d] = (uint16_t)__popcll(pm);
   }
   __syncthreads();
-  uint32_t tot = 0;  // thread d: the tile's pairs of digit d
-  for (int c = 0; c < OPA_TILE_CHUNKS; ++c)
-    for (int ww = 0; ww < 4; ++ww) {
-      const uint32_t v = cnt[c][ww][tid];
-      cnt[c][ww][tid] = (uint16_t)tot;
-      tot += v;
-    }
-  const uint32_t db = block_excl_scan_add<uint32_t>(tot, sh, nullptr);
-  dbase[tid] = db;
-  gbase[tid] = offs[(int64_t)tid * ntiles + blockIdx.x];
+  uint32_t tot[kPer], all = 0;  // the thread's digits: the tile's pairs of each
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    tot[j] = 0;
+    for (int c = 0; c < OPA_TILE_CHUNKS; ++c)
+      for (int ww = 0; ww < 4; ++ww) {
+        const uint32_t v = cnt[c][ww][tid * kPer + j];
+        cnt[c][ww][tid * kPer + j] = (uint16_t)tot[j];
+        tot[j] += v;
+      }
+    all += tot[j];
+  }
+  uint32_t db = block_excl_scan_add<uint32_t>(all, sh, nullptr);
+  uint32_t gb = 0;
+  if (totals) {  // uniform
+    uint32_t t = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) t += totals[tid * kPer + j];
+    gb = block_excl_scan_add<uint32_t>(t, sh, nullptr);
+  }
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int d = tid * kPer + j;
+    dbase[d] = db;
+    gbase[d] = gb + offs[(int64_t)d * ntiles + blockIdx.x];
+    db += tot[j];
+    if (totals) gb += totals[d];
+  }
   __syncthreads();
 #pragma unroll
   for (int c = 0; c < OPA_TILE_CHUNKS; ++c) {
     const int64_t x = base + c * 256 + tid;
     if (x < n) {
-      const uint32_t d = (key[c] >> shift) & 255u;
+      const uint32_t d = (key[c] >> shift) & (kDigits - 1);
       const uint32_t lp = dbase[d] + cnt[c][w][d] + lr[c];
       lk[lp] = key[c];
       lv[lp] = val[c];
@@ -274,7 +330,7 @@ __global__ void __launch_bounds__(256) k_rs_scatter(const uint32_t *__restrict__
   __syncthreads();
   const int nl = (int)(n - base < OPA_TILE ? n - base : OPA_TILE);
   for (int j = tid; j < nl; j += 256) {
-    const uint32_t k = lk[j], d = (k >> shift) & 255u;
+    const uint32_t k = lk[j], d = (k >> shift) & (kDigits - 1);
     const uint32_t dst = gbase[d] + ((uint32_t)j - dbase[d]);
     kout[dst] = k;
     vout[dst] = lv[j];
@@ -282,24 +338,30 @@ __global__ void __launch_bounds__(256) k_rs_scatter(const uint32_t *__restrict__
 }
 
 // the digit histograms of every tile, then the scan's chunk sums
-size_t radix_hist_entries(int64_t n) {
+size_t radix_hist_entries(int64_t n, int digit_bits) {
   const int64_t nt = (n + OPA_TILE - 1) / OPA_TILE;
-  const int64_t h = (nt > 0 ? nt : 1) * 256;
+  const int64_t h = (nt > 0 ? nt : 1) << digit_bits;
   return (size_t)h + scan_scratch_entries(h);
 }
 
 bool radix_sort_pairs(uint32_t *k0, uint32_t *v0, uint32_t *k1, uint32_t *v1, int64_t n,
                       int begin_bit, int end_bit, uint32_t *hist, hipStream_t s,
-                      const int64_t *n_dev) {
+                      const int64_t *n_dev, int digit_bits, uint32_t *totals) {
   if (n <= 0) return false;
   const int64_t nt = (n + OPA_TILE - 1) / OPA_TILE;
+  const int64_t nh = nt << digit_bits;
   bool in1 = false;
-  for (int sh = begin_bit; sh < end_bit; sh += 8) {
+  for (int sh = begin_bit; sh < end_bit; sh += digit_bits) {
     uint32_t *ki = in1 ? k1 : k0, *ko = in1 ? k0 : k1;
     uint32_t *vi = in1 ? v1 : v0, *vo = in1 ? v0 : v1;
-    k_rs_hist<<<(unsigned)nt, 256, 0, s>>>(ki, n, n_dev, sh, hist, nt);
-    scan_excl_inplace(hist, nt * 256, hist + nt * 256, s);
-    k_rs_scatter<<<(unsigned)nt, 256, 0, s>>>(ki, vi, ko, vo, n, n_dev, sh, hist, nt);
+    if (digit_bits == 9) k_rs_hist<9><<<(unsigned)nt, 256, 0, s>>>(ki, n, n_dev, sh, hist, nt);
+    else k_rs_hist<8><<<(unsigned)nt, 256, 0, s>>>(ki, n, n_dev, sh, hist, nt);
+    if (totals) k_rs_column<<<1u << digit_bits, 256, 0, s>>>(hist, nt, totals);
+    else scan_excl_inplace(hist, nh, hist + nh, s);
+    if (digit_bits == 9)
+      k_rs_scatter<9><<<(unsigned)nt, 256, 0, s>>>(ki, vi, ko, vo, n, n_dev, sh, hist, nt, totals);
+    else
+      k_rs_scatter<8><<<(unsigned)nt, 256, 0, s>>>(ki, vi, ko, vo, n, n_dev, sh, hist, nt, totals);
     in1 = !in1;
   }
   return in1;

@@ -165,6 +165,29 @@ def test_aggregate_ops_heavy_rows(T):
     assert diag["status"] == want["diag"]["status"] == 0
 
 
+@pytest.mark.parametrize("n_ops", [6_144, 65_535, 65_536, 131_072, 262_142, 262_143])
+def test_aggregate_ops_many_rows(n_ops):
+    """Item sorts on either side of 16, 17 and 18 bits of rows (digits of 8 or
+    of 9 bits) over a few tiles and a ragged last one, the highest rows among
+    them."""
+    import torch
+
+    print(f"case aggregate_ops many rows {n_ops}", flush=True)
+    T = 3 * 4096 + 77
+    tr = cases.random_trace(11, T=T, R=8, n_ops=n_ops)
+    rng = np.random.default_rng(n_ops)
+    P = tr["counters"].shape[0]
+    match = rng.integers(-1, P, size=T).astype(np.int32)
+    op = rng.integers(-1, n_ops, size=T).astype(np.int32)
+    op[::5] = rng.integers(n_ops - 3, n_ops, size=op[::5].size)
+    want = O.aggregate_ops(tr, match, op)
+    out = opattr.opattr_aggregate_ops(opattr.to_device(tr, DEV), torch.from_numpy(match).to(DEV),
+                                      torch.from_numpy(op).to(DEV))
+    torch.cuda.synchronize()
+    parity.assert_table(out.table_host(), want["table"])
+    assert opattr.read_diag(out["diag"])["status"] == want["diag"]["status"] == 0
+
+
 def test_attribute_tiered_pipeline():
     """The tiered pipeline as library calls (match + dedup broadcast, walk,
     tiers, table by tier operator) against the oracle's stages on GPT-2
