@@ -165,6 +165,35 @@ def test_aggregate_ops_heavy_rows(T):
     assert diag["status"] == want["diag"]["status"] == 0
 
 
+@pytest.mark.parametrize("T, longest", [(150_001, 8), (4_400_003, 8), (2_200_000, 2)])
+def test_aggregate_ops_window_groups(T, longest):
+    """Runs of 1 to 8 launches (or 1 and 2) over three busy rows and 800 rare
+    ones: windows and groups of windows inside one row, on its edges and over
+    many rows, by references of uneven lengths, at the window counts of each
+    group size."""
+    import torch
+
+    print(f"case aggregate_ops window groups T={T} longest={longest}", flush=True)
+    rng = np.random.default_rng(T)
+    n_ops, P = 803, 50_000
+    tr = cases.random_trace(6, T=64, R=8, n_ops=n_ops)
+    tr.update(seq=np.arange(T, dtype=np.uint32), start_ns=np.arange(T, dtype=np.uint64) * 10,
+              dur_ns=rng.integers(1, 5000, size=T).astype(np.uint32),
+              stream_id=np.zeros(T, np.uint16), name_id=np.zeros(T, np.uint32), part_id=None,
+              pf_name=np.zeros(P, np.uint32),
+              counters=rng.random((P, 20), dtype=np.float32), part_rep=None, n_parts=0)
+    run = np.repeat(np.arange(T), rng.integers(1, longest + 1, size=T))[:T]
+    row = np.where(rng.random(T) < 0.97, rng.integers(-1, 2, size=T), rng.integers(2, n_ops, size=T))
+    op = row[run].astype(np.int32)
+    match = rng.integers(-1, P, size=T).astype(np.int32)
+    want = O.aggregate_ops(tr, match, op)
+    out = opattr.opattr_aggregate_ops(opattr.to_device(tr, DEV), torch.from_numpy(match).to(DEV),
+                                      torch.from_numpy(op).to(DEV))
+    torch.cuda.synchronize()
+    parity.assert_table(out.table_host(), want["table"])
+    assert opattr.read_diag(out["diag"])["status"] == want["diag"]["status"] == 0
+
+
 @pytest.mark.parametrize("n_ops", [6_144, 65_535, 65_536, 131_072, 262_142, 262_143])
 def test_aggregate_ops_many_rows(n_ops):
     """Item sorts on either side of 16, 17 and 18 bits of rows (digits of 8 or
