@@ -75,18 +75,22 @@ __device__ __forceinline__ void wave_rank(const uint32_t (&key)[CH], uint32_t K,
   }
 }
 
-// After wave_rank over a 4-wave block: turn the per-wave counters cnt[w*K+n]
-// into the count of key n in earlier waves, and write the block totals to
-// total[n] (if given). Call from all threads; ends with a barrier.
+// After wave_rank over a block of kWaves waves: turn the per-wave counters
+// cnt[w*K+n] into the count of key n in earlier waves, and write the block
+// totals to total[n] (if given). Call from all threads; ends with a barrier.
+template <int kWaves = 4>
 __device__ __forceinline__ void block_rank_bases(uint16_t *cnt, uint32_t K, uint32_t *total) {
   __syncthreads();
   for (uint32_t n = threadIdx.x; n < K; n += blockDim.x) {
-    const uint32_t a = cnt[n], b = cnt[K + n], c = cnt[2 * K + n], d = cnt[3 * K + n];
-    cnt[n] = 0;
-    cnt[K + n] = (uint16_t)a;
-    cnt[2 * K + n] = (uint16_t)(a + b);
-    cnt[3 * K + n] = (uint16_t)(a + b + c);
-    if (total) total[n] = a + b + c + d;
+    uint32_t v[kWaves], run = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) v[w] = cnt[w * K + n];
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      cnt[w * K + n] = (uint16_t)run;
+      run += v[w];
+    }
+    if (total) total[n] = run;
   }
   __syncthreads();
 }

@@ -120,10 +120,20 @@ struct TlArgs {
   opattr_diag *vdiag;   // under OPATTR_VALIDATE: the density check reports here (else NULL)
 };
 
-// Element e of a tile sits in wave e / 1024, chunk (e / 64) % 16, lane e % 64.
+// A tile over kWaves waves: a wave has OPA_TILE / kWaves consecutive elements,
+// in chunks of 64.
+template <int kWaves = 4>
 __device__ __forceinline__ int tile_elem(int c) {
-  return wave_id() * (OPA_TILE / 4) + c * OPA_WAVE + lane_id();
+  return wave_id() * (OPA_TILE / kWaves) + c * OPA_WAVE + lane_id();
 }
+
+// The kernels that only rank by name take sixteen waves a tile for few names,
+// else four: a wave ranks its chunks one after the other (each reads the
+// counters the last one wrote), so four chunks a wave end sooner than sixteen.
+// 1.9M rows, 464 tiles, 64 names: histogram 15.5 us by four waves, 9.9 by
+// sixteen, slots 17.1 and 11.4. The counters are cleared and scanned for every
+// wave and name, which takes the gain back at about 1000 names.
+constexpr uint32_t kWideNames = 512;
 
 // Ranking key of launch j (its name if eligible for replay -- no partition,
 // or a partition that is its own class representative -- else NN) and
@@ -740,7 +750,9 @@ struct RankArgs {
 // rank = (eligible launches of the name in earlier tiles) + (rank in the
 // bucket, which is in seq order); row = slot[off[name] + rank] while the
 // name has rows left (Alg. 1)
-__global__ void __launch_bounds__(256) k_f_pass2(RankArgs m) {
+template <int kWaves>
+__global__ void __launch_bounds__(kWaves * OPA_WAVE) k_f_pass2(RankArgs m) {
+  constexpr int kCh = OPA_TILE / OPA_WAVE / kWaves;
   OPA_DYN_LDS(uint16_t, cnt);
   const int64_t tile = blockIdx.x, base = tile * OPA_TILE;
   const uint32_t NN = m.NN;
@@ -750,22 +762,22 @@ __global__ void __launch_bounds__(256) k_f_pass2(RankArgs m) {
   }
   const uint32_t n = m.cnt[tile];
   if (n == 0) return;
-  for (uint32_t i = threadIdx.x; i < 4 * NN; i += OPA_TILE_THREADS) cnt[i] = 0;
+  for (uint32_t i = threadIdx.x; i < kWaves * NN; i += kWaves * OPA_WAVE) cnt[i] = 0;
   __syncthreads();
-  uint32_t key[kWaveChunks], pos[kWaveChunks], rank[kWaveChunks];
+  uint32_t key[kCh], pos[kCh], rank[kCh];
 #pragma unroll
-  for (int c = 0; c < kWaveChunks; ++c) {
-    const int e = tile_elem(c);
+  for (int c = 0; c < kCh; ++c) {
+    const int e = tile_elem<kWaves>(c);
     const uint32_t r = (uint32_t)e < n ? m.rec[base + e] : (NN << OPA_SLOT_BITS);
     key[c] = r >> OPA_SLOT_BITS;
     pos[c] = r & (OPA_TILE - 1);
   }
-  wave_rank<kWaveChunks>(key, NN, bits_for(NN), cnt + wave_id() * NN, rank);
-  block_rank_bases(cnt, NN, nullptr);
+  wave_rank<kCh>(key, NN, bits_for(NN), cnt + wave_id() * NN, rank);
+  block_rank_bases<kWaves>(cnt, NN, nullptr);
   const uint16_t *wb = cnt + wave_id() * NN;
   const uint32_t *pre = m.tlh + tile * NN;
 #pragma unroll
-  for (int c = 0; c < kWaveChunks; ++c) {
+  for (int c = 0; c < kCh; ++c) {
     const uint32_t k = key[c];
     if (k >= NN) continue;
     const uint32_t r = pre[k] + wb[k] + rank[c];
@@ -862,18 +874,20 @@ struct PfArgs {
   uint32_t NN;
 };
 
-__global__ void __launch_bounds__(256) k_pf_hist_w(PfArgs a, uint32_t *pfh, opattr_diag *diag) {
+template <int kWaves>
+__global__ void __launch_bounds__(kWaves * OPA_WAVE) k_pf_hist_w(PfArgs a, uint32_t *pfh, opattr_diag *diag) {
+  constexpr int kCh = OPA_TILE / OPA_WAVE / kWaves;
   OPA_DYN_LDS(uint16_t, cnt);
   __shared__ uint32_t sbad;
   const int64_t tile = blockIdx.x, base = tile * OPA_TILE;
   const uint32_t NN = a.NN;
-  for (uint32_t i = threadIdx.x; i < 4 * NN; i += OPA_TILE_THREADS) cnt[i] = 0;
+  for (uint32_t i = threadIdx.x; i < kWaves * NN; i += kWaves * OPA_WAVE) cnt[i] = 0;
   if (threadIdx.x == 0) sbad = 0;
   __syncthreads();
-  uint32_t key[kWaveChunks], rank[kWaveChunks], bad = 0;
+  uint32_t key[kCh], rank[kCh], bad = 0;
 #pragma unroll
-  for (int c = 0; c < kWaveChunks; ++c) {
-    const int64_t x = base + tile_elem(c);
+  for (int c = 0; c < kCh; ++c) {
+    const int64_t x = base + tile_elem<kWaves>(c);
     uint32_t n = NN;
     if (x < a.P) {
       n = a.name[x];
@@ -884,26 +898,28 @@ __global__ void __launch_bounds__(256) k_pf_hist_w(PfArgs a, uint32_t *pfh, opat
     }
     key[c] = n;
   }
-  wave_rank<kWaveChunks>(key, NN, bits_for(NN), cnt + wave_id() * NN, rank);
-  block_rank_bases(cnt, NN, pfh + tile * NN);
+  wave_rank<kCh>(key, NN, bits_for(NN), cnt + wave_id() * NN, rank);
+  block_rank_bases<kWaves>(cnt, NN, pfh + tile * NN);
   if (bad) atomicAdd(&sbad, bad);
   __syncthreads();
   if (threadIdx.x == 0 && sbad)
     atomicAdd((unsigned long long *)&diag->bad_records, (unsigned long long)sbad);
 }
 
-__global__ void __launch_bounds__(256) k_pf_slot_w(PfArgs a, const uint32_t *__restrict__ pfh,
+template <int kWaves>
+__global__ void __launch_bounds__(kWaves * OPA_WAVE) k_pf_slot_w(PfArgs a, const uint32_t *__restrict__ pfh,
                                                    const uint32_t *__restrict__ off,
                                                    int32_t *slot) {
+  constexpr int kCh = OPA_TILE / OPA_WAVE / kWaves;
   OPA_DYN_LDS(uint16_t, cnt);
   const int64_t tile = blockIdx.x, base = tile * OPA_TILE;
   const uint32_t NN = a.NN;
-  for (uint32_t i = threadIdx.x; i < 4 * NN; i += OPA_TILE_THREADS) cnt[i] = 0;
+  for (uint32_t i = threadIdx.x; i < kWaves * NN; i += kWaves * OPA_WAVE) cnt[i] = 0;
   __syncthreads();
-  uint32_t key[kWaveChunks], rank[kWaveChunks];
+  uint32_t key[kCh], rank[kCh];
 #pragma unroll
-  for (int c = 0; c < kWaveChunks; ++c) {
-    const int64_t x = base + tile_elem(c);
+  for (int c = 0; c < kCh; ++c) {
+    const int64_t x = base + tile_elem<kWaves>(c);
     uint32_t n = NN;
     if (x < a.P) {
       n = a.name[x];
@@ -911,14 +927,14 @@ __global__ void __launch_bounds__(256) k_pf_slot_w(PfArgs a, const uint32_t *__r
     }
     key[c] = n;
   }
-  wave_rank<kWaveChunks>(key, NN, bits_for(NN), cnt + wave_id() * NN, rank);
-  block_rank_bases(cnt, NN, nullptr);
+  wave_rank<kCh>(key, NN, bits_for(NN), cnt + wave_id() * NN, rank);
+  block_rank_bases<kWaves>(cnt, NN, nullptr);
   const uint32_t *row = pfh + tile * NN;
   const uint16_t *wb = cnt + wave_id() * NN;
 #pragma unroll
-  for (int c = 0; c < kWaveChunks; ++c) {
+  for (int c = 0; c < kCh; ++c) {
     const uint32_t n = key[c];
-    if (n < NN) slot[off[n] + row[n] + wb[n] + rank[c]] = (int32_t)(base + tile_elem(c));
+    if (n < NN) slot[off[n] + row[n] + wb[n] + rank[c]] = (int32_t)(base + tile_elem<kWaves>(c));
   }
 }
 
@@ -1524,7 +1540,8 @@ void run_match(const IomArgs &x, hipStream_t s) {
   const bool seg = pl.seg;  // implies the fast path
   const bool buckets = seg && x.buckets;
   const bool fast = NN <= kFastNames, fast_pf = NN <= kFastKeys;
-  const size_t lds = (size_t)4 * NN * sizeof(uint16_t);
+  const size_t lds = (size_t)4 * NN * sizeof(uint16_t);  // four waves' counters
+  const bool wide = NN <= kWideNames;
   uint32_t *tlh = at<uint32_t>(ws, pl.tlh), *pfh = at<uint32_t>(ws, pl.pfh);
   uint32_t *tlc = at<uint32_t>(ws, pl.tlc), *pfc = at<uint32_t>(ws, pl.pfc);
   uint32_t *off = at<uint32_t>(ws, pl.off);
@@ -1579,7 +1596,8 @@ void run_match(const IomArgs &x, hipStream_t s) {
   }
   probe_begin(OPATTR_PROBE_PF_HIST, sp);
   if (ntp > 0) {
-    if (fast_pf) k_pf_hist_w<<<(unsigned)ntp, 256, lds, sp>>>(pa, pfh, x.diag);
+    if (wide) k_pf_hist_w<16><<<(unsigned)ntp, 1024, 4 * lds, sp>>>(pa, pfh, x.diag);
+    else if (fast_pf) k_pf_hist_w<4><<<(unsigned)ntp, 256, lds, sp>>>(pa, pfh, x.diag);
     else k_pf_hist<<<(unsigned)ntp, 256, 0, sp>>>(pa, pfh, x.diag);
   }
   probe_end(OPATTR_PROBE_PF_HIST, sp);
@@ -1587,7 +1605,10 @@ void run_match(const IomArgs &x, hipStream_t s) {
   if (NN) k_pf_off<<<1, 1024, 0, sp>>>(pfc, NN, off);
   probe_begin(OPATTR_PROBE_PF_SLOT, sp);
   if (ntp > 0) {
-    if (fast_pf) k_pf_slot_w<<<(unsigned)ntp, 256, lds, sp>>>(pa, pfh, off, at<int32_t>(ws, pl.slot));
+    if (wide)
+      k_pf_slot_w<16><<<(unsigned)ntp, 1024, 4 * lds, sp>>>(pa, pfh, off, at<int32_t>(ws, pl.slot));
+    else if (fast_pf)
+      k_pf_slot_w<4><<<(unsigned)ntp, 256, lds, sp>>>(pa, pfh, off, at<int32_t>(ws, pl.slot));
     else k_pf_slot<<<(unsigned)ntp, 256, 0, sp>>>(pa, pfh, off, at<int32_t>(ws, pl.slot));
   }
   probe_end(OPATTR_PROBE_PF_SLOT, sp);
@@ -1659,7 +1680,12 @@ void run_match(const IomArgs &x, hipStream_t s) {
     m.name_counts = x.name_counts;
     m.diag = x.diag;
     m.strict = strict;
-    k_f_pass2<<<(unsigned)(pl.nt + (NN ? 1 : 0)), 256, lds, s>>>(m);
+    const unsigned nb = (unsigned)(pl.nt + (NN ? 1 : 0));
+    // 2M launches, 490 full buckets: 23 us by four waves, 15 by sixteen.
+    // Where the rows are fewer than half of the launches most are layer
+    // duplicates, the buckets hold little and four waves are enough.
+    if (wide && P >= pl.T / 2) k_f_pass2<16><<<nb, 1024, 4 * lds, s>>>(m);
+    else k_f_pass2<4><<<nb, 256, lds, s>>>(m);
   } else if (pl.nt > 0) {
     if (fast) {
       LookArgs m;

@@ -320,3 +320,21 @@ def test_fused_graph_replay():
         torch.cuda.synchronize()
         print(f"case fused graph replay {rep}", flush=True)
         parity.assert_attribute(o, want, opattr.read_diag(o["diag"]))
+
+
+@pytest.mark.parametrize("n_names", [512, 513])
+@pytest.mark.parametrize("dedup", [False, True])
+def test_fused_ranking_waves(n_names, dedup):
+    """On either side of the name count up to which a tile is ranked by
+    sixteen waves, with full buckets and, by layer duplicates, mostly empty
+    ones; bad names among the profiled rows and the launches."""
+    T = (1 << 20) + 4_099
+    tr = cases.random_trace(8100 + n_names, T=T, S=5, n_names=n_names, R=T // 40, n_ops=900,
+                            t_max=20 * T, max_depth=3, dedup=dedup, drop=0.02)
+    tr, _, _ = cases.stream_major(tr)
+    tr["name_id"][::100_003] = n_names
+    tr["pf_name"][::70_001] = n_names + 3
+    print(f"case ranking waves names={n_names} dedup={dedup}", flush=True)
+    want = O.attribute(tr)
+    out, diag = _run(tr)
+    parity.assert_attribute(out, want, diag)
