@@ -624,7 +624,8 @@ void plan_items(const EncArgs &x, hipStream_t s) {
     // enclosure pass counted the items
     if (pl.T > 0) {
       k_item_hist_w<<<tgrid, 256, lds, s>>>(w);
-      column_scan(w.ith, pl.ntrt, pl.G, at<uint32_t>(x.ws, pl.itch), w.gcnt, s, w.meta + 2);
+      column_scan(w.ith, pl.ntrt, pl.G, at<uint32_t>(x.ws, pl.itch), w.gcnt, s, w.meta + 2,
+                  pl.T);
     }
     k_row_offsets<<<1, 1024, 0, s>>>(w);
     if (pl.T > 0) k_item_scatter_w<<<tgrid, 256, lds, s>>>(w);

@@ -188,6 +188,11 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
       pl.ftabs = (int)(chunks < kTabBlocks ? chunks : kTabBlocks);
     }
   }
+  // A thousand blocks of the run reduction run at once (four waves a SIMD by
+  // registers): up to 4M launches, eight launches a lane make less than two
+  // rounds of blocks, half of them idle in the last (2M: 58 us at eight, 50 at
+  // four). For longer lists the last round weighs less than the partials.
+  pl.aper = mode != PlanMode::kPlain && pl.T <= kShortCall ? 4 : 8;
   pl.remap = remap_ok && pl.fused && !pl.compact;
   const size_t permuted = b.off;
   if (remap_ok && pl.fused) {  // the compact path has its partials there

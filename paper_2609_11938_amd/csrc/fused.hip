@@ -2,7 +2,7 @@
 // layer-dedup broadcast (Sec. 3.7) and aggregation (Eq. 1, Sec. 3.8.1) over
 // the launches in storage order.
 //
-// 1. k_f_agg: each lane takes eight consecutive launches. Their matches come
+// 1. k_f_agg: each lane takes four or eight consecutive launches. Their matches come
 //    first: the matching leaves, by seq rank, the row and name of every
 //    eligible launch (mbs, nbs); each launch takes its own entry, and a
 //    duplicate the entry of the representative's launch at the same
@@ -17,7 +17,7 @@
 //    unattributed row on its own) and writes them to its own region with a
 //    (count, offset) entry per bucket; anything past that goes to a row
 //    accumulator with device-scope atomics. The blocks are taken per XCD in
-//    the order k_f_order gives (launch-order windows).
+//    the order block_order gives (launch-order windows).
 // 2. k_f_comb: one wave per (bucket, share of the blocks) adds the bucket's
 //    partial results of those blocks in LDS (each partial read field-wise
 //    by 25 lanes) and writes one partial per row; 32 more waves add the
@@ -33,10 +33,7 @@
 
 namespace opa {
 
-constexpr int kAPer = 8;                      // launches per lane (aggregation)
-constexpr int kAHalf = 8;                      // of them in registers at a time
 constexpr int kAThreads = 256;                 // threads per block
-constexpr int kASpan = kAPer * kAThreads;      // launches per block
 constexpr int kASlots = 32;                    // partial results a wave keeps
 constexpr int kABlockCap = kASlots * (kAThreads / OPA_WAVE);  // and a block
 constexpr int kHot = 32;                       // combine waves of the unattributed row
@@ -126,34 +123,10 @@ __device__ __forceinline__ void match_of(const MatchParams &a, int64_t i, int nv
 // launch (a counting sort into kOrderBuckets windows), and each XCD takes a
 // contiguous part of that order, so that the blocks sharing those reads
 // run at about the same time on one L2. The order only moves work between
-// workgroups: every block still reduces its own launches.
+// workgroups: every block still reduces its own launches. (block_order, in
+// a block beside the profiled side's name offsets.)
 // ---------------------------------------------------------------------------
-constexpr int kOrderBuckets = 1024;
 constexpr uint32_t kXcds = 8;  // workgroups go round robin over the XCDs in dispatch order
-
-__global__ void __launch_bounds__(kOrderBuckets) k_f_order(const uint32_t *__restrict__ seq,
-                                                           int64_t T, int64_t nb, int span,
-                                                           uint32_t *order) {
-  __shared__ uint32_t hist[kOrderBuckets];
-  __shared__ uint32_t sh[kOrderBuckets / OPA_WAVE];
-  const int tid = threadIdx.x;
-  hist[tid] = 0;
-  __syncthreads();
-  auto bucket = [&](int64_t b) -> uint32_t {
-    const uint64_t q = seq[b * span];
-    const uint64_t c = q < (uint64_t)T ? q : (uint64_t)T - 1;  // a broken promise: any window
-    return (uint32_t)(c * kOrderBuckets / (uint64_t)T);
-  };
-  for (int64_t b = tid; b < nb; b += kOrderBuckets) atomicAdd(&hist[bucket(b)], 1u);
-  __syncthreads();
-  uint32_t tot;
-  const uint32_t base = block_excl_scan_add<uint32_t>(hist[tid], sh, &tot);
-  __syncthreads();
-  hist[tid] = base;
-  __syncthreads();
-  for (int64_t b = tid; b < nb; b += kOrderBuckets)
-    order[atomicAdd(&hist[bucket(b)], 1u)] = (uint32_t)b;
-}
 
 // The block workgroup i reduces: dispatch index i runs on XCD i % kXcds,
 // and XCD x takes the part of the order after the parts of XCDs 0 .. x-1
@@ -177,7 +150,7 @@ struct AggParams {
   int64_t R_in;
   AggIn in;
   RowOut o;
-  const uint32_t *order;    // [blocks] processing order (k_f_order), or NULL
+  const uint32_t *order;    // [blocks] processing order (block_order), or NULL
 };
 
 // A partial result staged in LDS: its 25 fields and its row (live 0: merged
@@ -263,7 +236,7 @@ __device__ __forceinline__ void rows_of(const AggParams &a, const int32_t (&rid)
   }
 }
 
-template <bool DEF>  // DEF: the default aggregation kinds
+template <bool DEF, int kAPer>  // DEF: the default aggregation kinds; kAPer launches per lane
 __global__ void __launch_bounds__(kAThreads) __attribute__((amdgpu_waves_per_eu(3)))
 k_f_agg(AggParams a) {
   __shared__ Slot slots[kAThreads / OPA_WAVE][kASlots];
@@ -275,7 +248,7 @@ k_f_agg(AggParams a) {
   const AggIn &in = a.in;
   const uint32_t mx = DEF ? kDefMaxMask : in.maxmask, dw = DEF ? kDefDwMask : in.dwmask;
   const int64_t blk = order_slot(a.order, blockIdx.x, gridDim.x);
-  const int64_t ib = blk * kASpan + (int64_t)tid * kAPer;
+  const int64_t ib = blk * (kAPer * kAThreads) + (int64_t)tid * kAPer;
   const int nv = (int)(a.T - ib < 0 ? 0 : (a.T - ib < kAPer ? a.T - ib : kAPer));
   Slot *wslot = slots[w];
   int nst = 0;      // staged partials of the wave (uniform)
@@ -289,41 +262,35 @@ k_f_agg(AggParams a) {
   if (ln > 0 && nv > 0) gprev = row_of(a, a.range_id[ib - 1]);
   uint32_t gcur = 0xFFFFFFFFu;
   uint32_t err = 0;  // dedup errors of the lane's launches
-#pragma unroll 1
-  for (int h = 0; h < kAPer / kAHalf; ++h) {
-    const int64_t i0 = ib + h * kAHalf;
-    const int nh = nv - h * kAHalf < 0 ? 0 : (nv - h * kAHalf < kAHalf ? nv - h * kAHalf : kAHalf);
-    int32_t mt[kAHalf], rid[kAHalf];
-    uint32_t du[kAHalf], g[kAHalf];
-    match_of<kAHalf>(a.m, i0, nh, mt, err);
-    load_n<kAHalf>(in.dur, i0, nh, du);
-    load_n<kAHalf>(a.range_id, i0, nh, rid);
-    rows_of<kAHalf>(a, rid, nh, g);
+  {
+    int32_t mt[kAPer], rid[kAPer];
+    uint32_t du[kAPer], g[kAPer];
+    match_of<kAPer>(a.m, ib, nv, mt, err);
+    load_n<kAPer>(in.dur, ib, nv, du);
+    load_n<kAPer>(a.range_id, ib, nv, rid);
+    rows_of<kAPer>(a, rid, nv, g);
 #pragma unroll
-    for (int k = 0; k < kAHalf; ++k) {
-      const int kk = h * kAHalf + k;
+    for (int k = 0; k < kAPer; ++k) {
       const uint32_t prev = k ? g[k - 1] : gprev;
-      if (k < nh && g[k] != prev) hm |= 1u << kk;
+      if (k < nv && g[k] != prev) hm |= 1u << k;
     }
-    gprev = g[kAHalf - 1];
-    if (h == 0) gcur = g[0];
+    gcur = g[0];
     // launch k is always at position 0 of the arrays: they shift by one per
     // step (a run-time index would move them to scratch memory). The loop
     // is uniform over the wave: staging is cooperative.
 #pragma unroll 1
-    for (int k = 0; k < kAHalf; ++k) {
-      const int kk = h * kAHalf + k;
-      const bool cut = kk > 0 && k < nh && ((hm >> kk) & 1u);
+    for (int k = 0; k < kAPer; ++k) {
+      const bool cut = k > 0 && k < nv && ((hm >> k) & 1u);
       const int idx = stage_put(cut, gcur, inc, wslot, nst, a.o.acc, mx);
       // the lane's first piece continues the previous lane's run
-      if (cut && (hm & 1u) == 0 && (hm & ((1u << kk) - 1u)) == 0) fslot = idx;
+      if (cut && (hm & 1u) == 0 && (hm & ((1u << k) - 1u)) == 0) fslot = idx;
       if (cut) {
         acc_zero(inc);
         gcur = g[0];
       }
-      if (k < nh) acc_launch(inc, in, mt[0], du[0], mx, dw);
+      if (k < nv) acc_launch(inc, in, mt[0], du[0], mx, dw);
 #pragma unroll
-      for (int j = 0; j + 1 < kAHalf; ++j) {
+      for (int j = 0; j + 1 < kAPer; ++j) {
         mt[j] = mt[j + 1];
         du[j] = du[j + 1];
         g[j] = g[j + 1];
@@ -710,8 +677,10 @@ __global__ void __launch_bounds__(256) k_f_rows(CombParams a) {
 uint32_t fused_rows_per_bucket(uint32_t G) { return (G + kBuckets - 1) / kBuckets; }
 
 // launches per block: the row-ordered reduction takes blocks small enough to
-// give every CU work, the run reduction kASpan
-int fused_span(const Plan &pl) { return pl.ftabs ? kTThreads * pl.fper : pl.fper ? kRThreads * pl.fper : kASpan; }
+// give every CU work, the run reduction kAThreads times aper
+int fused_span(const Plan &pl) {
+  return pl.ftabs ? kTThreads * pl.fper : pl.fper ? kRThreads * pl.fper : kAThreads * pl.aper;
+}
 int64_t fused_agg_blocks(int64_t T, int span) { return (T + span - 1) / span; }
 
 size_t fused_parts_bytes(int64_t cap) { return (size_t)cap * sizeof(PartRow); }
@@ -733,13 +702,6 @@ size_t fused_acc_bytes(uint32_t G) { return (size_t)G * sizeof(PartRow) + 256; }
 
 void fused_acc_clear(FillJobs &j, void *ws, const Plan &pl) {
   j.add(at<uint32_t>(ws, pl.acc), 0u, (int64_t)(fused_acc_bytes(pl.G) / 4));
-}
-
-void run_fused_order(const opattr_kernels *k, void *ws, const Plan &pl, hipStream_t s) {
-  const int span = fused_span(pl);
-  const int64_t nb = fused_agg_blocks(pl.T, span);
-  if (nb > 0)
-    k_f_order<<<1, kOrderBuckets, 0, s>>>(k->seq, pl.T, nb, span, at<uint32_t>(ws, pl.forder));
 }
 
 void run_fused_agg(const FusedIn &x, hipStream_t s) {
@@ -776,7 +738,7 @@ void run_fused_agg(const FusedIn &x, hipStream_t s) {
   a.o.pcap = (uint32_t)pl.fcap;
   const bool def = a.in.maxmask == kDefMaxMask && a.in.dwmask == kDefDwMask;
   const int64_t nb = fused_agg_blocks(pl.T, fused_span(pl));
-  a.order = x.ordered ? at<uint32_t>(x.ws, pl.forder) : nullptr;  // from run_fused_order
+  a.order = x.ordered ? at<uint32_t>(x.ws, pl.forder) : nullptr;  // from the matching
   probe_begin(OPATTR_PROBE_AGG_RUNS, s);
   if (pl.ftabs && nb > 0) {
     unsigned long long *tabs = reinterpret_cast<unsigned long long *>(a.o.parts);
@@ -791,8 +753,8 @@ void run_fused_agg(const FusedIn &x, hipStream_t s) {
     if (pl.fper == 2) def ? k_r_agg<true, 2><<<gr, bl, lr, s>>>(a) : k_r_agg<false, 2><<<gr, bl, lr, s>>>(a);
     else if (pl.fper == 4) def ? k_r_agg<true, 4><<<gr, bl, lr, s>>>(a) : k_r_agg<false, 4><<<gr, bl, lr, s>>>(a);
     else if (pl.fper == 8) def ? k_r_agg<true, 8><<<gr, bl, lr, s>>>(a) : k_r_agg<false, 8><<<gr, bl, lr, s>>>(a);
-    else if (def) k_f_agg<true><<<(unsigned)nb, kAThreads, 0, s>>>(a);
-    else k_f_agg<false><<<(unsigned)nb, kAThreads, 0, s>>>(a);
+    else if (pl.aper == 4) def ? k_f_agg<true, 4><<<gr, kAThreads, 0, s>>>(a) : k_f_agg<false, 4><<<gr, kAThreads, 0, s>>>(a);
+    else def ? k_f_agg<true, 8><<<gr, kAThreads, 0, s>>>(a) : k_f_agg<false, 8><<<gr, kAThreads, 0, s>>>(a);
   }
   probe_end(OPATTR_PROBE_AGG_RUNS, s);
   probe_begin(OPATTR_PROBE_AGGREGATE, s);

@@ -62,6 +62,7 @@ struct Plan {
   int64_t nct, ncp;  // its tiles of launches and of profiled rows
   size_t ctl, cpf, csum, csamp;
   int fper;      // launches per lane of the row-ordered reduction (0: the run reduction)
+  int aper;      // launches per lane of the run reduction
   int ftabs;     // blocks of the reduction with the whole table in LDS (0: another one)
   int64_t fcap;  // partials there is room for
   size_t acc, fparts, fbkt, fbase, fsplit, forder, fhot;
@@ -138,9 +139,12 @@ struct CoreRanges {
 void launch_scan_excl(const uint32_t *in, uint32_t *out, int64_t n, int64_t *total_out,
                       hipStream_t s);
 // Exclusive prefix down each column of a [rows][cols] table in place, column
-// totals in totals; rows_dev (optional) holds the actual row count on device.
+// totals in totals; rows_dev (optional) holds the actual row count on device;
+// launches: of the whole call.
+constexpr int64_t kShortCall = 1 << 22;   // launches up to which the host's launches bound a call
+constexpr int64_t kOneScanRows = 1024;    // rows one launch scans
 void column_scan(uint32_t *tab, int64_t rows, uint32_t cols, uint32_t *chs, uint32_t *totals,
-                 hipStream_t s, const int64_t *rows_dev);
+                 hipStream_t s, const int64_t *rows_dev, int64_t launches);
 // bits to hold the values 0..v (host)
 inline int bits_for_host(uint32_t v) {
   int b = 1;
@@ -377,15 +381,13 @@ struct FusedIn {
   opattr_diag *diag;
   void *ws;
   const Plan *pl;
-  bool ordered = false;  // run_fused_order filled the block order
+  bool ordered = false;  // the matching filled the block order
 };
 // every launch's match (from the bucket path's mbs / nbs, with the dedup
 // broadcast and its errors), the operator table from it and range_id, the
 // summary and the final status (the row accumulators and the done count must
 // be zero: fused_acc_clear)
 void run_fused_agg(const FusedIn &x, hipStream_t s);
-// the processing order of the run reduction's blocks (reads only seq)
-void run_fused_order(const opattr_kernels *k, void *ws, const Plan &pl, hipStream_t s);
 int fused_span(const Plan &pl);                   // launches per block of the reduction
 int64_t fused_agg_blocks(int64_t T, int span);    // its blocks
 int64_t fused_block_cap();                        // partials a block of the run reduction keeps

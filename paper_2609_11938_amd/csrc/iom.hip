@@ -1116,9 +1116,56 @@ __global__ void __launch_bounds__(256) k_colbase_few(uint32_t *tab, int64_t rows
   if (w == 3 && (int64_t)blockIdx.y == nc - 1) totals[col] = run;
 }
 
+// Few rows: each block scans its 64 columns over all rows in one launch, a
+// sixteenth of the rows a wave: their sums, then the prefixes from the rows
+// read again. 489 rows of 64 columns: two launches of 6.6 and 4.2 us before,
+// one of 7.3 now; the call's host time counts as much (4 to 5 us a launch). Not
+// in calls on long lists, which the GPU bounds: beside their other streams'
+// kernels the few blocks' dependent loads take 45 us for 245 rows of 1000
+// columns, the two kernels' 34.
+__global__ void __launch_bounds__(1024) k_colscan(uint32_t *tab, int64_t rows, uint32_t cols,
+                                                  uint32_t *totals, const int64_t *rows_dev) {
+  constexpr int kW = 16, kAt = 8;  // waves; rows in flight
+  __shared__ uint32_t part[kW][64];
+  rows = rows_of(rows, rows_dev);
+  if (rows <= 0) return;
+  const int l = lane_id(), w = wave_id();
+  const uint32_t col = blockIdx.x * 64 + l;
+  const bool ok = col < cols;
+  const int64_t per = (rows + kW - 1) / kW, lo = w * per, hi = lo + per < rows ? lo + per : rows;
+  uint32_t s = 0;
+  for (int64_t r0 = lo; r0 < hi; r0 += kAt) {
+    uint32_t v[kAt];
+#pragma unroll
+    for (int i = 0; i < kAt; ++i) v[i] = ok && r0 + i < hi ? tab[(r0 + i) * cols + col] : 0u;
+#pragma unroll
+    for (int i = 0; i < kAt; ++i) s += v[i];
+  }
+  part[w][l] = s;
+  __syncthreads();
+  if (!ok) return;
+  uint32_t run = 0;
+  for (int ww = 0; ww < w; ++ww) run += part[ww][l];
+  for (int64_t r0 = lo; r0 < hi; r0 += kAt) {
+    uint32_t v[kAt];
+#pragma unroll
+    for (int i = 0; i < kAt; ++i) v[i] = r0 + i < hi ? tab[(r0 + i) * cols + col] : 0u;
+#pragma unroll
+    for (int i = 0; i < kAt; ++i) {
+      if (r0 + i < hi) tab[(r0 + i) * cols + col] = run;
+      run += v[i];
+    }
+  }
+  if (w == kW - 1) totals[col] = run;
+}
+
 void column_scan(uint32_t *tab, int64_t rows, uint32_t cols, uint32_t *chs, uint32_t *totals,
-                 hipStream_t s, const int64_t *rows_dev) {
+                 hipStream_t s, const int64_t *rows_dev, int64_t launches) {
   if (rows <= 0 || cols == 0) return;
+  if (rows <= kOneScanRows && launches <= kShortCall) {
+    k_colscan<<<(cols + 63) / 64, 1024, 0, s>>>(tab, rows, cols, totals, rows_dev);
+    return;
+  }
   const int64_t nch = (rows + kColChunk - 1) / kColChunk;
   dim3 g((cols + 63) / 64, (unsigned)nch);
   k_colsum<<<g, 256, 0, s>>>(tab, rows, cols, chs, rows_dev);
@@ -1130,10 +1177,31 @@ void column_scan(uint32_t *tab, int64_t rows, uint32_t cols, uint32_t *chs, uint
   }
 }
 
-// off[n] = rows of names before n (one block)
+// off[n] = rows of names before n, by the first block; a second block, if
+// there is one, the run reduction's block order: two short jobs on the
+// profiled rows' stream in one launch. Up to 4M launches only: there the
+// host's 5 us a launch bound the call, and the order takes about as long as
+// the offsets; 10M launches' order takes 14 us, which the slots would wait for.
+struct OrderJob {
+  const uint32_t *seq;
+  int64_t T, nb;
+  int span;
+  uint32_t *order;
+};
+__global__ void __launch_bounds__(kOrderBuckets) k_f_order(OrderJob o) {
+  __shared__ uint32_t sh[kOrderBuckets / OPA_WAVE];
+  __shared__ uint32_t hist[kOrderBuckets];
+  block_order(o.seq, o.T, o.nb, o.span, o.order, hist, sh);
+}
+
 __global__ void __launch_bounds__(1024) k_pf_off(const uint32_t *__restrict__ pfc, uint32_t NN,
-                                                 uint32_t *off) {
+                                                 uint32_t *off, OrderJob o) {
   __shared__ uint32_t sh[16];
+  __shared__ uint32_t hist[kOrderBuckets];
+  if (blockIdx.x == 1) {
+    block_order(o.seq, o.T, o.nb, o.span, o.order, hist, sh);
+    return;
+  }
   uint32_t carry = 0;
   for (uint32_t base = 0; base < NN; base += 1024) {
     const uint32_t n = base + threadIdx.x;
@@ -1601,8 +1669,14 @@ void run_match(const IomArgs &x, hipStream_t s) {
     else k_pf_hist<<<(unsigned)ntp, 256, 0, sp>>>(pa, pfh, x.diag);
   }
   probe_end(OPATTR_PROBE_PF_HIST, sp);
-  column_scan(pfh, ntp, NN, at<uint32_t>(ws, pl.pfch), pfc, sp, nullptr);
-  if (NN) k_pf_off<<<1, 1024, 0, sp>>>(pfc, NN, off);
+  column_scan(pfh, ntp, NN, at<uint32_t>(ws, pl.pfch), pfc, sp, nullptr, pl.T);
+  OrderJob oj{};
+  if (x.fused_order && sp != s) {
+    const int span = fused_span(pl);
+    oj = OrderJob{k->seq, pl.T, fused_agg_blocks(pl.T, span), span, at<uint32_t>(ws, pl.forder)};
+  }
+  const bool order_beside = oj.nb > 0 && NN && pl.T <= kShortCall;
+  if (NN) k_pf_off<<<order_beside ? 2 : 1, 1024, 0, sp>>>(pfc, NN, off, oj);
   probe_begin(OPATTR_PROBE_PF_SLOT, sp);
   if (ntp > 0) {
     if (wide)
@@ -1612,7 +1686,7 @@ void run_match(const IomArgs &x, hipStream_t s) {
     else k_pf_slot<<<(unsigned)ntp, 256, 0, sp>>>(pa, pfh, off, at<int32_t>(ws, pl.slot));
   }
   probe_end(OPATTR_PROBE_PF_SLOT, sp);
-  if (x.fused_order && sp != s) run_fused_order(k, ws, pl, sp);
+  if (oj.nb > 0 && !order_beside) k_f_order<<<1, kOrderBuckets, 0, sp>>>(oj);
   if (sp != s) note(hipEventRecord(x.pf_join, sp));
 
   // the timeline side
@@ -1656,7 +1730,7 @@ void run_match(const IomArgs &x, hipStream_t s) {
     k_part_prep<<<(unsigned)((pl.NP + 255) / 256), 256, 0, s>>>(d->part_rep, pl.NP, pfirst, plast,
                                                                 pheads, prec, x.diag);
   probe_begin(OPATTR_PROBE_COL_SCAN, s);
-  column_scan(tlh, pl.nt, NN, at<uint32_t>(ws, pl.tlch), tlc, s, nullptr);
+  column_scan(tlh, pl.nt, NN, at<uint32_t>(ws, pl.tlch), tlc, s, nullptr, pl.T);
   probe_end(OPATTR_PROBE_COL_SCAN, s);
   if (sp != s) note(hipStreamWaitEvent(s, x.pf_join, 0));
   const int strict = x.policy == OPATTR_MISMATCH_STRICT ? 1 : 0;

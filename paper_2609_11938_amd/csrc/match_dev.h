@@ -87,4 +87,30 @@ __device__ __forceinline__ void rep_check_one(const int32_t *part_rep, uint32_t 
     atomicAdd((unsigned long long *)&diag->bad_records, (unsigned long long)__popcll(m));
 }
 
+// The processing order of the run reduction's nb blocks of span launches, by
+// the seq rank of each block's first launch (a counting sort into windows).
+// One block of kOrderBuckets threads; hist holds kOrderBuckets entries, sh
+// one per wave.
+constexpr int kOrderBuckets = 1024;
+__device__ inline void block_order(const uint32_t *__restrict__ seq, int64_t T, int64_t nb,
+                                   int span, uint32_t *order, uint32_t *hist, uint32_t *sh) {
+  const int tid = threadIdx.x;
+  hist[tid] = 0;
+  __syncthreads();
+  auto bucket = [&](int64_t b) -> uint32_t {
+    const uint64_t q = seq[b * span];
+    const uint64_t c = q < (uint64_t)T ? q : (uint64_t)T - 1;  // a broken promise: any window
+    return (uint32_t)(c * kOrderBuckets / (uint64_t)T);
+  };
+  for (int64_t b = tid; b < nb; b += kOrderBuckets) atomicAdd(&hist[bucket(b)], 1u);
+  __syncthreads();
+  uint32_t tot;
+  const uint32_t base = block_excl_scan_add<uint32_t>(hist[tid], sh, &tot);
+  __syncthreads();
+  hist[tid] = base;
+  __syncthreads();
+  for (int64_t b = tid; b < nb; b += kOrderBuckets)
+    order[atomicAdd(&hist[bucket(b)], 1u)] = (uint32_t)b;
+}
+
 }  // namespace opa

@@ -338,3 +338,16 @@ def test_fused_ranking_waves(n_names, dedup):
     want = O.attribute(tr)
     out, diag = _run(tr)
     parity.assert_attribute(out, want, diag)
+
+
+@pytest.mark.parametrize("T", [1 << 22, (1 << 22) + 1])
+def test_fused_short_call_edge(T):
+    """The launch count up to which a lane reduces four launches, not eight,
+    and one launch scans the tiles' name counts, and one more."""
+    tr = cases.random_trace(8300, T=T, S=3, n_names=70, R=T // 30, n_ops=900, t_max=20 * T,
+                            max_depth=3)
+    tr, _, _ = cases.stream_major(tr)
+    print(f"case short call edge T={T}", flush=True)
+    want = O.attribute(tr)
+    out, diag = _run(tr)
+    parity.assert_attribute(out, want, diag)
