@@ -744,9 +744,19 @@ __global__ void __launch_bounds__(kRThreads) k_c_row(CompactArgs a) {
 
 // ---------------------------------------------------------------------------
 // 5. the rows of a bucket from all blocks' partials and the row accumulators;
-// the unattributed row in a block of its own, then the finish
+// the unattributed row in a block of its own, then the finish. Every wave (or
+// half wave, while the rows are few) adds to a copy of the rows of its own,
+// and the copies are added up in pairs: a row in every block (the
+// unattributed one above all) would otherwise take one addition after the
+// other, 1500 of them for 180k launches, whose roundings add up (1.2e-15 of
+// the table's 2-norm; 1.2e-16 with the copies, as a final rounding gives).
 // ---------------------------------------------------------------------------
 constexpr int kCRowThreads = 512, kCRowWaves = kCRowThreads / OPA_WAVE;
+// copies of a bucket's rb rows (200 bytes each): 100 KB of LDS at most
+__host__ __device__ inline int c_row_copies(uint32_t rb) {
+  return rb <= 32 ? 2 * kCRowWaves : kCRowWaves;
+}
+static_assert(kFusedMaxRows / kBuckets <= 64, "the copies fit in LDS");
 
 template <bool DEF>
 __global__ void __launch_bounds__(kCRowThreads) k_c_rows(CombParams a) {
@@ -768,8 +778,12 @@ __global__ void __launch_bounds__(kCRowThreads) k_c_rows(CombParams a) {
   if (g0 >= g1) return;
   const uint32_t nr = g1 - g0;
   const unsigned long long *acc = reinterpret_cast<const unsigned long long *>(a.acc + g0);
-  for (uint32_t x = tid; x < nr * kFFields; x += kCRowThreads) tab[x] = acc[x];
+  const uint32_t ne = nr * kFFields;  // elements of a copy
+  const int copies = c_row_copies(a.rb);
+  for (uint32_t x = tid; x < ne * copies; x += kCRowThreads) tab[x] = 0;
   __syncthreads();
+  unsigned long long *mine_tab =
+      tab + (size_t)(copies == kCRowWaves ? w : 2 * w + (ln >> 5)) * ne;
   const unsigned long long *parts64 = reinterpret_cast<const unsigned long long *>(a.parts);
   const int64_t per = (a.nblocks + kCRowWaves - 1) / kCRowWaves, b_lo = w * per;
   const int64_t b_hi = b_lo + per < a.nblocks ? b_lo + per : a.nblocks;
@@ -783,8 +797,20 @@ __global__ void __launch_bounds__(kCRowThreads) k_c_rows(CombParams a) {
       xv[k] = (b < b_hi ? a.pbase[b] : 0u) + (e >> 16);
       mine += ev[k];
     }
-    comb_add<kPre>(tab, list[w], parts64, ev, xv, mine, un ? 1u : a.rb, mx);
+    comb_add<kPre>(mine_tab, list[w], parts64, ev, xv, mine, un ? 1u : a.rb, mx);
     wave_sync_lds();
+  }
+  __syncthreads();
+  for (uint32_t x = tid; x < ne; x += kCRowThreads) {
+    const int f = (int)(x % kFFields);
+    unsigned long long v[2 * kCRowWaves];
+#pragma unroll
+    for (int k = 0; k < 2 * kCRowWaves; ++k) v[k] = k < copies ? tab[(size_t)k * ne + x] : 0ull;
+#pragma unroll
+    for (int o = kCRowWaves; o > 0; o >>= 1)
+#pragma unroll
+      for (int k = 0; k < o; ++k) v[k] = merge_field(f, v[k], v[k + o], mx);
+    tab[x] = merge_field(f, acc[x], v[0], mx);  // only this thread reads element x of a copy
   }
   __syncthreads();
   for (uint32_t x = tid; x < nr * 24u; x += kCRowThreads) {
@@ -955,7 +981,7 @@ void run_compact(const CompactIn &x, hipStream_t s) {
     if (def) k_t_rows<true, false><<<gr, 1024, 0, s>>>(c, a.tabs, pl.ftabs);
     else k_t_rows<false, false><<<gr, 1024, 0, s>>>(c, a.tabs, pl.ftabs);
   } else {
-    const size_t lt = (size_t)a.o.rb * kFFields * 8;
+    const size_t lt = (size_t)c_row_copies(a.o.rb) * a.o.rb * kFFields * 8;
     if (def) k_c_rows<true><<<kBuckets + 2, kCRowThreads, lt, s>>>(c);
     else k_c_rows<false><<<kBuckets + 2, kCRowThreads, lt, s>>>(c);
   }

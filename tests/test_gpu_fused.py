@@ -351,3 +351,35 @@ def test_fused_short_call_edge(T):
     want = O.attribute(tr)
     out, diag = _run(tr)
     parity.assert_attribute(out, want, diag)
+
+
+@pytest.mark.parametrize("n_ops", [705, 8_190, 8_192, 16_383])
+def test_compact_row_sums_precision(n_ops):
+    """One row in every block's partials, on either side of the rows a bucket's
+    copies are halved at: the sums within 8 roundings (8.9e-16, relative) of
+    sums in extended precision, where additions one after the other over 1500
+    partials leave more."""
+    T = 180_157
+    tr = _regular_trace(T, 5, n_ops, min(n_ops, 900), seed=31)
+    order = np.random.default_rng(5).permutation(T)
+    tr["dur_ns"] = np.random.default_rng(6).integers(1, 5, size=T).astype(np.uint32)
+    rs = tr["r_start"].size
+    keep = np.arange(rs) % 7 == 0  # six launches in seven outside every range
+    for f in ("r_start", "r_end", "r_stream", "r_op"):
+        tr[f] = tr[f][keep]
+    given = {f: (tr[f][order] if f in ("seq", "start_ns", "dur_ns", "stream_id", "name_id") else v)
+             for f, v in tr.items()}
+    print(f"case compact row sums n_ops={n_ops}", flush=True)
+    want = O.attribute(given)
+    out, diag = _run(given, flags=opattr.SEQ_DENSE)
+    parity.assert_attribute(out, want, diag)
+    row = out.table_host()[n_ops]
+    un = parity.host(out["range_id"]) < 0
+    c = tr["counters"].astype(np.longdouble)[given["seq"][un]]  # every launch has its own row
+    d = given["dur_ns"][un].astype(np.longdouble)
+    assert np.array_equal(parity.host(out["match"]), given["seq"])
+    for k in range(20):
+        if k in (17, 19):
+            continue
+        ref = c[:, k].sum() if k in (0, 1, 2, 10, 14, 18) else (c[:, k] * d).sum() / d.sum()
+        assert abs(row["value"][k] - ref) <= 8.9e-16 * ref, (k, row["value"][k], ref)
