@@ -99,7 +99,7 @@ __global__ void __launch_bounds__(kRlThreads) k_rlocal(RangeWork w) {
 // while the candidate's maximum is below the tile's, jump to the
 // candidate's candidate.
 __global__ void __launch_bounds__(1024) k_rtiles(RangeWork w) {
-  const int32_t ntr = w.tbase[w.NS];
+  const int32_t nt = w.tbase[w.NS], ntr = nt < w.ntr_max ? nt : w.ntr_max;
   int32_t *cn = w.tnpg, *nn = w.tnpg2;
   int64_t *cm = w.tmx, *nm = w.tmx2;
   for (int32_t t = threadIdx.x; t < ntr; t += 1024) {
@@ -148,9 +148,14 @@ __global__ void k_rresolve(RangeWork w) {
   if (x >= w.cr.n || w.npg[x] != -2) return;
   const uint32_t s = w.cr.st[x];
   const int64_t ex = w.ree[x];
-  const int32_t t = w.tbase[s] + (int32_t)((x - w.rblk[s]) / kRangeTile);
+  int32_t t0 = 0;
+  const int32_t t = tile_of_range(w, s, x, t0);
+  if (t < 0) {
+    w.npg[x] = -1;
+    return;
+  }
   int64_t acc = w.mxv[x];
-  int32_t u = (t > w.tbase[s]) ? t - 1 : -1;
+  int32_t u = t > t0 ? t - 1 : -1;
   int steps = 0;
   while (u >= 0 && w.tM[u] < ex && steps < (1 << 20)) {
     const int64_t v = w.tM[u] > w.tmx[u] ? w.tM[u] : w.tmx[u];

@@ -211,6 +211,17 @@ __device__ __forceinline__ void rresolve_in_tile(const RangeWork &w, int64_t x, 
   if (ex >= 0 && acc > (int64_t)w.cr.s[x]) w.sflag[s] = 1;
 }
 
+// The tile that holds range x of stream s (its stream's first tile in t0), or
+// -1. Under a broken order promise a stream's block holds ranges of other
+// streams, of ids past the last among them, whose tile may not exist.
+__device__ __forceinline__ int32_t tile_of_range(const RangeWork &w, uint32_t s, int64_t x,
+                                                 int32_t &t0) {
+  if (s >= w.NS || x < w.rblk[s] || x >= w.rblk[s + 1]) return -1;
+  t0 = w.tbase[s];
+  const int32_t t = t0 + (int32_t)((x - w.rblk[s]) / kRangeTile);
+  return t < w.ntr_max ? t : -1;
+}
+
 // Parents in earlier tiles for the ranges [x0, x0 + blockDim.x), with the
 // maximum tree over all tiles (at most kRangeTile of them) built in the
 // block: no pass over the tiles of its own.
@@ -225,8 +236,9 @@ __device__ inline void rresolve_tree(const RangeWork &w, int64_t x0, int64_t *tr
   if (!need) return;
   const uint32_t s = w.cr.st[x];
   const int64_t ex = w.ree[x];
-  const int32_t t0 = w.tbase[s], t = t0 + (int32_t)((x - w.rblk[s]) / kRangeTile);
-  if (x < w.rblk[s] || t0 < 0 || t >= ntr || t >= kRangeTile) {  // a broken order promise
+  int32_t t0 = 0;
+  const int32_t t = tile_of_range(w, s, x, t0);
+  if (t < 0) {
     w.npg[x] = -1;
     return;
   }
