@@ -424,6 +424,35 @@ def test_counters_out_layouts(T, layout):
     np.testing.assert_array_equal(parity.host(out), O.counters_out(tr, match, absent_mask=absent))
 
 
+@pytest.mark.parametrize("kept", [20, 16, 18, 4])
+def test_counters_out_rows_without_absent_counters(kept):
+    """Rows of 20, 16, 18 or 4 counters, packed to a stride of 16-byte pieces
+    (20, 16, 20 and 4 floats), the last row ending the buffer; the others
+    absent. Absent counters are not read: the rows may end before them."""
+    import torch
+
+    T, P = 1031, 300
+    print(f"case counters_out kept={kept}", flush=True)
+    tr = cases.random_trace(78, T=T, P=P)
+    rng = np.random.default_rng(kept)
+    tr["counters"] = rng.random((P, 20), dtype=np.float32)
+    tr["pf_name"] = np.zeros(P, np.uint32)
+    match = rng.integers(-1, P + 2, size=T).astype(np.int32)
+    match[-1] = P - 1
+    absent = 0xFFFFF & ~((1 << kept) - 1)
+    dt = opattr.to_device(tr, DEV)
+    stride = (kept + 3) // 4 * 4
+    flat = torch.full(((P - 1) * stride + kept,), 9.0, device=DEV)
+    rows = flat.as_strided((P, kept), (stride, 1))
+    rows.copy_(dt["counters"][:, :kept])
+    dt["counters"] = rows
+    out = torch.empty((T, 20), dtype=torch.float32, device=DEV)
+    opattr.opattr_dedup_broadcast(dt, torch.from_numpy(match).to(DEV), counters_out=out,
+                                  absent_mask=absent)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(parity.host(out), O.counters_out(tr, match, absent_mask=absent))
+
+
 def test_determinism_and_poisoned_outputs():
     import torch
 
