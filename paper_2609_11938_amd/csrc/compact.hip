@@ -119,10 +119,12 @@ __global__ void __launch_bounds__(kCThreads) k_c_pro(CompactArgs a) {
       break;
     }
     case 3: {  // the launch-order view (a false density promise leaves stale
-               // entries in it: every reader checks their range)
+               // entries in it: every reader checks their range; and launches
+               // that no rank holds, which step 4 by rank leaves as here)
       const int64_t i = (int64_t)b * kCThreads + tid;
       bool bad = false;
       if (i < a.T) {
+        if (a.via) a.match[i] = a.range_id[i] = -1;
         const uint32_t s = a.seq[i];
         if ((int64_t)s < a.T) a.sv[s] = (int32_t)i;
         else bad = a.validate != 0;

@@ -1429,10 +1429,9 @@ __global__ void k_remap_back(const int32_t *inv, const int32_t *m2, const int32_
                              int32_t *match, int32_t *range_id) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= T) return;
-  const int32_t x = inv[i];
-  if (x < 0) return;  // no seq rank holds the launch (a false density promise)
-  match[i] = m2[x];
-  range_id[i] = r2[x];
+  const int32_t x = inv[i];  // -1: no seq rank holds the launch (a false density promise)
+  match[i] = x < 0 ? -1 : m2[x];
+  range_id[i] = x < 0 ? -1 : r2[x];
 }
 
 void remap_back(void *ws, const Plan &pl, int32_t *match, int32_t *range_id, hipStream_t s) {

@@ -107,3 +107,20 @@ def test_false_nesting_promise_foreign_streams(n_names, S):
     _run(tr, HINTS)
     _, _, diag = _run(tr, HINTS | opattr.VALIDATE)
     assert diag["status"] in (-8, -9) and diag["flags"] & opattr.F_ORDER
+
+
+@pytest.mark.parametrize("T", [30_000, (1 << 20) + 77])
+@pytest.mark.parametrize("kind", ["shared", "past_end"])
+def test_false_density_promise_any_order(T, kind):
+    """Dense seq promised for launches in any order, with values shared by
+    launches or past the end: launches that no rank holds have ids all the
+    same (compact path, and the permutation of longer lists)."""
+    tr = cases.random_trace(4200 + T % 97, T=T, S=3, n_names=20, R=T // 20, n_ops=30,
+                            t_max=10 * T, max_depth=4)
+    seq = tr["seq"].copy()
+    seq[::3] = T // 2 if kind == "shared" else T + 5 + np.arange(seq[::3].size)
+    tr["seq"] = seq
+    print(f"case false density T={T} {kind}", flush=True)
+    m, r, _ = _run(tr, opattr.SEQ_DENSE)
+    if kind == "past_end":
+        assert (m[::3] == -1).all() and (r[::3] == -1).all()
