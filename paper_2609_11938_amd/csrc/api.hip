@@ -93,7 +93,7 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
   // the bucket view's counts, or the radix histograms of the seq sort (in a
   // plan that must not grow)
   pl.rank_view = !pl.seq_dense && mode != PlanMode::kPlain;
-  pl.rv = b.take(pl.rank_view ? rank_view_entries() * 4 : 0);
+  pl.rv = b.take(pl.rank_view ? rank_view_entries(pl.T) * 4 : 0);
   pl.rs_hist = b.take(radix_hist_entries(pl.seq_dense || pl.rank_view ? 0 : pl.T) * 4);
   pl.tlh = b.take((size_t)pl.nt * NN * 4);
   pl.pfh = b.take((size_t)pl.ntp * NN * 4);

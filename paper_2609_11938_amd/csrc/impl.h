@@ -223,7 +223,7 @@ void run_match(const IomArgs &a, hipStream_t s);
 // the view when seq is not promised dense (rankview.hip)
 constexpr int kRvWidthBits = 18;                      // values of the widest bucket
 constexpr int kRvBuckets = 1 << (32 - kRvWidthBits);  // buckets that cover any 32-bit range
-size_t rank_view_entries();
+size_t rank_view_entries(int64_t T);
 void run_rank_view(const opattr_kernels *k, void *ws, const Plan &pl, opattr_diag *diag,
                    hipStream_t s);
 // the launches of a remapped call in stream-major order (the launch-order

@@ -7,19 +7,24 @@
 //   4. k_rv_scatter  (seq, launch) records to their buckets, in any order
 //   5. k_rv_rank     per bucket: a bitmap of its seq values in LDS; a launch's
 //                    rank is the bucket's base plus the set bits below its own
+//   6. k_rv_sort     returns at once, unless equal values call for it
 // Seq values are unique, so the order inside a bucket needs no sort. The
 // buckets are at most 2^18 values wide (all of 32 bits in 16384 buckets) and
-// hold about a thousand launches each when seq is spread evenly; uneven seq
-// only unbalances step 5. Equal seq values (an error, reported as ORDER) are
-// seen there as a bit already set. A bucket of up to 4096 launches then counts
-// the smaller (seq, launch) records for each; after a larger one the view is
-// rebuilt by a stable radix sort in one block (k_rv_equal), which otherwise
-// ends at once. Either way ties go by input index, as the general sort has it.
+// hold about a thousand launches each when seq is spread evenly. Uneven seq (a
+// far value beside a dense run, two captures far apart) leaves nearly all
+// launches in a few buckets: step 3 lists the overfull ones in parts, and in
+// step 5 a block per part builds the bucket's bitmap and ranks its part.
+// Equal seq values (an error, reported as ORDER) are seen in step 5 as a bit
+// already set. A bucket of up to 4096 launches then counts the smaller (seq,
+// launch) records for each; after a larger one step 6 sorts all pairs. Either
+// way ties go by input index, as the general sort has it. 2M launches, one far
+// value and one pair of equal ones: 21.3 ms the call when one block sorted all
+// pairs, 0.85 ms now (all equal 20.2 and 0.39 ms).
 // 3M launches of 8 streams: 77 us (10 + 16 + 7 + 21 + 19 + 4), bound by the
 // scatter's partial lines and by the latency of short kernels; the whole call
 // 559 us with the sort, 375 us with this. 500k shuffled: 328 us and 229 us.
-// Blocks of 256 and 1024 threads in step 5 and 2048 launches per bucket: the
-// same within 3 us.
+// Blocks of 256 and 1024 threads in step 5, 2048 launches per bucket and four
+// loads in flight instead of eight: the same within 3 us.
 #include "common.h"
 #include "impl.h"
 
@@ -32,13 +37,30 @@ constexpr int kRvWords = (1 << kRvWidthBits) / 32;
 struct RvArgs {
   const uint32_t *seq;
   int64_t T;
-  uint32_t *mm;        // [0] smallest, [1] largest seq, [2] equal values seen
+  // [0] smallest, [1] largest seq, [2] parts of overfull buckets, [3] equal
+  // values in a large bucket, [4] next work item of k_rv_sort, [8 + p] items
+  // of its phase p that are done
+  uint32_t *mm;
   uint32_t *cnt, *cur; // [kRvBuckets + 1] counts, then bases; next free place
   uint64_t *rec;       // [T] seq << 32 | launch, by bucket
   int32_t *sv, *rk;
   opattr_diag *diag;
-  uint32_t *k0, *k1, *v0, *v1;  // [T] each: the sort of k_rv_equal (rec is k0 and k1)
+  uint32_t *k0, *k1, *v0, *v1;  // [T] each: the sort of k_rv_sort (rec is k0 and k1)
+  uint32_t *hist;               // [kRvItems][256] digit counts of the sort's items
+  uint2 *part;                  // parts of overfull buckets: bucket, first launch in it
 };
+
+// Launches of a bucket from which it is ranked in parts, and of a part. By one
+// block a bucket, 2M launches in 256 buckets of 7,812 took 608 us the call, in
+// 8 buckets 1254 us; in parts 547 and 573 us, spread evenly 537 us. Up to 4096
+// launches are a round of a block's loads.
+constexpr uint32_t kRvFull = 4096, kRvPart = 8192;
+__host__ __device__ inline uint32_t rv_full(int64_t T) {  // (even buckets of long lists hold more)
+  const int64_t even = 4 * (T / kRvBuckets);
+  return even > kRvFull ? (uint32_t)even : kRvFull;
+}
+// (a bucket of n > kRvFull launches has at most 2 n / kRvPart parts)
+inline size_t rv_max_parts(int64_t T) { return (size_t)(2 * T / kRvPart + 1); }
 
 // log2 of the buckets' width: about T >> per_bits buckets over the range, but
 // none wider than the bitmap
@@ -145,6 +167,21 @@ __global__ void __launch_bounds__(1024) k_rv_base(RvArgs a) {
     cur[k] = e;
   }
   if (threadIdx.x == 1023) a.cnt[kRvBuckets] = run;
+  // the overfull buckets' parts
+  const uint32_t full = rv_full(a.T);
+  auto parts = [&](uint32_t n) { return n > full ? (n + kRvPart - 1) / kRvPart : 0u; };
+  uint32_t np = 0, total;
+#pragma unroll
+  for (int k = 0; k < kQuads; ++k) np += parts(v[k].x) + parts(v[k].y) + parts(v[k].z) + parts(v[k].w);
+  if (!__syncthreads_or(np != 0)) return;
+  uint32_t p = block_excl_scan_add<uint32_t>(np, sh, &total);
+  if (threadIdx.x == 0) a.mm[2] = total;
+  if (np == 0) return;
+  const uint32_t b0 = threadIdx.x * 4 * kQuads, b1 = b0 + 4 * kQuads;
+  for (uint32_t b = b0; b < b1; ++b) {  // (the counts are bases by now; run: the end of the last)
+    const uint32_t n = (b + 1 < b1 ? a.cnt[b + 1] : run) - a.cnt[b];
+    for (uint32_t q = 0; q < parts(n); ++q) a.part[p++] = make_uint2(b, q * kRvPart);
+  }
 }
 
 __global__ void __launch_bounds__(kRvThreads) k_rv_scatter(RvArgs a) {
@@ -166,143 +203,284 @@ __global__ void __launch_bounds__(kRvThreads) k_rv_scatter(RvArgs a) {
   }
 }
 
-constexpr int kRvRankThreads = 512, kRvUnroll = 4;
+constexpr int kRvRankThreads = 512, kRvUnroll = 8, kRvPartUnroll = 16;
 constexpr uint32_t kRvEqualMax = 4096;
 
-__global__ void __launch_bounds__(kRvRankThreads) k_rv_rank(RvArgs a) {
-  __shared__ uint32_t bits[kRvWords];
-  __shared__ uint32_t tb[kRvRankThreads];  // set bits before each thread's words
-  __shared__ uint32_t sh[kRvRankThreads / OPA_WAVE];
-  __shared__ uint32_t equal;
+struct RvRankLds {
+  uint32_t bits[kRvWords];
+  uint32_t tb[kRvRankThreads];  // set bits before each thread's words
+  uint32_t sh[kRvRankThreads / OPA_WAVE];
+};
+
+// The launches [i_lo, i_hi) of bucket b (places inside it) ranked, by the
+// whole block. kUnroll of a thread's records are in flight while the bitmap of
+// the whole bucket is built.
+template <int kUnroll>
+__device__ __forceinline__ void rv_rank_bucket(const RvArgs &a, int shift, uint32_t lo, uint32_t b,
+                                               uint32_t i_lo, uint32_t i_hi, RvRankLds &l) {
   const int tid = threadIdx.x;
-  const uint32_t lo = a.mm[0], hi = a.mm[1];
-  const int shift = rv_shift(a, lo, hi);
-  const uint32_t nb = ((hi - lo) >> shift) + 1u;
   const uint32_t words = shift > 5 ? 1u << (shift - 5) : 1u, mask = (1u << shift) - 1u;
   const uint32_t ch = (words + kRvRankThreads - 1) / kRvRankThreads;
-  for (uint32_t b = blockIdx.x; b < nb; b += gridDim.x) {
-    const uint32_t x0 = a.cnt[b], n = a.cnt[b + 1] - x0;
-    if (n == 0) continue;  // uniform over the block
-    const uint64_t *rec = a.rec + x0;
-    for (uint32_t x = tid; x < words; x += kRvRankThreads) bits[x] = 0;
-    if (tid == 0) equal = 0;
+  const uint32_t x0 = a.cnt[b], n = a.cnt[b + 1] - x0;
+  if (i_hi > n) i_hi = n;
+  const uint64_t *rec = a.rec + x0;
+  const uint32_t *val = reinterpret_cast<const uint32_t *>(rec) + 1;  // every other word
+  uint32_t set = 0;
+  if (n <= 1u << shift) {  // else there are equal values
+    for (uint32_t x = tid; x < words; x += kRvRankThreads) l.bits[x] = 0;
     __syncthreads();
-    bool eq = false;
-    for (uint32_t i0 = tid; i0 < n; i0 += kRvRankThreads * kRvUnroll) {
-      uint32_t v[kRvUnroll];
+    for (uint32_t i0 = tid; i0 < n; i0 += kRvRankThreads * kUnroll) {
+      uint32_t v[kUnroll];
+#pragma unroll
+      for (int k = 0; k < kUnroll; ++k) {
+        const uint32_t i = i0 + k * kRvRankThreads;
+        v[k] = (val[2 * (size_t)(i < n ? i : i0)] - lo) & mask;  // past the end: the first once more
+      }
+#pragma unroll
+      for (int k = 0; k < kUnroll; ++k) atomicOr(&l.bits[v[k] >> 5], 1u << (v[k] & 31));
+    }
+    __syncthreads();
+    uint32_t c = 0;
+    for (uint32_t k = 0; k < ch; ++k) {
+      const uint32_t x = tid * ch + k;
+      if (x < words) c += (uint32_t)__popc(l.bits[x]);
+    }
+    l.tb[tid] = x0 + block_excl_scan_add<uint32_t>(c, l.sh, &set);
+    __syncthreads();
+  }
+  if (set != n) {  // equal values; uniform
+    if (tid == 0) {
+      if (n > kRvEqualMax) a.mm[3] = 1u;
+      atomicOr(&a.diag->flags, OPATTR_F_ORDER);
+    }
+    if (n <= kRvEqualMax)
+      for (uint32_t i = tid; i < n; i += kRvRankThreads) {
+        const uint64_t r = rec[i];
+        uint32_t q = x0;
+        for (uint32_t j = 0; j < n; ++j) q += rec[j] < r ? 1u : 0u;
+        a.sv[q] = (int32_t)(uint32_t)r;
+        a.rk[(uint32_t)r] = (int32_t)q;
+      }
+  } else {
+    for (uint32_t i0 = i_lo + tid; i0 < i_hi; i0 += kRvRankThreads * kRvUnroll) {
+      uint64_t r[kRvUnroll];
 #pragma unroll
       for (int k = 0; k < kRvUnroll; ++k) {
         const uint32_t i = i0 + k * kRvRankThreads;
-        v[k] = i < n ? ((uint32_t)(rec[i] >> 32) - lo) & mask : 0u;
+        r[k] = i < i_hi ? rec[i] : 0u;
       }
 #pragma unroll
-      for (int k = 0; k < kRvUnroll; ++k)
-        if (i0 + k * kRvRankThreads < n)
-          eq |= (atomicOr(&bits[v[k] >> 5], 1u << (v[k] & 31)) >> (v[k] & 31)) & 1u;
-    }
-    if (eq) equal = 1;
-    __syncthreads();
-    if (equal) {  // uniform
-      if (tid == 0) {
-        if (n > kRvEqualMax) a.mm[2] = 1u;
-        atomicOr(&a.diag->flags, OPATTR_F_ORDER);
-      }
-      if (n <= kRvEqualMax)
-        for (uint32_t i = tid; i < n; i += kRvRankThreads) {
-          const uint64_t r = rec[i];
-          uint32_t q = x0;
-          for (uint32_t j = 0; j < n; ++j) q += rec[j] < r ? 1u : 0u;
-          a.sv[q] = (int32_t)(uint32_t)r;
-          a.rk[(uint32_t)r] = (int32_t)q;
-        }
-    } else {
-      uint32_t c = 0;
-      for (uint32_t k = 0; k < ch; ++k) {
-        const uint32_t x = tid * ch + k;
-        if (x < words) c += (uint32_t)__popc(bits[x]);
-      }
-      tb[tid] = x0 + block_excl_scan_add<uint32_t>(c, sh, nullptr);
-      __syncthreads();
-      for (uint32_t i0 = tid; i0 < n; i0 += kRvRankThreads * kRvUnroll) {
-        uint64_t r[kRvUnroll];
-#pragma unroll
-        for (int k = 0; k < kRvUnroll; ++k) {
-          const uint32_t i = i0 + k * kRvRankThreads;
-          r[k] = i < n ? rec[i] : 0u;
-        }
-#pragma unroll
-        for (int k = 0; k < kRvUnroll; ++k) {
-          if (i0 + k * kRvRankThreads >= n) continue;
-          const uint32_t v = ((uint32_t)(r[k] >> 32) - lo) & mask, wd = v >> 5;
-          uint32_t q = tb[wd / ch] + (uint32_t)__popc(bits[wd] & ((1u << (v & 31)) - 1u));
-          for (uint32_t x = wd / ch * ch; x < wd; ++x) q += (uint32_t)__popc(bits[x]);
-          a.sv[q] = (int32_t)(uint32_t)r[k];
-          a.rk[(uint32_t)r[k]] = (int32_t)q;
-        }
+      for (int k = 0; k < kRvUnroll; ++k) {
+        if (i0 + k * kRvRankThreads >= i_hi) continue;
+        const uint32_t v = ((uint32_t)(r[k] >> 32) - lo) & mask, wd = v >> 5;
+        uint32_t q = l.tb[wd / ch] + (uint32_t)__popc(l.bits[wd] & ((1u << (v & 31)) - 1u));
+        for (uint32_t x = wd / ch * ch; x < wd; ++x) q += (uint32_t)__popc(l.bits[x]);
+        a.sv[q] = (int32_t)(uint32_t)r[k];
+        a.rk[(uint32_t)r[k]] = (int32_t)q;
       }
     }
-    __syncthreads();  // the bitmap is free for the next bucket
+  }
+  __syncthreads();  // the bitmap is free for the next bucket
+}
+
+__global__ void __launch_bounds__(kRvRankThreads) k_rv_rank(RvArgs a) {
+  __shared__ RvRankLds lds;
+  const uint32_t lo = a.mm[0], hi = a.mm[1], np = a.mm[2], full = rv_full(a.T);
+  const int shift = rv_shift(a, lo, hi);
+  const uint32_t nb = ((hi - lo) >> shift) + 1u;
+  for (uint32_t p = blockIdx.x; p < np; p += gridDim.x) {
+    const uint2 e = a.part[p];
+    rv_rank_bucket<kRvPartUnroll>(a, shift, lo, e.x, e.y, e.y + kRvPart, lds);
+  }
+  for (uint32_t b = blockIdx.x; b < nb; b += gridDim.x) {
+    const uint32_t n = a.cnt[b + 1] - a.cnt[b];
+    if (n == 0 || n > full) continue;  // uniform over the block
+    rv_rank_bucket<kRvUnroll>(a, shift, lo, b, 0, n, lds);
   }
 }
 
-// Only after equal seq values: a stable sort of (seq, launch) in one block,
-// 8 bits a pass, a tile of one pair per thread at a time.
-__global__ void __launch_bounds__(kRvThreads) k_rv_equal(RvArgs a) {
-  if (a.mm[2] == 0) return;  // uniform
-  constexpr int kWaves = kRvThreads / OPA_WAVE;
-  __shared__ uint32_t gb[256], wc[kWaves][256], sh[kWaves];
+// The sort of all (seq, launch) pairs, only when an earlier step asked for it:
+// a stable LSD radix sort of the range's bits, 8 a pass, in one launch. A pass
+// is two phases over stretches of tiles, at most kRvItems of them: the
+// stretches' digit counts, then the scatter, which adds up the counts before
+// its stretch itself; the last one writes the view. The stretches are handed
+// out in order by one counter, and before its stretch a block waits for the
+// whole phase before: all of that was handed out earlier, to blocks that run
+// and wait for still earlier phases only, so every wait ends, however few
+// blocks run at a time. (Few stretches, because a stretch ends with the
+// write-back of an L2.)
+constexpr int kRvSortPer = 4, kRvSortTile = kRvSortPer * kRvThreads;
+constexpr int kRvItems = 128, kRvPhases = 8;
+constexpr int kRvWaves = kRvThreads / OPA_WAVE;
+
+struct RvSortLds {
+  uint16_t cnt[kRvSortPer * kRvWaves * 256];
+  uint32_t c[256], part[4][256], less[4][256];
+  uint32_t sh[kRvWaves], item;
+};
+
+// digit counts of the tiles [t0, t1) to hist[256]
+__device__ __forceinline__ void rv_sort_count(const uint32_t *keys, uint32_t lo, int64_t T,
+                                              int64_t t0, int64_t t1, int shift, uint32_t *hist,
+                                              RvSortLds &l) {
+  const int tid = threadIdx.x;
+  if (tid < 256) l.c[tid] = 0;
+  __syncthreads();
+  const int64_t x1 = t1 * kRvSortTile < T ? t1 * kRvSortTile : T;
+  for (int64_t x0 = t0 * kRvSortTile + tid; x0 < x1; x0 += kRvSortTile) {
+#pragma unroll
+    for (int k = 0; k < kRvSortPer; ++k) {
+      const int64_t x = x0 + k * kRvThreads;
+      if (x < x1) atomicAdd(&l.c[((keys[x] - lo) >> shift) & 255u], 1u);
+    }
+  }
+  __syncthreads();
+  if (tid < 256) hist[tid] = l.c[tid];
+}
+
+// The tiles [t0, t1) of item k (of n items, hist their counts) scattered; with
+// out.sv the places are the launches' ranks.
+struct RvOut {
+  uint32_t *key, *val;
+  int32_t *sv, *rk;
+};
+__device__ __forceinline__ void rv_sort_scatter(const uint32_t *ki, const uint32_t *vi,
+                                                const RvOut &out, uint32_t lo, int64_t T,
+                                                int64_t t0, int64_t t1, int shift,
+                                                const uint32_t *hist, uint32_t k, uint32_t n,
+                                                RvSortLds &l) {
   const int tid = threadIdx.x, w = wave_id();
-  for (int pass = 0; pass < 4; ++pass) {
-    const int shift = 8 * pass;
-    const uint32_t *ki = (pass & 1) ? a.k1 : a.k0, *vi = (pass & 1) ? a.v1 : a.v0;
-    uint32_t *ko = (pass & 1) ? a.k0 : a.k1, *vo = (pass & 1) ? a.v0 : a.v1;
-    auto key = [&](int64_t i) { return pass ? ki[i] : a.seq[i]; };
-    if (tid < 256) gb[tid] = 0;
-    __syncthreads();
-    for (int64_t i = tid; i < a.T; i += kRvThreads) atomicAdd(&gb[(key(i) >> shift) & 255u], 1u);
-    __syncthreads();
-    const uint32_t g = tid < 256 ? gb[tid] : 0u;
-    const uint32_t e = block_excl_scan_add<uint32_t>(g, sh, nullptr);
-    if (tid < 256) gb[tid] = e;
-    for (int64_t t0 = 0; t0 < a.T; t0 += kRvThreads) {
-      for (int x = tid; x < kWaves * 256; x += kRvThreads) (&wc[0][0])[x] = 0;
-      __syncthreads();
-      const int64_t i = t0 + tid;
-      const bool ok = i < a.T;
-      const uint32_t k = ok ? key(i) : 0u, v = ok ? (pass ? vi[i] : (uint32_t)i) : 0u;
-      const uint32_t d = (k >> shift) & 255u;
-      const uint64_t pm = peers8(d) & __ballot(ok);
-      const uint32_t lr = (uint32_t)__popcll(pm & lanemask_lt());
-      if (ok && lr == 0) wc[w][d] = (uint32_t)__popcll(pm);
-      __syncthreads();
-      if (tid < 256) {
-        uint32_t run = gb[tid];
-        for (int x = 0; x < kWaves; ++x) {
-          const uint32_t c = wc[x][tid];
-          wc[x][tid] = run;
-          run += c;
-        }
-        gb[tid] = run;
-      }
-      __syncthreads();
-      if (ok) {
-        const uint32_t dst = wc[w][d] + lr;
-        ko[dst] = k;
-        vo[dst] = v;
-      }
-      __syncthreads();
+  {  // each digit's launches in all items, and in those before k: four threads a digit
+    const int d = tid & 255, q = tid >> 8;
+    uint32_t all = 0, less = 0;
+#pragma unroll 8
+    for (uint32_t x = q; x < n; x += 4) {
+      const uint32_t v = hist[x * 256 + d];
+      all += v;
+      less += x < k ? v : 0u;
     }
-    __threadfence_block();
+    l.part[q][d] = all;
+    l.less[q][d] = less;
     __syncthreads();
+    uint32_t v = 0, b = 0;
+    if (tid < 256)
+      for (int y = 0; y < 4; ++y) {
+        v += l.part[y][tid];
+        b += l.less[y][tid];
+      }
+    const uint32_t e = block_excl_scan_add<uint32_t>(v, l.sh, nullptr);
+    if (tid < 256) l.c[tid] = e + b;  // the digit's next place
   }
-  for (int64_t i = tid; i < a.T; i += kRvThreads) {  // four passes: back in k0, v0
-    const uint32_t j = a.v0[i];
-    a.sv[i] = (int32_t)j;
-    a.rk[j] = (int32_t)i;
+  uint32_t *c32 = reinterpret_cast<uint32_t *>(l.cnt);
+  for (int64_t t = t0; t < t1; ++t) {
+    for (int x = tid; x < kRvSortPer * kRvWaves * 256 / 2; x += kRvThreads) c32[x] = 0;
+    __syncthreads();
+    uint32_t key[kRvSortPer], val[kRvSortPer], lr[kRvSortPer];
+#pragma unroll
+    for (int j = 0; j < kRvSortPer; ++j) {
+      const int64_t x = t * kRvSortTile + j * kRvThreads + tid;
+      const bool ok = x < T;
+      key[j] = ok ? ki[x] : lo;
+      val[j] = ok ? (vi ? vi[x] : (uint32_t)x) : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < kRvSortPer; ++j) {
+      const bool ok = t * kRvSortTile + j * kRvThreads + tid < T;
+      const uint32_t d = ((key[j] - lo) >> shift) & 255u;
+      const uint64_t pm = peers8(d) & __ballot(ok);
+      lr[j] = (uint32_t)__popcll(pm & lanemask_lt());
+      if (ok && lr[j] == 0) l.cnt[(j * kRvWaves + w) * 256 + d] = (uint16_t)__popcll(pm);
+    }
+    __syncthreads();
+    {  // the digit's counts over (j, wave), in order: four threads a digit again
+      constexpr int kQ = kRvSortPer * kRvWaves / 4;
+      const int d = tid & 255, q = tid >> 8;
+      uint32_t v[kQ], run = 0;
+#pragma unroll
+      for (int y = 0; y < kQ; ++y) {
+        v[y] = l.cnt[(q * kQ + y) * 256 + d];
+        run += v[y];
+      }
+      l.part[q][d] = run;
+      if (q == 0) l.less[0][d] = l.c[d];  // the digit's first place in this tile
+      __syncthreads();
+      run = 0;
+      for (int y = 0; y < q; ++y) run += l.part[y][d];
+#pragma unroll
+      for (int y = 0; y < kQ; ++y) {
+        l.cnt[(q * kQ + y) * 256 + d] = (uint16_t)run;
+        run += v[y];
+      }
+      if (q == 3) l.c[d] = l.less[0][d] + run;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kRvSortPer; ++j) {
+      if (t * kRvSortTile + j * kRvThreads + tid >= T) continue;
+      const uint32_t d = ((key[j] - lo) >> shift) & 255u;
+      const uint32_t dst = l.less[0][d] + l.cnt[(j * kRvWaves + w) * 256 + d] + lr[j];
+      if (out.sv) {
+        out.sv[dst] = (int32_t)val[j];
+        out.rk[val[j]] = (int32_t)dst;
+      } else {
+        out.key[dst] = key[j];
+        out.val[dst] = val[j];
+      }
+    }
+    __syncthreads();
   }
 }
 
-size_t rank_view_entries() { return 2 * ((size_t)kRvBuckets + 64) + 64; }
+__global__ void __launch_bounds__(kRvThreads) k_rv_sort(RvArgs a) {
+  if (a.mm[3] == 0) return;  // uniform: written by earlier kernels only
+  __shared__ RvSortLds l;
+  const int tid = threadIdx.x;
+  const uint32_t lo = a.mm[0];
+  const int64_t nt = (a.T + kRvSortTile - 1) / kRvSortTile;
+  const uint32_t n = nt < kRvItems ? (uint32_t)nt : (uint32_t)kRvItems;  // items of a phase
+  const uint32_t passes = ((uint32_t)bits_for(a.mm[1] - lo) + 7) / 8;
+  for (;;) {
+    __syncthreads();
+    if (tid == 0) l.item = atomicAdd(&a.mm[4], 1u);
+    __syncthreads();
+    const uint32_t phase = l.item / n, k = l.item - phase * n, pass = phase >> 1;
+    if (pass >= passes) return;  // uniform
+    if (phase > 0) {
+      if (tid == 0) {
+        while (__hip_atomic_load(&a.mm[8 + phase - 1], __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT) < n)
+          __builtin_amdgcn_s_sleep(2);
+        __threadfence();
+      }
+      __syncthreads();
+    }
+    const int64_t t0 = nt * k / n, t1 = nt * (k + 1) / n;
+    const int shift = 8 * (int)pass;
+    const bool odd = pass & 1u, last = pass + 1 == passes;
+    const uint32_t *ki = pass == 0 ? a.seq : odd ? a.k0 : a.k1;
+    const uint32_t *vi = pass == 0 ? nullptr : odd ? a.v0 : a.v1;
+    if ((phase & 1u) == 0) {
+      rv_sort_count(ki, lo, a.T, t0, t1, shift, a.hist + k * 256, l);
+    } else {
+      const RvOut out{odd ? a.k1 : a.k0, odd ? a.v1 : a.v0, last ? a.sv : nullptr, a.rk};
+      rv_sort_scatter(ki, vi, out, lo, a.T, t0, t1, shift, a.hist, k, n, l);
+    }
+    // the block's writes are made visible before the item counts as done
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (tid == 0) {
+      __threadfence();
+      __hip_atomic_fetch_add(&a.mm[8 + phase], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+}
+
+static_assert(8 + kRvPhases <= 64, "the phases' counts");
+
+// the counters and buckets, the sort's digit counts, the overfull buckets' parts
+size_t rank_view_entries(int64_t T) {
+  return 2 * ((size_t)kRvBuckets + 64) + 64 + kRvItems * 256 + 2 * rv_max_parts(T);
+}
 
 void run_rank_view(const opattr_kernels *k, void *ws, const Plan &pl, opattr_diag *diag,
                    hipStream_t s) {
@@ -318,6 +496,8 @@ void run_rank_view(const opattr_kernels *k, void *ws, const Plan &pl, opattr_dia
   a.mm = m;
   a.cnt = m + 64;
   a.cur = a.cnt + kRvBuckets + 64;
+  a.hist = a.cur + kRvBuckets + 64;
+  a.part = reinterpret_cast<uint2 *>(a.hist + kRvItems * 256);
   a.sv = at<int32_t>(ws, pl.sv);
   a.rk = at<int32_t>(ws, pl.rk);
   a.diag = diag;
@@ -334,7 +514,7 @@ void run_rank_view(const opattr_kernels *k, void *ws, const Plan &pl, opattr_dia
   const int64_t want = pl.T >> kRvPerBits;
   k_rv_rank<<<(unsigned)(want < 512 ? 512 : (want < kRvBuckets ? want : kRvBuckets)),
               kRvRankThreads, 0, s>>>(a);
-  k_rv_equal<<<1, kRvThreads, 0, s>>>(a);
+  k_rv_sort<<<kRvItems, kRvThreads, 0, s>>>(a);
 }
 
 }  // namespace opa

@@ -163,13 +163,18 @@ def test_compact_edges(T, S, n_names, n_ops, order):
 @pytest.mark.parametrize("T,kind", [
     (1, "even"), (1023, "even"), (50_001, "even"), (2 ** 20 + 9, "even"), (8192, "dense"),
     (70_000, "far"), (70_000, "ends"), (300_000, "captures"),
-    (70_000, "pairs"), (20_000, "same"), (1025, "same")])
+    (70_000, "pairs"), (20_000, "same"), (1025, "same"),
+    (600_001, "far"), (600_001, "far_pair"), (300_000, "same"),
+    (100_001, 4096), (100_001, 4097), (100_001, 8192), (100_001, 8193), (100_001, 33_000)])
 def test_launch_ranks_by_buckets(T, kind):
     """Ranks of launches whose seq is not promised dense: the smallest and
     largest values, one far value beside a dense run (buckets of 2^18 values,
     most of them empty), two captures far apart, and equal values, whose
     ranks go by input index, in small buckets and in one larger than a
-    bucket's own count of smaller launches takes."""
+    bucket's own count of smaller launches takes (by the sort of all pairs, in
+    stretches of one tile and of several). A number: clumps of that many
+    consecutive values far apart, around the sizes from which a bucket is
+    ranked in parts."""
     rng = np.random.default_rng(T)
     tr = cases.random_trace(6900 + T % 977, T=T, S=3, n_names=min(T, 70), R=T // 8, n_ops=50,
                             t_max=8 * T + 8, max_depth=5, dedup=False)
@@ -179,6 +184,11 @@ def test_launch_ranks_by_buckets(T, kind):
         seq = np.arange(T) + 77
     elif kind == "far":
         seq = np.append(np.arange(T - 1) + 5, 2 ** 32 - 1)
+    elif kind == "far_pair":
+        seq = np.append(np.arange(T - 1) + 5, 2 ** 32 - 1)
+        seq[T // 3] = seq[T // 3 + 1]
+    elif not isinstance(kind, str):
+        seq = np.arange(T) // kind * (1 << 24) + np.arange(T) % kind
     elif kind == "ends":
         seq = np.append(np.arange(T // 2), 2 ** 32 - T + T // 2 + np.arange(T - T // 2))
     elif kind == "captures":
@@ -192,7 +202,38 @@ def test_launch_ranks_by_buckets(T, kind):
     want = O.attribute(tr)
     out, diag = _run(tr, flags=0)
     parity.assert_attribute(out, want, diag)
-    assert bool(diag["flags"] & opattr.F_ORDER) == (kind in ("pairs", "same"))
+    assert bool(diag["flags"] & opattr.F_ORDER) == (kind in ("pairs", "same", "far_pair"))
+
+
+def test_launch_ranks_time_of_uneven_and_equal_values():
+    """A far value beside a dense run, and equal values in a large bucket, cost
+    a few times an even spread, not a serial pass over the list (500k launches:
+    217 us the call for an even spread, 280 with a far value, 430 with a pair
+    of equal ones too, 230 all equal)."""
+    import torch
+
+    T = 500_000
+    rng = np.random.default_rng(1)
+    tr = cases.random_trace(6990, T=T, S=3, n_names=70, R=T // 20, n_ops=50, t_max=8 * T + 8,
+                            max_depth=5)
+    far = np.append(np.arange(T - 1), 2 ** 32 - 1)
+    pair = far.copy()
+    pair[T // 3] = pair[T // 3 + 1]
+    us = {}
+    for kind, seq in (("even", 3 * np.arange(T)), ("far", far), ("pair", pair),
+                      ("same", np.full(T, 7))):
+        print(f"case launch ranks time {kind}", flush=True)
+        tr["seq"] = rng.permutation(seq).astype(np.uint32)
+        dt, ws = opattr.to_device(tr, DEV), opattr.Workspace(DEV)
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(12)]
+        for e in ev:
+            opattr.opattr_attribute(dt, flags=0, ws=ws, raise_strict=False)
+            e.record()
+        torch.cuda.synchronize()
+        us[kind] = np.median([a.elapsed_time(b) * 1e3 for a, b in zip(ev[1:], ev[2:])])
+    print(us, flush=True)
+    assert us["far"] < 2.5 * us["even"]
+    assert us["pair"] < 6 * us["even"] and us["same"] < 6 * us["even"]
 
 
 @pytest.mark.parametrize("R,t_max", [(1024, 4000), (1025, 50), (4097, 9000), (5000, 3),
