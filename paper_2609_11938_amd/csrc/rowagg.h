@@ -331,14 +331,34 @@ constexpr int kTThreads = 1024;
 constexpr int kTHot = 12;   // lanes of one row above which they are reduced first
 constexpr int kTSegs = 40;  // stretches of lanes of one row up to which they are scanned
 
-// the thread's kPer consecutive launches (nv of them exist) added to the
-// block's table in LDS
+// The waves of a block add to its table in turns, so that a row's sums are
+// added up in one order whatever the scheduling: turn r * waves + w is wave w's
+// r-th. A wave that waits for its turn waits for waves of its own block only,
+// which run and end their turns without waiting for later ones. The adds are
+// atomic in any order; a wave's LDS instructions execute in order, so the next
+// wave's come after them without a wait for their completion.
+__device__ __forceinline__ void turn_begin(uint32_t *turn, uint32_t mine) {
+  while (__hip_atomic_load(turn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != mine) {
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+__device__ __forceinline__ void turn_end(uint32_t *turn, uint32_t mine) {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  if (lane_id() == 0)
+    __hip_atomic_store(turn, mine + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// The thread's kPer consecutive launches (nv of them exist) added to the
+// block's table in LDS; called by the whole block, kPer turns a wave from turn
+// t0 * waves on.
 template <bool DEF, int kPer>
-__device__ __forceinline__ void tab_add(unsigned long long *tab, const AggIn &in, int nv,
-                                        int32_t (&mt)[kPer], uint32_t (&du)[kPer],
-                                        uint32_t (&g)[kPer]) {
+__device__ __forceinline__ void tab_add(unsigned long long *tab, uint32_t *turn, uint32_t t0,
+                                        const AggIn &in, int nv, int32_t (&mt)[kPer],
+                                        uint32_t (&du)[kPer], uint32_t (&g)[kPer]) {
+  constexpr uint32_t kWaves = kTThreads / OPA_WAVE;
   const uint32_t mx = DEF ? kDefMaxMask : in.maxmask, dw = DEF ? kDefDwMask : in.dwmask;
   const int ln = lane_id();
+  uint32_t my = t0 * kWaves + (uint32_t)wave_id();
   Acc acc;
   acc_zero(acc);
   const uint32_t g0 = g[0];
@@ -347,15 +367,19 @@ __device__ __forceinline__ void tab_add(unsigned long long *tab, const AggIn &in
   // launch k is always at position 0 of the arrays (see k_f_agg)
 #pragma unroll 1
   for (int k = 0; k < kPer; ++k) {
-    if (k < nv) {
-      if (g[0] != gc) {
-        slot_add(tab + (size_t)gc * kFFields, acc, mx);
+    if (k > 0) {
+      const bool flush = k < nv && g[0] != gc;
+      turn_begin(turn, my);
+      if (flush) slot_add(tab + (size_t)gc * kFFields, acc, mx);
+      turn_end(turn, my);
+      my += kWaves;
+      if (flush) {
         acc_zero(acc);
         gc = g[0];
         changed = true;
       }
-      acc_launch(acc, in, mt[0], du[0], mx, dw);
     }
+    if (k < nv) acc_launch(acc, in, mt[0], du[0], mx, dw);
 #pragma unroll
     for (int j = 0; j + 1 < kPer; ++j) {
       mt[j] = mt[j + 1];
@@ -372,24 +396,30 @@ __device__ __forceinline__ void tab_add(unsigned long long *tab, const AggIn &in
   const bool start = ln == 0 || changed || nv == 0 || g0 != gp;
   const unsigned long long sm = __ballot(start);
   const unsigned long long act = __ballot(nv > 0);
+  bool add = nv > 0;
+  Acc hot;
+  bool with_hot = false;
+  uint32_t gm = 0;
   if (__popcll(sm & act) <= kTSegs) {
     const unsigned long long upto = ln == OPA_WAVE - 1 ? sm : sm & ((2ull << ln) - 1);
     acc_seg_scan(acc, 63 - __clzll((long long)upto), mx);
     const bool last = ln == OPA_WAVE - 1 || ((sm >> (ln + 1)) & 1ull);
-    if (nv > 0 && last) slot_add(tab + (size_t)gc * kFFields, acc, mx);
-    return;
+    add = add && last;
+  } else {
+    gm = (uint32_t)__builtin_amdgcn_readlane((int)gc, 31);
+    const bool in_hot = nv > 0 && gc == gm;
+    with_hot = __popcll(__ballot(in_hot)) >= kTHot;
+    if (with_hot) {
+      hot = acc;
+      if (!in_hot) acc_zero(hot);
+      acc_wave_reduce(hot, mx);
+      add = add && !in_hot;
+    }
   }
-  const uint32_t gm = (uint32_t)__builtin_amdgcn_readlane((int)gc, 31);
-  const bool in_hot = nv > 0 && gc == gm;
-  if (__popcll(__ballot(in_hot)) >= kTHot) {
-    Acc t = acc;
-    if (!in_hot) acc_zero(t);
-    acc_wave_reduce(t, mx);
-    if (ln == 0) slot_add(tab + (size_t)gm * kFFields, t, mx);
-    if (nv > 0 && !in_hot) slot_add(tab + (size_t)gc * kFFields, acc, mx);
-  } else if (nv > 0) {
-    slot_add(tab + (size_t)gc * kFFields, acc, mx);
-  }
+  turn_begin(turn, my);
+  if (with_hot && ln == 0) slot_add(tab + (size_t)gm * kFFields, hot, mx);
+  if (add) slot_add(tab + (size_t)gc * kFFields, acc, mx);
+  turn_end(turn, my);
 }
 
 __device__ __forceinline__ unsigned long long merge_field(int f, unsigned long long x,
