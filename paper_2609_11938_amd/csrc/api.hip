@@ -188,6 +188,14 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
       pl.ftabs = (int)(chunks < kTabBlocks ? chunks : kTabBlocks);
     }
   }
+  // Launches of one operator row in a wave from which a block adds them up: 200 /
+  // flong + 16 bytes a launch, where the general aggregation's arrays take
+  // about 40. The call at 2, 4 and 8: 96k over 5,014 rows 60.0, 64.8 and 69.7
+  // us, 1M with 600k ranges 204, 236 and 314 us, 2M with 400k ranges 272, 277
+  // and 307 us, 500k shuffled over 1,001 rows 193, 193 and 200 us. Two for short
+  // lists (1M: 117 MB, 72 MB more than the general aggregation's arrays), four
+  // for longer ones and launches that need the view's arrays as well.
+  pl.flong = mode == PlanMode::kLean ? 8 : pl.compact && sm_hint ? 2 : 4;
   // A thousand blocks of the run reduction run at once (four waves a SIMD by
   // registers): up to 4M launches, eight launches a lane make less than two
   // rounds of blocks, half of them idle in the last (2M: 58 us at eight, 50 at
@@ -255,33 +263,21 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
   if (pl.fused || pl.compact) {
     b.off = pl.compact ? permuted : shared;
     const int64_t nfb = fused_agg_blocks(pl.T, fused_span(pl));
-    pl.acc = b.take(fused_acc_bytes(pl.G));
+    pl.acc = b.take(pl.compact ? 0 : fused_acc_bytes(pl.G));
     pl.fbkt = b.take(fused_bkt_bytes(nfb));
-    pl.fbase = b.take((size_t)nfb * 4);
     pl.forder = b.take((size_t)nfb * 4);
-    pl.fsplit = b.take(pl.compact ? 0 : fused_split_bytes(pl.G));
+    pl.fsplit = b.take(pl.compact || pl.ftabs ? 0 : fused_split_bytes(pl.G, nfb));
     pl.fhot = b.take(fused_hot_bytes());
-    // Partials: the run reduction keeps a fixed count per block, the
-    // row-ordered reduction at most one per change of the innermost range and
-    // one per wave (half a partial per launch at most). What finds no room
-    // goes to the row accumulators by atomics, which costs little when the
-    // rows are many (96k launches over 5,014 rows in 188 blocks: 62 us for
-    // the reduction and the rows, 52 us with room), so launches in any order
-    // get what the other arrays leave.
     if (pl.compact) {
       pl.ctl = b.take((size_t)pl.nct * NN * 4);
       pl.cpf = b.take((size_t)pl.ncp * NN * 4);
       pl.csum = b.take((size_t)nfb * 4 * 8);
       pl.csamp = b.take((size_t)kCWindow * 8);
     }
-    const int64_t turns = 2 * pl.R + (int64_t)pl.NS + 1, half = pl.T / 2 + 1;
-    pl.fcap = pl.fper ? (turns < half ? turns : half) + 4 * nfb : nfb * fused_block_cap();
-    if (pl.ftabs) pl.fcap = (int64_t)pl.ftabs * pl.G;
-    if ((mode == PlanMode::kLean || (pl.compact && !sm_hint)) && pl.fper && !pl.ftabs) {  // no more than the other aggregation takes
-      const int64_t room = general > b.off ? (int64_t)((general - b.off) / 200) : 0;
-      pl.fcap = pl.fcap < room ? pl.fcap : room;
-    }
+    // partials: a fixed count per block, or the blocks' tables; launch records
+    pl.fcap = pl.ftabs ? (int64_t)pl.ftabs * pl.G : nfb * fused_part_cap(pl);
     pl.fparts = b.take(fused_parts_bytes(pl.fcap));
+    pl.frec = b.take(pl.fper && !pl.ftabs ? (size_t)nfb * fused_span(pl) * 16 : 0);
     if (b.off < general) b.off = general;
   }
   if (!sm_hint) pl.seg = pl.fused = false;  // the launches as given
@@ -855,7 +851,9 @@ int opattr_attribute_noalloc(const opattr_kernels *k, const opattr_profiled *p,
                              opattr_summary *sum, opattr_diag *diag, void *stream) {
   if (!attribute_args_ok(k, p, r, d, policy, agg_kind, match, range_id, table, sum, diag))
     return OPATTR_ERR_INVALID_ARG;
-  Plan pl = make_plan(k, p, r, d, false, PlanMode::kLean);
+  Plan pl = make_plan(k, p, r, d);
+  if (pl.total > OPATTR_NOALLOC_SCRATCH_BYTES)
+    pl = make_plan(k, p, r, d, false, PlanMode::kLean);
   if (pl.total > OPATTR_NOALLOC_SCRATCH_BYTES)
     pl = make_plan(k, p, r, d, false, PlanMode::kPlain);
   if (pl.total > OPATTR_NOALLOC_SCRATCH_BYTES) return OPATTR_ERR_SCRATCH;

@@ -747,8 +747,8 @@ __global__ void __launch_bounds__(kRThreads) k_c_row(CompactArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// 5. the rows of a bucket from all blocks' partials and the row accumulators;
-// the unattributed row in a block of its own, then the finish. Every wave (or
+// 5. the rows of a bucket from all blocks' partials and launch records; the
+// unattributed row in a block of its own, then the finish. Every wave (or
 // half wave, while the rows are few) adds to a copy of the rows of its own,
 // and the copies are added up in pairs: a row in every block (the
 // unattributed one above all) would otherwise take one addition after the
@@ -781,27 +781,16 @@ __global__ void __launch_bounds__(kCRowThreads) k_c_rows(CombParams a) {
   const uint32_t g1 = un ? a.G : (g0 + a.rb < a.NOPS ? g0 + a.rb : a.NOPS);
   if (g0 >= g1) return;
   const uint32_t nr = g1 - g0;
-  const unsigned long long *acc = reinterpret_cast<const unsigned long long *>(a.acc + g0);
   const uint32_t ne = nr * kFFields;  // elements of a copy
   const int copies = c_row_copies(a.rb);
   for (uint32_t x = tid; x < ne * copies; x += kCRowThreads) tab[x] = 0;
   __syncthreads();
   unsigned long long *mine_tab =
       tab + (size_t)(copies == kCRowWaves ? w : 2 * w + (ln >> 5)) * ne;
-  const unsigned long long *parts64 = reinterpret_cast<const unsigned long long *>(a.parts);
   const int64_t per = (a.nblocks + kCRowWaves - 1) / kCRowWaves, b_lo = w * per;
   const int64_t b_hi = b_lo + per < a.nblocks ? b_lo + per : a.nblocks;
   for (int64_t b0 = b_lo; b0 < b_hi; b0 += (int64_t)OPA_WAVE * kPre) {
-    uint32_t ev[kPre], xv[kPre], mine = 0;
-#pragma unroll
-    for (int k = 0; k < kPre; ++k) {
-      const int64_t b = b0 + ln + (int64_t)OPA_WAVE * k;
-      const uint32_t e = b < b_hi ? a.bkt[b * kBktStride + q] : 0u;
-      ev[k] = e & 0xFFFFu;
-      xv[k] = (b < b_hi ? a.pbase[b] : 0u) + (e >> 16);
-      mine += ev[k];
-    }
-    comb_add<kPre>(mine_tab, list[w], parts64, ev, xv, mine, un ? 1u : a.rb, mx);
+    comb_blocks<kPre>(mine_tab, un ? 1u : a.rb, list[w], a, q, b0, b_hi, mx, dw);
     wave_sync_lds();
   }
   __syncthreads();
@@ -814,7 +803,7 @@ __global__ void __launch_bounds__(kCRowThreads) k_c_rows(CombParams a) {
     for (int o = kCRowWaves; o > 0; o >>= 1)
 #pragma unroll
       for (int k = 0; k < o; ++k) v[k] = merge_field(f, v[k], v[k + o], mx);
-    tab[x] = merge_field(f, acc[x], v[0], mx);  // only this thread reads element x of a copy
+    tab[x] = v[0];  // only this thread reads element x of a copy
   }
   __syncthreads();
   for (uint32_t x = tid; x < nr * 24u; x += kCRowThreads) {
@@ -898,16 +887,14 @@ void run_compact(const CompactIn &x, hipStream_t s) {
   a.in = agg_inputs(e);
   a.o.NOPS = d->n_ops;
   a.o.rb = fused_rows_per_bucket(pl.G);
-  a.o.acc = at<PartRow>(ws, pl.acc);
   a.o.parts = at<PartRow>(ws, pl.fparts);
   a.o.bkt = at<uint32_t>(ws, pl.fbkt);
-  a.o.pbase = at<uint32_t>(ws, pl.fbase);
-  a.o.pcount = reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(ws) + pl.acc +
-                                            (size_t)pl.G * sizeof(PartRow)) + 1;
-  a.o.pcap = (uint32_t)pl.fcap;
+  a.o.rec = at<uint4>(ws, pl.frec);
+  a.o.pcap = (uint32_t)fused_part_cap(pl);
+  a.o.rcap = (uint32_t)fused_span(pl);
+  a.o.longrow = pl.flong;
   a.tabs = reinterpret_cast<unsigned long long *>(a.o.parts);
   a.csum = at<unsigned long long>(ws, pl.csum);
-  fused_acc_clear(a.fill, ws, pl);
   a.fill.add(at<uint8_t>(ws, pl.sflag), 0, sflag_words(pl.NS));
   if (parts) {
     a.fill.add(a.pfirst, 0xFFFFFFFFu, pl.NP);
@@ -956,8 +943,10 @@ void run_compact(const CompactIn &x, hipStream_t s) {
   c.absent = x.p->absent_mask;
   c.parts = a.o.parts;
   c.bkt = a.o.bkt;
-  c.pbase = a.o.pbase;
-  c.acc = a.o.acc;
+  c.pcap = a.o.pcap;
+  c.rec = a.o.rec;
+  c.rcap = a.o.rcap;
+  c.in = a.in;
   c.table = x.table;
   c.part = a.csum;
   c.diag = x.diag;

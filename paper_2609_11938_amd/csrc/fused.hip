@@ -37,7 +37,7 @@ constexpr int kAThreads = 256;                 // threads per block
 constexpr int kASlots = 32;                    // partial results a wave keeps
 constexpr int kABlockCap = kASlots * (kAThreads / OPA_WAVE);  // and a block
 constexpr int kHot = 32;                       // combine waves of the unattributed row
-constexpr int kSplits = 16;                    // shares of the blocks per bucket
+constexpr int kSplits = 16;                    // shares of the blocks per bucket at most
 constexpr int kPre = 8;                        // bucket entries a combine lane fetches at once
 constexpr uint32_t kNoSrc = 0xFFFFFFFFu;
 constexpr uint32_t kHash = 256;                // LDS table of a block's rows (> 2 x kept)
@@ -385,11 +385,10 @@ k_f_agg(AggParams a) {
   if (tid < kBuckets) cnt = hist[tid];
   const uint32_t off = block_excl_scan_add<uint32_t>(tid < kBuckets ? cnt : 0u, sh, &tot);
   const uint32_t hcnt = hist[kBuckets];  // the unattributed row's partial goes last
-  if (tid < kBuckets)
-    a.o.bkt[blk * kBktStride + tid] = (off << 16) | cnt;
+  if (tid < kBuckets) a.o.bkt[blk * kBktStride + tid] = off << 16;
   if (tid == 0) {
-    a.o.bkt[blk * kBktStride + kBuckets] = (tot << 16) | hcnt;
-    a.o.pbase[blk] = (uint32_t)(blk * kABlockCap);
+    a.o.bkt[blk * kBktStride + kBuckets] = tot << 16;
+    a.o.bkt[blk * kBktStride + kBuckets + 1] = (tot + hcnt) << 16;
   }
   __syncthreads();
   if (tid < kBuckets) hist[tid] = off;
@@ -420,10 +419,8 @@ k_f_agg(AggParams a) {
 // up in an LDS slot of the lane it starts in (at most one per lane, so the
 // slots never run out). The partials come out in row order: a bucket's
 // entry is a difference of the count of row starts before its first
-// launch and before its last. Bound by the gathers' latency at the eight
-// waves a CU that the slots leave and by the partials' scattered stores:
-// 96k launches, 62,800 ranges, 5,014 rows take 24 us, where the items of
-// the general aggregation took eleven launches and about 90 us.
+// launch and before its last. Rows of few launches of a wave are kept as
+// launch records instead.
 // ---------------------------------------------------------------------------
 template <bool DEF, int kPer>  // DEF: the default aggregation kinds; kPer launches per lane
 __global__ void __launch_bounds__(kRThreads) k_r_agg(AggParams a) {
@@ -515,22 +512,39 @@ template <bool DEF>
 __global__ void __launch_bounds__(64) k_f_comb(CombParams a) {
   extern __shared__ __align__(16) unsigned char comb_raw[];
   unsigned long long *tab = reinterpret_cast<unsigned long long *>(comb_raw);  // [rb][kFFields]
-  const uint32_t mx = DEF ? kDefMaxMask : a.mx;
-  const int ln = lane_id();
-  if (blockIdx.x >= (unsigned)(kBuckets * kSplits)) {
+  const uint32_t mx = DEF ? kDefMaxMask : a.mx, dw = DEF ? kDefDwMask : a.dw;
+  const int ln = lane_id(), ns = a.nsplit;
+  if (blockIdx.x >= (unsigned)(kBuckets * ns)) {
     // the unattributed row: a share of the blocks, each lane adding its
     // blocks' partials in registers, then the lanes across the wave
-    const int h = (int)blockIdx.x - kBuckets * kSplits;
+    const int h = (int)blockIdx.x - kBuckets * ns;
     const int64_t per = (a.nblocks + kHot - 1) / kHot;
     const int64_t b_lo = (int64_t)h * per, b_hi = b_lo + per < a.nblocks ? b_lo + per : a.nblocks;
     unsigned long long racc[kFFields];
 #pragma unroll
     for (int f = 0; f < kFFields; ++f) racc[f] = 0;
     for (int64_t b = b_lo + ln; b < b_hi; b += OPA_WAVE) {
-      const uint32_t e = a.bkt[b * kBktStride + kBuckets];
-      const uint32_t c = e & 0xFFFFu, o = e >> 16;
+      const uint32_t e = a.bkt[b * kBktStride + kBuckets], e1 = a.bkt[b * kBktStride + kBuckets + 1];
+      const uint32_t c = (e1 >> 16) - (e >> 16);
       const unsigned long long *pr =
-          reinterpret_cast<const unsigned long long *>(a.parts + (size_t)a.pbase[b] + o);
+          reinterpret_cast<const unsigned long long *>(a.parts + b * a.pcap + (e >> 16));
+      if (a.rec) {  // a few at most: short stretches of the waves
+        const uint4 *rc = a.rec + b * a.rcap;
+#pragma unroll 1
+        for (uint32_t x = e & 0xFFFFu; x < (e1 & 0xFFFFu); ++x) {
+          Acc t;
+          acc_zero(t);
+          acc_launch(t, a.in, (int32_t)rc[x].y, rc[x].z, mx, dw);
+          racc[0] += t.kc;
+          racc[1] += t.tns;
+          racc[2] += t.mc;
+          racc[3] += t.mns;
+#pragma unroll
+          for (int f = 0; f < OPATTR_NUM_COUNTERS; ++f)
+            racc[4 + f] = merge_field(4 + f, racc[4 + f], t.v[f], mx);
+          racc[24] |= t.nan;
+        }
+      }
 #pragma unroll 1
       for (uint32_t p = 0; p < c; ++p, pr += sizeof(PartRow) / 8)
 #pragma unroll
@@ -550,30 +564,19 @@ __global__ void __launch_bounds__(64) k_f_comb(CombParams a) {
     }
     return;
   }
-  const uint32_t q = blockIdx.x / kSplits, s = blockIdx.x % kSplits;
+  const uint32_t q = blockIdx.x / ns, s = blockIdx.x % ns;
   const uint32_t rb = a.rb, ne = rb * kFFields;
   for (uint32_t x = ln; x < ne; x += OPA_WAVE) tab[x] = 0;
   wave_sync_lds();
-  const int64_t per = (a.nblocks + kSplits - 1) / kSplits;
+  const int64_t per = (a.nblocks + ns - 1) / ns;
   const int64_t b_lo = (int64_t)s * per, b_hi = b_lo + per < a.nblocks ? b_lo + per : a.nblocks;
-  uint32_t *list = reinterpret_cast<uint32_t *>(tab + ne);  // [kList] partial indices
-  const unsigned long long *parts64 = reinterpret_cast<const unsigned long long *>(a.parts);
+  uint32_t *list = reinterpret_cast<uint32_t *>(tab + ne);  // [kList] entries
   for (int64_t b0 = b_lo; b0 < b_hi; b0 += (int64_t)OPA_WAVE * kPre) {
-    // the lane's next kPre blocks' entries for the bucket, loads in flight together
-    uint32_t ev[kPre], xv[kPre], mine = 0;  // count, first partial
-#pragma unroll
-    for (int k = 0; k < kPre; ++k) {
-      const int64_t b = b0 + ln + (int64_t)OPA_WAVE * k;
-      const uint32_t e = b < b_hi ? a.bkt[b * kBktStride + q] : 0u;
-      ev[k] = e & 0xFFFFu;
-      xv[k] = (b < b_hi ? a.pbase[b] : 0u) + (e >> 16);
-      mine += ev[k];
-    }
-    comb_add<kPre>(tab, list, parts64, ev, xv, mine, rb, mx);
+    comb_blocks<kPre>(tab, rb, list, a, q, b0, b_hi, mx, dw);
     wave_sync_lds();
   }
   unsigned long long *out =
-      reinterpret_cast<unsigned long long *>(a.split + ((size_t)q * kSplits + s) * rb);
+      reinterpret_cast<unsigned long long *>(a.split + ((size_t)q * ns + s) * rb);
   for (uint32_t x = ln; x < ne; x += OPA_WAVE) {
     const uint32_t rr = x / kFFields, ff = x % kFFields;
     out[rr * (sizeof(PartRow) / 8) + ff] = tab[x];
@@ -598,12 +601,13 @@ __global__ void __launch_bounds__(256) k_f_rows(CombParams a) {
     const uint32_t rr = x / kFFields, ff = x % kFFields;
     const uint32_t g = q * rb + rr;
     const unsigned long long *sp =
-        reinterpret_cast<const unsigned long long *>(a.split + (size_t)q * kSplits * rb) +
+        reinterpret_cast<const unsigned long long *>(a.split + (size_t)q * a.nsplit * rb) +
         (size_t)rr * (sizeof(PartRow) / 8) + ff;
     unsigned long long y[kSplits + 1];
     y[kSplits] = g < a.G ? reinterpret_cast<const unsigned long long *>(a.acc + g)[ff] : 0ull;
 #pragma unroll
-    for (int k = 0; k < kSplits; ++k) y[k] = sp[(size_t)k * rb * (sizeof(PartRow) / 8)];
+    for (int k = 0; k < kSplits; ++k)
+      y[k] = k < a.nsplit ? sp[(size_t)k * rb * (sizeof(PartRow) / 8)] : 0ull;
     unsigned long long v = y[kSplits];
 #pragma unroll
     for (int k = 0; k < kSplits; ++k) v = merge_field((int)ff, v, y[k], mx);
@@ -686,7 +690,9 @@ int fused_span(const Plan &pl) {
 int64_t fused_agg_blocks(int64_t T, int span) { return (T + span - 1) / span; }
 
 size_t fused_parts_bytes(int64_t cap) { return (size_t)cap * sizeof(PartRow); }
-int64_t fused_block_cap() { return kABlockCap; }
+int fused_part_cap(const Plan &pl) {  // partials a block keeps
+  return pl.fper ? fused_span(pl) / pl.flong : kABlockCap;
+}
 
 size_t fused_bkt_bytes(int64_t nb) { return (size_t)nb * kBktStride * 4; }
 
@@ -694,12 +700,12 @@ size_t fused_tab_bytes(uint32_t G) { return (size_t)G * kFFields * 8; }
 
 size_t fused_hot_bytes() { return (size_t)kHot * sizeof(PartRow); }
 
-size_t fused_split_bytes(uint32_t G) {
-  return (size_t)kBuckets * kSplits * fused_rows_per_bucket(G) * sizeof(PartRow);
+int fused_splits(int64_t) { return kSplits; }
+size_t fused_split_bytes(uint32_t G, int64_t nb) {
+  return (size_t)kBuckets * fused_splits(nb) * fused_rows_per_bucket(G) * sizeof(PartRow);
 }
 
 // the row accumulators, then the per-row reduction's count of finished blocks
-// and the row-ordered reduction's count of kept partials
 size_t fused_acc_bytes(uint32_t G) { return (size_t)G * sizeof(PartRow) + 256; }
 
 void fused_acc_clear(FillJobs &j, void *ws, const Plan &pl) {
@@ -733,11 +739,12 @@ void run_fused_agg(const FusedIn &x, hipStream_t s) {
   a.o.acc = at<PartRow>(x.ws, pl.acc);
   a.o.parts = at<PartRow>(x.ws, pl.fparts);
   a.o.bkt = at<uint32_t>(x.ws, pl.fbkt);
-  a.o.pbase = at<uint32_t>(x.ws, pl.fbase);
   uint32_t *counts = reinterpret_cast<uint32_t *>(reinterpret_cast<unsigned char *>(x.ws) + pl.acc +
                                                   (size_t)pl.G * sizeof(PartRow));
-  a.o.pcount = counts + 1;
-  a.o.pcap = (uint32_t)pl.fcap;
+  a.o.rec = at<uint4>(x.ws, pl.frec);
+  a.o.pcap = (uint32_t)fused_part_cap(pl);
+  a.o.rcap = (uint32_t)fused_span(pl);
+  a.o.longrow = pl.flong;
   const bool def = a.in.maxmask == kDefMaxMask && a.in.dwmask == kDefDwMask;
   const int64_t nb = fused_agg_blocks(pl.T, fused_span(pl));
   a.order = x.ordered ? at<uint32_t>(x.ws, pl.forder) : nullptr;  // from the matching
@@ -770,8 +777,12 @@ void run_fused_agg(const FusedIn &x, hipStream_t s) {
   c.absent = x.absent;
   c.parts = a.o.parts;
   c.bkt = a.o.bkt;
-  c.pbase = a.o.pbase;
+  c.pcap = a.o.pcap;
+  c.rec = pl.fper ? a.o.rec : nullptr;
+  c.rcap = a.o.rcap;
+  c.in = a.in;
   c.split = at<PartRow>(x.ws, pl.fsplit);
+  c.nsplit = fused_splits(nb);
   c.hot = at<PartRow>(x.ws, pl.fhot);
   c.acc = a.o.acc;
   c.table = x.table;
@@ -792,10 +803,10 @@ void run_fused_agg(const FusedIn &x, hipStream_t s) {
   const size_t lds = (size_t)rb * kFFields * 8;
   const size_t lds_comb = lds + (size_t)kList * 4;  // the table, then the partials' list
   if (def) {
-    k_f_comb<true><<<kBuckets * kSplits + kHot, 64, lds_comb, s>>>(c);
+    k_f_comb<true><<<kBuckets * c.nsplit + kHot, 64, lds_comb, s>>>(c);
     k_f_rows<true><<<kBuckets, 256, lds, s>>>(c);
   } else {
-    k_f_comb<false><<<kBuckets * kSplits + kHot, 64, lds_comb, s>>>(c);
+    k_f_comb<false><<<kBuckets * c.nsplit + kHot, 64, lds_comb, s>>>(c);
     k_f_rows<false><<<kBuckets, 256, lds, s>>>(c);
   }
   probe_end(OPATTR_PROBE_AGGREGATE, s);

@@ -62,10 +62,11 @@ struct Plan {
   int64_t nct, ncp;  // its tiles of launches and of profiled rows
   size_t ctl, cpf, csum, csamp;
   int fper;      // launches per lane of the row-ordered reduction (0: the run reduction)
+  int flong;     // launches of one row from which the row-ordered reduction adds them up
   int aper;      // launches per lane of the run reduction
   int ftabs;     // blocks of the reduction with the whole table in LDS (0: another one)
   int64_t fcap;  // partials there is room for
-  size_t acc, fparts, fbkt, fbase, fsplit, forder, fhot;
+  size_t acc, fparts, frec, fbkt, fsplit, forder, fhot;
   bool m2;  // the second set below exists
   size_t kblk2, tbnd2, tlh2, pfh2, tlch2, pfch2, tlc2, pfc2, off2, slot2, nbs2;
   // ranges
@@ -85,9 +86,9 @@ struct Plan {
   size_t misc;   // small device scalars
 };
 
-// How much the fused attribution may take: all it can use; no partials past
-// the space of the other aggregation's arrays; or only the run reduction
-// (kPlain, never larger than a plan without the row-ordered reduction).
+// What the fused attribution may take: all it can use; little more than the other
+// aggregation's arrays; or only the run reduction (kPlain, never larger than a
+// plan without the row-ordered reduction).
 enum class PlanMode { kFull, kLean, kPlain };
 
 // second_match: also a second set of the segment path's matching arrays
@@ -390,7 +391,7 @@ struct FusedIn {
 void run_fused_agg(const FusedIn &x, hipStream_t s);
 int fused_span(const Plan &pl);                   // launches per block of the reduction
 int64_t fused_agg_blocks(int64_t T, int span);    // its blocks
-int64_t fused_block_cap();                        // partials a block of the run reduction keeps
+int fused_part_cap(const Plan &pl);               // partials a block keeps
 // the clear of the row accumulators and the done count, as a fill job
 void fused_acc_clear(FillJobs &j, void *ws, const Plan &pl);
 // workspace sizes of the fused aggregation
@@ -398,7 +399,7 @@ size_t fused_parts_bytes(int64_t cap);
 uint32_t fused_rows_per_bucket(uint32_t G);
 size_t fused_tab_bytes(uint32_t G);  // a block's whole table
 size_t fused_bkt_bytes(int64_t nb);
-size_t fused_split_bytes(uint32_t G);
+size_t fused_split_bytes(uint32_t G, int64_t nb);
 size_t fused_hot_bytes();
 size_t fused_acc_bytes(uint32_t G);
 constexpr int64_t kFusedShort = 1 << 20;   // launches up to which blocks always order by row

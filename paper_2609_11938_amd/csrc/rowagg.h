@@ -10,10 +10,11 @@ namespace opa {
 
 constexpr int kFFields = 25;                   // kc, tns, mc, mns, 20 counters, NaN bits
 constexpr int kBuckets = 256;                  // buckets of operator rows
-// A block's bucket entries: the buckets, then the unattributed row (NOPS) on
-// its own: it has a partial in almost every block, which would make its
-// bucket's combine waves the last to finish by far.
-constexpr int kBktStride = kBuckets + 1;
+// A block's bucket entries: the partials (<< 16) and launch records kept before
+// each bucket, before the unattributed row (NOPS), which is on its own (it has
+// a partial in almost every block, which would make its bucket's combine waves
+// the last to finish by far), and in all.
+constexpr int kBktStride = kBuckets + 2;
 constexpr int kRThreads = 256;
 
 // LDS of k_r_agg: the row histogram, later the crossing rows' slots
@@ -118,26 +119,52 @@ __device__ __forceinline__ void slot_add(unsigned long long *q, const Acc &a, ui
   if (a.nan) atomicOr(reinterpret_cast<unsigned int *>(&q[24]), a.nan);
 }
 
-// What a block of the row-ordered reduction writes to.
+// What a block of an aggregation writes to: partials and records by bucket, in
+// a region of fixed size, so that what a block keeps does not depend on the
+// others.
 struct RowOut {
   uint32_t NOPS, rb;  // rb: operator rows per bucket
-  PartRow *acc;       // [G] row accumulators for what finds no room (zeroed)
-  PartRow *parts;     // kept partials, each block's by bucket (row in pad)
-  uint32_t *bkt;      // [blocks][kBktStride] offset << 16 | count
-  uint32_t *pbase;    // [blocks] first partial of each block
-  uint32_t *pcount;   // partials kept so far (zero at launch)
-  uint32_t pcap;      // partials there is room for
+  PartRow *acc;       // [G] row accumulators of the run reduction (zeroed)
+  PartRow *parts;     // [blocks][pcap] kept partials, by bucket (row in pad)
+  uint4 *rec;         // [blocks][rcap] launch records: row, match, duration, 0
+  uint32_t *bkt;      // [blocks][kBktStride]
+  uint32_t pcap, rcap;
+  int longrow;        // launches of one row in a wave from which they are added up
 };
+// The row-ordered reduction adds up a stretch of one row inside a wave if it
+// has longrow launches or more; those of a shorter one are kept as records, and
+// the combine reads their counters. So a block of n launches never has more
+// than n / longrow partials, however many rows it holds, and its region holds
+// whatever comes: 200 / longrow + 16 bytes a launch. (Partials past a common
+// room went to the row accumulators by atomics, in another order on each run.)
 template <int kPer>
 struct RowLds {
   uint2 md[kRThreads * kPer];     // match and duration, in row order
   uint16_t sg[kRThreads * kPer];  // row, in row order
-  uint16_t hx[kRThreads + 1];     // row starts before each thread's positions
-  uint8_t hms[kRThreads];
+  uint32_t hx[kRThreads];         // partials << 16 | records before each thread's positions
+  uint8_t lms[kRThreads];         // bit k: a long stretch starts at the thread's position k
+  uint8_t rms[kRThreads];         // bit k: the launch there is a record
   uint8_t ord[kRThreads / OPA_WAVE][OPA_WAVE];
-  uint32_t sh[4], sbase;
+  uint32_t sh[4], turn;
 };
 constexpr int kMidLanes = 6;  // lanes inside one row above which they are added up first
+
+// The waves of a block that add to one LDS array do so in turns, so that the
+// order does not depend on scheduling. A wave that waits for its turn waits for
+// waves of its own block only, which run and end their turns without waiting
+// for later ones. The adds are atomic in any order; a wave's LDS instructions
+// execute in order, so the next wave's come after them without a wait for
+// their completion.
+__device__ __forceinline__ void turn_begin(uint32_t *turn, uint32_t mine) {
+  while (__hip_atomic_load(turn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != mine) {
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+__device__ __forceinline__ void turn_end(uint32_t *turn, uint32_t mine) {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  if (lane_id() == 0)
+    __hip_atomic_store(turn, mine + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
 
 // The reduction of one block of launches (the thread's kPer consecutive ones:
 // match mt, duration du, row g, nv of them exist; nb in the block), by a
@@ -154,15 +181,17 @@ __device__ __forceinline__ void row_order_block(const RowOut &o, const AggIn &in
   auto &md = lds.md;
   auto &sg = lds.sg;
   auto &hx = lds.hx;
-  auto &hms = lds.hms;
   auto &sh = lds.sh;
-  auto &sbase = lds.sbase;
   const int tid = threadIdx.x, ln = lane_id(), w = wave_id();
   const uint32_t mx = DEF ? kDefMaxMask : in.maxmask, dw = DEF ? kDefDwMask : in.dwmask;
   const uint32_t words = r_hist_words(o.NOPS + 1u);
   uint32_t rk[kPer];
+  if (tid == 0) lds.turn = 0;
   __syncthreads();
-  // rank of every launch in its row: one atomic per run of the thread
+  // rank of every launch in its row: one atomic per run of the thread, the
+  // waves in turns (in whatever order they come, the last bits of a row's sums
+  // differ from run to run)
+  turn_begin(&lds.turn, (uint32_t)w);
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
     if (k >= nv) continue;
@@ -177,6 +206,7 @@ __device__ __forceinline__ void row_order_block(const RowOut &o, const AggIn &in
     const int s16 = (int)(g[k] & 1u) * 16;
     rk[k] = (atomicAdd(&hist[g[k] >> 1], len << s16) >> s16) & 0xFFFFu;
   }
+  turn_end(&lds.turn, (uint32_t)w);
   __syncthreads();
   // first position of every row: each thread scans a stretch of the words
   // (an odd count of them, so that the stretches start in different banks)
@@ -201,98 +231,113 @@ __device__ __forceinline__ void row_order_block(const RowOut &o, const AggIn &in
       md[p] = make_uint2((uint32_t)mt[k], du[k]);
       sg[p] = (uint16_t)g[k];
     }
-  // positions at which this thread's bucket starts and ends (kBuckets
-  // threads), and the unattributed row's first
-  const uint32_t bl = (uint32_t)tid * o.rb, bh = bl + o.rb;
-  const uint32_t p_lo = row_pos(bl < o.NOPS ? bl : o.NOPS), p_hi = row_pos(bh < o.NOPS ? bh : o.NOPS);
+  // position at which this thread's bucket starts (kBuckets threads), and the
+  // unattributed row's first
+  static_assert(kBuckets == kRThreads, "a bucket per thread");
+  const uint32_t bl = (uint32_t)tid * o.rb;
+  const uint32_t p_lo = row_pos(bl < o.NOPS ? bl : o.NOPS);
   const uint32_t p_un = row_pos(o.NOPS);
   __syncthreads();  // the histogram's space becomes the slots
-  // row starts among the thread's positions (a wave's first position is one)
+  // row starts among the thread's positions (a wave's first position is one),
+  // and those of long stretches: their row goes on longrow - 1 positions
+  // later, in the same wave
   const int p0 = tid * kPer;
-  uint32_t hm = 0;
+  const int we = (w + 1) * OPA_WAVE * kPer < nb ? (w + 1) * OPA_WAVE * kPer : nb;
+  const int np = nb - p0 < 0 ? 0 : (nb - p0 < kPer ? nb - p0 : kPer);
+  uint32_t hm = 0, lm = 0;
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
-    const int p = p0 + k;
-    if (p < nb && ((ln == 0 && k == 0) || p == 0 || sg[p] != sg[p - 1])) hm |= 1u << k;
+    const int p = p0 + k, pl = p + o.longrow - 1;
+    if (p < nb && ((ln == 0 && k == 0) || sg[p] != sg[p - 1])) {
+      hm |= 1u << k;
+      if (pl < we && sg[pl] == sg[p]) lm |= 1u << k;
+    }
   }
-  uint32_t nh;
-  const uint32_t h0 = block_excl_scan_add<uint32_t>((uint32_t)__popc(hm), sh, &nh);
-  hx[tid] = (uint16_t)h0;
-  hms[tid] = (uint8_t)hm;
-  if (tid == 0) {
-    hx[kRThreads] = (uint16_t)nh;
-    // room for the block's partials; a block that finds none left adds its
-    // results to the row accumulators
-    uint32_t base = atomicAdd(o.pcount, nh);
-    if (base > o.pcap || nh > o.pcap - base) base = 0xFFFFFFFFu;
-    sbase = base;
+  // is the stretch that goes on at the thread's first position a long one? (it
+  // started at the last row start of the nearest lane below that has one)
+  const unsigned long long hl = __ballot(hm != 0);
+  const unsigned long long ll = __ballot(hm != 0 && lm > (hm >> 1));
+  const unsigned long long below = hl & lanemask_lt();
+  const int from = below ? 63 - __clzll((long long)below) : 0;
+  const bool cont = (ll >> from) & 1ull;
+  uint32_t rm = 0;  // the launches of short stretches
+  {
+    bool lg = cont;
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+      if ((hm >> k) & 1u) lg = (lm >> k) & 1u;
+      if (k < np && !lg) rm |= 1u << k;
+    }
   }
+  uint32_t all;  // partials << 16 | records
+  const uint32_t h0 = block_excl_scan_add<uint32_t>(
+      ((uint32_t)__popc(lm) << 16) | (uint32_t)__popc(rm), sh, &all);
+  hx[tid] = h0;
+  lds.lms[tid] = (uint8_t)lm;
+  lds.rms[tid] = (uint8_t)rm;
   unsigned long long *wslot = slots + (size_t)w * OPA_WAVE * kFFields;
   for (int x = ln; x < OPA_WAVE * kFFields; x += OPA_WAVE) wslot[x] = 0;
   __syncthreads();
-  const uint32_t base = sbase;
-  const bool keep = base != 0xFFFFFFFFu;
-  auto starts_before = [&](uint32_t p) -> uint32_t {  // row starts at positions below p
+  auto kept_before = [&](uint32_t p) -> uint32_t {  // partials << 16 | records of positions below p
     const uint32_t t = p / kPer;
-    return t >= (uint32_t)kRThreads ? nh
-                                    : hx[t] + (uint32_t)__popc(hms[t] & ((1u << (p % kPer)) - 1u));
+    if (t >= (uint32_t)kRThreads) return all;
+    const uint32_t m = (1u << (p % kPer)) - 1u;
+    return hx[t] + ((uint32_t)__popc(lds.lms[t] & m) << 16) + (uint32_t)__popc(lds.rms[t] & m);
   };
   {
-    const uint32_t first = starts_before(p_lo), e = starts_before(p_hi), u = starts_before(p_un);
-    o.bkt[blk * kBktStride + tid] = keep ? (first << 16) | (e - first) : 0u;
+    uint32_t *e = o.bkt + blk * kBktStride;
+    e[tid] = kept_before(p_lo);
     if (tid == 0) {
-      o.bkt[blk * kBktStride + kBuckets] = keep ? (u << 16) | (nh - u) : 0u;
-      o.pbase[blk] = keep ? base : 0u;
+      e[kBuckets] = kept_before(p_un);
+      e[kBuckets + 1] = all;
     }
   }
-  // the lane's launches; kind of a piece: started in an earlier lane (its
-  // slot's lane is the nearest below with a row start), started here
-  const unsigned long long hl = __ballot(hm != 0);
-  const unsigned long long below = hl & lanemask_lt();
-  const int from = below ? 63 - __clzll((long long)below) : 0;
-  const int np = nb - p0 < 0 ? 0 : (nb - p0 < kPer ? nb - p0 : kPer);
+  PartRow *parts = o.parts + blk * o.pcap;
+  uint4 *rec = o.rec + blk * o.rcap + (h0 & 0xFFFFu);
   // the next lane goes on with this lane's last row
   const uint32_t np_n = __shfl_down((uint32_t)np, 1, OPA_WAVE), hm_n = __shfl_down(hm, 1, OPA_WAVE);
   const bool out = ln < OPA_WAVE - 1 && np_n > 0 && (hm_n & 1u) == 0;
-  Acc acc;
+  Acc acc;  // of the long stretch the lane is in, else zero
   acc_zero(acc);
-  bool here = false;  // the piece started in this lane
-  uint32_t hi = h0;   // row starts before the piece
+  bool here = false;       // the stretch started in this lane
+  bool lg = cont;          // it is a long one
+  uint32_t hi = h0 >> 16;  // partials before it
   uint32_t gc = 0;
-  auto flush_inside = [&]() {  // a row that ends in this lane
+  auto flush_inside = [&]() {  // a long stretch that ends in this lane
     if (!here) slot_add(wslot + (size_t)from * kFFields, acc, mx);
-    else if (keep) part_store(o.parts, (size_t)base + hi, gc, acc);
-    else acc_to_table(o.acc, gc, acc, mx);
+    else part_store(parts, hi, gc, acc);
   };
 #pragma unroll 1
   for (int k = 0; k < kPer; ++k) {
     if (k >= np) break;
     if ((hm >> k) & 1u) {
-      if (k > 0) {
+      if (k > 0 && lg) {
         flush_inside();
         acc_zero(acc);
         if (here) ++hi;
       }
       here = true;
+      lg = (lm >> k) & 1u;
       gc = sg[p0 + k];
     }
     const uint2 e = md[p0 + k];
-    acc_launch(acc, in, (int32_t)e.x, e.y, mx, dw);
+    if (lg) acc_launch(acc, in, (int32_t)e.x, e.y, mx, dw);
+    else *rec++ = make_uint4(sg[p0 + k], e.x, e.y, 0u);
   }
-  const bool mine_out = here && out;  // this lane's slot holds a row that goes on
+  const bool mine_out = here && lg && out;  // this lane's slot holds a row that goes on
   // lanes inside one row: where they are many, they are added up across the
   // lanes first (LDS atomics on one address go one after the other), and the
   // last one adds their total to the slot of the lane the row starts in
-  const bool mid = np > 0 && hm == 0;
+  const bool mid = np > 0 && hm == 0 && lg;
   if (__popcll(__ballot(mid)) >= kMidLanes) {
     acc_seg_scan(acc, hm != 0 ? ln : from, mx);
     const bool last = ln == OPA_WAVE - 1 || np_n == 0 || hm_n != 0;
-    if (np > 0 && last) {
+    if (np > 0 && lg && last) {
       if (mid) slot_add(wslot + (size_t)from * kFFields, acc, mx);
       else if (mine_out) slot_add(wslot + (size_t)ln * kFFields, acc, mx);
       else flush_inside();
     }
-  } else if (np > 0) {
+  } else if (np > 0 && lg) {
     if (mine_out) slot_add(wslot + (size_t)ln * kFFields, acc, mx);
     else flush_inside();
   }
@@ -305,25 +350,13 @@ __device__ __forceinline__ void row_order_block(const RowOut &o, const AggIn &in
   for (int x = ln; x < nl * kFFields; x += OPA_WAVE) {
     const int r = x / kFFields, f = x - r * kFFields, s = ord[r];
     const int st = w * OPA_WAVE + s;  // its thread: the slot's row is the thread's last start
-    const uint32_t hs = hms[st];
-    const uint32_t sk = 31u - (uint32_t)__clz((int)hs);
+    const uint32_t ls = lds.lms[st];
+    const uint32_t sk = 31u - (uint32_t)__clz((int)ls);
     const uint32_t row = sg[st * kPer + (int)sk];
-    const uint32_t idx = hx[st] + (uint32_t)__popc(hs) - 1u;
+    const uint32_t idx = (hx[st] >> 16) + (uint32_t)__popc(ls) - 1u;
     const unsigned long long v = wslot[(size_t)s * kFFields + f];
-    if (keep) {
-      unsigned long long *d = reinterpret_cast<unsigned long long *>(o.parts + (size_t)base + idx);
-      d[f] = f < 24 ? v : ((v & 0xFFFFFFFFull) | ((unsigned long long)row << 32));
-    } else {
-      unsigned long long *d = reinterpret_cast<unsigned long long *>(o.acc + row);
-      if (f < 4) {
-        atomicAdd(&d[f], v);
-      } else if (f < 24) {
-        if ((mx >> (f - 4)) & 1u) atomicMax(&d[f], v);
-        else unsafeAtomicAdd(reinterpret_cast<double *>(&d[f]), bits2d(v));
-      } else if ((uint32_t)v) {
-        atomicOr(reinterpret_cast<unsigned int *>(&d[24]), (uint32_t)v);
-      }
-    }
+    reinterpret_cast<unsigned long long *>(parts + idx)[f] =
+        f < 24 ? v : ((v & 0xFFFFFFFFull) | ((unsigned long long)row << 32));
   }
 }
 
@@ -331,26 +364,10 @@ constexpr int kTThreads = 1024;
 constexpr int kTHot = 12;   // lanes of one row above which they are reduced first
 constexpr int kTSegs = 40;  // stretches of lanes of one row up to which they are scanned
 
-// The waves of a block add to its table in turns, so that a row's sums are
-// added up in one order whatever the scheduling: turn r * waves + w is wave w's
-// r-th. A wave that waits for its turn waits for waves of its own block only,
-// which run and end their turns without waiting for later ones. The adds are
-// atomic in any order; a wave's LDS instructions execute in order, so the next
-// wave's come after them without a wait for their completion.
-__device__ __forceinline__ void turn_begin(uint32_t *turn, uint32_t mine) {
-  while (__hip_atomic_load(turn, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != mine) {
-  }
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-__device__ __forceinline__ void turn_end(uint32_t *turn, uint32_t mine) {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  if (lane_id() == 0)
-    __hip_atomic_store(turn, mine + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
 // The thread's kPer consecutive launches (nv of them exist) added to the
-// block's table in LDS; called by the whole block, kPer turns a wave from turn
-// t0 * waves on.
+// block's table in LDS, in turns, so that a row's sums are added up in one
+// order: turn r * waves + w is wave w's r-th. Called by the whole block, kPer
+// turns a wave from turn t0 * waves on.
 template <bool DEF, int kPer>
 __device__ __forceinline__ void tab_add(unsigned long long *tab, uint32_t *turn, uint32_t t0,
                                         const AggIn &in, int nv, int32_t (&mt)[kPer],
@@ -461,10 +478,14 @@ struct CombParams {
   uint32_t rb, G, NOPS;
   uint32_t mx, dw, absent;
   const PartRow *parts;
-  const uint32_t *bkt, *pbase;
-  PartRow *split;              // [kBuckets][kSplits][rb]
+  const uint4 *rec;            // launch records, or NULL: there are none
+  const uint32_t *bkt;
+  uint32_t pcap, rcap;         // of a block (see RowOut)
+  AggIn in;                    // the records' counters
+  PartRow *split;              // [kBuckets][nsplit][rb]
+  int nsplit;                  // shares of the blocks per bucket
   PartRow *hot;                // [kHot] the unattributed row's shares
-  const PartRow *acc;          // [G] row accumulators (the blocks' overflow)
+  const PartRow *acc;          // [G] row accumulators (the run reduction's overflow)
   opattr_op_row *table;
   unsigned long long *part;    // [kBuckets][4] summary sums per bucket
   // the finalisation, by the last block of the per-row reduction to finish
@@ -475,50 +496,96 @@ struct CombParams {
   opattr_summary *sum;
 };
 
-// The partials of a wave's bucket entries (per lane kPre entries: ev partials
-// from xv on, mine in all) added into an LDS table of rb rows, field by field:
-// the partials are listed in LDS and read with 25 lanes each (two per load
-// instruction, kBatch in flight), so that a partial costs two cache lines of
-// requests instead of 25.
-constexpr int kList = 512;                     // partials a combine wave lists in LDS at once
-constexpr int kBatch = 8;                      // partial loads per lane in flight
-template <int kPre>
-__device__ __forceinline__ void comb_add(unsigned long long *tab, uint32_t *list,
-                                         const unsigned long long *parts64,
-                                         const uint32_t (&ev)[kPre], const uint32_t (&xv)[kPre],
-                                         uint32_t mine, uint32_t rb, uint32_t mx) {
-  const int ln = lane_id(), half = ln >> 5, f = ln & 31;
+// kEntries partials (kRec: launch records), a half wave each, added into an LDS
+// table of rb rows field by field: 25 lanes read the fields of one, so that it
+// costs two cache lines of requests instead of 25, and kBatch of them are in
+// flight. at(j) gives the place of the half's j-th entry, or -1.
+constexpr int kList = 512;                     // entries a combine wave lists in LDS at once
+constexpr int kBatch = 8;                      // loads per lane in flight
+template <bool kRec, int kN, typename At>
+__device__ __forceinline__ void comb_batch(unsigned long long *tab, uint32_t rb, const CombParams &a,
+                                           At at, uint32_t mx, uint32_t dw) {
+  const int ln = lane_id(), f = ln & 31;
+  if constexpr (!kRec) {
+    const unsigned long long *parts64 = reinterpret_cast<const unsigned long long *>(a.parts);
+    unsigned long long v[kN];
+    bool ok[kN];
+#pragma unroll
+    for (int j = 0; j < kN; ++j) {
+      const int64_t x = at(j);
+      ok[j] = x >= 0 && f < kFFields;
+      v[j] = ok[j] ? parts64[(size_t)x * (sizeof(PartRow) / 8) + f] : 0ull;
+    }
+#pragma unroll
+    for (int j = 0; j < kN; ++j) {
+      const uint32_t g = (uint32_t)(__shfl(v[j], (ln & 32) + 24, OPA_WAVE) >> 32);
+      if (ok[j]) field_add(tab + (size_t)(g % rb) * kFFields + f, f, v[j], mx);
+    }
+  } else {
+    uint4 r[kN];
+    float v[kN];
+    bool ok[kN], hit[kN];
+    const int c = f - 4;
+#pragma unroll
+    for (int j = 0; j < kN; ++j) {
+      const int64_t x = at(j);
+      ok[j] = x >= 0;
+      r[j] = ok[j] ? a.rec[x] : make_uint4(0u, 0xFFFFFFFFu, 0u, 0u);
+    }
+#pragma unroll
+    for (int j = 0; j < kN; ++j) {
+      const int32_t m = (int32_t)r[j].y;
+      hit[j] = m >= 0 && (int64_t)m < a.in.P;
+      v[j] = hit[j] && c >= 0 && c < OPATTR_NUM_COUNTERS
+                 ? a.in.counters[(int64_t)m * a.in.rs + (int64_t)c * a.in.cs] : 0.0f;
+    }
+#pragma unroll
+    for (int j = 0; j < kN; ++j) {
+      if (!ok[j] || f >= kFFields - 1) continue;
+      unsigned long long *t = tab + (size_t)(r[j].x % rb) * kFFields + f;
+      if (c < 0) {
+        const unsigned long long d = (f & 1) ? r[j].z : 1u;
+        if (f < 2 || hit[j]) atomicAdd(t, d);
+      } else if (hit[j]) {
+        if ((mx >> c) & 1u) {
+          atomicMax(t, (unsigned long long)f2key(v[j]));
+          if (v[j] != v[j]) atomicOr(reinterpret_cast<unsigned int *>(t - f + 24), 1u << c);
+        } else {
+          const double x = (double)v[j];  // as acc_launch
+          unsafeAtomicAdd(reinterpret_cast<double *>(t), ((dw >> c) & 1u) ? x * (double)r[j].z : x);
+        }
+      }
+    }
+  }
+}
+
+// The entries of a wave's blocks in a bucket (per lane kPre blocks: ev entries
+// from xv on, mine in all) added into an LDS table: listed in LDS, then kBatch
+// of each half wave at a time.
+template <bool kRec, int kPre>
+__device__ __forceinline__ void comb_add(unsigned long long *tab, uint32_t rb, uint32_t *list,
+                                         const CombParams &a, const uint32_t (&ev)[kPre],
+                                         const uint32_t (&xv)[kPre], uint32_t mine, uint32_t mx,
+                                         uint32_t dw) {
+  const int half = lane_id() >> 5;
   const uint32_t incl = wave_incl_scan_add<uint32_t>(mine);
   const uint32_t n = __shfl(incl, OPA_WAVE - 1, OPA_WAVE);
   if (n == 0) return;
   if (n <= (uint32_t)kList) {
-    // the partials listed in LDS, then read by 25 lanes each (two
-    // partials per instruction, kBatch instructions in flight) and added
-    // field by field
     uint32_t w = incl - mine;
 #pragma unroll
     for (int k = 0; k < kPre; ++k) {
       for (uint32_t p = 0; p < ev[k]; ++p) list[w++] = xv[k] + p;
     }
     wave_sync_lds();
-    for (uint32_t i = 0; i < n; i += 2 * kBatch) {
-      unsigned long long v[kBatch];
-#pragma unroll
-      for (int j = 0; j < kBatch; ++j) {
+    for (uint32_t i = 0; i < n; i += 2 * kBatch)
+      comb_batch<kRec, kBatch>(tab, rb, a, [&](int j) -> int64_t {
         const uint32_t idx = i + 2 * j + half;
-        v[j] = (idx < n && f < kFFields)
-                   ? parts64[(size_t)list[idx] * (sizeof(PartRow) / 8) + f] : 0ull;
-      }
-#pragma unroll
-      for (int j = 0; j < kBatch; ++j) {
-        const uint32_t g = (uint32_t)(__shfl(v[j], (ln & 32) + 24, OPA_WAVE) >> 32);
-        const uint32_t idx = i + 2 * j + half;
-        if (idx < n && f < kFFields) field_add(tab + (size_t)(g % rb) * kFFields + f, f, v[j], mx);
-      }
-    }
+        return idx < n ? (int64_t)list[idx] : -1;
+      }, mx, dw);
+    wave_sync_lds();  // the list is free again
   } else {
-    // more partials than the list holds (rare): one lane's entry at a
-    // time, its partials read two at a time by 25 lanes each
+    // more than the list holds: one lane's blocks at a time
 #pragma unroll 1
     for (int k = 0; k < kPre; ++k) {
       uint32_t e = 0, xe = 0;
@@ -530,17 +597,48 @@ __device__ __forceinline__ void comb_add(unsigned long long *tab, uint32_t *list
       for (uint64_t m = __ballot(e != 0); m; m &= m - 1) {
         const int src = __ffsll((unsigned long long)m) - 1;
         const uint32_t c = __shfl(e, src, OPA_WAVE);
-        const uint64_t x0 = __shfl(xe, src, OPA_WAVE);
-        for (uint32_t p = 0; p < c; p += 2) {
-          const uint32_t pp = p + half;
-          const unsigned long long v = (pp < c && f < kFFields)
-              ? parts64[(x0 + pp) * (sizeof(PartRow) / 8) + f] : 0ull;
-          const uint32_t g = (uint32_t)(__shfl(v, (ln & 32) + 24, OPA_WAVE) >> 32);
-          if (pp < c && f < kFFields) field_add(tab + (size_t)(g % rb) * kFFields + f, f, v, mx);
-        }
+        const uint32_t x0 = __shfl(xe, src, OPA_WAVE);
+        for (uint32_t p = 0; p < c; p += 4)
+          comb_batch<kRec, 2>(tab, rb, a, [&](int j) -> int64_t {
+            const uint32_t pp = p + 2 * j + half;
+            return pp < c ? (int64_t)(x0 + pp) : -1;
+          }, mx, dw);
       }
     }
   }
+}
+
+// A wave adds the partials and records of bucket q in the blocks b0 + lane + 64 k.
+template <int kPre>
+__device__ __forceinline__ void comb_blocks(unsigned long long *tab, uint32_t rb, uint32_t *list,
+                                            const CombParams &a, uint32_t q, int64_t b0,
+                                            int64_t b_hi, uint32_t mx, uint32_t dw) {
+  uint32_t e0[kPre], e1[kPre], ev[kPre], xv[kPre], mine = 0;
+#pragma unroll
+  for (int k = 0; k < kPre; ++k) {
+    const int64_t b = b0 + lane_id() + (int64_t)OPA_WAVE * k;
+    const uint32_t *e = a.bkt + b * kBktStride + q;
+    e0[k] = b < b_hi ? e[0] : 0u;
+    e1[k] = b < b_hi ? e[1] : 0u;
+  }
+#pragma unroll
+  for (int k = 0; k < kPre; ++k) {
+    const int64_t b = b0 + lane_id() + (int64_t)OPA_WAVE * k;
+    ev[k] = (e1[k] >> 16) - (e0[k] >> 16);
+    xv[k] = (uint32_t)b * a.pcap + (e0[k] >> 16);
+    mine += ev[k];
+  }
+  comb_add<false, kPre>(tab, rb, list, a, ev, xv, mine, mx, dw);
+  if (!a.rec) return;
+  mine = 0;
+#pragma unroll
+  for (int k = 0; k < kPre; ++k) {
+    const int64_t b = b0 + lane_id() + (int64_t)OPA_WAVE * k;
+    ev[k] = (e1[k] & 0xFFFFu) - (e0[k] & 0xFFFFu);
+    xv[k] = (uint32_t)b * a.rcap + (e0[k] & 0xFFFFu);
+    mine += ev[k];
+  }
+  comb_add<true, kPre>(tab, rb, list, a, ev, xv, mine, mx, dw);
 }
 
 // The blocks' tables added up, kTRows rows a block (one element per thread

@@ -33,7 +33,8 @@ def _setup():
 def _run(tr, flags=HINTS, **kw):
     import torch
 
-    out = opattr.opattr_attribute(opattr.to_device(tr, DEV), flags=flags, raise_strict=False, **kw)
+    dt = opattr.to_device(tr, DEV) if isinstance(tr["seq"], np.ndarray) else tr
+    out = opattr.opattr_attribute(dt, flags=flags, raise_strict=False, **kw)
     torch.cuda.synchronize()
     return out, opattr.read_diag(out["diag"])
 
@@ -277,8 +278,8 @@ def test_permuted_launches(T, S, kinds, dense):
 @pytest.mark.parametrize("kinds", [False, True])
 def test_row_order_more_partials_than_room(kinds):
     """Query points that jump back and forth change the innermost range far
-    more often than the ranges' starts and ends: the partials past the room
-    for them go to the row accumulators."""
+    more often than the ranges' starts and ends: far more short stretches than
+    ranges, kept as launch records."""
     rng = np.random.default_rng(5)
     T, R = 120_000, 400
     tr = _regular_trace(T=T, run=T // R, n_ops=900, cycle=R, seed=93)
@@ -288,6 +289,38 @@ def test_row_order_more_partials_than_room(kinds):
     print(f"case row order overflow T={T} R={R} kinds={kinds}", flush=True)
     want = O.attribute(tr, **kw)
     out, diag = _run(tr, **kw)
+    parity.assert_attribute(out, want, diag)
+
+
+@pytest.mark.parametrize("T,n_names,kinds,cols", [
+    (700, 7, False, False), (40_000, 7, False, True), (40_000, 2100, True, False),
+    (300_000, 7, True, False), (2 ** 20 + 700, 7, False, False)])
+def test_row_order_short_and_long_stretches(T, n_names, kinds, cols):
+    """Operators of one to six launches in a block, beside one that holds half of
+    its launches and unattributed ones: stretches on both sides of the length
+    from which a block adds them up itself, and more launch records of one
+    bucket than a combine wave lists at once (64 operators of one bucket, each
+    a few times in every block), with NaN counters."""
+    rng = np.random.default_rng(T)
+    tr = _regular_trace(T=T, run=1, n_ops=16383, cycle=1, seed=94)
+    tr["name_id"] = (np.arange(T) % n_names).astype(np.uint32)
+    tr["pf_name"], tr["n_names"] = tr["name_id"].copy(), n_names
+    u = rng.random(T)
+    op = np.where(u < 0.5, 5000, np.where(u < 0.85, rng.integers(0, 64, T),
+                                          rng.integers(0, 16383, T)))
+    keep = rng.random(T) > 0.05
+    for f in ("r_start", "r_end", "r_stream"):
+        tr[f] = tr[f][keep]
+    tr["r_op"] = op[keep].astype(np.uint32)
+    tr["counters"][::971, 5] = np.nan
+    tr["counters"][::973, 19] = np.nan
+    kw = dict(agg_kind=np.array([(c * 7 + 1) % 3 for c in range(20)], np.uint8)) if kinds else {}
+    print(f"case row order stretches T={T} names={n_names} kinds={kinds} cols={cols}", flush=True)
+    want = O.attribute(tr, **kw)
+    dt = opattr.to_device(tr, DEV)
+    if cols:
+        dt["counters"] = dt["counters"].t().contiguous().t()
+    out, diag = _run(dt, **kw)
     parity.assert_attribute(out, want, diag)
 
 

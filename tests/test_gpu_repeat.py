@@ -66,3 +66,18 @@ def test_table_in_lds_repeats(T, R, n_ops, order, kind):
     print(f"case repeat table T={T} R={R} ops={n_ops} {order}", flush=True)
     tr, flags = _trace(9700 + T % 97, T, R, n_ops, order)
     _assert_repeats(tr, flags, **({} if kind is None else {"agg_kind": kind}))
+
+
+@pytest.mark.parametrize("T,R,n_ops,order,kind", [
+    (10_000, 6_000, 5_000, "stream", None),       # two launches a lane
+    (200_000, 120_000, 5_000, "gaps", None),
+    (400_000, 100_000, 2_000, "dense", MIXED),    # four
+    (300_000, 2_000, 1_500, "dense", None),       # few ranges: the rows change with the streams
+    (1_100_000, 300_000, 3_000, "stream", None),  # eight, more than the compact path takes
+])
+def test_rows_ordered_in_blocks_repeat(T, R, n_ops, order, kind):
+    """Launches ordered by operator row in each block: the waves rank theirs in
+    turns, and what a block keeps does not depend on the others."""
+    print(f"case repeat rows T={T} R={R} ops={n_ops} {order}", flush=True)
+    tr, flags = _trace(9800 + T % 97, T, R, n_ops, order)
+    _assert_repeats(tr, flags, **({} if kind is None else {"agg_kind": kind}))
