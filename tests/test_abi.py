@@ -130,6 +130,14 @@ def test_workspace_of_row_ordered_calls(lib, T, R, NN, NS, NOPS, flags, before):
     assert mib <= before + (more * T + 17 * 200 * NOPS) / 2 ** 20 + 6, mib
 
 
+def test_workspace_of_few_launches_over_many_rows(lib):
+    """The combine's shares go by the launches as well as by the rows: 20,000
+    launches over 15,000 rows, with more names than the compact path takes, needed
+    52 MiB when it always had sixteen (2.3 MiB by the general aggregation)."""
+    k, p, r, d = _structs(T=20_000, P=20_000, R=15_000, NN=3000, NS=4, NOPS=14_999, flags=7)
+    assert lib.opattr_workspace_bytes(C.byref(k), C.byref(p), C.byref(r), C.byref(d)) < 14 << 20
+
+
 def test_argument_errors_return_before_any_device_work(lib):
     k, p, r, d = _structs()
     fake = C.c_void_p(0x1000)
