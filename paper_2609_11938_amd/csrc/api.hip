@@ -178,7 +178,12 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
   // (2M launches with 20k ranges and 200 rows take 201 us
   // reduced in place and 203 us by row tables; 1M with 250k ranges 625 us in
   // place, 185 us ordered by row and 161 us by row tables)
-  if (mode != PlanMode::kPlain && !(long_runs && pl.T > kFusedShort)) {
+  // The in-place reduction adds what a wave cannot keep by device atomics, in
+  // another order on each run; launches with gaps in seq, whose general path
+  // adds in one order, are ordered by row whatever their runs (2M shuffled with
+  // 100k ranges and 1,001 rows 547 us in place, 570 us so, 720 us by the general
+  // path; 4M 1017, 1071 and 1330 us).
+  if (mode != PlanMode::kPlain && !(long_runs && pl.T > kFusedShort && pl.seq_dense)) {
     // launches per lane: as few as leave no CU without a block, up to the
     // point where more blocks only write more partials
     pl.fper = pl.T <= (1 << 18) ? 2 : pl.T <= (1 << 20) ? 4 : 8;
@@ -194,8 +199,10 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
   // us, 1M with 600k ranges 204, 236 and 314 us, 2M with 400k ranges 272, 277
   // and 307 us, 500k shuffled over 1,001 rows 193, 193 and 200 us. Two for short
   // lists (1M: 117 MB, 72 MB more than the general aggregation's arrays), four
-  // for longer ones and launches that need the view's arrays as well.
-  pl.flong = mode == PlanMode::kLean ? 8 : pl.compact && sm_hint ? 2 : 4;
+  // for longer ones and launches that need the view's arrays as well, eight
+  // where the runs are long (4M with 100k ranges 1072 us at four and at eight).
+  pl.flong = mode == PlanMode::kLean || (!pl.compact && long_runs) ? 8
+             : pl.compact && sm_hint ? 2 : 4;
   // A thousand blocks of the run reduction run at once (four waves a SIMD by
   // registers): up to 4M launches, eight launches a lane make less than two
   // rounds of blocks, half of them idle in the last (2M: 58 us at eight, 50 at
