@@ -799,11 +799,7 @@ __global__ void __launch_bounds__(kCRowThreads) k_c_rows(CombParams a) {
     unsigned long long v[2 * kCRowWaves];
 #pragma unroll
     for (int k = 0; k < 2 * kCRowWaves; ++k) v[k] = k < copies ? tab[(size_t)k * ne + x] : 0ull;
-#pragma unroll
-    for (int o = kCRowWaves; o > 0; o >>= 1)
-#pragma unroll
-      for (int k = 0; k < o; ++k) v[k] = merge_field(f, v[k], v[k + o], mx);
-    tab[x] = v[0];  // only this thread reads element x of a copy
+    tab[x] = merge_tree(f, v, mx);  // only this thread reads element x of a copy
   }
   __syncthreads();
   for (uint32_t x = tid; x < nr * 24u; x += kCRowThreads) {

@@ -603,20 +603,18 @@ __global__ void __launch_bounds__(256) k_f_rows(CombParams a) {
     const unsigned long long *sp =
         reinterpret_cast<const unsigned long long *>(a.split + (size_t)q * a.nsplit * rb) +
         (size_t)rr * (sizeof(PartRow) / 8) + ff;
-    unsigned long long y[kSplits + 1];
-    y[kSplits] = g < a.G ? reinterpret_cast<const unsigned long long *>(a.acc + g)[ff] : 0ull;
+    const unsigned long long ac =
+        g < a.G ? reinterpret_cast<const unsigned long long *>(a.acc + g)[ff] : 0ull;
+    unsigned long long y[kSplits];
 #pragma unroll
     for (int k = 0; k < kSplits; ++k)
       y[k] = k < a.nsplit ? sp[(size_t)k * rb * (sizeof(PartRow) / 8)] : 0ull;
-    unsigned long long v = y[kSplits];
-#pragma unroll
-    for (int k = 0; k < kSplits; ++k) v = merge_field((int)ff, v, y[k], mx);
+    unsigned long long v = merge_field((int)ff, ac, merge_tree((int)ff, y, mx), mx);
     if (g == a.NOPS) {  // the unattributed row's own shares, loads in flight together
       unsigned long long hv[kHot];
 #pragma unroll
       for (int h = 0; h < kHot; ++h) hv[h] = reinterpret_cast<const unsigned long long *>(a.hot + h)[ff];
-#pragma unroll
-      for (int h = 0; h < kHot; ++h) v = merge_field((int)ff, v, hv[h], mx);
+      v = merge_field((int)ff, v, merge_tree((int)ff, hv, mx), mx);
     }
     tab[x] = v;
   }

@@ -446,6 +446,19 @@ __device__ __forceinline__ unsigned long long merge_field(int f, unsigned long l
   return x | y;
 }
 
+// field f of kN (a power of two) partial results added up in pairs, so that a
+// sum takes log2(kN) roundings and not one after the other
+template <int kN>
+__device__ __forceinline__ unsigned long long merge_tree(int f, unsigned long long (&v)[kN],
+                                                         uint32_t mx) {
+  static_assert((kN & (kN - 1)) == 0, "pairs");
+#pragma unroll
+  for (int o = kN / 2; o > 0; o >>= 1)
+#pragma unroll
+    for (int k = 0; k < o; ++k) v[k] = merge_field(f, v[k], v[k + o], mx);
+  return v[0];
+}
+
 // output field o (four counts, then the counters) of a row from its 25
 // accumulated fields p
 __device__ __forceinline__ unsigned long long row_field(const unsigned long long *p, int o,
@@ -673,18 +686,17 @@ __global__ void __launch_bounds__(1024) k_t_rows(CombParams a, const unsigned lo
         const int t = t0 + j * kTShares;
         y[j] = t < ntabs ? tabs[(size_t)t * ne + x] : 0ull;
       }
-#pragma unroll
-      for (int j = 0; j < kB; ++j)
-        if (t0 + j * kTShares < ntabs) v = merge_field(f, v, y[j], mx);
+      v = merge_field(f, v, merge_tree(f, y, mx), mx);
     }
     part[sh][e] = v;
   }
   __syncthreads();
   if (tid < kEl && x < ne) {
-    unsigned long long v = part[0][tid];
+    unsigned long long y[16];
+    static_assert(kTShares <= 16, "all shares");
 #pragma unroll
-    for (int s = 1; s < kTShares; ++s) v = merge_field(f, v, part[s][tid], mx);
-    part[0][tid] = v;
+    for (int s = 0; s < 16; ++s) y[s] = s < kTShares ? part[s][tid] : 0ull;
+    part[0][tid] = merge_tree(f, y, mx);
   }
   __syncthreads();
   // 24 output fields a row

@@ -457,3 +457,40 @@ def test_compact_row_sums_precision(n_ops):
             continue
         ref = c[:, k].sum() if k in (0, 1, 2, 10, 14, 18) else (c[:, k] * d).sum() / d.sum()
         assert abs(row["value"][k] - ref) <= 8.9e-16 * ref, (k, row["value"][k], ref)
+
+
+@pytest.mark.parametrize("T,run,n_ops,cover", [
+    (1_000_000, 4, 500, 1.0),            # tables in LDS
+    (2 ** 20 + 50_000, 5, 600, 1.0),     # more launches than the compact path takes
+    (2 ** 20 + 50_000, 40, 5000, 0.1)])  # unattributed launches: 32 shares of their row
+def test_table_rounding(T, run, n_ops, cover):
+    """The relative errors of duration-weighted means against extended precision,
+    root mean square: a rounding of a value leaves 0.42 * 2^-53 = 4.7e-17; the
+    division leaves one, a sum in pairs one in its last step, half the
+    variance in the one before, and so on, together sqrt 3 times that, sqrt 4.5
+    = 1.0e-16 with the steps inside the blocks. One after the other, the last
+    ten partial results leave 1.1e-16 and 32 of them 1.6e-16."""
+    tr = _regular_trace(T, run, n_ops, n_ops, seed=32)
+    rng = np.random.default_rng(7)
+    tr["r_op"] = rng.integers(0, n_ops, tr["r_op"].size).astype(np.uint32)
+    keep = rng.random(tr["r_start"].size) < cover
+    for f in ("r_start", "r_end", "r_stream", "r_op"):
+        tr[f] = tr[f][keep]
+    # products of 48 bits, so that their sums are not exact
+    tr["dur_ns"] = rng.integers(2 ** 20, 2 ** 24, size=T).astype(np.uint32)
+    tr["counters"] = np.exp(rng.standard_normal((T, 20), dtype=np.float32))
+    print(f"case table rounding T={T} n_ops={n_ops} cover={cover}", flush=True)
+    out, diag = _run(tr, agg_kind=np.full(20, opattr.AGG_DWMEAN, np.uint8))
+    assert diag["status"] == 0 and np.array_equal(parity.host(out["match"]), tr["seq"])
+    rid = parity.host(out["range_id"])
+    op = np.where(rid < 0, n_ops, tr["r_op"][np.maximum(rid, 0)]).astype(np.int64)
+    order = np.argsort(op, kind="stable")
+    if cover < 1:  # the unattributed row
+        order = order[op[order] == n_ops]
+    first = np.flatnonzero(np.diff(op[order], prepend=-1))
+    got = out.table_host()["value"][op[order][first]].astype(np.longdouble)
+    d = tr["dur_ns"][order].astype(np.longdouble)[:, None]
+    want = (np.add.reduceat(tr["counters"][order] * d, first) / np.add.reduceat(d, first))
+    rms = float(np.sqrt((((got - want) / want) ** 2).mean()))
+    print(f"error {rms:.2e}", flush=True)
+    assert rms <= 1.0e-16
