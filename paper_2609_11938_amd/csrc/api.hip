@@ -197,12 +197,11 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
   // flong + 16 bytes a launch, where the general aggregation's arrays take
   // about 40. The call at 2, 4 and 8: 96k over 5,014 rows 60.0, 64.8 and 69.7
   // us, 1M with 600k ranges 204, 236 and 314 us, 2M with 400k ranges 272, 277
-  // and 307 us, 500k shuffled over 1,001 rows 193, 193 and 200 us. Two for short
-  // lists (1M: 117 MB, 72 MB more than the general aggregation's arrays), four
-  // for longer ones and launches that need the view's arrays as well, eight
-  // where the runs are long (4M with 100k ranges 1072 us at four and at eight).
-  pl.flong = mode == PlanMode::kLean || (!pl.compact && long_runs) ? 8
-             : pl.compact && sm_hint ? 2 : 4;
+  // and 307 us; where the runs are long, 4M with 100k ranges 1072 us at four and
+  // at eight. Two for short lists in which most stretches are short (1M: 117 MB,
+  // 72 MB more than the general aggregation's arrays).
+  const bool short_runs = pl.R * 4 > pl.T && pl.compact && sm_hint;
+  pl.flong = mode == PlanMode::kLean || long_runs ? 8 : short_runs ? 2 : 4;
   // A thousand blocks of the run reduction run at once (four waves a SIMD by
   // registers): up to 4M launches, eight launches a lane make less than two
   // rounds of blocks, half of them idle in the last (2M: 58 us at eight, 50 at

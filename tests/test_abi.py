@@ -114,19 +114,20 @@ def test_workspace_for_all_inputs_covers_every_entry_point(lib):
 
 
 @pytest.mark.parametrize("T,R,NN,NS,NOPS,flags,before", [
+    (500_000, 25_000, 40, 4, 899, 7, 29.4), (500_000, 25_000, 40, 4, 899, 0, 34.8),
     (96_000, 62_800, 60, 4, 5014, 7, 7.2), (1_000_000, 600_000, 100, 8, 5000, 7, 69.5),
     (1_000_000, 600_000, 100, 8, 5000, 0, 112.4), (2_000_000, 400_000, 100, 8, 5000, 7, 118.1),
     (4_000_000, 2_000_000, 100, 8, 15_999, 7, 306.5),
     (10_000_000, 5_000_000, 100, 8, 15_999, 7, 763.2)])
 def test_workspace_of_row_ordered_calls(lib, T, R, NN, NS, NOPS, flags, before):
     """Blocks that order their launches by operator row keep 200 / 4 + 16 bytes a
-    launch (200 / 2 + 16 for at most 2^20 stream-major ones), however many
-    ranges there are, in the place of the general aggregation's arrays (about
+    launch (200 / 2 + 16 for at most 2^20 stream-major ones with a range for every
+    four, 200 / 8 + 16 for all with one for every sixteen), in the place of the general aggregation's arrays (about
     40 bytes), and the combine sixteen shares of 200 bytes a row; MiB before: of
     the general aggregation alone."""
     k, p, r, d = _structs(T=T, P=min(T, 400_000), R=R, NN=NN, NS=NS, NOPS=NOPS, flags=flags)
     mib = lib.opattr_workspace_bytes(C.byref(k), C.byref(p), C.byref(r), C.byref(d)) / 2 ** 20
-    more = 76 if flags and T <= 2 ** 20 else 26
+    more = 2 if R * 16 <= T else 76 if flags and T <= 2 ** 20 else 26
     assert mib <= before + (more * T + 17 * 200 * NOPS) / 2 ** 20 + 6, mib
 
 
