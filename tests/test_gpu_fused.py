@@ -1,8 +1,10 @@
-"""Parity of the fused attribution path (kernels stream-major with dense
-seq, at most one range per 16 launches, at most 16384 operator rows): the
-matching stops at the eligible launches, one pass resolves every launch's
-match with the dedup broadcast, one pass reduces the runs of launches of one
-operator row (block partials sorted by row bucket, then added per bucket).
+"""Parity of opattr_attribute's paths of at most 16384 operator rows: the
+compact path (up to 2^20 launches), and the fused path (stream-major launches
+with dense seq, or permuted into that order), where the matching stops at the
+eligible launches, one pass resolves every launch's match with the dedup
+broadcast, and one reduces the launches by operator row: runs in place (long
+lists with few ranges; block partials sorted by row bucket, then added per
+bucket), launches ordered by row in each block, or a table in LDS.
 
 Random traces with ties, partitions, drops, extra profiled rows, range kinds
 and non-default aggregation kinds, sized so that some blocks hold more runs
@@ -12,6 +14,7 @@ import pytest
 
 import cases
 import parity
+import paths
 from oracle import oracle as O
 from paper_2609_11938_amd import opattr, tracegen as tg
 
@@ -30,10 +33,12 @@ def _setup():
     O.build(force=False)
 
 
-def _run(tr, flags=HINTS, **kw):
+def _run(tr, flags=HINTS, path=None, **kw):
     import torch
 
     dt = opattr.to_device(tr, DEV) if isinstance(tr["seq"], np.ndarray) else tr
+    if path:  # the path the test is meant for
+        assert paths.attribute(dt, flags, **kw) == path
     out = opattr.opattr_attribute(dt, flags=flags, raise_strict=False, **kw)
     torch.cuda.synchronize()
     return out, opattr.read_diag(out["diag"])
@@ -41,7 +46,20 @@ def _run(tr, flags=HINTS, **kw):
 
 @pytest.mark.parametrize("seed", range(16))
 def test_fused_random(seed):
+    """Compact, or fused in the seeds with range kinds."""
     T = 20_000 + 1777 * seed
+    _random(seed, T, "fused" if seed % 5 == 3 else "compact")
+
+
+@pytest.mark.parametrize("seed", [0, 2, 3, 7])
+def test_run_reduction_random(seed):
+    """The same from the launch count on from which runs are reduced in place:
+    duplicate layers and extra rows, absent counters, range and aggregation
+    kinds."""
+    _random(seed, paths.LONG + 1777 * seed, "fused")
+
+
+def _random(seed, T, path):
     tr = cases.random_trace(5000 + seed, T=T, S=1 + seed % 6, n_names=7 + 3 * seed,
                             R=T // (17 + 7 * (seed % 4)), n_ops=13 + 50 * seed,
                             t_max=T * (3 + seed % 5), max_depth=1 + seed % 7,
@@ -57,7 +75,7 @@ def test_fused_random(seed):
         kw["absent_mask"] = (1 << 5) | (1 << 17)
     print(f"case fused seed={seed} T={T} R={tr['r_start'].size} G={tr['n_ops'] + 1}", flush=True)
     want = O.attribute(tr, **kw)
-    out, diag = _run(tr, **kw)
+    out, diag = _run(tr, path=path, **kw)
     parity.assert_attribute(out, want, diag)
 
 
@@ -92,46 +110,49 @@ def _regular_trace(T, run, n_ops, cycle, seed, with_ranges=True, NC=20):
                 part_rep=None, n_names=7, n_streams=1, n_ops=n_ops, n_parts=0)
 
 
-def test_fused_combine_list_overflow():
+@pytest.mark.parametrize("T,path", [(400_000, "compact"), (paths.LONG, "fused")])
+def test_fused_combine_list_overflow(T, path):
     """More partial results for one bucket of operator rows in a combine
     wave's round than its LDS list holds: 64 operators of one bucket, each in
     every block, over more blocks than one round lists (the per-entry path)."""
-    tr = _regular_trace(T=400_000, run=32, n_ops=16383, cycle=64, seed=91)
+    tr = _regular_trace(T=T, run=32, n_ops=16383, cycle=64, seed=91)
     print(f"case combine overflow T={tr['seq'].size} R={tr['r_start'].size}", flush=True)
     want = O.attribute(tr)
-    out, diag = _run(tr)
+    out, diag = _run(tr, path=path)
     parity.assert_attribute(out, want, diag)
 
 
 @pytest.mark.parametrize("with_ranges", [False, True])
-def test_fused_unattributed(with_ranges):
+@pytest.mark.parametrize("T,path", [(300_000, "compact"), (paths.LONG, "fused")])
+def test_fused_unattributed(with_ranges, T, path):
     """No ranges at all (every launch in the unattributed row, which has a
     partial in every block and combine waves of its own), and ranges whose
     operator rows all fall in the unattributed row's bucket."""
-    tr = _regular_trace(T=300_000, run=40, n_ops=3, cycle=3, seed=92, with_ranges=with_ranges)
-    print(f"case unattributed ranges={with_ranges}", flush=True)
+    tr = _regular_trace(T=T, run=40, n_ops=3, cycle=3, seed=92, with_ranges=with_ranges)
+    print(f"case unattributed T={T} ranges={with_ranges}", flush=True)
     want = O.attribute(tr)
-    out, diag = _run(tr)
+    out, diag = _run(tr, path=path)
     parity.assert_attribute(out, want, diag)
 
 
+@pytest.mark.parametrize("n_names", [9, paths.COMPACT_NAMES + 1])  # compact, or its own kernels
 @pytest.mark.parametrize("T,per_range,n_ops,S", [
     (1, 1, 1, 1), (511, 2, 16383, 1), (512, 3, 2, 2), (513, 2, 700, 3),
     (2 ** 18 + 1, 2, 5000, 4), (2 ** 20 + 1, 3, 900, 5),  # four, eight launches a lane
     (1023, 2, 703, 2), (1025, 2, 704, 2),                  # the largest table in LDS, one row more
     (2 ** 18 + 1, 40, 703, 3), (2 ** 19 + 1, 2, 50, 2), (2 ** 20 + 1, 5, 300, 4),
 ])
-def test_row_order_edges(T, per_range, n_ops, S):
+def test_row_order_edges(T, per_range, n_ops, S, n_names):
     """Launches ordered by operator row inside each block, or added to a
     table in LDS: block, wave and lane edges, one launch, the widest row
     table, the sizes at which the launches per lane change; rows inside a
     lane, across lanes and waves."""
-    tr = cases.random_trace(6000 + T % 977, T=T, S=S, n_names=9, R=max(1, T // per_range),
+    tr = cases.random_trace(6000 + T % 977, T=T, S=S, n_names=n_names, R=max(1, T // per_range),
                             n_ops=n_ops, t_max=4 * T + 8, max_depth=4)
     tr, _, _ = cases.stream_major(tr)
-    print(f"case row order T={T} R={tr['r_start'].size} G={n_ops + 1}", flush=True)
+    print(f"case row order T={T} R={tr['r_start'].size} G={n_ops + 1} names={n_names}", flush=True)
     want = O.attribute(tr)
-    out, diag = _run(tr)
+    out, diag = _run(tr, path="compact" if n_names == 9 and T <= paths.COMPACT_MAX else "fused")
     parity.assert_attribute(out, want, diag)
 
 
@@ -271,7 +292,7 @@ def test_permuted_launches(T, S, kinds, dense):
         tr["stream_id"][::701] = 63 + np.arange(len(range(0, T, 701))) % 3
     print(f"case permuted T={T} S={S} kinds={kinds} dense={dense}", flush=True)
     want = O.attribute(tr)
-    out, diag = _run(tr, flags=opattr.SEQ_DENSE if dense else 0)
+    out, diag = _run(tr, flags=opattr.SEQ_DENSE if dense else 0, path="permuted")
     parity.assert_attribute(out, want, diag)
 
 
@@ -324,11 +345,12 @@ def test_row_order_short_and_long_stretches(T, n_names, kinds, cols):
     parity.assert_attribute(out, want, diag)
 
 
-def test_fused_dedup_errors():
+@pytest.mark.parametrize("T,path", [(30_000, "compact"), (paths.LONG, "fused")])
+def test_fused_dedup_errors(T, path):
     """Duplicates whose representative is shorter or has another name at a
     position, and a partition split in two: the same dedup errors, statuses
     and outputs as the oracle."""
-    tr = cases.random_trace(4711, T=30_000, S=3, n_names=9, R=1_200, n_ops=40, t_max=90_000,
+    tr = cases.random_trace(4711, T=T, S=3, n_names=9, R=T // 25, n_ops=40, t_max=3 * T,
                             max_depth=4, dedup=True)
     tr, _, _ = cases.stream_major(tr)
     part = tr["part_id"].copy()
@@ -340,7 +362,7 @@ def test_fused_dedup_errors():
     names[order[dup[5::97]]] = (names[order[dup[5::97]]] + 1) % tr["n_names"]
     t = dict(tr, name_id=names)
     want = O.attribute(t)
-    out, diag = _run(t)
+    out, diag = _run(t, path=path)
     assert want["diag"]["dedup_errors"] > 0
     parity.assert_attribute(out, want, diag)
     # a hole in one partition
@@ -351,23 +373,24 @@ def test_fused_dedup_errors():
     part2[order] = ps2
     t2 = dict(tr, part_id=part2)
     want2 = O.attribute(t2)
-    out2, diag2 = _run(t2)
+    out2, diag2 = _run(t2, path=path)
     assert want2["diag"]["status"] == diag2["status"] != 0
     parity.assert_attribute(out2, want2, diag2)
 
 
-def test_fused_graph_replay():
-    """The fused path captured in a HIP graph (caller stream and both side
-    streams) replays to the oracle's outputs, replay after replay, with the
-    outputs poisoned and eager work in between."""
+@pytest.mark.parametrize("T,path", [(60_000, "compact"), (paths.LONG, "fused")])
+def test_fused_graph_replay(T, path):
+    """The compact path and the fused path (caller stream and both side
+    streams) captured in a HIP graph replay to the oracle's outputs, replay
+    after replay, with the outputs poisoned and eager work in between."""
     import torch
 
-    T = 60_000
     tr = cases.random_trace(808, T=T, S=4, n_names=31, R=T // 25, n_ops=300, t_max=4 * T,
                             max_depth=5, dedup=True)
     tr, _, _ = cases.stream_major(tr)
     want = O.attribute(tr)
     dt = opattr.to_device(tr, DEV)
+    assert paths.attribute(dt, HINTS) == path
     ws = opattr.Workspace(DEV)
     R = tr["r_start"].size
     o = opattr.Outputs(

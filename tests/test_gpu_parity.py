@@ -10,6 +10,7 @@ import pytest
 
 import cases
 import parity
+import paths
 from oracle import oracle as O
 from paper_2609_11938_amd import opattr, tracegen as tg
 
@@ -151,29 +152,35 @@ def test_fused_path_random_times(seed):
 
 
 @pytest.mark.parametrize("seed", [0, 1, 2])
-def test_dense_seq_in_any_order(seed):
+@pytest.mark.parametrize("n_names,path", [(40, "compact"),
+                                          (paths.COMPACT_NAMES + 40, "permuted")])
+def test_dense_seq_in_any_order(seed, n_names, path):
     """Launches in random storage order with seq promised dense (and ranges
-    at most one per 16 launches): opattr_attribute permutes them into
-    stream-major order through the launch-order view, runs the fused path and
-    permutes match and range_id back."""
-    tr = cases.random_trace(9300 + seed, T=40_000 + 1013 * seed, S=2 + 2 * seed, n_names=40,
+    at most one per 16 launches): on the compact path by their ranks; with more
+    names opattr_attribute permutes them into stream-major order through the
+    launch-order view, runs the fused path and permutes match and range_id
+    back."""
+    tr = cases.random_trace(9300 + seed, T=40_000 + 1013 * seed, S=2 + 2 * seed, n_names=n_names,
                             R=2000 + 90 * seed, n_ops=60, t_max=400_000, max_depth=5,
                             dedup=seed != 1, drop=0.1 if seed == 2 else 0.0)
     T, R = tr["seq"].size, tr["r_start"].size
     assert R * 16 <= T
-    print(f"case dense seq any order seed={seed} T={T} R={R}", flush=True)
+    print(f"case dense seq any order seed={seed} T={T} R={R} names={n_names}", flush=True)
+    assert paths.attribute(opattr.to_device(tr, DEV), opattr.SEQ_DENSE) == path
     out, diag = _run(tr, flags=opattr.SEQ_DENSE)
     parity.assert_attribute(out, O.attribute(tr), diag)
 
 
+@pytest.mark.parametrize("n_names,path", [(20, "compact"),
+                                          (paths.COMPACT_NAMES + 20, "permuted")])
 @pytest.mark.parametrize("kind", ["shared_seq", "bad_stream"])
-def test_dense_seq_any_order_broken(kind):
-    """The permuted path on a false density promise (one seq value on two
+def test_dense_seq_any_order_broken(kind, n_names, path):
+    """The compact and the permuted path on a false density promise (one seq value on two
     launches) stays within its buffers; a launch on a stream past the last
     one is counted as a bad record, as on the other paths."""
     import numpy as np
 
-    tr = dict(cases.random_trace(9400, T=30_000, S=3, n_names=20, R=1500, n_ops=30,
+    tr = dict(cases.random_trace(9400, T=30_000, S=3, n_names=n_names, R=1500, n_ops=30,
                                  t_max=300_000, max_depth=4))
     if kind == "shared_seq":
         seq = tr["seq"].copy()
@@ -183,7 +190,8 @@ def test_dense_seq_any_order_broken(kind):
         st = tr["stream_id"].copy()
         st[123] = 3  # n_streams is 3
         tr["stream_id"] = st
-    print(f"case dense seq any order broken kind={kind}", flush=True)
+    print(f"case dense seq any order broken kind={kind} names={n_names}", flush=True)
+    assert paths.attribute(opattr.to_device(tr, DEV), opattr.SEQ_DENSE) == path
     out, diag = _run(tr, flags=opattr.SEQ_DENSE)
     if kind == "bad_stream":
         assert diag["bad_records"] >= 1 and diag["status"] == -9
