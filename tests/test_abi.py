@@ -139,6 +139,29 @@ def test_workspace_of_few_launches_over_many_rows(lib):
     assert lib.opattr_workspace_bytes(C.byref(k), C.byref(p), C.byref(r), C.byref(d)) < 14 << 20
 
 
+@pytest.mark.parametrize("T,per_range,NN,NS,NOPS,flags", [
+    (921087, 20, 40, 4, 899, 0), (952320, 20, 40, 4, 899, 4), (670528, 20, 40, 4, 899, 2),
+    (1168736, 20, 40, 4, 899, 7), (1094592, 3, 40, 4, 899, 7), (1105919, 3, 40, 4, 299, 7),
+    (716930, 3, 40, 4, 899, 0), (915456, 3, 40, 4, 899, 2), (888960, 20, 2100, 4, 899, 0),
+    (652608, 20, 2100, 4, 899, 2), (491200, 20, 2100, 16, 8999, 7),
+    (801600, 2, 2100, 16, 8999, 7), (847872, 20, 5000, 4, 899, 0),
+    (669632, 5, 300, 200, 19999, 0), (956544, 5, 300, 200, 19999, 7), (1255424, 60, 12, 2, 99, 7),
+    (729600, 60, 12, 2, 99, 6), (975680, 60, 12, 2, 99, 4), (780161, 2, 100, 8, 4999, 5)])
+def test_noalloc_accepts_what_fits_the_general_path(lib, T, per_range, NN, NS, NOPS, flags):
+    """The most launches of each shape whose arrays fit the scratch by the run
+    reduction and the general path alone: not refused, whatever the other paths'
+    plans take (without a device the scratch's address cannot be had; a launch
+    more is not asserted, other plans may take it)."""
+    import torch
+
+    if torch.cuda.device_count() > 0:
+        pytest.skip("the arrays are not there to be read")
+    k, p, r, d = _structs(T=T, P=T // 4, R=T // per_range, NN=NN, NS=NS, NOPS=NOPS, flags=flags)
+    fake = C.c_void_p(0x1000)
+    assert lib.opattr_attribute_noalloc(C.byref(k), C.byref(p), C.byref(r), C.byref(d), 0, None,
+                                        fake, fake, None, None, fake, fake, fake, None) == -3
+
+
 def test_argument_errors_return_before_any_device_work(lib):
     k, p, r, d = _structs()
     fake = C.c_void_p(0x1000)
