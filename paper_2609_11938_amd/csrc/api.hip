@@ -171,24 +171,35 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
   // takes it: a plan without ranges must stay within the size of the plan
   // with them). Ranges at most one per 16 launches of a long list keep the
   // runs of one operator row long: reduced in place. Shorter runs and shorter
-  // lists are ordered by row inside each block.
+  // lists go by row tables in LDS, or, with more rows, are ordered by row inside
+  // each block; long stream-major ones take the general path then (short runs,
+  // 3,001 rows, R = T / 8: 1.5M launches 211 us ordered, 240 us by the general
+  // path; 3M 353 and 345; 6M 620 and 569. Permuted ones stay: the general path
+  // takes 1020 us for 6M in launch order, the permuted 884).
   const bool long_runs = pl.R * 16 <= pl.T;
+  const bool by_row = pl.T <= kRowOrderMax || pl.G <= kTabMaxRows || !sm_hint;
   pl.fused = pl.seg && r != nullptr && pl.G <= kFusedMaxRows && pl.T > 0 &&
-             (mode != PlanMode::kPlain || long_runs);
+             (long_runs || (mode != PlanMode::kPlain && by_row));
   // (2M launches with 20k ranges and 200 rows take 201 us
   // reduced in place and 203 us by row tables; 1M with 250k ranges 625 us in
-  // place, 185 us ordered by row and 161 us by row tables)
+  // place)
   // The in-place reduction adds what a wave cannot keep by device atomics, in
   // another order on each run; launches with gaps in seq, whose general path
   // adds in one order, are ordered by row whatever their runs (2M shuffled with
   // 100k ranges and 1,001 rows 547 us in place, 570 us so, 720 us by the general
   // path; 4M 1017, 1071 and 1330 us).
   if (mode != PlanMode::kPlain && !(long_runs && pl.T > kFusedShort && pl.seq_dense)) {
-    // launches per lane: as few as leave no CU without a block, up to the
-    // point where more blocks only write more partials
-    pl.fper = pl.T <= (1 << 18) ? 2 : pl.T <= (1 << 20) ? 4 : 8;
+    // Launches per lane: as few as leave no CU without a block, up to the
+    // point where more blocks only write more partials (3,001 rows, two, four
+    // and eight: 250k launches 166, 171 and 188 us, 400k 185, 182 and 194, 1.5M
+    // 267, 249 and 255, 3M 462, 423 and 415; 5,001 rows, 2M 284 and 277).
+    pl.fper = pl.T <= (1 << 18) ? 2 : pl.T <= (3 << 19) ? 4 : 8;
     if ((pl.fused || pl.compact) && pl.G <= kTabMaxRows) {  // the whole table fits in LDS
-      pl.fper = pl.T <= (1 << 18) ? 1 : pl.T <= (1 << 19) ? 2 : 4;
+      // A block of the compact path takes one chunk of launches, so up to four a
+      // lane; the others take chunk after chunk with one a lane (501 rows, one,
+      // two and four: 400k 158, 159 and 165 us, 1.5M 182, 183 and 200, 6M 494,
+      // 507 and 517; ordered by row 176, 239 and 694 us).
+      pl.fper = !pl.compact || pl.T <= (1 << 18) ? 1 : pl.T <= (1 << 19) ? 2 : 4;
       const int64_t chunks = fused_agg_blocks(pl.T, 1024 * pl.fper);
       pl.ftabs = (int)(chunks < kTabBlocks ? chunks : kTabBlocks);
     }

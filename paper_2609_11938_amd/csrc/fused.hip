@@ -454,18 +454,14 @@ __global__ void __launch_bounds__(kRThreads) k_r_agg(AggParams a) {
 // ---------------------------------------------------------------------------
 // 1''. the reduction for few operator rows: a block holds the whole table in
 // LDS and adds its launches' results to it, then writes it out; the tables
-// of all blocks are added up element by element (k_t_rows). A lane adds its
-// consecutive launches of one row in registers first; where many lanes of a
-// wave hold one row (one operator, or none, over most launches), they are
-// reduced across the lanes and added once, as LDS atomics on one address
-// go one after the other. 1M launches, 250k ranges, 501 rows: the whole call
-// 161 us replayed from a graph, 185 us ordered by row (57 us of it in
-// k_r_agg, whose 977 blocks each write nearly every row), 192 us with the
-// items of the general aggregation.
+// of all blocks are added up element by element (k_t_rows). Lanes of one row in
+// a wave are added up across the lanes first, as LDS atomics on one address go
+// one after the other. A block takes its chunks one launch a lane at a time (two
+// and four are slower, see make_plan).
 // ---------------------------------------------------------------------------
-template <bool DEF, int kPer>
+template <bool DEF>
 __global__ void __launch_bounds__(kTThreads) k_t_agg(AggParams a, unsigned long long *tabs) {
-  constexpr int kN = kTThreads * kPer;
+  constexpr int kPer = 1, kN = kTThreads * kPer;
   extern __shared__ __align__(16) unsigned char tagg_raw[];
   unsigned long long *tab = reinterpret_cast<unsigned long long *>(tagg_raw);  // [G][kFFields]
   const int tid = threadIdx.x, ln = lane_id();
@@ -757,9 +753,8 @@ void run_fused_agg(const FusedIn &x, hipStream_t s) {
     unsigned long long *tabs = reinterpret_cast<unsigned long long *>(a.o.parts);
     const size_t lt = (size_t)pl.G * kFFields * 8;
     const unsigned gt = (unsigned)pl.ftabs;
-    if (pl.fper == 1) def ? k_t_agg<true, 1><<<gt, kTThreads, lt, s>>>(a, tabs) : k_t_agg<false, 1><<<gt, kTThreads, lt, s>>>(a, tabs);
-    else if (pl.fper == 2) def ? k_t_agg<true, 2><<<gt, kTThreads, lt, s>>>(a, tabs) : k_t_agg<false, 2><<<gt, kTThreads, lt, s>>>(a, tabs);
-    else def ? k_t_agg<true, 4><<<gt, kTThreads, lt, s>>>(a, tabs) : k_t_agg<false, 4><<<gt, kTThreads, lt, s>>>(a, tabs);
+    if (def) k_t_agg<true><<<gt, kTThreads, lt, s>>>(a, tabs);
+    else k_t_agg<false><<<gt, kTThreads, lt, s>>>(a, tabs);
   } else if (nb > 0) {
     const size_t lr = r_agg_lds(pl.G);
     const dim3 gr((unsigned)nb), bl(kRThreads);

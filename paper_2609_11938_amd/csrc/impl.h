@@ -403,6 +403,7 @@ size_t fused_split_bytes(uint32_t G, int64_t nb);
 size_t fused_hot_bytes();
 size_t fused_acc_bytes(uint32_t G);
 constexpr int64_t kFusedShort = 1 << 20;   // launches up to which blocks always order by row
+constexpr int64_t kRowOrderMax = 3 << 20;  // stream-major launches that are ordered by row
 constexpr uint32_t kTabMaxRows = 704;      // rows of 200 B whose table a block holds in LDS
 constexpr int kTabBlocks = 256;
 constexpr uint32_t kFusedMaxRows = 16384;  // rows the per-bucket LDS tables hold

@@ -22,6 +22,7 @@ def const(name):
 COMPACT_MAX = const("kCompactMax")      # launches of the compact path
 COMPACT_NAMES = const("kCompactNames")  # and its names
 TAB_ROWS = const("kTabMaxRows")         # operator rows of a table in LDS
+ROW_MAX = const("kRowOrderMax")         # stream-major launches that are ordered by row
 # launches from which runs are reduced in place (dense seq, long runs)
 LONG = max(COMPACT_MAX, const("kFusedShort")) + 1
 

@@ -138,7 +138,7 @@ def test_fused_unattributed(with_ranges, T, path):
 @pytest.mark.parametrize("n_names", [9, paths.COMPACT_NAMES + 1])  # compact, or its own kernels
 @pytest.mark.parametrize("T,per_range,n_ops,S", [
     (1, 1, 1, 1), (511, 2, 16383, 1), (512, 3, 2, 2), (513, 2, 700, 3),
-    (2 ** 18 + 1, 2, 5000, 4), (2 ** 20 + 1, 3, 900, 5),  # four, eight launches a lane
+    (2 ** 18 + 1, 2, 5000, 4), (2 ** 20 + 1, 3, 900, 5),  # four launches a lane
     (1023, 2, 703, 2), (1025, 2, 704, 2),                  # the largest table in LDS, one row more
     (2 ** 18 + 1, 40, 703, 3), (2 ** 19 + 1, 2, 50, 2), (2 ** 20 + 1, 5, 300, 4),
 ])
@@ -311,6 +311,35 @@ def test_row_order_more_partials_than_room(kinds):
     want = O.attribute(tr, **kw)
     out, diag = _run(tr, **kw)
     parity.assert_attribute(out, want, diag)
+
+
+@pytest.mark.parametrize("T,n_ops,path", [
+    (3 << 19, 900, "fused"), ((3 << 19) + 1, 900, "fused"),  # four, eight launches a lane
+    (paths.ROW_MAX, 900, "fused"), (paths.ROW_MAX + 1, 900, "general"),
+    (paths.ROW_MAX + 1, paths.TAB_ROWS - 1, "fused")])
+def test_row_order_long_lists(T, n_ops, path):
+    """Short runs of long stream-major lists: ordered by row up to a size, above
+    it by the general path, and by row tables whatever the size. (The oracle
+    would take minutes for so many flat ranges: launch i is in range i // run
+    and takes row i.)"""
+    run = 3
+    tr = _regular_trace(T=T, run=run, n_ops=n_ops, cycle=n_ops, seed=95)
+    print(f"case row order long T={T} n_ops={n_ops}", flush=True)
+    out, diag = _run(tr, path=path, agg_kind=np.full(20, opattr.AGG_SUM, np.uint8))
+    i = np.arange(T)
+    rid = np.where(i // run < T // run, i // run, -1)
+    op = np.where(rid < 0, n_ops, rid % n_ops)
+    assert diag["status"] == 0
+    assert np.array_equal(parity.host(out["match"]), i)
+    assert np.array_equal(parity.host(out["range_id"]), rid)
+    got, n = out.table_host(), np.bincount(op, minlength=n_ops + 1)
+    for f, want in (("kernel_count", n), ("total_ns", 5 * n), ("matched_count", n),
+                    ("matched_ns", 5 * n)):
+        assert np.array_equal(got[f], want), f
+    for c in range(20):
+        want = np.bincount(op, weights=tr["counters"][:, c], minlength=n_ops + 1)
+        want[n == 0] = np.nan
+        parity.assert_values_close(got["value"][:, c], want, 1e-12)
 
 
 @pytest.mark.parametrize("T,n_names,kinds,cols", [

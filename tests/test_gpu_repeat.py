@@ -73,7 +73,8 @@ def test_table_in_lds_repeats(T, R, n_ops, order, kind):
     (200_000, 120_000, 5_000, "gaps", None),
     (400_000, 100_000, 2_000, "dense", MIXED),    # four
     (300_000, 2_000, 1_500, "dense", None),       # few ranges: the rows change with the streams
-    (1_100_000, 300_000, 3_000, "stream", None),  # eight, more than the compact path takes
+    (1_100_000, 300_000, 3_000, "stream", None),  # more than the compact path takes
+    (1_600_000, 300_000, 3_000, "stream", None),  # eight
     (1_100_000, 60_000, 1_000, "gaps", None),     # long runs, permuted by the launches' ranks
 ])
 def test_rows_ordered_in_blocks_repeat(T, R, n_ops, order, kind):
