@@ -436,8 +436,8 @@ int opattr_attribute(const opattr_kernels *k, const opattr_profiled *p, const op
    stage on `stream` alone (no side streams). Same arguments, outputs and
    diag as opattr_attribute. Returns OPATTR_ERR_SCRATCH, enqueueing nothing,
    when the call's arrays do not fit the scratch (opattr_workspace_bytes may
-   exceed it a little: it has room for partial results that this call adds
-   up in place instead), and
+   exceed it: where it does, this call takes less room for partial results, or
+   a path that needs none), and
    OPATTR_ERR_HIP when the scratch's address cannot be had. Every call on a
    device shares that device's scratch: calls that may overlap on one device
    (other streams, other host threads) race and must be ordered by the

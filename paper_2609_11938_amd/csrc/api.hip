@@ -38,7 +38,8 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
   pl.seq_dense = (d->flags & OPATTR_SEQ_DENSE) != 0;
   pl.ranges_nested = (d->flags & OPATTR_RANGES_NESTED) != 0;
   const bool sm_hint = (d->flags & OPATTR_KERNELS_STREAM_MAJOR) != 0;
-  // Few launches: the compact path (single stream, five launches). Its tiles'
+  // Few launches: the compact path (single stream, five launches and what
+  // missing promises add). Its tiles'
   // name counts are a column of at most 1024 values per name, and its ranges'
   // tiles fit one maximum tree.
   pl.ctshift = pl.T > (1 << 18) || pl.P > (1 << 18) ? 12 : 10;
@@ -212,7 +213,8 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
   // at eight. Two for short lists in which most stretches are short (1M: 117 MB,
   // 72 MB more than the general aggregation's arrays).
   const bool short_runs = pl.R * 4 > pl.T && pl.compact && sm_hint;
-  pl.flong = mode == PlanMode::kLean || long_runs ? 8 : short_runs ? 2 : 4;
+  pl.flong = mode == PlanMode::kEight || long_runs ? 8
+             : mode == PlanMode::kFull && short_runs ? 2 : 4;
   // A thousand blocks of the run reduction run at once (four waves a SIMD by
   // registers): up to 4M launches, eight launches a lane make less than two
   // rounds of blocks, half of them idle in the last (2M: 58 us at eight, 50 at
@@ -281,7 +283,7 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
     b.off = pl.compact ? permuted : shared;
     const int64_t nfb = fused_agg_blocks(pl.T, fused_span(pl));
     pl.acc = b.take(pl.compact ? 0 : fused_acc_bytes(pl.G));
-    pl.fbkt = b.take(fused_bkt_bytes(nfb));
+    pl.fbkt = b.take(pl.ftabs ? 0 : fused_bkt_bytes(nfb));
     pl.forder = b.take((size_t)nfb * 4);
     pl.fsplit = b.take(pl.compact || pl.ftabs ? 0 : fused_split_bytes(pl.G, nfb));
     pl.fhot = b.take(fused_hot_bytes());
@@ -651,12 +653,11 @@ int opattr_aggregate(const opattr_kernels *k, const opattr_profiled *p, const in
   return launch_status();
 }
 
-// opattr_attribute on the fused path (kernels stream-major with dense seq,
-// ranges at most one per 16 launches): the ranges and the enclosure on a
-// side stream, the profiled slot table on a second one, the matching up to
-// the eligible launches' rows on the caller's stream; then one pass gives
-// every launch its match (dedup broadcast included) and reduces the runs of
-// launches of one operator row.
+// opattr_attribute on the fused path (kernels stream-major with dense seq, or
+// permuted into that order): the ranges and the enclosure on a side stream, the
+// profiled slot table on a second one, the matching up to the eligible launches'
+// rows on the caller's stream; then one pass gives every launch its match (dedup
+// broadcast included) and reduces the launches by operator row.
 static int attribute_fused(const opattr_kernels *k, const opattr_profiled *p,
                            const opattr_ranges *r, const opattr_dims *d, int policy,
                            const uint8_t *agg_kind, int32_t *match, int32_t *range_id,
@@ -868,11 +869,11 @@ int opattr_attribute_noalloc(const opattr_kernels *k, const opattr_profiled *p,
                              opattr_summary *sum, opattr_diag *diag, void *stream) {
   if (!attribute_args_ok(k, p, r, d, policy, agg_kind, match, range_id, table, sum, diag))
     return OPATTR_ERR_INVALID_ARG;
+  // (520k launches, 170k ranges, 900 rows: 110 us in partials of four launches at
+  // least, 130 of eight, 219 by the run reduction and the general path alone)
   Plan pl = make_plan(k, p, r, d);
-  if (pl.total > OPATTR_NOALLOC_SCRATCH_BYTES)
-    pl = make_plan(k, p, r, d, false, PlanMode::kLean);
-  if (pl.total > OPATTR_NOALLOC_SCRATCH_BYTES)
-    pl = make_plan(k, p, r, d, false, PlanMode::kPlain);
+  for (const PlanMode m : {PlanMode::kFour, PlanMode::kEight, PlanMode::kPlain})
+    if (pl.total > OPATTR_NOALLOC_SCRATCH_BYTES) pl = make_plan(k, p, r, d, false, m);
   if (pl.total > OPATTR_NOALLOC_SCRATCH_BYTES) return OPATTR_ERR_SCRATCH;
   void *ws = scratch_ptr();
   if (!ws) return OPATTR_ERR_HIP;

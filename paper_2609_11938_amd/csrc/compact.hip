@@ -1,5 +1,7 @@
 // opattr_attribute for at most a million launches, in five launches on the
-// caller's stream. Small calls are bound by the count of launches (5 us of
+// caller's stream (before them, where it is not promised: the rank view of a
+// seq with gaps, seven launches; the sort of the ranges, one and one for every
+// merge pass; under OPATTR_VALIDATE the checks of the layout). Small calls are bound by the count of launches (5 us of
 // host time each, two to three dozen of them) and by the chain of kernels,
 // each of which takes 3 to 20 us however little it does; so every step does
 // all the work that is ready, as jobs in disjoint block ranges of one grid:

@@ -26,9 +26,12 @@
 //    accumulators and writes the bucket's table rows (DW-mean = sum /
 //    matched ns, NaN rules) and summary sums; the last block to finish
 //    writes the summary and the status.
-// Integer fields are exact in any order; fp64 sums are added in an order
-// that depends on scheduling (well inside the 1e-9 tolerance); maxima are
-// exact.
+// Lists with many ranges take k_r_agg (launches ordered by row, 1') or k_t_agg
+// and k_t_rows (the table in LDS, 1'') in place of k_f_agg.
+// Integer fields and maxima are exact in any order. The fp64 sums of k_r_agg
+// and k_t_agg are added in one order; those of k_f_agg in an order that depends
+// on scheduling (a block's partials of one row, and what goes to the row
+// accumulators; well inside the 1e-9 tolerance).
 #include "rowagg.h"
 
 namespace opa {
@@ -116,7 +119,7 @@ __device__ __forceinline__ void match_of(const MatchParams &a, int64_t i, int nv
 
 // ---------------------------------------------------------------------------
 // 0. processing order of the run reduction's blocks. A block of 2048
-// launches in storage order holds one stream's launches over a window of
+// launches (1024 up to 4M) in storage order holds one stream's launches over a window of
 // launch order; its duplicates read the matches (and the counter rows) of
 // the representatives of that window, which every stream's blocks over the
 // window read too. The blocks are ordered by the seq rank of their first

@@ -86,10 +86,10 @@ struct Plan {
   size_t misc;   // small device scalars
 };
 
-// What the fused attribution may take: all it can use; little more than the other
-// aggregation's arrays; or only the run reduction (kPlain, never larger than a
-// plan without the row-ordered reduction).
-enum class PlanMode { kFull, kLean, kPlain };
+// What the fused attribution may take: all it can use; partials of four or of
+// eight launches at least; or only the run reduction (kPlain, never larger than
+// a plan without the row-ordered reduction).
+enum class PlanMode { kFull, kFour, kEight, kPlain };
 
 // second_match: also a second set of the segment path's matching arrays
 Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_ranges *r,

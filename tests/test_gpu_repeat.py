@@ -1,8 +1,9 @@
 """The operator table has the same bits on every run of a call: a row's
 fp64 sums are added up in an order that does not depend on scheduling.
-(Except by the run reduction of the fused path, whose partials past a wave's
-capacity are added by device atomics: more than 2^20 launches with dense seq
-promised and at most one range per 16 launches.)"""
+(Except by the run reduction of the fused path, which adds a block's partials of
+one row, and those past a wave's capacity, by atomics: more than 2^20 launches
+with dense seq promised and at most one range per 16 launches, and noalloc calls
+of such ranges that fit no other plan.)"""
 import numpy as np
 import pytest
 
