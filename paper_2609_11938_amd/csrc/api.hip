@@ -207,14 +207,11 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
   }
   // Launches of one operator row in a wave from which a block adds them up: 200 /
   // flong + 16 bytes a launch, where the general aggregation's arrays take
-  // about 40. The call at 2, 4 and 8: 96k over 5,014 rows 60.0, 64.8 and 69.7
-  // us, 1M with 600k ranges 204, 236 and 314 us, 2M with 400k ranges 272, 277
-  // and 307 us; where the runs are long, 4M with 100k ranges 1072 us at four and
-  // at eight. Two for short lists in which most stretches are short (1M: 117 MB,
-  // 72 MB more than the general aggregation's arrays).
-  const bool short_runs = pl.R * 4 > pl.T && pl.compact && sm_hint;
-  pl.flong = mode == PlanMode::kEight || long_runs ? 8
-             : mode == PlanMode::kFull && short_runs ? 2 : 4;
+  // about 40. The call at 2, 4, 6, 8 and 16: 96k over 5,014 rows 57.0, 55.0, 55.8,
+  // 55.8 and 55.7 us, 1M with 600k ranges 188, 183, 186, 241 and 247 us, 2M with 1M
+  // ranges 331, 314, 316, 320 and 354 us; with long runs (500k, 25k ranges) 83.9,
+  // 84.6, 83.9, 83.8 and 85.7 us.
+  pl.flong = mode == PlanMode::kLean || long_runs ? 8 : 6;
   // A thousand blocks of the run reduction run at once (four waves a SIMD by
   // registers): up to 4M launches, eight launches a lane make less than two
   // rounds of blocks, half of them idle in the last (2M: 58 us at eight, 50 at
@@ -869,10 +866,8 @@ int opattr_attribute_noalloc(const opattr_kernels *k, const opattr_profiled *p,
                              opattr_summary *sum, opattr_diag *diag, void *stream) {
   if (!attribute_args_ok(k, p, r, d, policy, agg_kind, match, range_id, table, sum, diag))
     return OPATTR_ERR_INVALID_ARG;
-  // (520k launches, 170k ranges, 900 rows: 110 us in partials of four launches at
-  // least, 130 of eight, 219 by the run reduction and the general path alone)
   Plan pl = make_plan(k, p, r, d);
-  for (const PlanMode m : {PlanMode::kFour, PlanMode::kEight, PlanMode::kPlain})
+  for (const PlanMode m : {PlanMode::kLean, PlanMode::kPlain})
     if (pl.total > OPATTR_NOALLOC_SCRATCH_BYTES) pl = make_plan(k, p, r, d, false, m);
   if (pl.total > OPATTR_NOALLOC_SCRATCH_BYTES) return OPATTR_ERR_SCRATCH;
   void *ws = scratch_ptr();

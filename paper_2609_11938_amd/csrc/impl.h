@@ -86,10 +86,11 @@ struct Plan {
   size_t misc;   // small device scalars
 };
 
-// What the fused attribution may take: all it can use; partials of four or of
-// eight launches at least; or only the run reduction (kPlain, never larger than
-// a plan without the row-ordered reduction).
-enum class PlanMode { kFull, kFour, kEight, kPlain };
+// What the fused attribution may take: all it can use; partials of eight launches
+// at least, which take no more than the other aggregation's arrays; or only the
+// run reduction (kPlain, never larger than a plan without the row-ordered
+// reduction).
+enum class PlanMode { kFull, kLean, kPlain };
 
 // second_match: also a second set of the segment path's matching arrays
 Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_ranges *r,

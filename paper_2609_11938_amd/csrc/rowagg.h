@@ -509,23 +509,24 @@ struct CombParams {
   opattr_summary *sum;
 };
 
-// kEntries partials (kRec: launch records), a half wave each, added into an LDS
-// table of rb rows field by field: 25 lanes read the fields of one, so that it
-// costs two cache lines of requests instead of 25, and kBatch of them are in
-// flight. at(j) gives the place of the half's j-th entry, or -1.
 constexpr int kList = 512;                     // entries a combine wave lists in LDS at once
 constexpr int kBatch = 8;                      // loads per lane in flight
-template <bool kRec, int kN, typename At>
-__device__ __forceinline__ void comb_batch(unsigned long long *tab, uint32_t rb, const CombParams &a,
-                                           At at, uint32_t mx, uint32_t dw) {
-  const int ln = lane_id(), f = ln & 31;
-  if constexpr (!kRec) {
+
+// Partials added into an LDS table of rb rows field by field: 25 lanes read the
+// fields of one, two partials an instruction, so that a partial costs two cache
+// lines of requests instead of 25. at(x) gives the place of entry x, or -1.
+struct CombParts {
+  static constexpr int kEach = 2;  // entries an instruction takes
+  template <int kN, typename At>
+  static __device__ __forceinline__ void add(unsigned long long *tab, uint32_t rb,
+                                             const CombParams &a, At at, uint32_t mx, uint32_t) {
+    const int ln = lane_id(), f = ln & 31;
     const unsigned long long *parts64 = reinterpret_cast<const unsigned long long *>(a.parts);
     unsigned long long v[kN];
     bool ok[kN];
 #pragma unroll
     for (int j = 0; j < kN; ++j) {
-      const int64_t x = at(j);
+      const int64_t x = at(2 * j + (ln >> 5));
       ok[j] = x >= 0 && f < kFFields;
       v[j] = ok[j] ? parts64[(size_t)x * (sizeof(PartRow) / 8) + f] : 0ull;
     }
@@ -534,14 +535,24 @@ __device__ __forceinline__ void comb_batch(unsigned long long *tab, uint32_t rb,
       const uint32_t g = (uint32_t)(__shfl(v[j], (ln & 32) + 24, OPA_WAVE) >> 32);
       if (ok[j]) field_add(tab + (size_t)(g % rb) * kFFields + f, f, v[j], mx);
     }
-  } else {
+  }
+};
+
+// Launch records: five lanes each read four counters of the launch's row and add
+// them, twelve records an instruction.
+struct CombRecs {
+  static constexpr int kEach = 12;
+  template <int kN, typename At>
+  static __device__ __forceinline__ void add(unsigned long long *tab, uint32_t rb,
+                                             const CombParams &a, At at, uint32_t mx,
+                                             uint32_t dw) {
+    const int ln = lane_id(), sub = ln / 5, q = ln - sub * 5;
     uint4 r[kN];
-    float v[kN];
+    float4 v[kN];
     bool ok[kN], hit[kN];
-    const int c = f - 4;
 #pragma unroll
     for (int j = 0; j < kN; ++j) {
-      const int64_t x = at(j);
+      const int64_t x = sub < kEach ? at(kEach * j + sub) : -1;
       ok[j] = x >= 0;
       r[j] = ok[j] ? a.rec[x] : make_uint4(0u, 0xFFFFFFFFu, 0u, 0u);
     }
@@ -549,38 +560,48 @@ __device__ __forceinline__ void comb_batch(unsigned long long *tab, uint32_t rb,
     for (int j = 0; j < kN; ++j) {
       const int32_t m = (int32_t)r[j].y;
       hit[j] = m >= 0 && (int64_t)m < a.in.P;
-      v[j] = hit[j] && c >= 0 && c < OPATTR_NUM_COUNTERS
-                 ? a.in.counters[(int64_t)m * a.in.rs + (int64_t)c * a.in.cs] : 0.0f;
+      v[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      if (!hit[j]) continue;
+      const float *row = a.in.counters + (int64_t)m * a.in.rs;
+      if (a.in.vec4) {
+        v[j] = reinterpret_cast<const float4 *>(row)[q];
+      } else {
+        const int64_t c = 4 * q;
+        v[j] = make_float4(row[c * a.in.cs], row[(c + 1) * a.in.cs], row[(c + 2) * a.in.cs],
+                           row[(c + 3) * a.in.cs]);
+      }
     }
 #pragma unroll
     for (int j = 0; j < kN; ++j) {
-      if (!ok[j] || f >= kFFields - 1) continue;
-      unsigned long long *t = tab + (size_t)(r[j].x % rb) * kFFields + f;
-      if (c < 0) {
-        const unsigned long long d = (f & 1) ? r[j].z : 1u;
-        if (f < 2 || hit[j]) atomicAdd(t, d);
-      } else if (hit[j]) {
+      if (!ok[j]) continue;
+      unsigned long long *t = tab + (size_t)(r[j].x % rb) * kFFields;
+      if (q < 2 || (q < 4 && hit[j])) atomicAdd(t + q, (unsigned long long)((q & 1) ? r[j].z : 1u));
+      if (!hit[j]) continue;
+      const float w[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+      const double d = (double)r[j].z;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {  // as acc_launch
+        const int c = 4 * q + k;
         if ((mx >> c) & 1u) {
-          atomicMax(t, (unsigned long long)f2key(v[j]));
-          if (v[j] != v[j]) atomicOr(reinterpret_cast<unsigned int *>(t - f + 24), 1u << c);
+          atomicMax(t + 4 + c, (unsigned long long)f2key(w[k]));
+          if (w[k] != w[k]) atomicOr(reinterpret_cast<unsigned int *>(t + 24), 1u << c);
         } else {
-          const double x = (double)v[j];  // as acc_launch
-          unsafeAtomicAdd(reinterpret_cast<double *>(t), ((dw >> c) & 1u) ? x * (double)r[j].z : x);
+          const double x = (double)w[k];
+          unsafeAtomicAdd(reinterpret_cast<double *>(t + 4 + c), ((dw >> c) & 1u) ? x * d : x);
         }
       }
     }
   }
-}
+};
 
 // The entries of a wave's blocks in a bucket (per lane kPre blocks: ev entries
-// from xv on, mine in all) added into an LDS table: listed in LDS, then kBatch
-// of each half wave at a time.
-template <bool kRec, int kPre>
+// from xv on, mine in all) added into an LDS table: listed in LDS, then some of
+// them at a time.
+template <typename Comb, int kN, int kPre>
 __device__ __forceinline__ void comb_add(unsigned long long *tab, uint32_t rb, uint32_t *list,
                                          const CombParams &a, const uint32_t (&ev)[kPre],
                                          const uint32_t (&xv)[kPre], uint32_t mine, uint32_t mx,
                                          uint32_t dw) {
-  const int half = lane_id() >> 5;
   const uint32_t incl = wave_incl_scan_add<uint32_t>(mine);
   const uint32_t n = __shfl(incl, OPA_WAVE - 1, OPA_WAVE);
   if (n == 0) return;
@@ -591,10 +612,9 @@ __device__ __forceinline__ void comb_add(unsigned long long *tab, uint32_t rb, u
       for (uint32_t p = 0; p < ev[k]; ++p) list[w++] = xv[k] + p;
     }
     wave_sync_lds();
-    for (uint32_t i = 0; i < n; i += 2 * kBatch)
-      comb_batch<kRec, kBatch>(tab, rb, a, [&](int j) -> int64_t {
-        const uint32_t idx = i + 2 * j + half;
-        return idx < n ? (int64_t)list[idx] : -1;
+    for (uint32_t i = 0; i < n; i += Comb::kEach * kN)
+      Comb::template add<kN>(tab, rb, a, [&](int x) -> int64_t {
+        return i + x < n ? (int64_t)list[i + x] : -1;
       }, mx, dw);
     wave_sync_lds();  // the list is free again
   } else {
@@ -611,10 +631,9 @@ __device__ __forceinline__ void comb_add(unsigned long long *tab, uint32_t rb, u
         const int src = __ffsll((unsigned long long)m) - 1;
         const uint32_t c = __shfl(e, src, OPA_WAVE);
         const uint32_t x0 = __shfl(xe, src, OPA_WAVE);
-        for (uint32_t p = 0; p < c; p += 4)
-          comb_batch<kRec, 2>(tab, rb, a, [&](int j) -> int64_t {
-            const uint32_t pp = p + 2 * j + half;
-            return pp < c ? (int64_t)(x0 + pp) : -1;
+        for (uint32_t p = 0; p < c; p += Comb::kEach * 2)
+          Comb::template add<2>(tab, rb, a, [&](int x) -> int64_t {
+            return p + x < c ? (int64_t)(x0 + p + x) : -1;
           }, mx, dw);
       }
     }
@@ -641,7 +660,7 @@ __device__ __forceinline__ void comb_blocks(unsigned long long *tab, uint32_t rb
     xv[k] = (uint32_t)b * a.pcap + (e0[k] >> 16);
     mine += ev[k];
   }
-  comb_add<false, kPre>(tab, rb, list, a, ev, xv, mine, mx, dw);
+  comb_add<CombParts, kBatch>(tab, rb, list, a, ev, xv, mine, mx, dw);
   if (!a.rec) return;
   mine = 0;
 #pragma unroll
@@ -651,7 +670,7 @@ __device__ __forceinline__ void comb_blocks(unsigned long long *tab, uint32_t rb
     xv[k] = (uint32_t)b * a.rcap + (e0[k] & 0xFFFFu);
     mine += ev[k];
   }
-  comb_add<true, kPre>(tab, rb, list, a, ev, xv, mine, mx, dw);
+  comb_add<CombRecs, kBatch / 2>(tab, rb, list, a, ev, xv, mine, mx, dw);
 }
 
 // The blocks' tables added up, kTRows rows a block (one element per thread

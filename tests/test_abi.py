@@ -120,14 +120,13 @@ def test_workspace_for_all_inputs_covers_every_entry_point(lib):
     (4_000_000, 2_000_000, 100, 8, 15_999, 7, 306.5),
     (10_000_000, 5_000_000, 100, 8, 15_999, 7, 763.2)])
 def test_workspace_of_row_ordered_calls(lib, T, R, NN, NS, NOPS, flags, before):
-    """Blocks that order their launches by operator row keep 200 / 4 + 16 bytes a
-    launch (200 / 2 + 16 for at most 2^20 stream-major ones with a range for every
-    four, 200 / 8 + 16 for all with one for every sixteen), in the place of the general aggregation's arrays (about
-    40 bytes), and the combine sixteen shares of 200 bytes a row; MiB before: of
-    the general aggregation alone."""
+    """Blocks that order their launches by operator row keep 200 / 6 + 16 bytes a
+    launch (200 / 8 + 16 with at most a range for every sixteen), in the place of
+    the general aggregation's arrays (about 40 bytes), and the combine sixteen
+    shares of 200 bytes a row; MiB before: of the general aggregation alone."""
     k, p, r, d = _structs(T=T, P=min(T, 400_000), R=R, NN=NN, NS=NS, NOPS=NOPS, flags=flags)
     mib = lib.opattr_workspace_bytes(C.byref(k), C.byref(p), C.byref(r), C.byref(d)) / 2 ** 20
-    more = 2 if R * 16 <= T else 76 if flags and T <= 2 ** 20 else 26
+    more = 2 if R * 16 <= T else 10
     assert mib <= before + (more * T + 17 * 200 * NOPS) / 2 ** 20 + 6, mib
 
 

@@ -346,18 +346,19 @@ def test_row_order_long_lists(T, n_ops, path):
     (700, 7, False, False), (40_000, 7, False, True), (40_000, 2100, True, False),
     (300_000, 7, True, False), (2 ** 20 + 700, 7, False, False)])
 def test_row_order_short_and_long_stretches(T, n_names, kinds, cols):
-    """Operators of one to six launches in a block, beside one that holds half of
-    its launches and unattributed ones: stretches on both sides of the length
-    from which a block adds them up itself, and more launch records of one
-    bucket than a combine wave lists at once (64 operators of one bucket, each
-    a few times in every block), with NaN counters."""
+    """Operators of one to a dozen launches in a wave, beside one that holds half
+    of the launches and unattributed ones: stretches on both sides of the
+    length from which a block adds them up itself, and more launch records of
+    one bucket than a combine wave lists at once (64 operators of one bucket,
+    each a few times in every block), with NaN counters."""
     rng = np.random.default_rng(T)
     tr = _regular_trace(T=T, run=1, n_ops=16383, cycle=1, seed=94)
     tr["name_id"] = (np.arange(T) % n_names).astype(np.uint32)
     tr["pf_name"], tr["n_names"] = tr["name_id"].copy(), n_names
     u = rng.random(T)
-    op = np.where(u < 0.5, 5000, np.where(u < 0.85, rng.integers(0, 64, T),
-                                          rng.integers(0, 16383, T)))
+    op = np.select([u < 0.5, u < 0.7, u < 0.85], [np.full(T, 5000), rng.integers(0, 64, T),
+                                                  rng.integers(200, 208, T)],
+                   rng.integers(0, 16383, T))
     keep = rng.random(T) > 0.05
     for f in ("r_start", "r_end", "r_stream"):
         tr[f] = tr[f][keep]

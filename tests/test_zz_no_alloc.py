@@ -79,8 +79,8 @@ def test_noalloc_two_calls_second_smaller(n_names, small_names, path, small_path
 
 
 @pytest.mark.parametrize("T,per_range,n_names,flags,path", [
-    # a partial for every four or eight launches of a row, where every two are usual
-    (520_000, 3, 40, HINTS, "compact"), (900_000, 3, 40, HINTS, "compact"),
+    # a partial for every eight launches of a row, where every six are usual
+    (1_000_000, 3, 40, HINTS, "compact"),
     # launches with gaps in seq: not permuted, their view by a radix sort
     (700_000, 20, paths.COMPACT_NAMES + 52, 0, "general"),
     # dense seq and long runs: permuted, and reduced in place however few
