@@ -662,12 +662,12 @@ __global__ void __launch_bounds__(kTThreads) k_c_tab(CompactArgs a) {
   c_launches<kPer, kTThreads, kVia>(a, i0, ib, nv, *reinterpret_cast<CWin *>(c_raw), sm, mt, du, g);
   unsigned long long *tab = reinterpret_cast<unsigned long long *>(c_raw);
   const uint32_t G = a.NOPS + 1u, ne = G * kFFields;
-  __shared__ uint32_t turn;
+  __shared__ uint32_t turn[kTurns];
   __syncthreads();  // the window's space becomes the table
   for (uint32_t x = tid; x < ne; x += kTThreads) tab[x] = 0;
-  if (tid == 0) turn = 0;
+  if (tid < kTurns) turn[tid] = 0;
   __syncthreads();
-  tab_add<DEF, kPer>(tab, &turn, 0, a.in, nv, mt, du, g);
+  tab_add<DEF, kPer>(tab, turn, 0, a.in, nv, mt, du, g);
   __syncthreads();
   unsigned long long *dst = a.tabs + (size_t)blockIdx.x * ne;
   for (uint32_t x = tid; x < ne; x += kTThreads) dst[x] = tab[x];

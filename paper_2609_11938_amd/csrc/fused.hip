@@ -470,9 +470,9 @@ __global__ void __launch_bounds__(kTThreads) k_t_agg(AggParams a, unsigned long 
   const int tid = threadIdx.x, ln = lane_id();
   const AggIn &in = a.in;
   const uint32_t ne = (a.o.NOPS + 1u) * kFFields;
-  __shared__ uint32_t turn;
+  __shared__ uint32_t turn[kTurns];
   for (uint32_t x = tid; x < ne; x += kTThreads) tab[x] = 0;
-  if (tid == 0) turn = 0;
+  if (tid < kTurns) turn[tid] = 0;
   __syncthreads();
   uint32_t err = 0;
   const int64_t nc = (a.T + kN - 1) / kN;  // chunks, a stretch of them per block
@@ -486,7 +486,7 @@ __global__ void __launch_bounds__(kTThreads) k_t_agg(AggParams a, unsigned long 
     load_n<kPer>(in.dur, ib, nv, du);
     load_n<kPer>(a.range_id, ib, nv, rid);
     rows_of<kPer>(a, rid, nv, g);
-    tab_add<DEF, kPer>(tab, &turn, (uint32_t)((c - c_lo) * kPer), in, nv, mt, du, g);
+    tab_add<DEF, kPer>(tab, turn, (uint32_t)((c - c_lo) * kPer), in, nv, mt, du, g);
   }
   {
     const unsigned long long e = wave_reduce_add((unsigned long long)err);

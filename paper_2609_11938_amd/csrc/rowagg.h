@@ -364,6 +364,37 @@ constexpr int kTThreads = 1024;
 constexpr int kTHot = 12;   // lanes of one row above which they are reduced first
 constexpr int kTSegs = 40;  // stretches of lanes of one row up to which they are scanned
 
+// A wave's adds to the table: its lanes with want set add acc to row g, and lane
+// 0 adds hot to row gh if with_hot is set. The fields go in kTurns groups with a
+// turn each, so that the next wave adds a group's fields while this one adds the
+// following group's: 300k launches over 700 rows 93 us the call by one turn for
+// all fields, 85 by four, 85 without an order.
+constexpr int kTurns = 4;  // a count and five counters each
+__device__ __forceinline__ void tab_turns(unsigned long long *tab, uint32_t *turn, uint32_t mine,
+                                          bool want, uint32_t g, const Acc &acc, bool with_hot,
+                                          uint32_t gh, const Acc &hot, uint32_t mx) {
+  constexpr int kEach = OPATTR_NUM_COUNTERS / kTurns;
+  static_assert(kTurns == 4 && kEach * kTurns == OPATTR_NUM_COUNTERS, "groups of fields");
+#pragma unroll
+  for (int t = 0; t < kTurns; ++t) {
+    auto add = [&](unsigned long long *q, const Acc &a) {
+      const unsigned long long n = t == 0 ? a.kc : t == 1 ? a.tns : t == 2 ? a.mc : a.mns;
+      if (t < 2 || a.mc) atomicAdd(&q[t], n);
+      if (a.mc == 0) return;  // no counter row reached
+#pragma unroll
+      for (int c = t * kEach; c < (t + 1) * kEach; ++c) {
+        if ((mx >> c) & 1u) atomicMax(&q[4 + c], a.v[c]);
+        else unsafeAtomicAdd(reinterpret_cast<double *>(&q[4 + c]), bits2d(a.v[c]));
+      }
+      if (t == kTurns - 1 && a.nan) atomicOr(reinterpret_cast<unsigned int *>(&q[24]), a.nan);
+    };
+    turn_begin(turn + t, mine);
+    if (with_hot && lane_id() == 0) add(tab + (size_t)gh * kFFields, hot);
+    if (want) add(tab + (size_t)g * kFFields, acc);
+    turn_end(turn + t, mine);
+  }
+}
+
 // The thread's kPer consecutive launches (nv of them exist) added to the
 // block's table in LDS, in turns, so that a row's sums are added up in one
 // order: turn r * waves + w is wave w's r-th. Called by the whole block, kPer
@@ -386,9 +417,7 @@ __device__ __forceinline__ void tab_add(unsigned long long *tab, uint32_t *turn,
   for (int k = 0; k < kPer; ++k) {
     if (k > 0) {
       const bool flush = k < nv && g[0] != gc;
-      turn_begin(turn, my);
-      if (flush) slot_add(tab + (size_t)gc * kFFields, acc, mx);
-      turn_end(turn, my);
+      tab_turns(tab, turn, my, flush, gc, acc, false, 0, acc, mx);
       my += kWaves;
       if (flush) {
         acc_zero(acc);
@@ -433,10 +462,7 @@ __device__ __forceinline__ void tab_add(unsigned long long *tab, uint32_t *turn,
       add = add && !in_hot;
     }
   }
-  turn_begin(turn, my);
-  if (with_hot && ln == 0) slot_add(tab + (size_t)gm * kFFields, hot, mx);
-  if (add) slot_add(tab + (size_t)gc * kFFields, acc, mx);
-  turn_end(turn, my);
+  tab_turns(tab, turn, my, add, gc, acc, with_hot, gm, hot, mx);
 }
 
 __device__ __forceinline__ unsigned long long merge_field(int f, unsigned long long x,
@@ -452,10 +478,22 @@ template <int kN>
 __device__ __forceinline__ unsigned long long merge_tree(int f, unsigned long long (&v)[kN],
                                                          uint32_t mx) {
   static_assert((kN & (kN - 1)) == 0, "pairs");
+  const bool count = f < 4, most = f >= 4 && f < 24 && ((mx >> (f - 4)) & 1u), sum = !most && f < 24;
+  if (count) {
 #pragma unroll
-  for (int o = kN / 2; o > 0; o >>= 1)
+    for (int k = 1; k < kN; ++k) v[0] += v[k];
+  } else if (most) {
 #pragma unroll
-    for (int k = 0; k < o; ++k) v[k] = merge_field(f, v[k], v[k + o], mx);
+    for (int k = 1; k < kN; ++k) v[0] = v[k] > v[0] ? v[k] : v[0];
+  } else if (sum) {
+#pragma unroll
+    for (int o = kN / 2; o > 0; o >>= 1)
+#pragma unroll
+      for (int k = 0; k < o; ++k) v[k] = d2bits(bits2d(v[k]) + bits2d(v[k + o]));
+  } else {
+#pragma unroll
+    for (int k = 1; k < kN; ++k) v[0] |= v[k];
+  }
   return v[0];
 }
 
@@ -705,7 +743,7 @@ __global__ void __launch_bounds__(1024) k_t_rows(CombParams a, const unsigned lo
         const int t = t0 + j * kTShares;
         y[j] = t < ntabs ? tabs[(size_t)t * ne + x] : 0ull;
       }
-      v = merge_field(f, v, merge_tree(f, y, mx), mx);
+      v = ntabs > kTShares ? merge_field(f, v, merge_tree(f, y, mx), mx) : y[0];
     }
     part[sh][e] = v;
   }
