@@ -193,8 +193,9 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
     // Launches per lane: as few as leave no CU without a block, up to the
     // point where more blocks only write more partials (3,001 rows, two, four
     // and eight: 250k launches 166, 171 and 188 us, 400k 185, 182 and 194, 1.5M
-    // 267, 249 and 255, 3M 462, 423 and 415; 5,001 rows, 2M 284 and 277).
-    pl.fper = pl.T <= (1 << 18) ? 2 : pl.T <= (3 << 19) ? 4 : 8;
+    // 267, 249 and 255, 3M 462, 423 and 415; 5,001 rows, 2M 284 and 277; with
+    // long runs, whose partials are few, 4M 1057 and 1071).
+    pl.fper = pl.T <= (1 << 18) ? 2 : pl.T <= (3 << 19) || long_runs ? 4 : 8;
     if ((pl.fused || pl.compact) && pl.G <= kTabMaxRows) {  // the whole table fits in LDS
       // A block of the compact path takes one chunk of launches, so up to four a
       // lane; the others take chunk after chunk with one a lane (501 rows, one,

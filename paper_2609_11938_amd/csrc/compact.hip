@@ -960,7 +960,7 @@ void run_compact(const CompactIn &x, hipStream_t s) {
     else if (pl.fper == 2) OPA_C_LAUNCH(k_c_tab, 2, kTThreads, lt);
     else OPA_C_LAUNCH(k_c_tab, 4, kTThreads, lt);
   } else {
-    const size_t lr = most(r_agg_lds(pl.G), sizeof(CWin));
+    const size_t lr = most(r_agg_lds(pl.G, pl.fper, pl.flong), sizeof(CWin));
     g = grid((int)c.nblocks, blocks_of(pl.R, kRThreads), 1, 0, 0, 0);
     if (pl.fper == 2) OPA_C_LAUNCH(k_c_row, 2, kRThreads, lr);
     else OPA_C_LAUNCH(k_c_row, 4, kRThreads, lr);

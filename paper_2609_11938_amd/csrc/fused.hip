@@ -759,7 +759,7 @@ void run_fused_agg(const FusedIn &x, hipStream_t s) {
     if (def) k_t_agg<true><<<gt, kTThreads, lt, s>>>(a, tabs);
     else k_t_agg<false><<<gt, kTThreads, lt, s>>>(a, tabs);
   } else if (nb > 0) {
-    const size_t lr = r_agg_lds(pl.G);
+    const size_t lr = r_agg_lds(pl.G, pl.fper, pl.flong);
     const dim3 gr((unsigned)nb), bl(kRThreads);
     if (pl.fper == 2) def ? k_r_agg<true, 2><<<gr, bl, lr, s>>>(a) : k_r_agg<false, 2><<<gr, bl, lr, s>>>(a);
     else if (pl.fper == 4) def ? k_r_agg<true, 4><<<gr, bl, lr, s>>>(a) : k_r_agg<false, 4><<<gr, bl, lr, s>>>(a);

@@ -17,13 +17,19 @@ constexpr int kBuckets = 256;                  // buckets of operator rows
 constexpr int kBktStride = kBuckets + 2;
 constexpr int kRThreads = 256;
 
-// LDS of k_r_agg: the row histogram, later the crossing rows' slots
+// LDS of the row-ordered reduction: the row histogram, later the crossing rows'
+// slots. Only stretches of longrow launches and more cross lanes into a slot, so
+// a wave of per launches a lane has at most 64 per / longrow of them.
 __host__ __device__ inline uint32_t r_hist_words(uint32_t G) { return (G + 1) / 2; }
-inline size_t r_agg_lds(uint32_t G) {
-  const size_t h = (size_t)r_hist_words(G) * 4, sl = (size_t)kRThreads * kFFields * 8;
+__host__ __device__ inline int r_slots(int per, int longrow) {
+  const int n = OPA_WAVE * per / longrow;
+  return n < OPA_WAVE ? n : OPA_WAVE;
+}
+inline size_t r_agg_lds(uint32_t G, int per, int longrow) {
+  const size_t h = (size_t)r_hist_words(G) * 4;
+  const size_t sl = (size_t)(kRThreads / OPA_WAVE) * r_slots(per, longrow) * kFFields * 8;
   return h > sl ? h : sl;
 }
-
 
 // vector of kN 32-bit elements (at most 16 bytes)
 template <int kN> struct VecOf { using type = uint4; };
@@ -275,8 +281,15 @@ __device__ __forceinline__ void row_order_block(const RowOut &o, const AggIn &in
   hx[tid] = h0;
   lds.lms[tid] = (uint8_t)lm;
   lds.rms[tid] = (uint8_t)rm;
-  unsigned long long *wslot = slots + (size_t)w * OPA_WAVE * kFFields;
-  for (int x = ln; x < OPA_WAVE * kFFields; x += OPA_WAVE) wslot[x] = 0;
+  // the next lane goes on with this lane's last row; if that is a long stretch
+  // started here, this lane has a slot for it
+  const uint32_t np_n = __shfl_down((uint32_t)np, 1, OPA_WAVE), hm_n = __shfl_down(hm, 1, OPA_WAVE);
+  const bool out = ln < OPA_WAVE - 1 && np_n > 0 && (hm_n & 1u) == 0;
+  const bool mine_out = out && hm != 0 && lm > (hm >> 1);
+  const unsigned long long live = __ballot(mine_out);
+  const int nl = __popcll(live);
+  unsigned long long *wslot = slots + (size_t)w * r_slots(kPer, o.longrow) * kFFields;
+  for (int x = ln; x < nl * kFFields; x += OPA_WAVE) wslot[x] = 0;
   __syncthreads();
   auto kept_before = [&](uint32_t p) -> uint32_t {  // partials << 16 | records of positions below p
     const uint32_t t = p / kPer;
@@ -294,9 +307,8 @@ __device__ __forceinline__ void row_order_block(const RowOut &o, const AggIn &in
   }
   PartRow *parts = o.parts + blk * o.pcap;
   uint4 *rec = o.rec + blk * o.rcap + (h0 & 0xFFFFu);
-  // the next lane goes on with this lane's last row
-  const uint32_t np_n = __shfl_down((uint32_t)np, 1, OPA_WAVE), hm_n = __shfl_down(hm, 1, OPA_WAVE);
-  const bool out = ln < OPA_WAVE - 1 && np_n > 0 && (hm_n & 1u) == 0;
+  unsigned long long *mine_slot = wslot + __popcll(live & lanemask_lt()) * kFFields;
+  unsigned long long *from_slot = wslot + __popcll(live & ((1ull << from) - 1ull)) * kFFields;
   Acc acc;  // of the long stretch the lane is in, else zero
   acc_zero(acc);
   bool here = false;       // the stretch started in this lane
@@ -304,7 +316,7 @@ __device__ __forceinline__ void row_order_block(const RowOut &o, const AggIn &in
   uint32_t hi = h0 >> 16;  // partials before it
   uint32_t gc = 0;
   auto flush_inside = [&]() {  // a long stretch that ends in this lane
-    if (!here) slot_add(wslot + (size_t)from * kFFields, acc, mx);
+    if (!here) slot_add(from_slot, acc, mx);
     else part_store(parts, hi, gc, acc);
   };
 #pragma unroll 1
@@ -324,7 +336,6 @@ __device__ __forceinline__ void row_order_block(const RowOut &o, const AggIn &in
     if (lg) acc_launch(acc, in, (int32_t)e.x, e.y, mx, dw);
     else *rec++ = make_uint4(sg[p0 + k], e.x, e.y, 0u);
   }
-  const bool mine_out = here && lg && out;  // this lane's slot holds a row that goes on
   // lanes inside one row: where they are many, they are added up across the
   // lanes first (LDS atomics on one address go one after the other), and the
   // last one adds their total to the slot of the lane the row starts in
@@ -333,16 +344,14 @@ __device__ __forceinline__ void row_order_block(const RowOut &o, const AggIn &in
     acc_seg_scan(acc, hm != 0 ? ln : from, mx);
     const bool last = ln == OPA_WAVE - 1 || np_n == 0 || hm_n != 0;
     if (np > 0 && lg && last) {
-      if (mid) slot_add(wslot + (size_t)from * kFFields, acc, mx);
-      else if (mine_out) slot_add(wslot + (size_t)ln * kFFields, acc, mx);
+      if (mid) slot_add(from_slot, acc, mx);
+      else if (mine_out) slot_add(mine_slot, acc, mx);
       else flush_inside();
     }
   } else if (np > 0 && lg) {
-    if (mine_out) slot_add(wslot + (size_t)ln * kFFields, acc, mx);
+    if (mine_out) slot_add(mine_slot, acc, mx);
     else flush_inside();
   }
-  const unsigned long long live = __ballot(mine_out);
-  const int nl = __popcll(live);
   uint8_t *ord = lds.ord[w];  // the live lanes in order
   if (mine_out) ord[__popcll(live & lanemask_lt())] = (uint8_t)ln;
   wave_sync_lds();
@@ -354,7 +363,7 @@ __device__ __forceinline__ void row_order_block(const RowOut &o, const AggIn &in
     const uint32_t sk = 31u - (uint32_t)__clz((int)ls);
     const uint32_t row = sg[st * kPer + (int)sk];
     const uint32_t idx = (hx[st] >> 16) + (uint32_t)__popc(ls) - 1u;
-    const unsigned long long v = wslot[(size_t)s * kFFields + f];
+    const unsigned long long v = wslot[x];
     reinterpret_cast<unsigned long long *>(parts + idx)[f] =
         f < 24 ? v : ((v & 0xFFFFFFFFull) | ((unsigned long long)row << 32));
   }
