@@ -198,10 +198,11 @@ Plan make_plan(const opattr_kernels *k, const opattr_profiled *p, const opattr_r
     pl.fper = pl.T <= (1 << 18) ? 2 : pl.T <= (3 << 19) || long_runs ? 4 : 8;
     if ((pl.fused || pl.compact) && pl.G <= kTabMaxRows) {  // the whole table fits in LDS
       // A block of the compact path takes one chunk of launches, so up to four a
-      // lane; the others take chunk after chunk with one a lane (501 rows, one,
-      // two and four: 400k 158, 159 and 165 us, 1.5M 182, 183 and 200, 6M 494,
-      // 507 and 517; ordered by row 176, 239 and 694 us).
-      pl.fper = !pl.compact || pl.T <= (1 << 18) ? 1 : pl.T <= (1 << 19) ? 2 : 4;
+      // lane; the others take chunk after chunk with two a lane (one, two and
+      // four: 100k over 501 rows 140, 144 and 157 us, 400k 158, 159 and 165, 2.5M
+      // 255, 262 and 273, with layers 194, 169 and 172, and mixed kinds 252, 203
+      // and 200; ordered by row 400k 176 us, 1.5M 239 against 182).
+      pl.fper = pl.T <= (1 << 18) ? 1 : pl.T <= (1 << 19) || !pl.compact ? 2 : 4;
       const int64_t chunks = fused_agg_blocks(pl.T, 1024 * pl.fper);
       pl.ftabs = (int)(chunks < kTabBlocks ? chunks : kTabBlocks);
     }

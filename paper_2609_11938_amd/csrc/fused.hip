@@ -459,12 +459,11 @@ __global__ void __launch_bounds__(kRThreads) k_r_agg(AggParams a) {
 // LDS and adds its launches' results to it, then writes it out; the tables
 // of all blocks are added up element by element (k_t_rows). Lanes of one row in
 // a wave are added up across the lanes first, as LDS atomics on one address go
-// one after the other. A block takes its chunks one launch a lane at a time (two
-// and four are slower, see make_plan).
+// one after the other.
 // ---------------------------------------------------------------------------
-template <bool DEF>
+template <bool DEF, int kPer>
 __global__ void __launch_bounds__(kTThreads) k_t_agg(AggParams a, unsigned long long *tabs) {
-  constexpr int kPer = 1, kN = kTThreads * kPer;
+  constexpr int kN = kTThreads * kPer;
   extern __shared__ __align__(16) unsigned char tagg_raw[];
   unsigned long long *tab = reinterpret_cast<unsigned long long *>(tagg_raw);  // [G][kFFields]
   const int tid = threadIdx.x, ln = lane_id();
@@ -756,8 +755,8 @@ void run_fused_agg(const FusedIn &x, hipStream_t s) {
     unsigned long long *tabs = reinterpret_cast<unsigned long long *>(a.o.parts);
     const size_t lt = (size_t)pl.G * kFFields * 8;
     const unsigned gt = (unsigned)pl.ftabs;
-    if (def) k_t_agg<true><<<gt, kTThreads, lt, s>>>(a, tabs);
-    else k_t_agg<false><<<gt, kTThreads, lt, s>>>(a, tabs);
+    if (pl.fper == 1) def ? k_t_agg<true, 1><<<gt, kTThreads, lt, s>>>(a, tabs) : k_t_agg<false, 1><<<gt, kTThreads, lt, s>>>(a, tabs);
+    else def ? k_t_agg<true, 2><<<gt, kTThreads, lt, s>>>(a, tabs) : k_t_agg<false, 2><<<gt, kTThreads, lt, s>>>(a, tabs);
   } else if (nb > 0) {
     const size_t lr = r_agg_lds(pl.G, pl.fper, pl.flong);
     const dim3 gr((unsigned)nb), bl(kRThreads);

@@ -17,14 +17,15 @@
 // Equal seq values (an error, reported as ORDER) are seen in step 5 as a bit
 // already set. A bucket of up to 4096 launches then counts the smaller (seq,
 // launch) records for each; after a larger one step 6 sorts all pairs. Either
-// way ties go by input index, as the general sort has it. 2M launches, one far
-// value and one pair of equal ones: 21.3 ms the call when one block sorted all
-// pairs, 0.85 ms now (all equal 20.2 and 0.39 ms).
+// way ties go by input index, as the general sort has it. 2M shuffled launches,
+// the call: spread evenly 698 us, one far value 707, one pair of equal ones too
+// 998 (one block sorted all pairs in 20 ms), all equal 484.
 // 3M launches of 8 streams: 77 us (10 + 16 + 7 + 21 + 19 + 4), bound by the
 // scatter's partial lines and by the latency of short kernels; the whole call
 // 559 us with the sort, 375 us with this. 500k shuffled: 328 us and 229 us.
-// Blocks of 256 and 1024 threads in step 5, 2048 launches per bucket and four
-// loads in flight instead of eight: the same within 3 us.
+// Blocks of 256 and 1024 threads in step 5 and 2048 launches per bucket: the
+// same within 3 us. Eight loads in flight there, or a loop of its own for the
+// parts: 4M launches 7 us longer, the call (beside its other streams' kernels).
 #include "common.h"
 #include "impl.h"
 
@@ -51,9 +52,9 @@ struct RvArgs {
 };
 
 // Launches of a bucket from which it is ranked in parts, and of a part. By one
-// block a bucket, 2M launches in 256 buckets of 7,812 took 608 us the call, in
-// 8 buckets 1254 us; in parts 547 and 573 us, spread evenly 537 us. Up to 4096
-// launches are a round of a block's loads.
+// block a bucket, 2M launches in 256 buckets of 7,812 took 71 us longer, in 8
+// buckets 720 us longer than spread evenly; in parts 0 and 7 us longer. Up to
+// 4096 launches are two rounds of a block's loads.
 constexpr uint32_t kRvFull = 4096, kRvPart = 8192;
 __host__ __device__ inline uint32_t rv_full(int64_t T) {  // (even buckets of long lists hold more)
   const int64_t even = 4 * (T / kRvBuckets);
@@ -203,7 +204,7 @@ __global__ void __launch_bounds__(kRvThreads) k_rv_scatter(RvArgs a) {
   }
 }
 
-constexpr int kRvRankThreads = 512, kRvUnroll = 8, kRvPartUnroll = 16;
+constexpr int kRvRankThreads = 512, kRvUnroll = 4;
 constexpr uint32_t kRvEqualMax = 4096;
 
 struct RvRankLds {
@@ -213,9 +214,8 @@ struct RvRankLds {
 };
 
 // The launches [i_lo, i_hi) of bucket b (places inside it) ranked, by the
-// whole block. kUnroll of a thread's records are in flight while the bitmap of
+// whole block. kRvUnroll of a thread's records are in flight while the bitmap of
 // the whole bucket is built.
-template <int kUnroll>
 __device__ __forceinline__ void rv_rank_bucket(const RvArgs &a, int shift, uint32_t lo, uint32_t b,
                                                uint32_t i_lo, uint32_t i_hi, RvRankLds &l) {
   const int tid = threadIdx.x;
@@ -229,15 +229,16 @@ __device__ __forceinline__ void rv_rank_bucket(const RvArgs &a, int shift, uint3
   if (n <= 1u << shift) {  // else there are equal values
     for (uint32_t x = tid; x < words; x += kRvRankThreads) l.bits[x] = 0;
     __syncthreads();
-    for (uint32_t i0 = tid; i0 < n; i0 += kRvRankThreads * kUnroll) {
-      uint32_t v[kUnroll];
+    for (uint32_t i0 = tid; i0 < n; i0 += kRvRankThreads * kRvUnroll) {
+      uint32_t v[kRvUnroll];
 #pragma unroll
-      for (int k = 0; k < kUnroll; ++k) {
+      for (int k = 0; k < kRvUnroll; ++k) {
         const uint32_t i = i0 + k * kRvRankThreads;
         v[k] = (val[2 * (size_t)(i < n ? i : i0)] - lo) & mask;  // past the end: the first once more
       }
 #pragma unroll
-      for (int k = 0; k < kUnroll; ++k) atomicOr(&l.bits[v[k] >> 5], 1u << (v[k] & 31));
+      for (int k = 0; k < kRvUnroll; ++k)
+        if (i0 + k * kRvRankThreads < n) atomicOr(&l.bits[v[k] >> 5], 1u << (v[k] & 31));
     }
     __syncthreads();
     uint32_t c = 0;
@@ -288,14 +289,18 @@ __global__ void __launch_bounds__(kRvRankThreads) k_rv_rank(RvArgs a) {
   const uint32_t lo = a.mm[0], hi = a.mm[1], np = a.mm[2], full = rv_full(a.T);
   const int shift = rv_shift(a, lo, hi);
   const uint32_t nb = ((hi - lo) >> shift) + 1u;
-  for (uint32_t p = blockIdx.x; p < np; p += gridDim.x) {
-    const uint2 e = a.part[p];
-    rv_rank_bucket<kRvPartUnroll>(a, shift, lo, e.x, e.y, e.y + kRvPart, lds);
-  }
-  for (uint32_t b = blockIdx.x; b < nb; b += gridDim.x) {
-    const uint32_t n = a.cnt[b + 1] - a.cnt[b];
-    if (n == 0 || n > full) continue;  // uniform over the block
-    rv_rank_bucket<kRvUnroll>(a, shift, lo, b, 0, n, lds);
+  for (uint32_t w = blockIdx.x; w < np + nb; w += gridDim.x) {  // parts, then whole buckets
+    uint32_t b = w - np, i_lo = 0, i_hi;
+    if (w < np) {
+      const uint2 e = a.part[w];
+      b = e.x;
+      i_lo = e.y;
+      i_hi = e.y + kRvPart;
+    } else {
+      i_hi = a.cnt[b + 1] - a.cnt[b];
+      if (i_hi == 0 || i_hi > full) continue;  // uniform over the block
+    }
+    rv_rank_bucket(a, shift, lo, b, i_lo, i_hi, lds);
   }
 }
 
