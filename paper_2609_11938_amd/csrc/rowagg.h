@@ -561,7 +561,8 @@ constexpr int kBatch = 8;                      // loads per lane in flight
 
 // Partials added into an LDS table of rb rows field by field: 25 lanes read the
 // fields of one, two partials an instruction, so that a partial costs two cache
-// lines of requests instead of 25. at(x) gives the place of entry x, or -1.
+// lines of requests instead of 25. at(x) gives the place of entry x, or kNoEntry.
+constexpr uint32_t kNoEntry = 0xFFFFFFFFu;
 struct CombParts {
   static constexpr int kEach = 2;  // entries an instruction takes
   template <int kN, typename At>
@@ -573,8 +574,8 @@ struct CombParts {
     bool ok[kN];
 #pragma unroll
     for (int j = 0; j < kN; ++j) {
-      const int64_t x = at(2 * j + (ln >> 5));
-      ok[j] = x >= 0 && f < kFFields;
+      const uint32_t x = at(2 * j + (ln >> 5));
+      ok[j] = x != kNoEntry && f < kFFields;
       v[j] = ok[j] ? parts64[(size_t)x * (sizeof(PartRow) / 8) + f] : 0ull;
     }
 #pragma unroll
@@ -599,8 +600,8 @@ struct CombRecs {
     bool ok[kN], hit[kN];
 #pragma unroll
     for (int j = 0; j < kN; ++j) {
-      const int64_t x = sub < kEach ? at(kEach * j + sub) : -1;
-      ok[j] = x >= 0;
+      const uint32_t x = sub < kEach ? at(kEach * j + sub) : kNoEntry;
+      ok[j] = x != kNoEntry;
       r[j] = ok[j] ? a.rec[x] : make_uint4(0u, 0xFFFFFFFFu, 0u, 0u);
     }
 #pragma unroll
@@ -660,8 +661,8 @@ __device__ __forceinline__ void comb_add(unsigned long long *tab, uint32_t rb, u
     }
     wave_sync_lds();
     for (uint32_t i = 0; i < n; i += Comb::kEach * kN)
-      Comb::template add<kN>(tab, rb, a, [&](int x) -> int64_t {
-        return i + x < n ? (int64_t)list[i + x] : -1;
+      Comb::template add<kN>(tab, rb, a, [&](int x) -> uint32_t {
+        return i + x < n ? list[i + x] : kNoEntry;
       }, mx, dw);
     wave_sync_lds();  // the list is free again
   } else {
@@ -679,8 +680,8 @@ __device__ __forceinline__ void comb_add(unsigned long long *tab, uint32_t rb, u
         const uint32_t c = __shfl(e, src, OPA_WAVE);
         const uint32_t x0 = __shfl(xe, src, OPA_WAVE);
         for (uint32_t p = 0; p < c; p += Comb::kEach * 2)
-          Comb::template add<2>(tab, rb, a, [&](int x) -> int64_t {
-            return p + x < c ? (int64_t)(x0 + p + x) : -1;
+          Comb::template add<2>(tab, rb, a, [&](int x) -> uint32_t {
+            return p + x < c ? x0 + p + x : kNoEntry;
           }, mx, dw);
       }
     }
