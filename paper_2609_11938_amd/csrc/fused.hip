@@ -14,8 +14,8 @@
 //    is staged in LDS; the piece a lane ends with is carried across the
 //    wave by a segmented lane scan. A block keeps up to 128 partial results,
 //    sorts them by bucket of operator rows (256 buckets, then the
-//    unattributed row on its own) and writes them to its own region with a
-//    (count, offset) entry per bucket; anything past that goes to a row
+//    unattributed row on its own) and writes them to its own region with
+//    the count of them before each bucket; anything past that goes to a row
 //    accumulator with device-scope atomics. The blocks are taken per XCD in
 //    the order block_order gives (launch-order windows).
 // 2. k_f_comb: one wave per (bucket, share of the blocks) adds the bucket's
@@ -419,11 +419,10 @@ k_f_agg(AggParams a) {
 // of the block is one stretch and leaves one partial per wave it touches. A
 // lane then adds kPer consecutive launches of that order; a row that lies
 // inside a lane is written by the lane, a row that crosses lanes is added
-// up in an LDS slot of the lane it starts in (at most one per lane, so the
-// slots never run out). The partials come out in row order: a bucket's
-// entry is a difference of the count of row starts before its first
-// launch and before its last. Rows of few launches of a wave are kept as
-// launch records instead.
+// up in an LDS slot (one for every row that can cross lanes, so the slots
+// never run out). Rows of few launches of a wave are kept as launch records
+// instead. Both come out in row order: a bucket's are those before the next
+// bucket's first launch and not before its own first.
 // ---------------------------------------------------------------------------
 template <bool DEF, int kPer>  // DEF: the default aggregation kinds; kPer launches per lane
 __global__ void __launch_bounds__(kRThreads) k_r_agg(AggParams a) {

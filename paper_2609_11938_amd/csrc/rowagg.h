@@ -141,8 +141,9 @@ struct RowOut {
 // has longrow launches or more; those of a shorter one are kept as records, and
 // the combine reads their counters. So a block of n launches never has more
 // than n / longrow partials, however many rows it holds, and its region holds
-// whatever comes: 200 / longrow + 16 bytes a launch. (Partials past a common
-// room went to the row accumulators by atomics, in another order on each run.)
+// whatever comes: 200 / longrow + 16 bytes a launch. (A common room for all
+// blocks' partials fills in another order on each run, and what finds none left
+// has to be added by atomics.)
 template <int kPer>
 struct RowLds {
   uint2 md[kRThreads * kPer];     // match and duration, in row order
